@@ -24,9 +24,9 @@
 extern "C" {
 #endif
 
-#define OKV_LINEAR_MAX_ROWS 128     /* rows that one launch of the product kernels takes whatever the shape   */
-#define OKV_LINEAR_MAX_ROWS_STAGED 192  /* ... and when n_in is a multiple of 256 and the workspace is there    */
-#define OKV_LINEAR_MAX_BATCH 4096   /* rows per call: beyond that a call issues several launches              */
+#define OKV_LINEAR_MAX_ROWS 128     /* rows that the simple product kernel takes                               */
+#define OKV_LINEAR_MAX_ROWS_STAGED 192  /* rows that the staged product kernel takes                            */
+#define OKV_LINEAR_MAX_BATCH 4096   /* rows per call                                                          */
 
 struct okv_ctx;   /* okv.h */
 
@@ -41,11 +41,8 @@ struct okv_ctx;   /* okv.h */
 int okv_pack_linear_weight(void *dst, const void *src, int32_t n_out, int32_t n_in, void *stream);
 
 /* out = act(x * W^T + bias) + residual for a batch of m <= OKV_LINEAR_MAX_BATCH rows
- * (paper §IV-D: the linear layers of the decode stage, 2 n_out n_in flops per row).  Up to
- * OKV_LINEAR_MAX_ROWS rows are one launch, in which every weight is read once, and up to
- * OKV_LINEAR_MAX_ROWS_STAGED when the input width is a multiple of 256 (and the workspace of
- * okv_linear_workspace_bytes is passed); more rows are cut into the fewest launches of nearly
- * equal size, each of which reads the weights again.
+ * (paper §IV-D: the linear layers of the decode stage, 2 n_out n_in flops per row), one product launch
+ * whatever the number of rows (a second small one adds up the shares where the inputs are cut).
  *   x         fp16 [m][n_in]
  *   w_packed  fp16, as okv_pack_linear_weight leaves it
  *   bias      fp16 [n_out] or NULL
@@ -58,13 +55,11 @@ int okv_pack_linear_weight(void *dst, const void *src, int32_t n_out, int32_t n_
  *   workspace DEVICE scratch memory of at least okv_linear_workspace_bytes(m, n_out, n_in)
  *             bytes (workspace_bytes says how much there is); its contents before and
  *             after the call mean nothing.  Calls that may run at the same time (different
- *             streams) need workspaces of their own.  With more than 8 rows and n_in a
- *             multiple of 256 the fast kernel runs: where that fills the GPU better the
+ *             streams) need workspaces of their own.  Where that fills the GPU better the
  *             input dimension is cut across workgroups, their fp32 shares go through the
  *             workspace and a second small kernel adds them in a fixed order (results do
- *             not vary from run to run).  With fewer rows or another n_in, or when a cut
- *             is wanted and the workspace is NULL or too small, a simpler kernel runs that
- *             needs no workspace.
+ *             not vary from run to run).  When a cut is wanted and the workspace is NULL or
+ *             too small for it, a form that needs less or none runs.
  * Products accumulate in fp32 on the matrix cores; the result is rounded to fp16 once.
  * residual may alias out[0] (each element is read before it is written, by the same lane). */
 int okv_linear(const void *x, const void *w_packed, const void *bias, const void *residual,

@@ -1,8 +1,8 @@
 // Linear layers and layer norm of a decoder layer in the decode stage, for gfx950.
 //
-// out[m][n] = sum_k x[m][k] W[n][k] for a batch of at most 128 rows (paper §IV-D: the
+// out[m][n] = sum_k x[m][k] W[n][k] for a batch of m rows (paper §IV-D: the
 // 8 h1^2 + 4 h1 h2 flops per token of the four projections and the feed-forward block).
-// With so few rows every weight is read once and used `m` times: the product is bound by
+// With a decode batch's few rows every weight is read once and used `m` times: the product is bound by
 // streaming W from HBM, so the kernel is built like the attention kernel -- long runs of
 // 16-byte-per-lane loads kept many deep in flight -- with the matrix cores doing the
 // arithmetic on the side (one fp16 instruction per KiB of weights and 16 rows of x: a few
@@ -32,13 +32,15 @@
 //     fences, which on this GPU write back and invalidate the L2 caches: 75 us instead of 11.
 //     Where three tiles per workgroup fill the compute units without a cut (12288 features on
 //     256 units) the workgroups have three streaming wavefronts and there is no second kernel;
-//   * up to 8 rows, and shapes the fast kernel does not take (input dimension not a multiple
+//   * up to 8 rows, and some shapes the fast kernel does not take (input dimension not a multiple
 //     of 256), run the simple kernel: a workgroup per 16 features, its wavefronts split the
-//     inputs and add up through LDS, x by gather.
+//     inputs and add up through LDS, x by gather;
+//   * with hundreds of rows the matrix cores and what feeds them bound the product: linear_tile_kernel.
 #include "okv_kernels.h"
 #include "okv_layer.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace okv {
 
@@ -92,6 +94,29 @@ __device__ __forceinline__ void seg_of(const LinearArgs &a, int mrow, int n, int
     seg = 1 + r / a.seg_cols;
     at = (size_t)mrow * a.seg_cols + (r - (seg - 1) * a.seg_cols);
   }
+}
+
+// Epilogue for eight neighbouring features n .. n + 7 of row mrow: bias, ReLU, residual, one rounding, one 16-byte store.
+// (Feature counts and segment widths are multiples of 16, so a group of eight never straddles a segment.)
+__device__ __forceinline__ void store_eight(const LinearArgs &a, int mrow, int n, const float4 t0, const float4 t1) {
+  const float v[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
+  int seg;
+  size_t at;
+  seg_of(a, mrow, n, seg, at);
+  uint4 bb = make_uint4(0u, 0u, 0u, 0u), rb = bb;
+  if (a.bias) bb = *reinterpret_cast<const uint4 *>(a.bias + n);
+  if (a.residual) rb = *reinterpret_cast<const uint4 *>(a.residual + at);
+  const _Float16 *bp = reinterpret_cast<const _Float16 *>(&bb), *rp = reinterpret_cast<const _Float16 *>(&rb);
+  uint4 yo;
+  _Float16 *yp = reinterpret_cast<_Float16 *>(&yo);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float y = v[e] + (float)bp[e];
+    if (a.relu) y = fmaxf(y, 0.f);
+    y += (float)rp[e];
+    yp[e] = (_Float16)y;
+  }
+  *reinterpret_cast<uint4 *>(a.out[seg] + at) = yo;
 }
 
 __device__ __forceinline__ floatx4 mfma16(const uint2 a, const uint2 b, floatx4 c) {
@@ -208,7 +233,7 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
 }
 
 // Fast path: NW wavefronts x 16 features, x staged in LDS by one or two more wavefronts, input
-// dimension cut across workgroups.  NW = 4 or 3 and the number of cuts: whatever linear_plan's model of the
+// dimension cut across workgroups.  NW = 4 or 3 and the number of cuts: whatever staged_plan's model of the
 // launch prefers (3 and no cut for 12288 features on 256 compute units, which saves the kernel that adds up
 // the shares).
 // 32-input blocks per staged chunk of x: 8 (256 inputs), 4 from 112 rows on.  A chunk takes chunk x MF KiB of LDS
@@ -411,25 +436,217 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
     const int mrow = o / VPR, n = n0 + 8 * (o % VPR);
     if (n >= a.n_out) continue;
     const float4 *t = reinterpret_cast<const float4 *>(tile + mrow * kTileCols + 8 * (o % VPR));
-    const float4 t0 = t[0], t1 = t[1];
-    float v[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
-    int seg;
-    size_t at;
-    seg_of(a, mrow, n, seg, at);
-    uint4 bb = make_uint4(0u, 0u, 0u, 0u), rb = bb;
-    if (a.bias) bb = *reinterpret_cast<const uint4 *>(a.bias + n);
-    if (a.residual) rb = *reinterpret_cast<const uint4 *>(a.residual + at);
-    const _Float16 *bp = reinterpret_cast<const _Float16 *>(&bb), *rp = reinterpret_cast<const _Float16 *>(&rb);
-    uint4 yo;
-    _Float16 *yp = reinterpret_cast<_Float16 *>(&yo);
+    store_eight(a, mrow, n, t[0], t[1]);
+  }
+}
+
+// ---- many rows: tiles of rows x features -------------------------------------------------------
+//
+// With a few hundred rows and more the product is no longer a stream of weights with some arithmetic beside it:
+// the staged kernel above has every streaming wavefront read every row of x from LDS for 16 features, and takes
+// the weights once per 192 rows.  Here a workgroup owns a tile of 16 FM WM rows x 16 FN WN features and its WM x WN
+// wavefronts a 16 FM x 16 FN piece each, so an operand read from LDS serves FN products and a weight FM.
+//
+//   * x goes through LDS, 64 inputs at a time (a stage), fetched by the load that writes LDS directly (16 bytes per
+//     lane, no registers), whole 128-byte lines of 8 rows per instruction; the weights go from memory straight into
+//     the registers of the wavefronts that use them: packed, one load is one operand of the matrix instruction;
+//   * the direct loads are written as assembly because the compiler, which cannot tell the stage being
+//     written from the one being read, waits for all of them in front of every LDS read otherwise.  It does not
+//     count them either: its waits for the weights are at worst longer than they need to be;
+//   * loads retire in order, so a stage of x needs no more lead than the weights have: WD stages of both are in
+//     flight (WD + 1 LDS buffers).
+//
+// Measured (weights from HBM), before = launches of at most 192 rows of the staged kernel, each reading the weights
+// again: 1024 rows x 16384 x 4096 221 -> 114 us (1.2 PFLOP/s; the library's fp16 product of 8192 x 8192 x 8192 runs at
+// 1.49), 12288 x 4096 166 -> 92, 4096 x 4096 98 -> 41, 4096 x 16384 291 -> 130 with its share reduction; 512 rows 116 -> 68,
+// 89 -> 61, 50 -> 31, 146 -> 77.  What bounds it: with every operand in the L2s (timing builds) the same walk takes
+// 105 of the 114 us, with x packed nothing less; reading LDS a step ahead of the matrix instructions, or two
+// fragments at a time, was slower, two stages in flight instead of one 8-15 % faster.
+//
+// LDS layout of a stage: 16 rows x 64 inputs (8 pieces of 16 bytes a row) are 128 units.  Row rr, piece p = 2 v + ql
+// sits at unit 64 (rr & 1) + 16 (2 (v >> 1) + ql) + (rr + v) % 16: an instruction's 64 units are the eight even (odd)
+// rows with all their pieces, and an operand read (lane 16 q + rr takes piece 4 i + q of row rr) meets every
+// bank once in each of the groups of 16 lanes that the LDS serves together (see linear_lds_kernel).
+template <int FM, int FN, int WM, int WN, int WD>
+struct TileShape {
+  static constexpr int kThreads = WM * WN * 64, kRows = 16 * FM * WM, kCols = 16 * FN * WN;
+  static constexpr int kBuffers = WD + 1, kStageBytes = kRows * 128;
+  static constexpr int kLoads = 2 * FM / WN;             // staging instructions of a wavefront per stage
+  static constexpr int kOutStride = 16 * FN + 4;         // floats between two rows of a wavefront's results in LDS
+  static constexpr int kOutBytes = WM * WN * 32 * kOutStride * 4;
+  static constexpr int kLds = kBuffers * kStageBytes > kOutBytes ? kBuffers * kStageBytes : kOutBytes;
+  static_assert(2 * FM % WN == 0 && FM % 2 == 0, "staging instructions and result chunks come out even");
+  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+  static_assert(WD * 2 * FN + (WD - 1) * kLoads <= 63, "the wait for a stage must fit the load counter");
+};
+
+// One 16-byte-per-lane load from `base` + off straight into LDS: lane l's bytes land at lds + 16 l.
+__device__ __forceinline__ void load_to_lds(const void *base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+
+template <int FM, int FN, int WM, int WN, int WD>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1, 2))) void linear_tile_kernel(
+    const uint4 *w, const uint4 *x, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
+    const int32_t n_tiles, const int32_t m_tiles, const int32_t n_groups, const LinearArgs a) {
+  using S = TileShape<FM, FN, WM, WN, WD>;
+  __shared__ __attribute__((aligned(1024))) char lds[S::kLds];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  // Workgroups are dealt to the 8 XCDs in rotation; tiles that share weights (all row tiles of a feature group)
+  // and neighbouring groups are put on the same XCD, whose L2 then reads them from memory once.
+  const int total = gridDim.x, xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
+  const int tile = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
+  const int mt = tile % m_tiles, group = (tile / m_tiles) % n_groups, cut = tile / (m_tiles * n_groups);
+  // This workgroup's stages of 64 inputs.  Where the inputs are an odd number of blocks of 32, the very last stage is
+  // half full: it is the last one walked by the cut that has it (no shift of the walk then).
+  const int all_stages = (n_kb + 1) >> 1, stage0 = (int)((int64_t)cut * all_stages / splits);
+  const int n_stages = (int)((int64_t)(cut + 1) * all_stages / splits) - stage0;
+  const int half_stage = n_kb & 1 ? all_stages - 1 : -1;
+  const int full_stages = n_stages - (stage0 + n_stages - 1 == half_stage ? 1 : 0);
+  const int rot = m_tiles == 1 && half_stage < 0 ? (int)(((unsigned)group * 5u + (unsigned)cut * 3u) % (unsigned)n_stages) : 0;
+  auto stage_at = [&](int s) {                           // position in this workgroup's walk -> stage; past the end: the last again
+    const int t = min(s, n_stages - 1) + rot;
+    return stage0 + (t >= n_stages ? t - n_stages : t);
+  };
+
+  // staging: this wavefront's instructions are kLoads * wave + j; instruction 2 f + t holds rows of parity t of fragment f
+  const int row0 = mt * S::kRows, last_row = m - 1 - row0;
+  const uint32_t row_bytes = (uint32_t)n_in * 2;
+  uint32_t xoff[S::kLoads];
+  const uint32_t second = lane >> 5 ? 64 : 0;            // this lane fetches of the stage's second 32 inputs
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float y = v[e] + (float)bp[e];
-      if (a.relu) y = fmaxf(y, 0.f);
-      y += (float)rp[e];
-      yp[e] = (_Float16)y;
+  for (int j = 0; j < S::kLoads; ++j) {
+    const int ii = wave * S::kLoads + j, f = ii >> 1, t = ii & 1;
+    const int bank = lane & 15, ql = (lane >> 4) & 1;
+    const int v = 2 * (lane >> 5) + ((bank - t) & 1);
+    const int rr = (bank - v) & 15;
+    xoff[j] = (uint32_t)min(16 * f + rr, last_row) * row_bytes + (uint32_t)(2 * v + ql) * 16;   // rows past the batch: the last again
+  }
+  const char *xbase = reinterpret_cast<const char *>(x) + (size_t)row0 * row_bytes;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds);
+  auto stage_x = [&](int s, int buf) {
+    const int st = stage_at(s);
+    const char *src = xbase + (size_t)st * 128;
+    const uint32_t back = st == half_stage ? second : 0;       // a half-full stage: its first half twice (the second is never used)
+    const uint32_t dst = lds0 + (uint32_t)buf * S::kStageBytes + (uint32_t)(wave * S::kLoads) * 1024;
+#pragma unroll
+    for (int j = 0; j < S::kLoads; ++j) load_to_lds(src, xoff[j] - back, dst + j * 1024);
+  };
+  // weights: FN runs of 1 KiB per 32 inputs (a tile past the last one streams the last one and is never stored)
+  const int tile0 = (group * WN + wn) * FN;
+  const uint4 *wp[FN];
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn) wp[fn] = w + (size_t)min(tile0 + fn, n_tiles - 1) * n_kb * 64;
+  uint4 wbuf[WD][2][FN];
+  auto load_w = [&](uint4 (&dst)[FN], int s, int i) {
+    const size_t at = (size_t)min(2 * stage_at(s) + i, n_kb - 1) * 64;
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) dst[fn] = wp[fn][at + lane];
+  };
+  const int rr = lane & 15, q = lane >> 4;
+  int xunit[2];                                          // where this lane's piece of 32 inputs i of fragment 0 sits in a stage
+#pragma unroll
+  for (int i = 0; i < 2; ++i) xunit[i] = 64 * (rr & 1) + 16 * (2 * i + (q & 1)) + ((rr + 2 * i + (q >> 1)) & 15);
+
+  floatx4 acc[FM][FN];
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  auto read_half = [&](uint4 (&dst)[FM], int buf, int i) {
+    const uint4 *xs = reinterpret_cast<const uint4 *>(lds + buf * S::kStageBytes) + wm * FM * 128 + xunit[i];
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm) dst[fm] = xs[fm * 128];
+  };
+  auto multiply = [&](const uint4 (&wf)[FN], const uint4 (&xf)[FM]) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = mfma32(wf[fn], xf[fm], acc[fm][fn]);
+    __builtin_amdgcn_s_setprio(0);
+  };
+#pragma unroll
+  for (int u = 0; u < WD; ++u) {
+    stage_x(u, u);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) load_w(wbuf[u][i], u, i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // a stage of x has landed once no more loads are outstanding than were issued after it
+  constexpr int kInFlight = WD * 2 * FN + (WD - 1) * S::kLoads;
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight));
+  __syncthreads();
+  int buf = 0, fill = WD, s0 = 0;
+  for (; s0 + WD <= full_stages; s0 += WD) {
+#pragma unroll
+    for (int u = 0; u < WD; ++u) {
+      stage_x(s0 + u + WD, fill);                        // into the buffer that the stage before this one was read from
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        uint4 xf[FM];
+        read_half(xf, buf, i);
+        multiply(wbuf[u][i], xf);
+        __builtin_amdgcn_sched_barrier(0);
+        load_w(wbuf[u][i], s0 + u + WD, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      buf = buf + 1 == S::kBuffers ? 0 : buf + 1;
+      fill = fill + 1 == S::kBuffers ? 0 : fill + 1;
+      __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight));   // the next stage has landed
+      __syncthreads();
     }
-    *reinterpret_cast<uint4 *>(a.out[seg] + at) = yo;
+  }
+  // What does not fill a round of WD stages (at most WD of them, a half-full one last) is on its way or here already.  (A
+  // way out in the middle of a round instead cost 15 % of the whole walk: the compiler's waits in front of the weights
+  // then cover every path that may have led there.)
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(0));             // nothing may still be on its way into LDS afterwards
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < WD; ++u)
+    if (s0 + u < n_stages) {
+      uint4 xf[FM];
+      read_half(xf, buf, 0);
+      multiply(wbuf[u][0], xf);
+      if (stage0 + s0 + u != half_stage) {
+        read_half(xf, buf, 1);
+        multiply(wbuf[u][1], xf);
+      }
+      buf = buf + 1 == S::kBuffers ? 0 : buf + 1;
+    }
+  __syncthreads();
+
+  // Results: acc[fm][fn][r] is row 16 fm + lane % 16, feature 16 fn + 4 (lane / 16) + r of the wavefront's piece.  They pass
+  // through LDS that belongs to the wavefront, 32 rows at a time, and leave as 16-byte pieces of whole rows.
+  float *mine = reinterpret_cast<float *>(lds) + wave * 32 * S::kOutStride;
+  const bool to_shares = splits > 1 || a.to_shares;
+#pragma unroll
+  for (int c = 0; c < FM / 2; ++c) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn)
+        *reinterpret_cast<floatx4 *>(mine + (16 * h + rr) * S::kOutStride + 16 * fn + 4 * q) = acc[2 * c + h][fn];
+#pragma unroll
+    for (int k = 0; k < FN; ++k) {
+      const int o = k * 64 + lane, r = o / (2 * FN), pc = o % (2 * FN);
+      const int mrow = row0 + (wm * FM + 2 * c) * 16 + r, n = tile0 * 16 + pc * 8;
+      const float4 *t = reinterpret_cast<const float4 *>(mine + r * S::kOutStride + pc * 8);
+      const float4 t0 = t[0], t1 = t[1];
+      if (mrow >= m || n >= a.n_out) continue;
+      if (to_shares) {
+        float4 *dst = reinterpret_cast<float4 *>(a.shares + ((size_t)cut * m + mrow) * a.n_out + n);
+        dst[0] = t0;
+        dst[1] = t1;
+      } else {
+        store_eight(a, mrow, n, t0, t1);
+      }
+    }
   }
 }
 
@@ -645,6 +862,19 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
   }
 }
 
+// The kernel that adds the cuts' shares up (and takes the layer norm of the sums, if asked to).
+void launch_reduce(const LinearArgs &args, hipStream_t stream) {
+  if (args.ln_out && (args.n_out >> 3) <= kLnMaxThreads)
+    hipLaunchKernelGGL(reduce_layernorm_kernel<1>, dim3(args.m), dim3(ln_threads(args.n_out)), 0, stream, args.shares, args.n_out,
+                       args.splits, args.m, args);
+  else if (args.ln_out)
+    hipLaunchKernelGGL(reduce_layernorm_kernel<2>, dim3(args.m), dim3(ln_threads(args.n_out)), 0, stream, args.shares, args.n_out,
+                       args.splits, args.m, args);
+  else
+    hipLaunchKernelGGL(reduce_epilogue_kernel, dim3((args.n_out + 1023) / 1024, args.m), dim3(256), 0, stream, args.shares,
+                       args.n_out, args.splits, args.m, args);
+}
+
 template <int MF>
 hipError_t launch_linear_mf(const LinearArgs &args, int n_tiles, bool fast, int fast_waves, hipStream_t stream) {
   if (fast) {
@@ -656,28 +886,66 @@ hipError_t launch_linear_mf(const LinearArgs &args, int n_tiles, bool fast, int 
     if (args.splits > 1 || args.to_shares) {
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
-      if (args.ln_out && (args.n_out >> 3) <= kLnMaxThreads)
-        hipLaunchKernelGGL(reduce_layernorm_kernel<1>, dim3(args.m), dim3(ln_threads(args.n_out)), 0, stream, args.shares, args.n_out,
-                           args.splits, args.m, args);
-      else if (args.ln_out)
-        hipLaunchKernelGGL(reduce_layernorm_kernel<2>, dim3(args.m), dim3(ln_threads(args.n_out)), 0, stream, args.shares, args.n_out,
-                           args.splits, args.m, args);
-      else
-        hipLaunchKernelGGL(reduce_epilogue_kernel, dim3((args.n_out + 1023) / 1024, args.m), dim3(256), 0, stream, args.shares,
-                           args.n_out, args.splits, args.m, args);
+      launch_reduce(args, stream);
     }
   } else if constexpr (MF <= OKV_LINEAR_MAX_ROWS / 16) {
     hipLaunchKernelGGL(linear_kernel<MF>, dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.n_kb, args.n_in,
                        args.m, args);
   } else {
-    return hipErrorInvalidValue;                       // more than OKV_LINEAR_MAX_ROWS rows: the staged kernel only
+    return hipErrorInvalidValue;                       // more than OKV_LINEAR_MAX_ROWS rows: the staged or the tile kernel only
   }
   return hipGetLastError();
 }
 
-}  // namespace
+// The forms linear_tile_kernel is built in, with what a stage of 64 inputs takes a workgroup when every compute unit
+// has one (us, measured on MI355X with the weights coming from HBM: 1024 rows x 16384 x 4096 for 256 x 256, 1024 x 12288 x
+// 4096 for 256 x 192, 512 x 16384 x 4096 for 128 x 256, 1024 x 4096 x 4096 for 128 x 128, 4224- and 1056-wide
+// products for the small ones), and whether a compute unit has room for more than one.  Wavefronts side by side in
+// the rows (2 x 4) load every weight twice, which the widest forms need to keep their accumulators in registers; at 128
+// rows and below one row of wavefronts measured faster (128 x 128 at 1024 x 4096 x 4096: 41 us as 1 x 4, 47 as 2 x 2).
+struct TileForm {
+  int rows, cols;
+  double stage_us;
+  bool shares_cu;
+};
+constexpr TileForm kTileForms[] = {{256, 256, 1.55, false}, {256, 192, 1.24, false}, {128, 256, 0.83, false}, {128, 128, 0.52, true},
+                                   {96, 128, 0.41, true},   {64, 128, 0.40, true},   {64, 64, 0.22, true},    {32, 64, 0.17, true}};
+constexpr int kTileFormCount = sizeof(kTileForms) / sizeof(kTileForms[0]);
 
-// Streaming wavefronts per workgroup (4 or 3) and cuts of the input dimension for the fast kernel, by a small
+template <int FM, int FN, int WM, int WN, int WD>
+void launch_tile_as(const LinearArgs &a, hipStream_t stream) {
+  using S = TileShape<FM, FN, WM, WN, WD>;
+  const int m_tiles = (a.m + S::kRows - 1) / S::kRows, groups = (a.n_out + S::kCols - 1) / S::kCols;
+  hipLaunchKernelGGL((linear_tile_kernel<FM, FN, WM, WN, WD>), dim3(m_tiles * groups * a.splits), dim3(S::kThreads), 0, stream, a.w, a.x,
+                     a.n_kb, a.splits, a.n_in, a.m, a.n_tiles, m_tiles, groups, a);
+}
+
+hipError_t launch_linear_tile(const LinearArgs &a, int form, hipStream_t stream) {
+  switch (form) {
+    case 0: launch_tile_as<8, 4, 2, 4, 2>(a, stream); break;
+    case 1: launch_tile_as<8, 3, 2, 4, 2>(a, stream); break;
+    case 2: launch_tile_as<8, 2, 1, 8, 2>(a, stream); break;
+    case 3: launch_tile_as<8, 2, 1, 4, 4>(a, stream); break;
+    case 4: launch_tile_as<6, 2, 1, 4, 4>(a, stream); break;
+    case 5: launch_tile_as<4, 2, 1, 4, 4>(a, stream); break;
+    case 6: launch_tile_as<4, 1, 1, 4, 4>(a, stream); break;
+    case 7: launch_tile_as<2, 1, 1, 4, 4>(a, stream); break;
+    default: return hipErrorInvalidValue;
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.splits == 1) return e;
+  launch_reduce(a, stream);
+  return hipGetLastError();
+}
+
+// Which kernel a product runs and how its input dimension is cut, with the time a small model of the launch gives it.
+struct LinearPlan {
+  enum Kind { kSimple, kStaged, kTile } kind;
+  int waves, cuts, form;
+  double us;
+};
+
+// Streaming wavefronts per workgroup (4 or 3) and cuts of the input dimension for the staged kernel, by a small
 // model of the launch, in microseconds:
 //   max(weights / 6.0 MB/us, (weights + rows of x fetched) / 10 MB/us) / fill + second kernel
 // -- the weights come from HBM, they and the rows of x (every workgroup fetches the rows of its stretch:
@@ -689,12 +957,13 @@ hipError_t launch_linear_mf(const LinearArgs &args, int n_tiles, bool fast, int 
 // workgroups per compute unit is not considered (longer-lived workgroups measured faster than more of them).
 // Examples on 256 compute units: 12288 x 4096 -> 3 wavefronts, no cut (256 workgroups); 6144 x 4096 -> 3
 // wavefronts, 2 cuts; 4096 x 4096 and 4096 x 16384 -> 4 wavefronts, 4 cuts; 16384 x 4096 -> 4, none.
-// Cuts 0: not a shape for the fast kernel.
-void linear_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int *waves, int *cuts) {
-  *waves = 4;
-  *cuts = 0;
+// Cuts 0: not a shape for the staged kernel.  `us` is the plan's time with 13 MB/us through the L2s, which is what the
+// kernel gets from 129 rows on (16384 x 4096 at 192 rows: 43 us, 4096 x 16384: 53).
+LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
+  LinearPlan plan = {LinearPlan::kStaged, 4, 0, 0, 0.0};
+  if (m > OKV_LINEAR_MAX_ROWS_STAGED) return plan;
   const int chunk = lin_chunk((m + 15) / 16), pace = lin_weight_lead((m + 15) / 16);
-  if (n_in % (32 * chunk * pace)) return;
+  if (n_in % (32 * chunk * pace)) return plan;
   const int chunks = n_in / (32 * chunk);
   const double weight_mb = (double)n_out * n_in * 2 / 1e6;
   double best = 0;
@@ -708,31 +977,66 @@ void linear_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int *wav
       if (s > 1 && wgs > 2 * (int64_t)n_cus) break;
       const int64_t rounds = (wgs + n_cus - 1) / n_cus;
       const double fill = (double)wgs / (double)(rounds * n_cus);
-      double t = std::max(weight_mb / 6.0, (weight_mb + x_mb) / 10.0) / fill;
-      if (s > 1) t += 4.5 + 2.0 * s * m * n_out * 4 / 1e6 / 3.0;
-      if (*cuts == 0 || t < best * 0.98) {                      // on a near tie the first one found: 4 wavefronts, fewer cuts
+      const double second = s > 1 ? 4.5 + 2.0 * s * m * n_out * 4 / 1e6 / 3.0 : 0.0;
+      const double t = std::max(weight_mb / 6.0, (weight_mb + x_mb) / 10.0) / fill + second;
+      if (plan.cuts == 0 || t < best * 0.98) {                  // on a near tie the first one found: 4 wavefronts, fewer cuts
         best = t;
-        *waves = w;
-        *cuts = s;
+        plan.waves = w;
+        plan.cuts = s;
+        plan.us = std::max(weight_mb / 6.0, (weight_mb + x_mb) / 13.0) / fill + second;
       }
     }
   }
+  return plan;
 }
+
+// The tile kernel's form and cuts: 4 us for the launch, the weights at 12 MB/us (the part of their way from HBM that
+// the walk does not hide: the same tiles take 6-12 us longer with 134 MB of weights than with 33), the walk, and for a
+// cut 3.5 us and the shares at 5 MB/us (written and read back).  Forms of which a compute unit holds several
+// workgroups are taken half way between whole and broken rounds.
+LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
+  LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
+  const int stages = (n_in + 63) / 64;
+  const double weight_mb = (double)n_out * n_in * 2 / 1e6;
+  for (int f = 0; f < kTileFormCount; ++f) {
+    const TileForm &form = kTileForms[f];
+    const int64_t tiles = (int64_t)((m + form.rows - 1) / form.rows) * ((n_out + form.cols - 1) / form.cols);
+    for (int s = 1; s <= 8; ++s) {
+      if (s > 1 && (stages / s < 4 || (int64_t)s * m * n_out * 4 > workspace_bytes)) break;
+      const double q = (double)(tiles * s) / n_cus, whole = std::ceil(q);
+      const double rounds = form.shares_cu ? 0.5 * (whole + std::max(1.0, q)) : whole;
+      double t = 4.0 + weight_mb / 12.0 + rounds * ((stages + s - 1) / s) * form.stage_us;
+      if (s > 1) t += 3.5 + (double)s * m * n_out * 4 / 5e6;
+      if (plan.cuts == 0 || t < plan.us) plan.us = t, plan.form = f, plan.cuts = s;
+    }
+  }
+  return plan;
+}
+
+// The kernel for a product.  Up to OKV_LIN_SIMPLE_ROWS rows the simple one.  Else the staged one where it takes the
+// shape, unless the tile kernel is faster by more than the models are good for: it is from about 130 rows on where
+// the inputs are many and the features few (4096 x 16384 at 192 rows: 45 us against 53; 12288 x 4096: 39 against
+// 37, which stays), and always beyond the staged kernel's 192 rows.  Where the staged kernel does not take the shape (inputs
+// not a multiple of its chunks, or a cut without a workspace) the simple kernel's time follows the row fragments and
+// the blocks of a wavefront: 1056 x 4224 takes it 13.4 us at 32 rows, 21.9 at 64 and 37.6 at 128, the tile kernel 8.1, 9.7
+// and 11.3; at 1056 x 1056 and 32 rows 4.6 against 6.2.
+LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
+  const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0};
+  if (m <= OKV_LIN_SIMPLE_ROWS) return simple;
+  const LinearPlan staged = staged_plan(m, n_out, n_in, n_cus), tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
+  if (staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes))
+    return tile.us < 0.95 * staged.us ? tile : staged;
+  if (m > OKV_LINEAR_MAX_ROWS) return tile;
+  const double simple_us = 2.0 + n_in / 128.0 * (0.09 + 0.12 * ((m + 15) / 16)) * std::max(1.0, n_out / 16 / (0.5 * n_cus));
+  return tile.us < simple_us ? tile : simple;
+}
+
+}  // namespace
 
 int64_t linear_workspace_bytes(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
-  int waves = 4, s = 0;
-  if (m > OKV_LIN_SIMPLE_ROWS) linear_plan(m, n_out, n_in, n_cus, &waves, &s);
-  return s < 1 ? 0 : (int64_t)s * m * n_out * 4;        // a single cut still goes through a share when a layer norm follows
-}
-
-// Whether one launch of the staged kernel takes m rows of this product with the workspace at hand (the only
-// kernel there is for more than OKV_LINEAR_MAX_ROWS rows).
-bool linear_staged_takes(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, bool have_workspace, int64_t workspace_bytes) {
-  if (m <= OKV_LIN_SIMPLE_ROWS || m > OKV_LINEAR_MAX_ROWS_STAGED) return false;
-  int waves = 4, s = 0;
-  linear_plan(m, n_out, n_in, n_cus, &waves, &s);
-  if (s < 1) return false;
-  return s == 1 || (have_workspace && workspace_bytes >= (int64_t)s * m * n_out * 4);
+  const LinearPlan plan = choose_linear(m, n_out, n_in, n_cus, INT64_MAX);
+  // a single cut of the staged kernel still goes through a share when a layer norm follows
+  return plan.kind == LinearPlan::kStaged || plan.cuts > 1 ? (int64_t)plan.cuts * m * n_out * 4 : 0;
 }
 
 hipError_t launch_linear(const LinearLaunch &l, hipStream_t stream) {
@@ -751,42 +1055,40 @@ hipError_t launch_linear(const LinearLaunch &l, hipStream_t stream) {
   const int n_tiles = l.n_out / 16;
   a.n_tiles = n_tiles;
   a.n_out = l.n_out;
-  a.splits = 1;
-  a.shares = nullptr;
   a.to_shares = 0;
   a.ln_gamma = static_cast<const _Float16 *>(l.ln_gamma);
   a.ln_beta = static_cast<const _Float16 *>(l.ln_beta);
   a.ln_out = nullptr;
   a.ln_eps = l.ln_eps;
-  bool fast = false;
-  int fast_waves = 4, s = 0;
-  linear_plan(l.m, l.n_out, l.n_in, l.n_cus, &fast_waves, &s);
-  if (l.m > OKV_LIN_SIMPLE_ROWS && (s == 1 || (s > 1 && l.workspace && l.workspace_bytes >= linear_workspace_bytes(l.m, l.n_out, l.n_in, l.n_cus)))) {
-    fast = true;
-    a.splits = s;
-    a.shares = static_cast<float *>(l.workspace);
-  }
-  // a layer norm of the result rides on the share reduction when there is one to ride on
-  const bool fuse_ln = l.ln_out && fast && l.n_seg == 1 && l.n_out <= kLnMaxWidth && l.workspace &&
-                       l.workspace_bytes >= (int64_t)a.splits * l.m * l.n_out * 4;
+  const int64_t have = l.workspace ? l.workspace_bytes : 0;
+  const LinearPlan plan = choose_linear(l.m, l.n_out, l.n_in, l.n_cus, have);
+  const bool fast = plan.kind == LinearPlan::kStaged;
+  a.splits = plan.kind == LinearPlan::kSimple ? 1 : plan.cuts;
+  a.shares = static_cast<float *>(l.workspace);
+  // a layer norm of the result rides on the share reduction when there is one to ride on (the staged kernel then writes
+  // its share also when there is a single cut; with the tile kernel's hundreds of rows a pass of its own over the fp16
+  // result moves less than fp32 shares would)
+  const bool fuse_ln = l.ln_out && l.n_seg == 1 && l.n_out <= kLnMaxWidth && (fast || a.splits > 1) &&
+                       have >= (int64_t)a.splits * l.m * l.n_out * 4;
   if (fuse_ln) {
     a.to_shares = 1;
     a.ln_out = static_cast<_Float16 *>(l.ln_out);
   }
   hipError_t e = hipErrorInvalidValue;
-  switch ((l.m + 15) / 16) {
-    case 1: e = launch_linear_mf<1>(a, n_tiles, fast, fast_waves, stream); break;
-    case 2: e = launch_linear_mf<2>(a, n_tiles, fast, fast_waves, stream); break;
-    case 3: e = launch_linear_mf<3>(a, n_tiles, fast, fast_waves, stream); break;
-    case 4: e = launch_linear_mf<4>(a, n_tiles, fast, fast_waves, stream); break;
-    case 5: e = launch_linear_mf<5>(a, n_tiles, fast, fast_waves, stream); break;
-    case 6: e = launch_linear_mf<6>(a, n_tiles, fast, fast_waves, stream); break;
-    case 7: e = launch_linear_mf<7>(a, n_tiles, fast, fast_waves, stream); break;
-    case 8: e = launch_linear_mf<8>(a, n_tiles, fast, fast_waves, stream); break;
-    case 9: e = launch_linear_mf<9>(a, n_tiles, fast, fast_waves, stream); break;
-    case 10: e = launch_linear_mf<10>(a, n_tiles, fast, fast_waves, stream); break;
-    case 11: e = launch_linear_mf<11>(a, n_tiles, fast, fast_waves, stream); break;
-    case 12: e = launch_linear_mf<12>(a, n_tiles, fast, fast_waves, stream); break;
+  if (plan.kind == LinearPlan::kTile) e = launch_linear_tile(a, plan.form, stream);
+  else switch ((l.m + 15) / 16) {
+    case 1: e = launch_linear_mf<1>(a, n_tiles, fast, plan.waves, stream); break;
+    case 2: e = launch_linear_mf<2>(a, n_tiles, fast, plan.waves, stream); break;
+    case 3: e = launch_linear_mf<3>(a, n_tiles, fast, plan.waves, stream); break;
+    case 4: e = launch_linear_mf<4>(a, n_tiles, fast, plan.waves, stream); break;
+    case 5: e = launch_linear_mf<5>(a, n_tiles, fast, plan.waves, stream); break;
+    case 6: e = launch_linear_mf<6>(a, n_tiles, fast, plan.waves, stream); break;
+    case 7: e = launch_linear_mf<7>(a, n_tiles, fast, plan.waves, stream); break;
+    case 8: e = launch_linear_mf<8>(a, n_tiles, fast, plan.waves, stream); break;
+    case 9: e = launch_linear_mf<9>(a, n_tiles, fast, plan.waves, stream); break;
+    case 10: e = launch_linear_mf<10>(a, n_tiles, fast, plan.waves, stream); break;
+    case 11: e = launch_linear_mf<11>(a, n_tiles, fast, plan.waves, stream); break;
+    case 12: e = launch_linear_mf<12>(a, n_tiles, fast, plan.waves, stream); break;
   }
   if (e != hipSuccess || !l.ln_out || fuse_ln) return e;
   return launch_layernorm(l.out[0], l.ln_gamma, l.ln_beta, l.ln_out, l.m, l.n_out, l.ln_eps, stream);   // the same in two steps
