@@ -1013,19 +1013,22 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
   return plan;
 }
 
-// The kernel for a product.  Up to OKV_LIN_SIMPLE_ROWS rows the simple one.  Else the staged one where it takes the
-// shape, unless the tile kernel is faster by more than the models are good for: it is from about 130 rows on where
-// the inputs are many and the features few (4096 x 16384 at 192 rows: 45 us against 53; 12288 x 4096: 39 against
-// 37, which stays), and always beyond the staged kernel's 192 rows.  Where the staged kernel does not take the shape (inputs
-// not a multiple of its chunks, or a cut without a workspace) the simple kernel's time follows the row fragments and
-// the blocks of a wavefront: 1056 x 4224 takes it 13.4 us at 32 rows, 21.9 at 64 and 37.6 at 128, the tile kernel 8.1, 9.7
-// and 11.3; at 1056 x 1056 and 32 rows 4.6 against 6.2.
+// The kernel for a product.  Up to OKV_LIN_SIMPLE_ROWS rows the simple one.  Up to OKV_LINEAR_MAX_ROWS rows the staged one
+// where it takes the shape (12288 x 4096 at 128 rows 28 us against the tile kernel's 31, 16384 x 4096 35 against 38; where the
+// inputs are many the tile kernel would win, 4096 x 16384 at 128 rows 35 against 43, with twice the cuts and so twice the
+// workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
+// for (4096 x 16384 at 192 rows: 45 us against 53, tiles; 12288 x 4096: 39 against 37, staged), beyond always the tile
+// kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
+// workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront: 4224 x 1056 takes it 7.6 us
+// at 32 rows, 11.6 at 64 and 17.9 at 128, the tile kernel 7.2, 9.0 and 8.9; at 1056 x 1056 and 32 rows 4.6 against 6.2.
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0};
   if (m <= OKV_LIN_SIMPLE_ROWS) return simple;
-  const LinearPlan staged = staged_plan(m, n_out, n_in, n_cus), tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
-  if (staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes))
-    return tile.us < 0.95 * staged.us ? tile : staged;
+  const LinearPlan staged = staged_plan(m, n_out, n_in, n_cus);
+  const bool staged_runs = staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes);
+  if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return staged;
+  const LinearPlan tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
+  if (staged_runs) return tile.us < 0.95 * staged.us ? tile : staged;
   if (m > OKV_LINEAR_MAX_ROWS) return tile;
   const double simple_us = 2.0 + n_in / 128.0 * (0.09 + 0.12 * ((m + 15) / 16)) * std::max(1.0, n_out / 16 / (0.5 * n_cus));
   return tile.us < simple_us ? tile : simple;
@@ -1034,7 +1037,8 @@ LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, 
 }  // namespace
 
 int64_t linear_workspace_bytes(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
-  const LinearPlan plan = choose_linear(m, n_out, n_in, n_cus, INT64_MAX);
+  // up to OKV_LINEAR_MAX_ROWS rows a shape that the staged kernel does not take asks for none
+  const LinearPlan plan = choose_linear(m, n_out, n_in, n_cus, m > OKV_LINEAR_MAX_ROWS || staged_plan(m, n_out, n_in, n_cus).cuts ? INT64_MAX : 0);
   // a single cut of the staged kernel still goes through a share when a layer norm follows
   return plan.kind == LinearPlan::kStaged || plan.cuts > 1 ? (int64_t)plan.cuts * m * n_out * 4 : 0;
 }
