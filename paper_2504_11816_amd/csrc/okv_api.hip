@@ -124,6 +124,7 @@ struct okv_ctx {
   int32_t max_groups = 1;                // wavefronts of a launch per KV head
   int32_t *d_items_dump = nullptr;
   int32_t max_waves = 0;                 // wavefronts of the persistent attention launch
+  bool keep_cached = true;               // the batch's keys and values of all layers fit the memory-side cache
   int64_t max_items = 0;
   float *part_o = nullptr, *part_ml = nullptr;
 
@@ -276,6 +277,7 @@ okv::AttnLaunch base_launch(okv_ctx *ctx) {
   a.part_ml = ctx->part_ml;
   a.out_fp32 = ctx->cfg.out_dtype;
   a.need_merge = ctx->need_merge;
+  a.keep_cached = ctx->keep_cached;
   if (ctx->spans) {
     a.pair_head = ctx->d_pair_head;
     a.n_groups = ctx->n_groups;
@@ -484,6 +486,9 @@ int exec_ops(okv_ctx *ctx, const std::vector<Op> &ops, const void *a0, const voi
 // Recomputes split size, item count and merge flag from the host lengths and
 // rebuilds the device work list (adding `inc` to every device length first).
 int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false) {
+  int64_t keys = 0;
+  for (int32_t b = 0; b < ctx->B; ++b) keys += ctx->h_ctx_lens[b];
+  ctx->keep_cached = keys * ctx->cfg.n_kv_heads * ctx->cfg.head_dim * 4 * ctx->cfg.n_layers <= okv::kKeepCachedBytes;
   if (upload_lens) {
     // the device lengths are replaced by the host's (after a bulk store); h_ctx_lens is pageable
     // memory, so the copy is over when the call returns, and the kernels below are enqueued after it
@@ -1995,6 +2000,9 @@ int okv_decode_attn_static(const okv_static_attn *a) {
   l.part_ml = reinterpret_cast<float *>(base + lay.part_ml);
   l.out_fp32 = a->out_dtype;
   l.need_merge = 1;
+  // neither the lengths nor the number of layers is known here: a layer that may hold half of the memory-side cache
+  // and more is taken for one of a stack that does not fit it
+  l.keep_cached = (int64_t)a->B * cap_tokens_of(&c) * G * D * 4 <= okv::kKeepCachedBytes / 2;
   l.pair_head = pair_head;
   l.n_groups = max_groups;
   l.n_groups_dev = plan;                                 // the kernel reads how many stretches are in use

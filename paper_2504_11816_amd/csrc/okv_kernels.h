@@ -42,6 +42,7 @@ struct AttnLaunch {
   float *part_ml;          // [n_items * H][2]  (max in log2 units, sum)
   int32_t out_fp32;
   int32_t need_merge;      // some sequence has more than one item
+  int32_t keep_cached = 1; // the KV of all layers fits the memory-side cache: loads that keep it there
   // How the launch's items are shared out.  pair_head NULL: every item is a group of its own, and the (item, KV
   // head) pairs are dealt out to the wavefronts round robin.  Else the records launch_step_advance_spans wrote
   // for pools of this shape: stretch j is a group of consecutive items, record j * G + g says what the wavefront
@@ -62,6 +63,10 @@ struct AttnLaunch {
   // in slot 2 b + (j & 1)); the appended rows go there and not across the link.
   int32_t mirror_is_tail = 0;
 };
+
+// Up to this many bytes of keys and values (over all layers that a step reads) launches keep them cached: the
+// memory-side cache of MI355X (see load_kv for both sides measured).
+constexpr int64_t kKeepCachedBytes = 256000000;
 
 // Store of the step's K/V rows and split-K partial attention over the launch's items.
 hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream,

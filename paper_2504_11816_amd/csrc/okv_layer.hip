@@ -129,7 +129,22 @@ __device__ __forceinline__ floatx4 mfma32(const uint4 a, const uint4 b, floatx4 
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
 }
 
-template <int MF>
+// 16 bytes of a weight matrix.  NT: a load that asks the caches not to keep the line.  A step reads every weight once
+// and a model with matrices of this size does not fit the memory-side cache (256 MiB), so what is kept is gone before it
+// is wanted again: from HBM, 16384 x 4096 takes 25.1 -> 22.6 us at 4 rows (5.9 TB/s), 27.0 -> 25.0 at 32, 33.8 -> 32.2 at 96;
+// 4096 x 16384 24.5 -> 22.4, 28.9 -> 26.4, 35.9 -> 34.6.  (The same matrix again and again, which stays cached: 20.9 -> 21.1, 23.0 ->
+// 23.8.)  Not for matrices below these sizes, which a small model may keep cached (2048 x 2048 at 4 rows: 3.8 us kept, 4.6
+// not), nor beyond 128 rows, where row tiles share a weight or the time follows x (4096 x 16384 at 192 rows: 48.9 -> 50.9;
+// 33 MB matrices lose from 64 rows on: 4096 x 4096 at 128 rows 15.9 -> 17.9).
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+template <bool NT>
+__device__ __forceinline__ uint4 load_weight(const uint4 *p) {
+  if constexpr (NT) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)));
+  else return *p;
+}
+constexpr int64_t kStreamSimpleBytes = 32 << 20, kStreamStagedBytes = 64 << 20;
+
+template <int MF, bool NT>
 __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, const uint4 *x, const int32_t n_kb,
                                                                    const int32_t n_in, const int32_t m, const LinearArgs a) {
   // (leading parameters: in scalar registers when the wavefront starts, see linear_lds_kernel)
@@ -164,7 +179,7 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
   auto load = [&](int slot, int k) {                           // k: position in this wavefront's walk
     int kk = k + rot;
     kk = kk >= nk ? kk - nk : kk;                              // block index relative to kb0
-    wbuf[slot] = wp[(size_t)kk * 64];
+    wbuf[slot] = load_weight<NT>(wp + (size_t)kk * 64);
 #pragma unroll
     for (int f = 0; f < MF; ++f) xbuf[slot][f] = xp[f][(size_t)kk * 4];
   };
@@ -258,7 +273,7 @@ constexpr int vmcnt_only(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >
 // up to 128 registers cost nothing (256 with more than 8 row fragments, whose accumulators and operand registers
 // need them: a SIMD holds two of the workgroup's six wavefronts at most); without the hint the compiler aimed
 // at the occupancy the launch bounds allow and capped the kernel at 64.
-template <int MF, int NW>
+template <int MF, int NW, bool NT>
 __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_waves_per_eu(1, MF > 8 ? 2 : 4))) void linear_lds_kernel(
     const uint4 *w, const uint4 *x, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
     const int32_t n_tiles, const LinearArgs a) {
@@ -369,7 +384,7 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
     for (int u = 0; u < WD; ++u)
 #pragma unroll
       for (int i = 0; i < C; ++i) {                          // oldest first: the loop waits for them in this order
-        wbuf[u][i] = wp[((size_t)ahead(u) * C + i) * 64];
+        wbuf[u][i] = load_weight<NT>(wp + ((size_t)ahead(u) * C + i) * 64);
         __builtin_amdgcn_sched_barrier(0);
       }
     __syncthreads();
@@ -397,7 +412,7 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
 #pragma unroll
           for (int f = 0; f < MF; ++f) acc[f] = mfma32(xr[i & 1][f], w, acc[f]);
           __builtin_amdgcn_sched_barrier(0);
-          wbuf[u][i] = wp[((size_t)cn * C + i) * 64];
+          wbuf[u][i] = load_weight<NT>(wp + ((size_t)cn * C + i) * 64);
           __builtin_amdgcn_sched_barrier(0);
         }
         buf = buf + 1 == NBUF ? 0 : buf + 1;
@@ -875,22 +890,35 @@ void launch_reduce(const LinearArgs &args, hipStream_t stream) {
                        args.n_out, args.splits, args.m, args);
 }
 
+template <int MF, int NW, bool NT>
+void launch_staged_as(const LinearArgs &args, int n_tiles, hipStream_t stream) {
+  hipLaunchKernelGGL((linear_lds_kernel<MF, NW, NT>), dim3((n_tiles + NW - 1) / NW, args.splits), dim3((NW + lin_stagers(MF)) * 64), 0, stream,
+                     args.w, args.x, args.n_kb, args.splits, args.n_in, args.m, args.n_tiles, args);
+}
+
+template <int MF, int NW>
+void launch_staged(const LinearArgs &args, int n_tiles, hipStream_t stream) {
+  if constexpr (MF <= OKV_LINEAR_MAX_ROWS / 16) {
+    if ((int64_t)args.n_out * args.n_in * 2 >= kStreamStagedBytes) return launch_staged_as<MF, NW, true>(args, n_tiles, stream);
+  }
+  launch_staged_as<MF, NW, false>(args, n_tiles, stream);
+}
+
 template <int MF>
 hipError_t launch_linear_mf(const LinearArgs &args, int n_tiles, bool fast, int fast_waves, hipStream_t stream) {
   if (fast) {
-    dim3 grid((n_tiles + fast_waves - 1) / fast_waves, args.splits);
-    if (fast_waves == 3) hipLaunchKernelGGL((linear_lds_kernel<MF, 3>), grid, dim3((3 + lin_stagers(MF)) * 64), 0, stream, args.w, args.x, args.n_kb,
-                                           args.splits, args.n_in, args.m, args.n_tiles, args);
-    else hipLaunchKernelGGL((linear_lds_kernel<MF, 4>), grid, dim3((4 + lin_stagers(MF)) * 64), 0, stream, args.w, args.x, args.n_kb,
-                            args.splits, args.n_in, args.m, args.n_tiles, args);
+    fast_waves == 3 ? launch_staged<MF, 3>(args, n_tiles, stream) : launch_staged<MF, 4>(args, n_tiles, stream);
     if (args.splits > 1 || args.to_shares) {
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       launch_reduce(args, stream);
     }
   } else if constexpr (MF <= OKV_LINEAR_MAX_ROWS / 16) {
-    hipLaunchKernelGGL(linear_kernel<MF>, dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.n_kb, args.n_in,
-                       args.m, args);
+    const bool stream_w = MF == 1 && args.m <= OKV_LIN_SIMPLE_ROWS && (int64_t)args.n_out * args.n_in * 2 >= kStreamSimpleBytes;
+    if (stream_w) hipLaunchKernelGGL((linear_kernel<1, true>), dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.n_kb,
+                                     args.n_in, args.m, args);
+    else hipLaunchKernelGGL((linear_kernel<MF, false>), dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.n_kb, args.n_in,
+                            args.m, args);
   } else {
     return hipErrorInvalidValue;                       // more than OKV_LINEAR_MAX_ROWS rows: the staged or the tile kernel only
   }
