@@ -651,14 +651,27 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
 // One wavefront per (b, h).  The items of a sequence are one contiguous range of the list per
 // block class.  Lane c first fetches (m_c, l_c) of item c, so the maxima and weights of up to
 // 64 items are formed by wavefront reductions instead of a chain of dependent loads; the
-// weighted sums then stream the partial rows four items at a time.
+// weighted sums then stream the partial rows four items at a time.  The launch is all latency (5 us for the 2000
+// items of a ragged batch): the rows of the first four items are asked for together with the maxima and weights, so
+// a sequence in at most four pieces waits for two round trips (the item range, then everything) and not for three, and
+// four (b, h) pairs share a workgroup.
 template <int D>
-__global__ __launch_bounds__(64) void attn_merge_kernel(const int32_t *chunk_prefix, const float *part_ml, const int32_t B,
-                                                         const int32_t n_cls, const int32_t H, const AttnArgs a) {
+__global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_prefix, const float *part_ml, const float *part_o,
+                                                          const int32_t B, const int32_t n_cls, const int32_t H, const AttnArgs a) {
   // (leading parameters: in scalar registers when the wavefront starts, so the first look-ups need no round trip
   // to the argument segment; most wavefronts of a launch find a sequence in one piece and leave at once)
   constexpr int EPT = D / 64;
-  const int b = blockIdx.y, h = blockIdx.x, lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int b = blockIdx.y, h = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (h >= H) return;
+  auto row_of = [&](int it) { return part_o + ((size_t)it * H + h) * D + lane * EPT; };
+  const int first0 = chunk_prefix[b], cnt0 = chunk_prefix[b + 1] - first0;
+  if (n_cls == 1 && cnt0 <= 1) return;                 // written by the split kernel
+  float ahead[4][EPT];                                 // rows of the first class's first four items (past its last: that one again)
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) ahead[k][e] = cnt0 > 0 ? row_of(first0 + min(k, cnt0 - 1))[e] : 0.f;
   float M = kNegBig;
   int total = 0;
   for (int cls = 0; cls < n_cls; ++cls) {
@@ -693,13 +706,22 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const int32_t *chunk_pre
       L += lw;
       const int cnt = min(64, n_chunks - c0);
       int i = 0;
+      if (cls == 0 && c0 == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (k < cnt) {
+            const float wk = __shfl(w, k);
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) acc[e] += ahead[k][e] * wk;
+          }
+        i = min(4, cnt);
+      }
       for (; i + 4 <= cnt; i += 4) {                     // four independent rows in flight
         float x[4][EPT];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-          for (int e = 0; e < EPT; ++e)
-            x[k][e] = a.part_o[((size_t)(first + c0 + i + k) * H + h) * D + lane * EPT + e];
+          for (int e = 0; e < EPT; ++e) x[k][e] = row_of(first + c0 + i + k)[e];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const float wk = __shfl(w, i + k);
@@ -710,8 +732,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const int32_t *chunk_pre
       for (; i < cnt; ++i) {
         const float wk = __shfl(w, i);
 #pragma unroll
-        for (int e = 0; e < EPT; ++e)
-          acc[e] += a.part_o[((size_t)(first + c0 + i) * H + h) * D + lane * EPT + e] * wk;
+        for (int e = 0; e < EPT; ++e) acc[e] += row_of(first + c0 + i)[e] * wk;
       }
     }
   }
@@ -839,11 +860,11 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream, hipEvent_
 hipError_t launch_merge(const AttnLaunch &a, hipStream_t stream) {
   const PoolShape &s = a.shape;
   const AttnArgs args = make_args(a);
-  dim3 mgrid(s.H, a.batch.B);
+  dim3 mgrid((s.H + 3) / 4, a.batch.B);
   if (s.D == 128)
-    hipLaunchKernelGGL(attn_merge_kernel<128>, mgrid, dim3(64), 0, stream, args.chunk_prefix, args.part_ml, args.B, args.n_cls, args.H, args);
+    hipLaunchKernelGGL(attn_merge_kernel<128>, mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args);
   else if (s.D == 64)
-    hipLaunchKernelGGL(attn_merge_kernel<64>, mgrid, dim3(64), 0, stream, args.chunk_prefix, args.part_ml, args.B, args.n_cls, args.H, args);
+    hipLaunchKernelGGL(attn_merge_kernel<64>, mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
