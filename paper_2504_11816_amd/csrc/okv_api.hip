@@ -281,6 +281,7 @@ okv::AttnLaunch base_launch(okv_ctx *ctx) {
   if (ctx->spans) {
     a.pair_head = ctx->d_pair_head;
     a.n_groups = ctx->n_groups;
+    a.waves_per_pair = okv::waves_per_pair(a.shape.D, a.shape.G, ctx->B, ctx->cap_tokens, ctx->max_groups, kMinSpanTiles);
   }
   a.max_waves = ctx->max_waves;
   a.item_first = 0;
@@ -2005,6 +2006,7 @@ int okv_decode_attn_static(const okv_static_attn *a) {
   l.keep_cached = (int64_t)a->B * cap_tokens_of(&c) * G * D * 4 <= okv::kKeepCachedBytes / 2;
   l.pair_head = pair_head;
   l.n_groups = max_groups;
+  l.waves_per_pair = okv::waves_per_pair(D, G, a->B, cap_tokens_of(&c), max_groups, kMinSpanTiles);
   l.n_groups_dev = plan;                                 // the kernel reads how many stretches are in use
   l.max_waves = max_waves;
   l.item_first = 0, l.item_count = (int32_t)max_items;

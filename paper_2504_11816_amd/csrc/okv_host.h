@@ -175,6 +175,26 @@ __host__ __device__ inline SpanPlan span_plan(int64_t total_tiles, int32_t max_g
   return p;
 }
 
+// Wavefronts that share a (stretch, KV head) pair of an attention launch with equal stretches: 1, 2 or 4.  More of them
+// shorten the chain of tiles per wavefront, which is what short launches and short items cost; on long launches of
+// uncut sequences at d = 128 one wavefront per pair already draws what the memory gives, and two are slower.  Measured on
+// MI355X, us a layer with 1 and 2 wavefronts (4 in brackets):
+//   d = 64    24 ragged sequences of 190..1150 keys, 32 heads: 32.0, 29.2 (31.4); 16 x 300 keys, 12 heads: 14.8, 12.4
+//             (12.8); 64 x 1024, 32 heads: 95.8, 92.8; 64 x 1500 contiguous: 129, 133-142
+//   d = 128   4 x 256 keys, 8 heads: 14.9, 12.3 (10.3); one sequence of 2048, 32 heads: 17.9, 15.4 (14.6); 32 x 1100, 2 heads:
+//             19.7, 16.9 (16.4); 32 x 660, 128 / 8 heads: 29.8, 27.4 (31.1); 64 x 2048, 64 / 8 heads: 99.9, 97.4; 128 x 290,
+//             32 / 8 heads: 37.6, 35.6; 32 x 512, 32 heads: 48.4, 48.9; 32 x 768, 32 heads: 64, 65-71
+// The choice may depend on nothing but what every entry point knows (okv_decode_attn_static does not know the lengths),
+// or the same step would be summed in another order there: so on the batch, the shape and the capacity, as if every
+// sequence were at it.  A batch that is a multiple of the stretches is cut least (not at all where lengths are equal).
+inline int32_t waves_per_pair(int32_t D, int32_t G, int32_t B, int64_t cap_tokens, int32_t max_groups, int32_t min_span) {
+  const int64_t tiles = (int64_t)B * ((cap_tokens + 15) >> 4);
+  const SpanPlan p = span_plan(tiles, max_groups, min_span);
+  if (D == 64) return p.span <= 128 ? 2 : 1;
+  if ((int64_t)p.n_groups * G <= 600) return 4;
+  return p.span <= (B % max_groups ? 96 : 40) ? 2 : 1;
+}
+
 // Pieces of a sequence whose tiles are [first, first + tiles) of the stream: it is cut at the multiples
 // of span strictly inside that range.  *k0 receives the first such multiple's index, so that piece c >= 1
 // starts at tile (k0 + c - 1) * span of the stream and piece c ends where piece c + 1 starts.

@@ -42,6 +42,7 @@ struct AttnLaunch {
   float *part_ml;          // [n_items * H][2]  (max in log2 units, sum)
   int32_t out_fp32;
   int32_t need_merge;      // some sequence has more than one item
+  int32_t waves_per_pair = 1;  // with pair_head: wavefronts that share a (stretch, KV head) pair (1, 2 or 4)
   int32_t keep_cached = 1; // the KV of all layers fits the memory-side cache: loads that keep it there
   // How the launch's items are shared out.  pair_head NULL: every item is a group of its own, and the (item, KV
   // head) pairs are dealt out to the wavefronts round robin.  Else the records launch_step_advance_spans wrote

@@ -265,11 +265,11 @@ __device__ __forceinline__ void tile_update_mfma(const half8_t (&qb)[D / 32], fl
 // for the 32 keys, and the weighted sum as 16 x 16 x 32 products.  Lane (quarter, rho) holds, of head rho, the
 // scores of keys 4 quarter .. + 3 of either tile; taken in that order (first tile's four, then the second's) they
 // are the eight key slots 8 quarter .. + 7 of the B operand of the second product, and its A operand, V^T,
-// is gathered from the same rows in the same order.  valid1 = 0: the second tile is not the item's (its
+// is gathered from the same rows in the same order.  The second tile begins tok_step tokens after the first.  valid1 = 0: the second tile is not the item's (its
 // buffer holds the last tile once more): every key of it is masked out.
 __device__ __forceinline__ void tile_update_pair(const half8_t (&qb)[2], float &m, float &l, floatx4_t (&o)[4],
                                                  const char *ks, const char *vs, const int lane, const int tok_tile,
-                                                 const bool valid1, const int lo, const int hi, const float scale,
+                                                 const int tok_step, const bool valid1, const int lo, const int hi, const float scale,
                                                  const bool masked) {
   constexpr int D = 64, S = lds_row_bytes<D>();
   const int quarter = lane >> 4, rho = lane & 15;
@@ -284,7 +284,7 @@ __device__ __forceinline__ void tile_update_pair(const half8_t (&qb)[2], float &
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int tok = tok_tile + 16 * h + 4 * quarter + r;
+      const int tok = tok_tile + tok_step * h + 4 * quarter + r;
       const bool in = (!masked || (tok >= lo && tok < hi)) && (h == 0 || valid1);
       s[4 * h + r] = in ? acc[r] * scale : -__builtin_inff();
     }
@@ -365,16 +365,26 @@ struct Unit {
 // everything else (the other arguments, the LDS addresses, the zeroed sums) is set up behind them.  Without
 // it (a split size fixed by the caller, block classes, more pairs than wavefronts) pairs are dealt out
 // round robin and the first item is found through group_first, the item list and the block table.
-template <int D, bool PAGED, int PIPE, bool HEADS, bool NT>
-__global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
+//
+// NS > 1 (with HEADS): a (stretch, KV head) pair has a workgroup of NS wavefronts to itself, which take the tiles of an item
+// in turn (wavefront s the tiles s, s + NS, ...) and put their sums together through LDS at the item's end ([B]).  Where
+// there are fewer pairs than the memory system wants wavefronts, or where items are short, what a launch takes is a
+// chain of tiles per wavefront, each a round trip to memory and through LDS; NS wavefronts shorten the chain without
+// cutting the keys any finer, so without more partial results or a merge (see waves_per_pair for when).
+template <int D, bool PAGED, int PIPE, bool HEADS, bool NT, int NS>
+__global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_split_mfma_kernel(
     const PairHead *pair_head, const uint16_t *pool, const uint16_t *q, const int32_t *n_groups_dev, const int32_t n_groups,
     const int32_t G, const int32_t H, const int32_t R, const int32_t v_tiles, const AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) char lds_all[kWavesPerBlock][2 * lds_tiles<D>() * lds_tile_bytes<D>()];
+  static_assert(NS == 1 || HEADS, "several wavefronts per pair need the table of heads");
+  constexpr int kRegion = 2 * lds_tiles<D>() * lds_tile_bytes<D>();     // LDS of a wavefront
+  static_assert(kRegion >= D / 16 * 1024 + 512, "a wavefront's sums, maxima and weights must fit its tiles' place");
+  __shared__ __attribute__((aligned(16))) char lds_all[NS > 1 ? NS : kWavesPerBlock][kRegion];
   constexpr int LPR = D / 8, RPL = 64 / LPR, LPT = D / 32;
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t n_waves = gridDim.x * kWavesPerBlock;
-  uint32_t pair = blockIdx.x * kWavesPerBlock + wave;    // of the unit N below
+  const int sub = NS > 1 ? (int)wave : 0;                // which of the pair's wavefronts this is
+  uint32_t pair = NS > 1 ? blockIdx.x : blockIdx.x * kWavesPerBlock + wave;    // of the unit N below
   // With a table of heads every (stretch, KV head) pair has a wavefront of its own and its head says what
   // the pair starts with; otherwise pairs are dealt out round robin.  The number of groups is a launch
   // argument, or (for callers that do not know the batch's lengths on the host) what the bookkeeping kernel
@@ -437,23 +447,22 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
                                                          // head rho, dims 32 c + 8 quarter .. + 7 (columns past the group's heads:
                                                          // head 0's, zeroed where the unit takes q over)
   if (by_head) {
-    // the first unit's first tiles and its q straight from the head, before anything else is set up
+    // the first unit's first tiles and its q straight from the head, before anything else is set up (the record
+    // holds the places of the item's first two tiles; the others the long way)
+    const int g0 = head.flags_g >> 8, last0 = (head.hi - 1) >> 4;
 #pragma unroll
-    for (int i = 0; i < (PIPE < 2 ? PIPE : 2); ++i) {
-      const uint4 *kp = reinterpret_cast<const uint4 *>(pool + (size_t)(uint32_t)(i ? head.base1 : head.base0) * (16 * D)) + lane;
-      const uint4 *vp = kp + ((size_t)v_tiles * (16 * D) * 2 / 16);
+    for (int i = 0; i < PIPE; ++i) {
+      const int k = sub + i * NS;                        // (with one wavefront per pair known at compile time)
+      if (k < 2) {
+        const uint4 *kp = reinterpret_cast<const uint4 *>(pool + (size_t)(uint32_t)(k ? head.base1 : head.base0) * (16 * D)) + lane;
+        const uint4 *vp = kp + ((size_t)v_tiles * (16 * D) * 2 / 16);
 #pragma unroll
-      for (int j = 0; j < LPT; ++j) buf[i].k[j] = load_kv<NT>(kp + j * 64);
+        for (int j = 0; j < LPT; ++j) buf[i].k[j] = load_kv<NT>(kp + j * 64);
 #pragma unroll
-      for (int j = 0; j < LPT; ++j) buf[i].v[j] = load_kv<NT>(vp + j * 64);
-    }
-    if (PIPE > 2) {                                      // the record holds two places: the deeper buffers the long way
-      const int g0 = head.flags_g >> 8, last0 = (head.hi - 1) >> 4;
-      const TileAddr ta0 = tile_addr<D>(G, a.gg, a.tcap, a.st_log2, g0);
-#pragma unroll
-      for (int i = 2; i < PIPE; ++i) {
-        const int tile = min((head.lo >> 4) + i, last0);
-        load_tile(buf[i], ta0, tile, blk_of(head.b, tile));
+        for (int j = 0; j < LPT; ++j) buf[i].v[j] = load_kv<NT>(vp + j * 64);
+      } else {
+        const int tile = min((head.lo >> 4) + k, last0);
+        load_tile(buf[i], tile_addr<D>(G, a.gg, a.tcap, a.st_log2, g0), tile, blk_of(head.b, tile));
       }
     }
     const uint4 *qp = reinterpret_cast<const uint4 *>(q + ((size_t)head.b * H + (size_t)(head.flags_g >> 8) * R + (rho < R ? rho : 0)) * D + 8 * quarter);
@@ -488,7 +497,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
         const const_i32_ptr dp = (const_i32_ptr)(uintptr_t)(a.item_desc + N.it);
         N.b = dp[0], N.lo = dp[1], N.hi = dp[2], N.flags = dp[3];
 #pragma unroll
-        for (int i = 0; i < PIPE; ++i) N.blk0[i] = blk_of(N.b, min((N.lo >> 4) + i, (N.hi - 1) >> 4));
+        for (int i = 0; i < PIPE; ++i) N.blk0[i] = blk_of(N.b, min((N.lo >> 4) + sub + i * NS, (N.hi - 1) >> 4));
       }
     }
     // [A] the next unit's first tiles and its q
@@ -496,7 +505,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
     const TileAddr ta_next = by_head && live ? ta : tile_addr<D>(G, a.gg, a.tcap, a.st_log2, N.g);
     if (has_next && (live || !by_head)) {
 #pragma unroll
-      for (int i = 0; i < PIPE; ++i) load_tile(buf[i], ta_next, min((N.lo >> 4) + i, (N.hi - 1) >> 4), N.blk0[i]);
+      for (int i = 0; i < PIPE; ++i) load_tile(buf[i], ta_next, min((N.lo >> 4) + sub + i * NS, (N.hi - 1) >> 4), N.blk0[i]);
       // (lanes past the group's heads read head 0's piece, which is dropped where q is taken over: no branch
       // around each load)
       const uint4 *qp = reinterpret_cast<const uint4 *>(q + ((size_t)N.b * H + (size_t)N.g * R + (rho < R ? rho : 0)) * D + 8 * quarter);
@@ -515,7 +524,41 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
       float lt = l;
       lt += __shfl_xor(lt, 16);
       lt += __shfl_xor(lt, 32);
-      if (rho < R) {
+      // NS > 1: every wavefront puts its sums (relative to its own maxima), maxima and weights where its tiles were; then
+      // each takes the dims of its share of the u below from all of them.
+      constexpr int kU = D / 32, kShare = NS > 1 ? (kU + NS - 1) / NS : kU;      // u's per wavefront
+      const int u0 = NS > 1 ? sub * kShare : 0;
+      if constexpr (NS > 1) {
+        floatx4_t *mine = reinterpret_cast<floatx4_t *>(ks) + lane;
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) mine[i * 64] = o[i];
+        reinterpret_cast<float2 *>(ks + D / 16 * 1024)[lane] = make_float2(m, lt);
+        __syncthreads();
+        float2 ml[NS];
+        float M = kNegBig;
+#pragma unroll
+        for (int s2 = 0; s2 < NS; ++s2) {
+          ml[s2] = reinterpret_cast<const float2 *>(lds_all[s2] + D / 16 * 1024)[lane];
+          M = fmaxf(M, ml[s2].x);
+        }
+        lt = 0.f;
+        floatx4_t sum[2 * kShare];
+#pragma unroll
+        for (int i = 0; i < 2 * kShare; ++i) sum[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s2 = 0; s2 < NS; ++s2) {
+          const float alpha = __builtin_amdgcn_exp2f(ml[s2].x - M);
+          lt += alpha * ml[s2].y;
+          const floatx4_t *theirs = reinterpret_cast<const floatx4_t *>(lds_all[s2]) + min(2 * u0, D / 16 - 2 * kShare) * 64 + lane;
+#pragma unroll
+          for (int i = 0; i < 2 * kShare; ++i) sum[i] += alpha * theirs[i * 64];
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * kShare; ++i) o[i] = sum[i];
+        m = M;
+        __syncthreads();                                 // the places are the next tiles' again
+      }
+      if (rho < R && u0 < kU) {
         const int h = C.g * R + rho;
         const float inv = seq_whole ? 1.0f / lt : 1.0f;
         const bool as_float = !seq_whole || a.out_fp32;
@@ -523,14 +566,14 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
                                 : a.part_o + ((size_t)C.it * H + h) * D;
         uint16_t *hdst = reinterpret_cast<uint16_t *>(a.out) + ((size_t)C.b * H + h) * D;
 #pragma unroll
-        for (int u = 0; u < D / 32; ++u) {
+        for (int u = 0; u < kShare; ++u) {
           float ot[8];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             ot[2 * r] = o[2 * u][r] * inv;
             ot[2 * r + 1] = o[2 * u + 1][r] * inv;
           }
-          const int dim0 = 32 * u + 8 * quarter;
+          const int dim0 = 32 * (u0 + u) + 8 * quarter;
           if (as_float) {
             float4 *dst = reinterpret_cast<float4 *>(fdst + dim0);
             dst[0] = make_float4(ot[0], ot[1], ot[2], ot[3]);
@@ -544,13 +587,13 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
                                                                  __builtin_bit_cast(uint32_t, h2), __builtin_bit_cast(uint32_t, h3));
           }
         }
-        if (!seq_whole && quarter == 0)
+        if (!seq_whole && quarter == 0 && sub == 0)
           *reinterpret_cast<float2 *>(a.part_ml + ((size_t)C.it * H + h) * 2) = make_float2(m, lt);
       }
       // The item that ends at the sequence's last key also stores this step's K/V rows (paper §II-A: keys
       // and values of every processed token are kept): row 0 of the load layout stores the K row, row 1 the V row.
       const int pos = C.hi - 1;
-      if (a.k_new != nullptr && (C.flags & kItemLast) && row < 2) {
+      if (a.k_new != nullptr && (C.flags & kItemLast) && row < 2 && sub == 0) {
         const int blk = blk_of(C.b, pos >> 4);
         const int64_t in_slab = (row == 0 ? ta.head_k : ta.head_v) + (int64_t)(pos & 15) * D + col * 8;
         const uint4 val = row == 0 ? k_row : v_row;
@@ -583,7 +626,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
       const const_i32_ptr dp = (const_i32_ptr)(uintptr_t)(a.item_desc + N.it);
       N.b = dp[0], N.lo = dp[1], N.hi = dp[2], N.flags = dp[3];
 #pragma unroll
-      for (int i = 0; i < PIPE; ++i) N.blk0[i] = blk_of(N.b, min((N.lo >> 4) + i, (N.hi - 1) >> 4));
+      for (int i = 0; i < PIPE; ++i) N.blk0[i] = blk_of(N.b, min((N.lo >> 4) + sub + i * NS, (N.hi - 1) >> 4));
     }
     const int b = C.b, lo = C.lo, hi = C.hi;
     // The rows to append are patched into the tile in registers, so the attention does not depend on
@@ -609,37 +652,39 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void attn_split_mfma_kernel(
     // one refill ahead through the scalar cache, which has its own counter.  A refill past the item's
     // last tile (only when the tile count is not a multiple of PIPE) asks for the last tile again.  The
     // last group's buffers are refilled at [A], from the next item.
+    // (A wavefront of several that share the pair takes every NS-th tile, from `sub` on; it may have none.)
     const int t1 = (hi + 15) >> 4, last_tile = t1 - 1;
     int next_blk[PIPE];
 #pragma unroll
-    for (int i = 0; i < PIPE; ++i) next_blk[i] = blk_of(b, min((lo >> 4) + PIPE + i, last_tile));
-    for (int t = lo >> 4; t < t1; t += PIPE) {
-      const bool last = t + PIPE >= t1;
+    for (int i = 0; i < PIPE; ++i) next_blk[i] = blk_of(b, min((lo >> 4) + sub + (PIPE + i) * NS, last_tile));
+    for (int t = (lo >> 4) + sub; t < t1; t += PIPE * NS) {
+      const bool last = t + PIPE * NS >= t1;
 #pragma unroll
       for (int i = 0; i < PIPE; ++i) {
         // at d = 64 two tiles are reduced together: buffer i (even) is staged and waits for buffer i + 1
         constexpr int PAIR = lds_tiles<D>();
         char *const ks_i = ks + (i % PAIR) * lds_tile_bytes<D>(), *const vs_i = vs + (i % PAIR) * lds_tile_bytes<D>();
-        if (i - i % PAIR == 0 || t + (i - i % PAIR) < t1) {   // else a second request for the last tile: skipped
-          if (last && appending && t + i == (pos >> 4)) {
+        const int ti = t + i * NS;
+        if (i - i % PAIR == 0 || t + (i - i % PAIR) * NS < t1) {   // else a second request for the last tile: skipped
+          if (last && appending && ti == (pos >> 4)) {
 #pragma unroll
             for (int j = 0; j < LPT; ++j)
-              if (((t + i) << 4) + row + j * RPL == pos) {
+              if ((ti << 4) + row + j * RPL == pos) {
                 buf[i].k[j] = k_row;
                 buf[i].v[j] = v_row;
               }
           }
-          tile_stage<D>(buf[i], ks_i, vs_i, lane, (t + i) << 4, lo, hi, last);
+          tile_stage<D>(buf[i], ks_i, vs_i, lane, ti << 4, lo, hi, last);
           if constexpr (PAIR == 1) {
-            tile_update_mfma<D>(qb, m, l, o, ks, vs, lane, (t + i) << 4, lo, hi, a.scale_log2e, last);
+            tile_update_mfma<D>(qb, m, l, o, ks, vs, lane, ti << 4, lo, hi, a.scale_log2e, last);
           } else if (i % PAIR == PAIR - 1) {
-            tile_update_pair(qb, m, l, o, ks, vs, lane, (t + i - 1) << 4, t + i < t1, lo, hi, a.scale_log2e, last);
+            tile_update_pair(qb, m, l, o, ks, vs, lane, (ti - NS) << 4, 16 * NS, ti < t1, lo, hi, a.scale_log2e, last);
           }
         }
         __builtin_amdgcn_sched_barrier(0);    // keep the refill behind the reduce that frees it,
         if (!last) {
-          load_tile(buf[i], ta, min(t + i + PIPE, last_tile), next_blk[i]);
-          next_blk[i] = blk_of(b, min(t + i + 2 * PIPE, last_tile));
+          load_tile(buf[i], ta, min(ti + PIPE * NS, last_tile), next_blk[i]);
+          next_blk[i] = blk_of(b, min(ti + 2 * PIPE * NS, last_tile));
         }
         __builtin_amdgcn_sched_barrier(0);    // and ahead of the next tile's reduce
       }
@@ -755,32 +800,38 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
 // at 6.2; launches of a few dozen microseconds gained less and the shortest lost to the longer loop body from
 // six on (11.3 us with two, 11.7 with four, 12.6 with six, 13.9 with eight): four, which tile_update_pair
 // reduces two at a time (6.25 TB/s).
-#ifndef OKV_PIPE_MULT
-#define OKV_PIPE_MULT 1
-#endif
-template <int D>
+// With several wavefronts per pair two tiles each are as many bytes per compute unit, and four are slower (32 x 64 heads,
+// 24 ragged sequences of 190..1150 keys: 29.2 us with two, 30.7 with four); at d = 128 two tiles instead of one likewise
+// (32 / 8 heads, 128 ragged sequences: 195 -> 200 us; one sequence of 2048 keys, 32 heads: 15.4 -> 15.7).
+template <int D, int NS>
 constexpr int base_depth() {
-  return (D == 64 ? 4 : 1) * OKV_PIPE_MULT;
+  return D == 64 ? (NS > 1 ? 2 : 4) : 1;
 }
 
-template <int D, bool PAGED, bool HEADS, bool NT>
+template <int D, bool PAGED, bool HEADS, bool NT, int NS>
 void launch_split_as(const AttnArgs &args, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_split_mfma_kernel<D, PAGED, base_depth<D>(), HEADS, NT>), grid, dim3(kWavesPerBlock * 64), 0, stream,
-                     args.pair_head, args.pool, args.q, args.n_groups_dev, args.n_groups, args.G, args.H, args.R,
+  hipLaunchKernelGGL((attn_split_mfma_kernel<D, PAGED, base_depth<D, NS>(), HEADS, NT, NS>), grid, dim3((NS > 1 ? NS : kWavesPerBlock) * 64), 0,
+                     stream, args.pair_head, args.pool, args.q, args.n_groups_dev, args.n_groups, args.G, args.H, args.R,
                      args.gg << args.st_log2, args);
 }
 
-template <int D, bool PAGED>
-void launch_split_paged(const AttnArgs &args, bool keep, dim3 grid, hipStream_t stream) {
-  if (args.pair_head)
-    keep ? launch_split_as<D, PAGED, true, false>(args, grid, stream) : launch_split_as<D, PAGED, true, true>(args, grid, stream);
-  else
-    keep ? launch_split_as<D, PAGED, false, false>(args, grid, stream) : launch_split_as<D, PAGED, false, true>(args, grid, stream);
+// (D = 64 knows one or two wavefronts per pair, see waves_per_pair)
+template <int D, bool PAGED, bool NT>
+void launch_split_kept(const AttnArgs &args, int waves, dim3 grid, hipStream_t stream) {
+  if (!args.pair_head) return launch_split_as<D, PAGED, false, NT, 1>(args, grid, stream);
+  if constexpr (D == 128) {
+    if (waves == 4) return launch_split_as<D, PAGED, true, NT, 4>(args, grid, stream);
+  }
+  if (waves == 2) return launch_split_as<D, PAGED, true, NT, 2>(args, grid, stream);
+  launch_split_as<D, PAGED, true, NT, 1>(args, grid, stream);
 }
 
 template <int D>
-hipError_t launch_split(const AttnArgs &args, bool paged, bool keep, dim3 grid, hipStream_t stream) {
-  paged ? launch_split_paged<D, true>(args, keep, grid, stream) : launch_split_paged<D, false>(args, keep, grid, stream);
+hipError_t launch_split(const AttnArgs &args, bool paged, bool keep, int waves, dim3 grid, hipStream_t stream) {
+  if (paged)
+    keep ? launch_split_kept<D, true, false>(args, waves, grid, stream) : launch_split_kept<D, true, true>(args, waves, grid, stream);
+  else
+    keep ? launch_split_kept<D, false, false>(args, waves, grid, stream) : launch_split_kept<D, false, true>(args, waves, grid, stream);
   return hipGetLastError();
 }
 
@@ -838,7 +889,10 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream, hipEvent_
   // persistent launch: no more wavefronts than there are (group, KV head) pairs, no more than a.max_waves
   const int64_t want = ((int64_t)args.n_groups * s.G + kWavesPerBlock - 1) / kWavesPerBlock;
   const int64_t cap = std::max<int64_t>(1, a.max_waves / kWavesPerBlock);
-  dim3 grid((unsigned)(a.n_groups_dev ? cap : std::min(want, cap)));
+  const int waves = a.pair_head ? a.waves_per_pair : 1;
+  if (waves != 1 && waves != 2 && !(waves == 4 && s.D == 128)) return hipErrorInvalidValue;
+  const int64_t pairs = (a.n_groups_dev ? cap : std::min(want, cap)) * kWavesPerBlock;      // that the grid covers
+  dim3 grid((unsigned)(waves > 1 ? std::min<int64_t>(pairs, (int64_t)args.n_groups * s.G) : pairs / kWavesPerBlock));
   // (stretches come with a table of heads, which needs a wavefront per (stretch, KV head) pair and a pool that
   // holds the blocks as the table numbers them)
   if (a.pair_head && (want > cap || a.id_base != 0 || a.item_first != 0)) return hipErrorInvalidValue;
@@ -847,9 +901,9 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream, hipEvent_
   if (R < 1 || R > 16 || R * s.G != s.H)
     e = hipErrorInvalidValue;
   else if (s.D == 128)
-    e = launch_split<128>(args, s.paged != 0, a.keep_cached != 0, grid, stream);
+    e = launch_split<128>(args, s.paged != 0, a.keep_cached != 0, waves, grid, stream);
   else if (s.D == 64)
-    e = launch_split<64>(args, s.paged != 0, a.keep_cached != 0, grid, stream);
+    e = launch_split<64>(args, s.paged != 0, a.keep_cached != 0, waves, grid, stream);
   else
     e = hipErrorInvalidValue;
   if (e != hipSuccess) return e;
