@@ -22,7 +22,8 @@
  *   - The caller owns every large buffer (KV pools, staging buffers, workspace,
  *     q / k / v / out) and keeps it alive until okv_destroy; the library never
  *     frees or reallocates them.  The library itself allocates only small
- *     bookkeeping arrays (O(max_batch * max_blocks_per_seq) integers, a few events).
+ *     bookkeeping arrays (O(max_batch * max_blocks_per_seq) integers, as much pinned host
+ *     memory to upload them from, a few events).
  *   - Work is enqueued on the two streams given at creation and the calls return
  *     without waiting for the GPU unless stated otherwise.  q / k_new / v_new / out
  *     may be reused once the work enqueued on the compute stream has finished.

@@ -124,6 +124,8 @@ struct okv_ctx {
   int32_t max_groups = 1;                // wavefronts of a launch per KV head
   int32_t *d_items_dump = nullptr;
   int32_t max_waves = 0;                 // wavefronts of the persistent attention launch
+  char *h_up = nullptr;                  // mapped host memory the small tables are uploaded from (NULL: synchronous copies)
+  int64_t up_cap = 0;
   bool keep_cached = true;               // the batch's keys and values of all layers fit the memory-side cache
   int64_t max_items = 0;
   float *part_o = nullptr, *part_ml = nullptr;
@@ -486,15 +488,48 @@ int exec_ops(okv_ctx *ctx, const std::vector<Op> &ops, const void *a0, const voi
 
 // Recomputes split size, item count and merge flag from the host lengths and
 // rebuilds the device work list (adding `inc` to every device length first).
+// One or two small host arrays to the device, before whatever is enqueued on the compute stream next.  Called with that
+// stream drained, so the memory of the upload before this one is free again; it grows to the largest upload and goes
+// with the context.  Where it cannot be had (pinned memory is limited) the arrays are copied synchronously.
+int upload_tables(okv_ctx *ctx, void *dst0, const void *src0, int64_t bytes0, void *dst1 = nullptr, const void *src1 = nullptr,
+                  int64_t bytes1 = 0) {
+  const int64_t at1 = (bytes0 + 255) / 256 * 256, need = at1 + bytes1;
+  if (need > ctx->up_cap) {
+    if (ctx->h_up) (void)hipHostFree(ctx->h_up);
+    ctx->h_up = nullptr;
+    ctx->up_cap = 0;
+    void *p = nullptr;
+    if (hipHostMalloc(&p, (size_t)need, hipHostMallocMapped) == hipSuccess) {
+      ctx->h_up = static_cast<char *>(p);
+      ctx->up_cap = need;
+    } else {
+      (void)hipGetLastError();                           // a refusal is no error of this call, nor of the next one
+    }
+  }
+  void *dev = nullptr;
+  if (!ctx->h_up || hipHostGetDevicePointer(&dev, ctx->h_up, 0) != hipSuccess) {
+    if (ctx->h_up) (void)hipGetLastError();
+    if (bytes0) OKV_HIP(ctx, hipMemcpy(dst0, src0, (size_t)bytes0, hipMemcpyHostToDevice));
+    if (bytes1) OKV_HIP(ctx, hipMemcpy(dst1, src1, (size_t)bytes1, hipMemcpyHostToDevice));
+    return OKV_OK;
+  }
+  if (bytes0) memcpy(ctx->h_up, src0, (size_t)bytes0);
+  if (bytes1) memcpy(ctx->h_up + at1, src1, (size_t)bytes1);
+  okv::UploadLaunch u;
+  u.dst[0] = dst0, u.src[0] = dev, u.words[0] = bytes0 / 4;
+  u.dst[1] = dst1, u.src[1] = static_cast<char *>(dev) + at1, u.words[1] = bytes1 / 4;
+  OKV_HIP(ctx, okv::launch_upload(u, ctx->compute));
+  return OKV_OK;
+}
+
 int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false) {
   int64_t keys = 0;
   for (int32_t b = 0; b < ctx->B; ++b) keys += ctx->h_ctx_lens[b];
   ctx->keep_cached = keys * ctx->cfg.n_kv_heads * ctx->cfg.head_dim * 4 * ctx->cfg.n_layers <= okv::kKeepCachedBytes;
   if (upload_lens) {
-    // the device lengths are replaced by the host's (after a bulk store); h_ctx_lens is pageable
-    // memory, so the copy is over when the call returns, and the kernels below are enqueued after it
+    // the device lengths are replaced by the host's (after a bulk store)
     OKV_HIP(ctx, hipStreamSynchronize(ctx->compute));
-    OKV_HIP(ctx, hipMemcpy(ctx->d_ctx_lens, ctx->h_ctx_lens.data(), (size_t)ctx->B * sizeof(int32_t), hipMemcpyHostToDevice));
+    if (int rc = upload_tables(ctx, ctx->d_ctx_lens, ctx->h_ctx_lens.data(), (int64_t)ctx->B * sizeof(int32_t))) return rc;
   }
   if (ctx->by_class) {
     ctx->split = ctx->split_override ? ctx->split_override : ctx->cfg.split_tokens ? ctx->cfg.split_tokens : kClassSplit;
@@ -928,6 +963,7 @@ int okv_destroy(okv_ctx *ctx) {
   (void)hipFree(ctx->d_item_desc);
   (void)hipFree(ctx->d_group_first);
   (void)hipFree(ctx->d_pair_head);
+  if (ctx->h_up) (void)hipHostFree(ctx->h_up);
   (void)hipFree(ctx->d_plan);
   (void)hipFree(ctx->d_items_dump);
   if (ctx->d2h) {
@@ -1010,12 +1046,13 @@ int okv_set_batch(okv_ctx *ctx, int32_t B, const int32_t *block_table, const int
   ctx->h_ctx_lens.assign(ctx_lens, ctx_lens + B);
   if (s.paged) {
     ctx->h_block_table.assign(block_table, block_table + (size_t)B * s.max_blocks);
-    OKV_HIP(ctx, hipMemcpy(ctx->d_block_table, block_table, (size_t)B * s.max_blocks * sizeof(int32_t), hipMemcpyHostToDevice));
     ctx->copy_bytes = (max_blk + 1) * ctx->block_bytes;
   } else {
     ctx->copy_bytes = (int64_t)B * ctx->block_bytes;
   }
-  OKV_HIP(ctx, hipMemcpy(ctx->d_ctx_lens, ctx_lens, (size_t)B * sizeof(int32_t), hipMemcpyHostToDevice));
+  rc = upload_tables(ctx, ctx->d_ctx_lens, ctx_lens, (int64_t)B * sizeof(int32_t), ctx->d_block_table, block_table,
+                     s.paged ? (int64_t)B * s.max_blocks * sizeof(int32_t) : 0);
+  if (rc) return rc;
   ctx->unit_offset.assign(1, 0);
   ctx->unit_bytes.assign(1, ctx->copy_bytes);
   if (ctx->by_class) {
@@ -1320,8 +1357,8 @@ int okv_prefill_begin(okv_ctx *ctx, const int32_t *n_new) {
     ctx->tiles_cap = n_tiles;
   }
   if (!ctx->d_row_base) OKV_HIP(ctx, hipMalloc(&ctx->d_row_base, (size_t)ctx->cfg.max_batch * sizeof(int32_t)));
-  if (n_tiles) OKV_HIP(ctx, hipMemcpy(ctx->d_tiles, flat.data(), (size_t)n_tiles * sizeof(int4), hipMemcpyHostToDevice));
-  OKV_HIP(ctx, hipMemcpy(ctx->d_row_base, row_base.data(), (size_t)B * sizeof(int32_t), hipMemcpyHostToDevice));
+  rc = upload_tables(ctx, ctx->d_row_base, row_base.data(), (int64_t)B * sizeof(int32_t), ctx->d_tiles, flat.data(), n_tiles * sizeof(int4));
+  if (rc) return rc;
   if (!ctx->d2h) {
     OKV_HIP(ctx, own_queue_stream(&ctx->d2h));
     OKV_HIP(ctx, hipEventCreateWithFlags(&ctx->rows_ready_ev, hipEventDisableTiming));

@@ -160,6 +160,15 @@ struct TailLaunch {
 };
 hipError_t launch_tail_rows(const TailLaunch &t, hipStream_t stream);
 
+// Up to two small tables from mapped host memory to the device, by a kernel on the stream: words[i] 4-byte words from
+// src[i] to dst[i] (16-byte aligned both; words 0: none).
+struct UploadLaunch {
+  void *dst[2] = {nullptr, nullptr};
+  const void *src[2] = {nullptr, nullptr};
+  int64_t words[2] = {0, 0};
+};
+hipError_t launch_upload(const UploadLaunch &u, hipStream_t stream);
+
 // items[it] = (b, lo, hi) decoded on the device.
 hipError_t launch_worklist_dump(const BatchState &batch, int32_t *items, hipStream_t stream);
 

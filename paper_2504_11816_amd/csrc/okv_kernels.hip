@@ -1274,6 +1274,21 @@ __global__ __launch_bounds__(256) void tail_rows_kernel(TailArgs a) {
   }
 }
 
+// Tables of a new batch or prompt, read from mapped host memory.  A synchronous copy of a few KiB costs the host 15-25 us
+// (a launch on another stream and a wait for it); this costs the stream about 4 us and the host a launch.
+__global__ __launch_bounds__(256) void upload_kernel(const UploadLaunch u) {
+  const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int64_t pieces = u.words[i] >> 2;
+    const uint4 *src = static_cast<const uint4 *>(u.src[i]);
+    uint4 *dst = static_cast<uint4 *>(u.dst[i]);
+    for (int64_t p = first; p < pieces; p += step) dst[p] = src[p];
+    if (first < (u.words[i] & 3))
+      reinterpret_cast<uint32_t *>(dst + pieces)[first] = reinterpret_cast<const uint32_t *>(src + pieces)[first];
+  }
+}
+
 __global__ void worklist_dump_kernel(BatchState bs, int32_t *items) {
   const int it = blockIdx.x * blockDim.x + threadIdx.x;
   if (it >= bs.n_items) return;
@@ -1379,6 +1394,12 @@ hipError_t launch_tail_rows(const TailLaunch &t, hipStream_t stream) {
   const int64_t pieces = t.block_elems / 8;
   const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>((pieces + 255) / 256, 64));
   hipLaunchKernelGGL(tail_rows_kernel, dim3(gx, t.B, t.mode == 0 ? 2 : t.n_layers), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(const UploadLaunch &u, hipStream_t stream) {
+  const int64_t pieces = std::max(u.words[0], u.words[1]) / 4 + 1;
+  hipLaunchKernelGGL(upload_kernel, dim3((unsigned)std::min<int64_t>((pieces + 255) / 256, 256)), dim3(256), 0, stream, u);
   return hipGetLastError();
 }
 
