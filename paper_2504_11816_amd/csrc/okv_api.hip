@@ -601,7 +601,7 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false) {
   OKV_HIP(ctx, okv::launch_step_advance_spans(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->d_group_first,
                                               ctx->d_plan, ctx->B, ctx->max_groups, kMinSpanTiles, inc, ctx->d_pair_head,
                                               okv::head_geom(ctx->shape, ctx->d_block_table, max_pairs(ctx->max_waves)),
-                                              ctx->compute));
+                                              ((int64_t)ctx->cap_tokens + 15) / 16, ctx->compute));
   return OKV_OK;
 }
 
@@ -2027,7 +2027,8 @@ int okv_decode_attn_static(const okv_static_attn *a) {
   s.max_blocks = s.paged ? a->max_blocks_per_seq : 1;
   OKV_HIP(nullptr, okv::launch_step_advance_spans(const_cast<int32_t *>(a->ctx_lens), chunk_prefix, item_desc, group_first, plan, a->B,
                                                   max_groups, kMinSpanTiles, 0, pair_head,
-                                                  okv::head_geom(s, a->block_table, max_pairs(max_waves)), stream));
+                                                  okv::head_geom(s, a->block_table, max_pairs(max_waves)),
+                                                  (cap_tokens_of(&c) + 15) / 16, stream));
   l.batch = okv::BatchState{a->block_table, a->ctx_lens, chunk_prefix, item_desc, a->B, 0, (int32_t)max_items, 1};
   l.q = a->q;
   l.pool = const_cast<void *>(a->pool);

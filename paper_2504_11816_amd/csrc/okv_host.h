@@ -159,16 +159,20 @@ __host__ __device__ inline ItemRange chunk_range(int32_t b, int32_t c, int32_t s
 // of sequences) that start in stretch j form group j.  There are at most max_groups stretches and none
 // is shorter than min_span tiles unless the whole launch is.  The same arithmetic runs on the host (item
 // count, checks) and in the kernel that builds the item list.
-struct SpanPlan {
-  int64_t span;        // tiles per stretch (>= 1)
+template <typename I>
+struct SpanPlanOf {
+  I span;              // tiles per stretch (>= 1)
   int32_t n_groups;    // stretches that hold at least one tile
 };
+using SpanPlan = SpanPlanOf<int64_t>;
 
-__host__ __device__ inline SpanPlan span_plan(int64_t total_tiles, int32_t max_groups, int32_t min_span) {
-  int64_t g = total_tiles / (min_span > 0 ? min_span : 1);
+// (I: int64_t, or int32_t where the tiles of the batch are known to fit it)
+template <typename I>
+__host__ __device__ inline SpanPlanOf<I> span_plan(I total_tiles, int32_t max_groups, int32_t min_span) {
+  I g = total_tiles / (min_span > 0 ? min_span : 1);
   if (g > max_groups) g = max_groups;
   if (g < 1) g = 1;
-  SpanPlan p;
+  SpanPlanOf<I> p;
   p.span = (total_tiles + g - 1) / g;
   if (p.span < 1) p.span = 1;
   p.n_groups = (int32_t)((total_tiles + p.span - 1) / p.span);
@@ -198,24 +202,25 @@ inline int32_t waves_per_pair(int32_t D, int32_t G, int32_t B, int64_t cap_token
 // Pieces of a sequence whose tiles are [first, first + tiles) of the stream: it is cut at the multiples
 // of span strictly inside that range.  *k0 receives the first such multiple's index, so that piece c >= 1
 // starts at tile (k0 + c - 1) * span of the stream and piece c ends where piece c + 1 starts.
-__host__ __device__ inline int32_t span_pieces(int64_t first, int64_t tiles, int64_t span, int64_t *k0) {
+template <typename I>
+__host__ __device__ inline int32_t span_pieces(I first, I tiles, I span, I *k0) {
   *k0 = first / span + 1;
   if (tiles <= 0) return 0;
-  const int64_t k_last = (first + tiles - 1) / span;
+  const I k_last = (first + tiles - 1) / span;
   return 1 + (k_last >= *k0 ? (int32_t)(k_last - *k0 + 1) : 0);
 }
 
 // Piece c of a sequence with n keys: keys [lo, hi) and the stretch it starts in.
-__host__ __device__ inline ItemRange span_piece(int32_t b, int32_t c, int32_t n, int64_t first, int64_t tiles,
-                                                int64_t span, int64_t k0, int64_t *group) {
-  const int64_t s = c == 0 ? first : (k0 + c - 1) * span;
-  int64_t e = (k0 + c) * span;
+template <typename I>
+__host__ __device__ inline ItemRange span_piece(int32_t b, int32_t c, int32_t n, I first, I tiles, I span, I k0, I *group) {
+  const I s = c == 0 ? first : (k0 + c - 1) * span;
+  I e = (k0 + c) * span;
   if (e > first + tiles) e = first + tiles;
-  *group = s / span;
+  *group = c == 0 ? k0 - 1 : k0 + c - 1;                 // = s / span
   ItemRange r;
   r.b = b;
   r.lo = (int32_t)((s - first) << 4);
-  const int64_t hi = (e - first) << 4;
+  const int64_t hi = (int64_t)(e - first) << 4;
   r.hi = hi < n ? (int32_t)hi : n;
   return r;
 }

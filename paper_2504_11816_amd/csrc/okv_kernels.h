@@ -90,6 +90,7 @@ hipError_t launch_step_advance(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *i
 // that item's descriptor, and where the head's K rows of its first two tiles lie in a pool of the geometry
 // given (the same for every layer).  An attention launch with max_waves wavefronts looks at the records of
 // the pairs below max(max_waves, 4) (and ignores those past the last stretch): geom.max_pairs is at least that.
+// cap_tiles: no sequence holds more 16-key tiles than this.
 // The bookkeeping kernel keeps what opens each stretch in LDS, for at most kHeadGroupsMax stretches: callers
 // keep max_groups at or below that.
 constexpr int kPairHeadBytes = 32, kHeadGroupsMax = 1024;
@@ -109,7 +110,7 @@ inline HeadGeom head_geom(const PoolShape &s, const int32_t *block_table, int32_
 }
 hipError_t launch_step_advance_spans(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *item_desc, int32_t *group_first,
                                      int32_t *plan_out, int32_t B, int32_t max_groups, int32_t min_span, int32_t inc,
-                                     void *pair_head, const HeadGeom &geom, hipStream_t stream);
+                                     void *pair_head, const HeadGeom &geom, int64_t cap_tiles, hipStream_t stream);
 
 // The same for block classes: runs[r] = (sequence, first position, one past the last position
 // the run can hold, class), sorted by (class, sequence, position); pair_first[cls * B + b] is the

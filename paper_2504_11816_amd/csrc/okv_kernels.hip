@@ -934,19 +934,20 @@ constexpr int kStepThreads = 256;
 // a shuffle scan inside every wavefront and one hand-over of the wavefronts' sums through LDS (two barriers,
 // where a scan through shared memory needs two per doubling: the kernel runs once per step, in front of every
 // layer's attention, and a single-sequence step is short enough to see the difference).
-__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t *wave_sums, int64_t *total) {
+template <typename I>
+__device__ __forceinline__ I block_scan(I v, I *wave_sums, I *total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
-    const int64_t up = __shfl_up(v, off);
+    const I up = __shfl_up(v, off);
     if (lane >= off) v += up;
   }
   if (lane == 63) wave_sums[wave] = v;
   __syncthreads();
-  int64_t before = 0, all = 0;
+  I before = 0, all = 0;
 #pragma unroll
   for (int w = 0; w < kStepThreads / 64; ++w) {
-    const int64_t sw = wave_sums[w];
+    const I sw = wave_sums[w];
     before += w < wave ? sw : 0;
     all += sw;
   }
@@ -972,7 +973,7 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_kernel(int32_t *ctx
     mine += cnt;
   }
   int64_t total_items;
-  int32_t at = (int32_t)(block_scan(mine, wave_sums, &total_items) - mine);   // exclusive prefix of this thread
+  int32_t at = (int32_t)(block_scan<int64_t>(mine, wave_sums, &total_items) - mine);   // exclusive prefix of this thread
   for (int b = b0; b < b1; ++b) {
     chunk_prefix[b] = at;
     const int32_t n = ctx_lens[b];
@@ -992,54 +993,66 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_kernel(int32_t *ctx
 // laid end to end, cut into stretches (span_plan), every sequence into the pieces the cuts leave
 // (span_pieces), and the first item of every stretch is noted in group_first.  plan_out receives
 // (number of stretches in use, number of items, tiles per stretch as two halves).
+//
+// The launch stands in front of every step (and of every call of the entry point without a context) and is all latency.
+// I is the type of the arithmetic on tiles: 32 bits wherever the batch at capacity fits them (a 64-bit division is a
+// few hundred instructions, and there is a chain of four), and with at most one sequence per thread a length is
+// read once and stays in its register.
+template <typename I>
 __global__ __launch_bounds__(kStepThreads) void step_advance_spans_kernel(int32_t *ctx_lens, int32_t *chunk_prefix,
                                                                          int4 *item_desc, int32_t *group_first,
                                                                          int32_t *plan_out, int32_t B,
                                                                          int32_t max_groups, int32_t min_span,
                                                                          int32_t inc, PairHead *pair_head,
-                                                                         const HeadGeom hg) {
-  __shared__ int64_t wave_sums[kStepThreads / 64];
+                                                                         const int32_t most_tiles, const HeadGeom hg) {
+  __shared__ I wave_sums[kStepThreads / 64];
   // what opens each stretch, for the per-pair records: its first item, that item's descriptor and the block
   // ids of the item's first two tiles (the second clamped to the item's last tile)
   __shared__ int32_t open_item[kHeadGroupsMax + 1];
   __shared__ int4 open_desc[kHeadGroupsMax];
   __shared__ int2 open_blk[kHeadGroupsMax];
   const int tid = threadIdx.x;
-  if (pair_head)
-    for (int j = tid; j <= kHeadGroupsMax; j += kStepThreads) open_item[j] = -1;
-  const int per = (B + kStepThreads - 1) / kStepThreads;     // consecutive sequences per thread
+  const bool one_each = B <= kStepThreads;
+  const int per = one_each ? 1 : (B + kStepThreads - 1) / kStepThreads;     // consecutive sequences per thread
   const int b0 = min(B, tid * per), b1 = min(B, b0 + per);
-  int64_t mine = 0;
+  const int32_t n0 = b0 < b1 ? ctx_lens[b0] + inc : 0;
+  auto len = [&](int b) -> int32_t { return one_each ? n0 : ctx_lens[b]; };  // (after the lengths have advanced)
+  // (a length no sequence can have, which only a caller's own device array could hold, does not leave the arithmetic)
+  auto tiles_of = [&](int32_t n) -> I { return min(max((n >> 4) + ((n & 15) != 0), 0), most_tiles); };
+  if (pair_head)
+    for (int j = tid; j <= min(max_groups, kHeadGroupsMax); j += kStepThreads) open_item[j] = -1;
+  I mine = 0;
   for (int b = b0; b < b1; ++b) {
-    const int32_t n = ctx_lens[b] + inc;
+    const int32_t n = b == b0 ? n0 : ctx_lens[b] + inc;
     if (inc) ctx_lens[b] = n;                                  // inc == 0: the lengths are only read
-    mine += (n + 15) >> 4;
+    mine += tiles_of(n);
   }
-  int64_t total_tiles;
-  const int64_t tile_first = block_scan(mine, wave_sums, &total_tiles) - mine;   // tiles before this thread's sequences
-  const SpanPlan plan = span_plan(total_tiles, max_groups, min_span);
-  int64_t items_mine = 0, first = tile_first;
+  I total_tiles;
+  const I tile_first = block_scan<I>(mine, wave_sums, &total_tiles) - mine;   // tiles before this thread's sequences
+  const SpanPlanOf<I> plan = span_plan<I>(total_tiles, max_groups, min_span);
+  I items_mine = 0, first = tile_first;
   for (int b = b0; b < b1; ++b) {
-    const int64_t tiles = (ctx_lens[b] + 15) >> 4;
-    int64_t k0;
-    items_mine += span_pieces(first, tiles, plan.span, &k0);
+    const I tiles = tiles_of(len(b));
+    I k0;
+    items_mine += span_pieces<I>(first, tiles, plan.span, &k0);
     first += tiles;
   }
-  int64_t total_items;
-  int32_t at = (int32_t)(block_scan(items_mine, wave_sums, &total_items) - items_mine);
+  I total_items;
+  int32_t at = (int32_t)(block_scan<I>(items_mine, wave_sums, &total_items) - items_mine);
   first = tile_first;
   for (int b = b0; b < b1; ++b) {
     chunk_prefix[b] = at;
-    const int32_t n = ctx_lens[b];
-    const int64_t tiles = (n + 15) >> 4;
-    int64_t k0;
-    const int32_t cnt = span_pieces(first, tiles, plan.span, &k0);
+    const int32_t n = len(b);
+    const I tiles = tiles_of(n);
+    I k0;
+    const int32_t cnt = span_pieces<I>(first, tiles, plan.span, &k0);
+    const bool opens = first == (k0 - 1) * plan.span;            // the sequence's first piece begins a stretch
     for (int32_t c = 0; c < cnt; ++c) {
-      int64_t group;
-      const ItemRange r = span_piece(b, c, n, first, tiles, plan.span, k0, &group);
+      I group;
+      const ItemRange r = span_piece<I>(b, c, n, first, tiles, plan.span, k0, &group);
       const int32_t flags = (c == cnt - 1 ? kItemLast : 0) | (cnt == 1 ? kItemWhole : 0);
       item_desc[at + c] = make_int4(r.b, r.lo, r.hi, flags);
-      if (c > 0 || first % plan.span == 0) {                               // the item opens its stretch
+      if (c > 0 || opens) {                                                // the item opens its stretch
         group_first[group] = at + c;
         if (pair_head && group < kHeadGroupsMax) {
           open_item[group] = at + c;
@@ -1097,8 +1110,8 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_spans_kernel(int32_
     chunk_prefix[B] = n_items;
     plan_out[0] = plan.n_groups;
     plan_out[1] = n_items;
-    plan_out[2] = (int32_t)(plan.span & 0x7fffffff);
-    plan_out[3] = (int32_t)(plan.span >> 31);
+    plan_out[2] = (int32_t)((int64_t)plan.span & 0x7fffffff);
+    plan_out[3] = (int32_t)((int64_t)plan.span >> 31);
   }
 }
 
@@ -1324,10 +1337,15 @@ hipError_t launch_step_advance(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *i
 
 hipError_t launch_step_advance_spans(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *item_desc, int32_t *group_first,
                                      int32_t *plan_out, int32_t B, int32_t max_groups, int32_t min_span, int32_t inc,
-                                     void *pair_head, const HeadGeom &geom, hipStream_t stream) {
-  hipLaunchKernelGGL(step_advance_spans_kernel, dim3(1), dim3(kStepThreads), 0, stream, ctx_lens, chunk_prefix,
-                     item_desc, group_first, plan_out, B, max_groups, min_span, inc, static_cast<PairHead *>(pair_head),
-                     geom);
+                                     void *pair_head, const HeadGeom &geom, int64_t cap_tiles, hipStream_t stream) {
+  // (32 bits hold the sums of tiles the kernel forms, up to one stretch past the last)
+  const int64_t most = (1 << 30) / std::max(B, 1);
+  if (cap_tiles <= most)
+    hipLaunchKernelGGL(step_advance_spans_kernel<int32_t>, dim3(1), dim3(kStepThreads), 0, stream, ctx_lens, chunk_prefix,
+                       item_desc, group_first, plan_out, B, max_groups, min_span, inc, static_cast<PairHead *>(pair_head), (int32_t)most, geom);
+  else
+    hipLaunchKernelGGL(step_advance_spans_kernel<int64_t>, dim3(1), dim3(kStepThreads), 0, stream, ctx_lens, chunk_prefix,
+                       item_desc, group_first, plan_out, B, max_groups, min_span, inc, static_cast<PairHead *>(pair_head), INT32_MAX, geom);
   return hipGetLastError();
 }
 
