@@ -434,8 +434,9 @@ int okv_prefill_end(okv_ctx *ctx);
  * caller's workspace, live here in OKV_STATIC_SCRATCH_BYTES of device memory that are part of the
  * library itself (every GPU the library runs on holds them until the process ends).  The call makes
  * no hipMalloc / hipFree and no library call that allocates; its first call on a device looks up the
- * array's address on that device.  It enqueues three kernels on `stream` (work list from the device
- * lengths, split-K attention with the store of k_new / v_new folded in, merge) and returns.
+ * array's address on that device.  It enqueues two or three kernels on `stream` (work list from the device
+ * lengths, where the attention launch does not cut the keys itself; split-K attention with the store of
+ * k_new / v_new folded in; merge) and returns.
  *
  * The batch's lengths are read on the device, so the host never needs them: ctx_lens[b] is the number
  * of keys sequence b attends to, INCLUDING the row stored by this call when k_new / v_new are given
@@ -446,7 +447,7 @@ int okv_prefill_end(okv_ctx *ctx);
  *
  * Every call on a GPU uses that GPU's one array: calls that may overlap on one GPU (two streams, two
  * host threads) race and must be ordered by the caller.  Nothing in the array has to be cleared
- * between calls: each call's first kernel rewrites what the others read.
+ * between calls: each call writes what it reads.
  * OKV_EINVAL: NULL / misaligned pointer, bad shape, B outside [1, OKV_STATIC_MAX_BATCH].
  * OKV_ENOSPC: (B + wavefronts per KV head) work items of n_q_heads * (head_dim + 2) floats, plus the
  * item list, exceed OKV_STATIC_SCRATCH_BYTES (32 query heads of 128: B up to about 1900). */

@@ -54,6 +54,10 @@ struct AttnLaunch {
   int32_t n_groups = 0;                   // stretches in use (with pair_head)
   const int32_t *n_groups_dev = nullptr;  // device: the same number when the host does not know it (the grid is
                            // then max_waves wavefronts)
+  // Instead of a work list: the launch (and the merge) cuts the keys into stretches from batch.ctx_lens itself, at most
+  // n_groups stretches of at least min_span tiles, and no more than grid_groups of them for the lengths there may be.  For
+  // B <= 64, waves_per_pair > 1 and keep_cached launches; the partial results need B + n_groups slots.
+  int32_t from_lens = 0, min_span = 0, grid_groups = 0;
   int32_t max_waves;       // wavefronts of the persistent launch (a multiple of 4)
   // The launch covers items [item_first, item_first + item_count) of the list: all of them, or
   // those of one block class.  `pool` then holds the blocks with ids from id_base on, and

@@ -123,6 +123,7 @@ struct AttnArgs {
   const int32_t *block_table, *chunk_prefix;
   const int4 *item_desc;           // [n_items] (sequence, first key, one past last key, flags)
   const int32_t *n_groups_dev;     // NULL, or where the number of groups is to be read (n_groups is then ignored)
+  const int32_t *lens;             // the batch's lengths, for a launch that finds its shares from them (else NULL)
   const PairHead *pair_head;       // what every (stretch, KV head) pair starts with: pair p is wavefront p's; or
                                    // NULL: group j is item j of the launch
   int32_t n_groups;
@@ -134,6 +135,7 @@ struct AttnArgs {
   int32_t mirror_shift;            // id_base minus the id of the first block of pool_mirror
   int32_t mirror_is_tail;          // pool_mirror is the layer's tail slots: block (2 b + (block index & 1)) of it
   int32_t B, n_cls;                // merge: chunk_prefix is [n_cls][B] (+ 1)
+  int32_t min_span;                // kFromLens: shortest stretch, in tiles
   float scale_log2e;
 };
 
@@ -325,6 +327,38 @@ __device__ __forceinline__ void tile_update_pair(const half8_t (&qb)[2], float &
   }
 }
 
+// ---- the work list from the lengths alone ----------------------------------------------------------------------
+//
+// For a batch of at most 64 sequences a wavefront cuts the keys into stretches by itself, a sequence per lane: the
+// lengths in one load, their tiles summed up by shuffles, and the same plan that the bookkeeping kernel makes.  The launch
+// of that kernel (4.8 us, as long as the attention over a small batch) is then not needed where a call has no context to
+// keep a work list in.  Partial results of sequence b in stretch j go to slot b + j.
+constexpr int kLensBatch = 64;
+struct LensPlan {
+  int n, tiles, before;      // this lane's sequence: keys, 16-key tiles, tiles of the sequences before it
+  int total, span, n_groups; // tiles of the batch, tiles per stretch, stretches
+};
+__device__ __forceinline__ LensPlan plan_from_lens(const int32_t *lens, const int B, const int max_groups, const int min_span, const int lane) {
+  LensPlan p;
+  p.n = lane < B ? lens[lane] : 0;
+  p.tiles = min(max((p.n >> 4) + ((p.n & 15) != 0), 0), 1 << 24);          // (a length no sequence can have stays within 32 bits)
+  int sum = p.tiles;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int up = __shfl_up(sum, off);
+    if (lane >= off) sum += up;
+  }
+  p.before = sum - p.tiles;
+  p.total = __builtin_amdgcn_readlane(sum, 63);
+  const SpanPlanOf<int32_t> plan = span_plan<int32_t>(p.total, max_groups, min_span);
+  p.span = __builtin_amdgcn_readfirstlane(plan.span);
+  p.n_groups = __builtin_amdgcn_readfirstlane(plan.n_groups);
+  return p;
+}
+
+// Where an attention launch finds its shares: the work list's items one by one, the table of heads, or the lengths.
+enum Source { kFromItems = 0, kFromHeads = 1, kFromLens = 2 };
+
 // A work unit as a wavefront sees it: an item (a run of keys of one sequence) for one KV head.  All
 // fields are wavefront-uniform and come through the scalar cache (constant address space: nothing
 // writes the item list or the block table while this kernel runs).
@@ -359,23 +393,26 @@ struct Unit {
 // keeping short.
 //
 // The start of a launch is the other fixed cost: until a wavefront's first tile arrives nothing hides the
-// round trips in front of it (a scalar load right after the launch takes 1-2 us).  With HEADS the
+// round trips in front of it (a scalar load right after the launch takes 1-2 us).  With kFromHeads the
 // wavefront's own (stretch, KV head) pair comes from a table the bookkeeping kernel wrote (PairHead): one
 // look-up, whose address needs only arguments that arrive in registers, then the first tile loads, and
 // everything else (the other arguments, the LDS addresses, the zeroed sums) is set up behind them.  Without
 // it (a split size fixed by the caller, block classes, more pairs than wavefronts) pairs are dealt out
 // round robin and the first item is found through group_first, the item list and the block table.
 //
-// NS > 1 (with HEADS): a (stretch, KV head) pair has a workgroup of NS wavefronts to itself, which take the tiles of an item
+// NS > 1 (not with kFromItems): a (stretch, KV head) pair has a workgroup of NS wavefronts to itself, which take the tiles of an item
 // in turn (wavefront s the tiles s, s + NS, ...) and put their sums together through LDS at the item's end ([B]).  Where
 // there are fewer pairs than the memory system wants wavefronts, or where items are short, what a launch takes is a
 // chain of tiles per wavefront, each a round trip to memory and through LDS; NS wavefronts shorten the chain without
 // cutting the keys any finer, so without more partial results or a merge (see waves_per_pair for when).
-template <int D, bool PAGED, int PIPE, bool HEADS, bool NT, int NS>
+//
+// SRC = kFromLens (with NS > 1, batches of at most kLensBatch): `pair_head` is the device array of lengths and n_groups the
+// most stretches there may be; the pair's items follow from the lengths (plan_from_lens).
+template <int D, bool PAGED, int PIPE, int SRC, bool NT, int NS>
 __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_split_mfma_kernel(
     const PairHead *pair_head, const uint16_t *pool, const uint16_t *q, const int32_t *n_groups_dev, const int32_t n_groups,
     const int32_t G, const int32_t H, const int32_t R, const int32_t v_tiles, const AttnArgs a) {
-  static_assert(NS == 1 || HEADS, "several wavefronts per pair need the table of heads");
+  static_assert(NS == 1 ? SRC != kFromLens : SRC != kFromItems, "several wavefronts per pair need a pair per workgroup");
   constexpr int kRegion = 2 * lds_tiles<D>() * lds_tile_bytes<D>();     // LDS of a wavefront
   static_assert(kRegion >= D / 16 * 1024 + 512, "a wavefront's sums, maxima and weights must fit its tiles' place");
   __shared__ __attribute__((aligned(16))) char lds_all[NS > 1 ? NS : kWavesPerBlock][kRegion];
@@ -393,10 +430,14 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
   // The parameters in front of `a` are the ones the first loads need: the build asks for the leading kernel
   // arguments to be in scalar registers when a wavefront starts, so the pair's record can be asked for at
   // once, and the first tiles as soon as it is there.
-  constexpr bool by_head = HEADS;                        // (pair_head is not NULL then)
+  constexpr bool by_head = SRC == kFromHeads;            // (pair_head is not NULL then)
+  constexpr bool by_lens = SRC == kFromLens;
   int32x8_t w = {0, 0, 0, 0, 0, 0, 0, 0};
   if (by_head) w = *(const_head_ptr)(uintptr_t)(pair_head + pair);
-  const uint32_t n_pairs = (n_groups_dev ? (uint32_t)((const_i32_ptr)(uintptr_t)n_groups_dev)[0] : (uint32_t)n_groups) * (uint32_t)G;
+  LensPlan lp = {};
+  if (by_lens) lp = plan_from_lens(reinterpret_cast<const int32_t *>(pair_head), a.B, n_groups, a.min_span, lane);
+  const uint32_t n_pairs = (by_lens ? (uint32_t)lp.n_groups : n_groups_dev ? (uint32_t)((const_i32_ptr)(uintptr_t)n_groups_dev)[0]
+                                                                          : (uint32_t)n_groups) * (uint32_t)G;
   asm volatile("" ::"s"(w[0]), "s"(n_pairs));           // (both asked for before either is waited for)
   if (pair >= n_pairs) return;
   PairHead head = {};
@@ -431,9 +472,20 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
     for (int j = 0; j < LPT; ++j) t.v[j] = load_kv<NT>(vp + j * 64);
   };
 
-  // the items of the pair: item .. item_end - 1 (relative to the launch's first item)
+  // the items of the pair: item .. item_end - 1 (relative to the launch's first item); by lengths: the pieces that the
+  // sequences leave in the stretch's tiles [first_tile, end_tile), `item` the sequence of the next one, 64: none
   int item, item_end;
-  if (by_head) {
+  int first_tile = 0, end_tile = 0, stretch = 0;
+  auto next_with_keys = [&](int after) -> int {          // first sequence behind `after` with tiles in front of end_tile
+    const uint64_t mask = __ballot(lp.tiles > 0 && lp.before < end_tile && lp.before + lp.tiles > first_tile && lane > after);
+    return mask ? (int)__builtin_ctzll(mask) : 64;
+  };
+  if (by_lens) {
+    stretch = (int)(pair / (uint32_t)G);
+    first_tile = stretch * lp.span, end_tile = min(first_tile + lp.span, lp.total);
+    item = next_with_keys(-1), item_end = 64;
+    if (item >= 64) return;                              // (a batch without keys)
+  } else if (by_head) {
     item = head.item, item_end = head.item + head.count;
   } else {
     item = (int)(pair / (uint32_t)G), item_end = item + 1;
@@ -481,13 +533,24 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
   floatx4_t o[D / 16];
   uint4 k_row = make_uint4(0u, 0u, 0u, 0u), v_row = k_row;
   C.it = C.g = C.b = C.lo = C.hi = C.flags = 0;
+  auto unit_from_lens = [&](int b) {                     // N: what of sequence b lies in the stretch
+    const int before = __builtin_amdgcn_readlane(lp.before, b), tiles = __builtin_amdgcn_readlane(lp.tiles, b);
+    const int from = max(first_tile - before, 0), to = min(end_tile - before, tiles);
+    N.it = b + stretch, N.g = (int)(pair % (uint32_t)G), N.b = b;
+    N.lo = from << 4, N.hi = to == tiles ? __builtin_amdgcn_readlane(lp.n, b) : to << 4;
+    N.flags = (to == tiles ? kItemLast : 0) | (to == tiles && from == 0 ? kItemWhole : 0);
+#pragma unroll
+    for (int i = 0; i < PIPE; ++i) N.blk0[i] = blk_of(b, min(from + sub + i * NS, to - 1));
+  };
 
   for (;;) {
     // N's descriptor and first block ids: for the first unit waited for here; for the others asked for
     // a whole item earlier ([C] below)
     if (!live) {
       N.it = a.item_first + item;
-      if (by_head) {                                     // its first tiles are on their way already
+      if (by_lens) {
+        unit_from_lens(item);
+      } else if (by_head) {                                     // its first tiles are on their way already
         N.g = head.flags_g >> 8;
         N.b = head.b, N.lo = head.lo, N.hi = head.hi, N.flags = head.flags_g & 0xff;
 #pragma unroll
@@ -502,7 +565,7 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
     }
     // [A] the next unit's first tiles and its q
     // (with a table of heads a wavefront stays with one KV head: nothing to work out again)
-    const TileAddr ta_next = by_head && live ? ta : tile_addr<D>(G, a.gg, a.tcap, a.st_log2, N.g);
+    const TileAddr ta_next = (by_head || by_lens) && live ? ta : tile_addr<D>(G, a.gg, a.tcap, a.st_log2, N.g);
     if (has_next && (live || !by_head)) {
 #pragma unroll
       for (int i = 0; i < PIPE; ++i) load_tile(buf[i], ta_next, min((N.lo >> 4) + sub + i * NS, (N.hi - 1) >> 4), N.blk0[i]);
@@ -611,7 +674,10 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
     C = N;
     ta = ta_next;
     live = true;
-    if (item + 1 < item_end) {
+    if (by_lens) {
+      item = next_with_keys(item);
+      has_next = item < 64;
+    } else if (item + 1 < item_end) {
       ++item;
     } else {
       pair += n_waves;
@@ -620,7 +686,9 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
         item = (int)(pair / (uint32_t)G), item_end = item + 1;
       }
     }
-    if (has_next) {
+    if (by_lens) {
+      if (has_next) unit_from_lens(item);
+    } else if (has_next) {
       N.g = by_head ? C.g : (int)(pair % (uint32_t)G);
       N.it = a.item_first + item;
       const const_i32_ptr dp = (const_i32_ptr)(uintptr_t)(a.item_desc + N.it);
@@ -700,7 +768,8 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
 // items of a ragged batch): the rows of the first four items are asked for together with the maxima and weights, so
 // a sequence in at most four pieces waits for two round trips (the item range, then everything) and not for three, and
 // four (b, h) pairs share a workgroup.
-template <int D>
+// LENS: `chunk_prefix` is the device array of lengths instead, and a sequence's pieces are where plan_from_lens puts them.
+template <int D, bool LENS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_prefix, const float *part_ml, const float *part_o,
                                                           const int32_t B, const int32_t n_cls, const int32_t H, const AttnArgs a) {
   // (leading parameters: in scalar registers when the wavefront starts, so the first look-ups need no round trip
@@ -710,7 +779,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
   const int b = blockIdx.y, h = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (h >= H) return;
   auto row_of = [&](int it) { return part_o + ((size_t)it * H + h) * D + lane * EPT; };
-  const int first0 = chunk_prefix[b], cnt0 = chunk_prefix[b + 1] - first0;
+  int first0, cnt0;
+  if (LENS) {
+    const LensPlan lp = plan_from_lens(chunk_prefix, B, a.n_groups, a.min_span, lane);
+    const int before = __builtin_amdgcn_readlane(lp.before, b), tiles = __builtin_amdgcn_readlane(lp.tiles, b);
+    const int j0 = before / lp.span, j1 = (before + tiles - 1) / lp.span;
+    first0 = b + j0, cnt0 = tiles > 0 ? j1 - j0 + 1 : 0;
+  } else {
+    first0 = chunk_prefix[b], cnt0 = chunk_prefix[b + 1] - first0;
+  }
   if (n_cls == 1 && cnt0 <= 1) return;                 // written by the split kernel
   float ahead[4][EPT];                                 // rows of the first class's first four items (past its last: that one again)
 #pragma unroll
@@ -720,8 +797,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
   float M = kNegBig;
   int total = 0;
   for (int cls = 0; cls < n_cls; ++cls) {
-    const int first = chunk_prefix[cls * B + b];
-    const int n_chunks = chunk_prefix[cls * B + b + 1] - first;
+    const int first = LENS ? first0 : chunk_prefix[cls * B + b];
+    const int n_chunks = LENS ? cnt0 : chunk_prefix[cls * B + b + 1] - first;
     total += n_chunks;
     for (int c0 = 0; c0 < n_chunks; c0 += 64) {
       const int c = c0 + lane;
@@ -736,8 +813,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
 #pragma unroll
   for (int e = 0; e < EPT; ++e) acc[e] = 0.f;
   for (int cls = 0; cls < n_cls; ++cls) {
-    const int first = chunk_prefix[cls * B + b];
-    const int n_chunks = chunk_prefix[cls * B + b + 1] - first;
+    const int first = LENS ? first0 : chunk_prefix[cls * B + b];
+    const int n_chunks = LENS ? cnt0 : chunk_prefix[cls * B + b + 1] - first;
     for (int c0 = 0; c0 < n_chunks; c0 += 64) {
       const int c = c0 + lane;
       float w = 0.f, lw = 0.f;
@@ -808,22 +885,29 @@ constexpr int base_depth() {
   return D == 64 ? (NS > 1 ? 2 : 4) : 1;
 }
 
-template <int D, bool PAGED, bool HEADS, bool NT, int NS>
+template <int D, bool PAGED, int SRC, bool NT, int NS>
 void launch_split_as(const AttnArgs &args, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_split_mfma_kernel<D, PAGED, base_depth<D, NS>(), HEADS, NT, NS>), grid, dim3((NS > 1 ? NS : kWavesPerBlock) * 64), 0,
-                     stream, args.pair_head, args.pool, args.q, args.n_groups_dev, args.n_groups, args.G, args.H, args.R,
-                     args.gg << args.st_log2, args);
+  hipLaunchKernelGGL((attn_split_mfma_kernel<D, PAGED, base_depth<D, NS>(), SRC, NT, NS>), grid, dim3((NS > 1 ? NS : kWavesPerBlock) * 64), 0,
+                     stream, SRC == kFromLens ? reinterpret_cast<const PairHead *>(args.lens) : args.pair_head, args.pool, args.q,
+                     args.n_groups_dev, args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args);
 }
 
-// (D = 64 knows one or two wavefronts per pair, see waves_per_pair)
+// (D = 64 knows one or two wavefronts per pair, see waves_per_pair; launches from the lengths are small ones: never one
+// wavefront per pair, nor more keys than the memory-side cache holds)
 template <int D, bool PAGED, bool NT>
 void launch_split_kept(const AttnArgs &args, int waves, dim3 grid, hipStream_t stream) {
-  if (!args.pair_head) return launch_split_as<D, PAGED, false, NT, 1>(args, grid, stream);
-  if constexpr (D == 128) {
-    if (waves == 4) return launch_split_as<D, PAGED, true, NT, 4>(args, grid, stream);
+  if constexpr (!NT) {
+    if constexpr (D == 128) {
+      if (args.lens && waves == 4) return launch_split_as<D, PAGED, kFromLens, NT, 4>(args, grid, stream);
+    }
+    if (args.lens) return launch_split_as<D, PAGED, kFromLens, NT, 2>(args, grid, stream);
   }
-  if (waves == 2) return launch_split_as<D, PAGED, true, NT, 2>(args, grid, stream);
-  launch_split_as<D, PAGED, true, NT, 1>(args, grid, stream);
+  if (!args.pair_head) return launch_split_as<D, PAGED, kFromItems, NT, 1>(args, grid, stream);
+  if constexpr (D == 128) {
+    if (waves == 4) return launch_split_as<D, PAGED, kFromHeads, NT, 4>(args, grid, stream);
+  }
+  if (waves == 2) return launch_split_as<D, PAGED, kFromHeads, NT, 2>(args, grid, stream);
+  launch_split_as<D, PAGED, kFromHeads, NT, 1>(args, grid, stream);
 }
 
 template <int D>
@@ -856,7 +940,9 @@ AttnArgs make_args(const AttnLaunch &a) {
   args.item_desc = a.batch.item_desc;
   args.n_groups_dev = a.n_groups_dev;
   args.pair_head = static_cast<const PairHead *>(a.pair_head);
-  args.n_groups = a.pair_head ? a.n_groups : a.item_count;
+  args.lens = a.from_lens ? a.batch.ctx_lens : nullptr;
+  args.min_span = a.min_span;
+  args.n_groups = a.pair_head || a.from_lens ? a.n_groups : a.item_count;
   args.H = s.H;
   args.G = s.G;
   args.R = s.H / s.G;
@@ -889,10 +975,14 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream, hipEvent_
   // persistent launch: no more wavefronts than there are (group, KV head) pairs, no more than a.max_waves
   const int64_t want = ((int64_t)args.n_groups * s.G + kWavesPerBlock - 1) / kWavesPerBlock;
   const int64_t cap = std::max<int64_t>(1, a.max_waves / kWavesPerBlock);
-  const int waves = a.pair_head ? a.waves_per_pair : 1;
+  const int waves = a.pair_head || a.from_lens ? a.waves_per_pair : 1;
+  if (a.from_lens && (waves < 2 || !a.keep_cached || a.pair_head || a.batch.B > kLensBatch ||
+                      a.n_groups < 1 || a.grid_groups < 1 || a.min_span < 1))
+    return hipErrorInvalidValue;
   if (waves != 1 && waves != 2 && !(waves == 4 && s.D == 128)) return hipErrorInvalidValue;
   const int64_t pairs = (a.n_groups_dev ? cap : std::min(want, cap)) * kWavesPerBlock;      // that the grid covers
-  dim3 grid((unsigned)(waves > 1 ? std::min<int64_t>(pairs, (int64_t)args.n_groups * s.G) : pairs / kWavesPerBlock));
+  dim3 grid((unsigned)(a.from_lens ? (int64_t)a.grid_groups * s.G
+                       : waves > 1 ? std::min<int64_t>(pairs, (int64_t)args.n_groups * s.G) : pairs / kWavesPerBlock));
   // (stretches come with a table of heads, which needs a wavefront per (stretch, KV head) pair and a pool that
   // holds the blocks as the table numbers them)
   if (a.pair_head && (want > cap || a.id_base != 0 || a.item_first != 0)) return hipErrorInvalidValue;
@@ -915,10 +1005,19 @@ hipError_t launch_merge(const AttnLaunch &a, hipStream_t stream) {
   const PoolShape &s = a.shape;
   const AttnArgs args = make_args(a);
   dim3 mgrid((s.H + 3) / 4, a.batch.B);
+  if (args.lens) {
+    if (s.D == 128)
+      hipLaunchKernelGGL((attn_merge_kernel<128, true>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args);
+    else if (s.D == 64)
+      hipLaunchKernelGGL((attn_merge_kernel<64, true>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args);
+    else
+      return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
   if (s.D == 128)
-    hipLaunchKernelGGL(attn_merge_kernel<128>, mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args);
+    hipLaunchKernelGGL((attn_merge_kernel<128, false>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args);
   else if (s.D == 64)
-    hipLaunchKernelGGL(attn_merge_kernel<64>, mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args);
+    hipLaunchKernelGGL((attn_merge_kernel<64, false>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

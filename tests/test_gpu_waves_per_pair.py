@@ -19,10 +19,13 @@ EDGES = [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 79, 80, 96, 112, 
 @pytest.mark.parametrize("what,H,G,d,T,B,cap", [
     ("d64 two", 8, 4, 64, 16, 22, 400), ("d64 two contiguous", 12, 12, 64, 0, 22, 300), ("d64 one", 16, 16, 64, 32, 64, 2112),
     ("d128 four", 8, 8, 128, 16, 22, 400), ("d128 four grouped", 16, 1, 128, 0, 22, 320), ("d128 two", 64, 32, 128, 16, 40, 500),
-    ("d128 one", 16, 16, 128, 16, 64, 720)])
+    ("d128 one", 16, 16, 128, 16, 64, 720),
+    # the entry point that allocates nothing: up to 64 sequences without a work list, beyond with one
+    ("d64 two at 64", 4, 2, 64, 16, 64, 160), ("d64 two at 65", 4, 2, 64, 16, 65, 160), ("d128 four at 64", 2, 1, 128, 0, 64, 160),
+    ("d128 two at 64", 64, 64, 128, 16, 64, 96)])
 def test_every_output(what, H, G, d, T, B, cap):
     print(f"{what}: H={H} G={G} d={d} T={T} B={B} cap={cap}", flush=True)
-    ctx = [(EDGES * 3)[b] if b < 44 else 97 + 13 * (b % 11) for b in range(B)]
+    ctx = [min(cap - 8, (EDGES * 3)[b] if b < 44 else 97 + 13 * (b % 11)) for b in range(B)]
     ctx[B // 2] = cap - 8                                  # one sequence near its capacity, cut several times
     for out_dtype in (0, 1):
         st = build_stack(L=1, H=H, G=G, d=d, T=T, ctx_before=ctx, cap_tokens=cap, out_dtype=out_dtype, seed=71)
