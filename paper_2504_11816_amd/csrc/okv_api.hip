@@ -491,21 +491,26 @@ int exec_ops(okv_ctx *ctx, const std::vector<Op> &ops, const void *a0, const voi
 // One or two small host arrays to the device, before whatever is enqueued on the compute stream next.  Called with that
 // stream drained, so the memory of the upload before this one is free again; it grows to the largest upload and goes
 // with the context.  Where it cannot be had (pinned memory is limited) the arrays are copied synchronously.
+constexpr int64_t kUploadTileBytes = 1 << 20;              // of a prompt store's tile list, reserved when the context is made
+
+void reserve_upload(okv_ctx *ctx, int64_t need) {
+  if (need <= ctx->up_cap) return;
+  if (ctx->h_up) (void)hipHostFree(ctx->h_up);
+  ctx->h_up = nullptr;
+  ctx->up_cap = 0;
+  void *p = nullptr;
+  if (hipHostMalloc(&p, (size_t)need, hipHostMallocMapped) == hipSuccess) {
+    ctx->h_up = static_cast<char *>(p);
+    ctx->up_cap = need;
+  } else {
+    (void)hipGetLastError();                               // a refusal is no error of this call, nor of the next one
+  }
+}
+
 int upload_tables(okv_ctx *ctx, void *dst0, const void *src0, int64_t bytes0, void *dst1 = nullptr, const void *src1 = nullptr,
                   int64_t bytes1 = 0) {
-  const int64_t at1 = (bytes0 + 255) / 256 * 256, need = at1 + bytes1;
-  if (need > ctx->up_cap) {
-    if (ctx->h_up) (void)hipHostFree(ctx->h_up);
-    ctx->h_up = nullptr;
-    ctx->up_cap = 0;
-    void *p = nullptr;
-    if (hipHostMalloc(&p, (size_t)need, hipHostMallocMapped) == hipSuccess) {
-      ctx->h_up = static_cast<char *>(p);
-      ctx->up_cap = need;
-    } else {
-      (void)hipGetLastError();                           // a refusal is no error of this call, nor of the next one
-    }
-  }
+  const int64_t at1 = (bytes0 + 255) / 256 * 256;
+  reserve_upload(ctx, at1 + bytes1);
   void *dev = nullptr;
   if (!ctx->h_up || hipHostGetDevicePointer(&dev, ctx->h_up, 0) != hipSuccess) {
     if (ctx->h_up) (void)hipGetLastError();
@@ -931,6 +936,10 @@ int okv_create(const okv_config *cfg, okv_ctx **out) {
   OKV_TRY_CREATE(hipMalloc(&ctx->d_pair_head, (size_t)max_pairs(ctx->max_waves) * okv::kPairHeadBytes));
   OKV_TRY_CREATE(hipMemset(ctx->d_pair_head, 0, (size_t)max_pairs(ctx->max_waves) * okv::kPairHeadBytes));
   OKV_TRY_CREATE(hipMalloc(&ctx->d_plan, 4 * sizeof(int32_t)));
+  // What a batch's tables and an ordinary prompt's tiles are uploaded from is had here: allocating it (and growing it) in
+  // the first calls made a new context's first batch and prompt 0.4 ms slower.
+  const int64_t tiles = (int64_t)cfg->max_batch * (((int64_t)ctx->cap_tokens + 15) / 16) * (int64_t)sizeof(int4);
+  reserve_upload(ctx, (int64_t)cfg->max_batch * (int64_t)sizeof(int32_t) + 256 + std::max<int64_t>((int64_t)tbl, std::min(tiles, kUploadTileBytes)));
   if (n_staging >= 2) OKV_TRY_CREATE(own_queue_stream(&ctx->h2d_odd));
   ctx->steps_ahead = !any_host ? 0 : by_class ? OKV_STEPS_AHEAD : OKV_STEPS_AHEAD_LAYERS;
   if (ctx->steps_ahead > 0)
