@@ -38,7 +38,7 @@ PCIE5_X16_GBPS = 64.0       # nominal, one direction
 # has changed since, `traffic` is reported as null.
 TRAFFIC_RECORD = {
     "workload": "cfg2",
-    "kernel_sha256": "4c135d3275e3190b620d8976b4f5fc71ff5b5ca8f61b208f23b0eb973c842efb",
+    "kernel_sha256": "7c6936ca60c09be0fbecd024546086a4d116507b5510e18d54fb691a23d52764",
     "fetch_kib": 199119.5, "fetch_scale": 2.0000, "algorithmic_bytes": 402915328,   # context 737..800
     "write_kib": 768.0, "write_scale": 1.0000,
 }

@@ -4,13 +4,15 @@
 // V element) reads every KV byte exactly once and does about one flop per byte,
 // so the kernel is organised around the memory system:
 //
-//   * one wavefront owns one work item = (sequence, KV head, a run of keys) and
-//     all H/G query heads that share the KV head, so K/V is read once per group;
+//   * one wavefront (two or four on short launches) owns one work item = (sequence, KV
+//     head, a run of keys) and all H/G query heads that share the KV head, so K/V is read
+//     once per group;
 //   * a K or V tile of 16 tokens is one contiguous run of 16*d*2 bytes; every
 //     load instruction moves 16 bytes per lane, 1 KiB per wavefront;
 //   * tiles are loaded PIPE deep ahead of their use into registers, 8 KiB in flight
 //     per wavefront at d = 128 (16 KiB at d = 64, see base_depth), one wavefront per
-//     SIMD: a thousand such streams is where the memory system runs best;
+//     SIMD: a thousand such streams is where the memory system runs best; where K and V of all
+//     layers exceed the memory-side cache the loads are nontemporal (64.2 -> 60.9 us per 403 MB);
 //   * the arithmetic of a tile (scores, online softmax, weighted sum of V rows) runs
 //     on the matrix cores, which takes it off the vector ALU; the tile passes through
 //     LDS that belongs to the wavefront alone to reach the operand layouts;
