@@ -477,6 +477,9 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
 // 89 -> 61, 50 -> 31, 146 -> 77.  What bounds it: with every operand in the L2s (timing builds) the same walk takes
 // 105 of the 114 us, with x packed nothing less; reading LDS a step ahead of the matrix instructions, or two
 // fragments at a time, was slower, two stages in flight instead of one 8-15 % faster.
+// The small tiles follow the bytes a compute unit takes in, about 62 KB/us with the weights coming from HBM and 77 from
+// its L2, alone on the chip as well (a stage of 96 x 128, 28 KiB: 0.47 and 0.365 us, where its matrix instructions take 0.16):
+// two or three teams of wavefronts along the inputs, or the next half stage read from LDS early, change nothing.
 //
 // LDS layout of a stage: 16 rows x 64 inputs (8 pieces of 16 bytes a row) are 128 units.  Row rr, piece p = 2 v + ql
 // sits at unit 64 (rr & 1) + 16 (2 (v >> 1) + ql) + (rr + v) % 16: an instruction's 64 units are the eight even (odd)
