@@ -675,8 +675,8 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
 __global__ __launch_bounds__(256) void reduce_epilogue_kernel(const float *shares, const int32_t n_out, const int32_t splits,
                                                                  const int32_t m, const LinearArgs a) {
   // four neighbouring features per thread; the shares are fetched four cuts at a time with loads that do not
-  // depend on one another (a cut past the last one re-reads the last with weight 0), so a thread waits for
-  // one round trip, not for one per cut
+  // depend on one another (past the last cut the last is read again and left out of the sum: not added with
+  // weight 0, which would make a NaN of an infinity), so a thread waits for one round trip, not for one per cut
   const int n = (blockIdx.x * 256 + threadIdx.x) * 4, mrow = blockIdx.y;
   if (n >= n_out) return;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -689,8 +689,8 @@ __global__ __launch_bounds__(256) void reduce_epilogue_kernel(const float *share
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float w = s2 + j < splits ? 1.f : 0.f;
-      v.x += w * part[j].x, v.y += w * part[j].y, v.z += w * part[j].z, v.w += w * part[j].w;
+      const bool in = s2 + j < splits;
+      v.x += in ? part[j].x : 0.f, v.y += in ? part[j].y : 0.f, v.z += in ? part[j].z : 0.f, v.w += in ? part[j].w : 0.f;
     }
   }
   int seg;                                                             // a segment is a multiple of 16 features wide
@@ -820,15 +820,15 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
         float4 lo[4], hi[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int sj = s2 + j < splits ? s2 + j : splits - 1;      // past the last cut: the last again, weight 0
+          const int sj = s2 + j < splits ? s2 + j : splits - 1;      // past the last cut: the last again, left out below
           const float4 *sp = reinterpret_cast<const float4 *>(shares + ((size_t)sj * m + mrow) * h + p * 8);
           lo[j] = sp[0], hi[j] = sp[1];
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float w = s2 + j < splits ? 1.f : 0.f;
-          acc[0] += w * lo[j].x, acc[1] += w * lo[j].y, acc[2] += w * lo[j].z, acc[3] += w * lo[j].w;
-          acc[4] += w * hi[j].x, acc[5] += w * hi[j].y, acc[6] += w * hi[j].z, acc[7] += w * hi[j].w;
+          const bool in = s2 + j < splits;
+          acc[0] += in ? lo[j].x : 0.f, acc[1] += in ? lo[j].y : 0.f, acc[2] += in ? lo[j].z : 0.f, acc[3] += in ? lo[j].w : 0.f;
+          acc[4] += in ? hi[j].x : 0.f, acc[5] += in ? hi[j].y : 0.f, acc[6] += in ? hi[j].z : 0.f, acc[7] += in ? hi[j].w : 0.f;
         }
       }
       uint4 rb = make_uint4(0u, 0u, 0u, 0u), bb = rb;

@@ -75,3 +75,34 @@ def test_tile_product_repeats_bit_for_bit_and_feeds_a_layer_norm():
         assert torch.equal(y, first)
         want = dl.layernorm(y.double().cpu().numpy(), g.double().cpu().numpy(), e.double().cpu().numpy(), 1e-5)
         assert np.max(np.abs(z.double().cpu().numpy() - want) - 2e-3 * np.abs(want)) <= 2e-3
+
+
+# cuts that are no multiple of the four shares the reductions fetch at a time, with one and two pieces a thread in the
+# reduction that takes a layer norm along
+@pytest.mark.parametrize("m,n_out,n_in,cuts", [(384, 4096, 4096, 2), (256, 768, 3072, 5), (512, 1056, 4224, 7), (200, 9216, 4096, 3)])
+def test_an_infinity_in_the_last_cut_stays_one(m, n_out, n_in, cuts):
+    print(f"m={m} {n_out}x{n_in} cuts={cuts}", flush=True)
+    x = synth.randn_f16_torch((m, n_in), synth.stream_seed(11, 1), DEV)
+    w = (synth.randn_f16_torch((n_out, n_in), synth.stream_seed(11, 2), DEV).float() / n_in ** 0.5).to(torch.float16)
+    row = m // 2
+    x[row, -1] = float("inf")
+    w[:, -1] = 0.5
+    w[::2, -1] = -0.5
+    sign = torch.where(torch.arange(n_out, device=DEV) % 2 == 0, -1.0, 1.0)
+    wp = torch.empty_like(w)
+    binding.okv_pack_linear_weight(wp, w, n_out, n_in)
+    nb = binding.okv_linear_workspace_bytes(m, n_out, n_in)
+    assert nb == cuts * m * n_out * 4
+    ws = torch.zeros(nb, dtype=torch.uint8, device=DEV)
+    g = torch.ones(n_out, dtype=torch.float16, device=DEV)
+    for relu in (False, True):
+        want = sign * float("inf")
+        if relu:
+            want = want.clamp_min(0.0)
+        y, y2, z = (torch.full((m, n_out), float("nan"), dtype=torch.float16, device=DEV) for _ in range(3))
+        binding.okv_linear(x, wp, None, None, y, m, n_out, n_in, relu, 0, ws, nb)
+        binding.okv_linear_layernorm(x, wp, None, None, y2, g, g, z, m, n_out, n_in, 1e-5, relu, 0, ws, nb)
+        torch.cuda.synchronize()
+        for got in (y, y2):
+            assert torch.equal(got[row].float(), want), (relu, got[row][:8])
+            assert bool(torch.isfinite(torch.cat([got[:row], got[row + 1:]])).all())
