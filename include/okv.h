@@ -443,7 +443,7 @@ int okv_prefill_end(okv_ctx *ctx);
  * (that row goes to position ctx_lens[b] - 1).  Pool layout, block table and the meaning of every
  * other argument are those of okv_config / kv_append / decode_attn; the keys of the batch are shared
  * out in equal stretches exactly as a context does with split_tokens = 0, so the results equal
- * decode_attn's bit for bit.
+ * decode_attn's bit for bit, whatever capacities (max_blocks_per_seq, max_ctx) either was given.
  *
  * Every call on a GPU uses that GPU's one array: calls that may overlap on one GPU (two streams, two
  * host threads) race and must be ordered by the caller.  Nothing in the array has to be cleared

@@ -38,6 +38,7 @@ constexpr int kEventRing = 8;            // > copies in flight (at most OKV_MAX_
 #endif
 constexpr int32_t kMinAutoSplit = 128;   // smallest stretch of keys the library cuts a launch into by itself
 constexpr int32_t kMinSpanTiles = kMinAutoSplit / 16;
+constexpr int64_t kLensMaxSpan = 128;      // longest stretch at capacity of an attention launch that cuts the keys itself
 // Records of the per-pair look-up table an attention launch with max_waves wavefronts may read: its grid is
 // whole workgroups of four.
 inline int32_t max_pairs(int32_t max_waves) { return std::max(max_waves, 4); }
@@ -283,7 +284,7 @@ okv::AttnLaunch base_launch(okv_ctx *ctx) {
   if (ctx->spans) {
     a.pair_head = ctx->d_pair_head;
     a.n_groups = ctx->n_groups;
-    a.waves_per_pair = okv::waves_per_pair(a.shape.D, a.shape.G, ctx->B, ctx->cap_tokens, ctx->max_groups, kMinSpanTiles);
+    a.waves_per_pair = okv::waves_per_pair(a.shape.D, a.shape.G, ctx->n_groups, ctx->span_tiles, ctx->n_items);
   }
   a.max_waves = ctx->max_waves;
   a.item_first = 0;
@@ -2044,24 +2045,25 @@ int okv_decode_attn_static(const okv_static_attn *a) {
   l.part_ml = reinterpret_cast<float *>(base + lay.part_ml);
   l.out_fp32 = a->out_dtype;
   l.need_merge = 1;
-  // neither the lengths nor the number of layers is known here: a layer that may hold half of the memory-side cache
-  // and more is taken for one of a stack that does not fit it
+  // Neither the lengths nor the number of layers is known here.  A layer that holds half of the memory-side cache and more
+  // is taken for one of a stack that does not fit it; where the capacity leaves that open, the kernel goes by the lengths
+  // (by the capacity alone, 16 x 512 keys, 8 heads x 128, with room for 32768 took 21.2 us a call against 17.4).
   l.keep_cached = (int64_t)a->B * cap_tokens_of(&c) * G * D * 4 <= okv::kKeepCachedBytes / 2;
   l.pair_head = pair_head;
   l.n_groups = max_groups;
-  l.waves_per_pair = okv::waves_per_pair(D, G, a->B, cap_tokens_of(&c), max_groups, kMinSpanTiles);
-  l.n_groups_dev = plan;                                 // the kernel reads how many stretches are in use
+  l.plan_dev = plan;                                     // the kernel reads how many stretches are in use
   l.max_waves = max_waves;
   l.item_first = 0, l.item_count = (int32_t)max_items;
   l.id_base = l.mirror_base = 0;
   // Small batches go without the bookkeeping launch: the attention launch cuts the keys itself (8 heads x 64, batch 4,
-  // context 256: 15.1 us a call with it, 12.0 without).  Not where one wavefront per pair is wanted or the keys do not fit
-  // the memory-side cache: those launches take dozens of microseconds, and the table of heads starts them sooner.
+  // context 256: 15.1 us a call with it, 12.0 without).  Not where the stretches may be long or the keys may not fit the
+  // memory-side cache: those launches take dozens of microseconds, and the table of heads starts them sooner.
   const int64_t cap_tiles = (cap_tokens_of(&c) + 15) / 16;
-  l.from_lens = a->B <= 64 && l.waves_per_pair > 1 && l.keep_cached && cap_tiles <= (1 << 24);
+  const okv::SpanPlan at_cap = okv::span_plan(a->B * cap_tiles, max_groups, kMinSpanTiles);
+  l.from_lens = a->B <= 64 && l.keep_cached && at_cap.span <= kLensMaxSpan && cap_tiles <= (1 << 24);
   if (l.from_lens) {
     l.pair_head = nullptr;
-    l.n_groups_dev = nullptr;
+    l.plan_dev = nullptr;
     l.min_span = kMinSpanTiles;
     l.grid_groups = (int32_t)std::min<int64_t>(max_groups, std::max<int64_t>(1, a->B * cap_tiles / kMinSpanTiles));
   } else {

@@ -188,16 +188,16 @@ __host__ __device__ inline SpanPlanOf<I> span_plan(I total_tiles, int32_t max_gr
 //   d = 128   4 x 256 keys, 8 heads: 14.9, 12.3 (10.3); one sequence of 2048, 32 heads: 17.9, 15.4 (14.6); 32 x 1100, 2 heads:
 //             19.7, 16.9 (16.4); 32 x 660, 128 / 8 heads: 29.8, 27.4 (31.1); 64 x 2048, 64 / 8 heads: 99.9, 97.4; 128 x 290,
 //             32 / 8 heads: 37.6, 35.6; 32 x 512, 32 heads: 48.4, 48.9; 32 x 768, 32 heads: 64, 65-71
-// The choice may depend on nothing but what every entry point knows (okv_decode_attn_static does not know the lengths),
-// or the same step would be summed in another order there: so on the batch, the shape and the capacity, as if every
-// sequence were at it.  A batch that is a multiple of the stretches is cut least (not at all where lengths are equal).
-inline int32_t waves_per_pair(int32_t D, int32_t G, int32_t B, int64_t cap_tokens, int32_t max_groups, int32_t min_span) {
-  const int64_t tiles = (int64_t)B * ((cap_tokens + 15) >> 4);
-  const SpanPlan p = span_plan(tiles, max_groups, min_span);
-  if (D == 64) return p.span <= 128 ? 2 : 1;
-  if ((int64_t)p.n_groups * G <= 600) return 4;
-  return p.span <= (B % max_groups ? 96 : 40) ? 2 : 1;
+// The choice decides the order of summation, and every entry point has to sum a batch in the same order.  So it follows
+// from the plan of the lengths alone, which each of them has: the host of a context, the bookkeeping kernel's record, and
+// a kernel that reads the lengths itself; capacities, the number of layers and where they lie have no part in it.
+__host__ __device__ inline int32_t waves_per_pair(int32_t D, int32_t G, int32_t n_groups, int64_t span, int32_t n_items) {
+  if (D == 64) return span <= 128 ? 2 : 1;
+  if ((int64_t)n_groups * G <= 600) return 4;
+  return span <= (n_items == n_groups ? 40 : 96) ? 2 : 1;
 }
+// The most there can be, which is what a launch is sized for where the host does not know the lengths.
+constexpr int32_t most_waves_per_pair(int32_t D) { return D == 64 ? 2 : 4; }
 
 // Pieces of a sequence whose tiles are [first, first + tiles) of the stream: it is cut at the multiples
 // of span strictly inside that range.  *k0 receives the first such multiple's index, so that piece c >= 1

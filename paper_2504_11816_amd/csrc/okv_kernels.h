@@ -42,7 +42,7 @@ struct AttnLaunch {
   float *part_ml;          // [n_items * H][2]  (max in log2 units, sum)
   int32_t out_fp32;
   int32_t need_merge;      // some sequence has more than one item
-  int32_t waves_per_pair = 1;  // with pair_head: wavefronts that share a (stretch, KV head) pair (1, 2 or 4)
+  int32_t waves_per_pair = 1;  // with pair_head: wavefronts that share a (stretch, KV head) pair (see waves_per_pair)
   int32_t keep_cached = 1; // the KV of all layers fits the memory-side cache: loads that keep it there
   // How the launch's items are shared out.  pair_head NULL: every item is a group of its own, and the (item, KV
   // head) pairs are dealt out to the wavefronts round robin.  Else the records launch_step_advance_spans wrote
@@ -52,11 +52,11 @@ struct AttnLaunch {
   // them (id_base 0).
   const void *pair_head = nullptr;        // device
   int32_t n_groups = 0;                   // stretches in use (with pair_head)
-  const int32_t *n_groups_dev = nullptr;  // device: the same number when the host does not know it (the grid is
-                           // then max_waves wavefronts)
-  // Instead of a work list: the launch (and the merge) cuts the keys into stretches from batch.ctx_lens itself, at most
-  // n_groups stretches of at least min_span tiles, and no more than grid_groups of them for the lengths there may be.  For
-  // B <= 64, waves_per_pair > 1 and keep_cached launches; the partial results need B + n_groups slots.
+  // Where the host does not know the lengths, the launch finds the plan and its wavefronts per pair itself: from what
+  // launch_step_advance_spans left at plan_dev (with pair_head), or, for up to 64 sequences and keep_cached launches, from
+  // batch.ctx_lens with no work list at all (from_lens; the merge likewise): at most n_groups stretches of at least min_span
+  // tiles, no more than grid_groups of them for the lengths there may be; the partial results need B + n_groups slots.
+  const int32_t *plan_dev = nullptr;
   int32_t from_lens = 0, min_span = 0, grid_groups = 0;
   int32_t max_waves;       // wavefronts of the persistent launch (a multiple of 4)
   // The launch covers items [item_first, item_first + item_count) of the list: all of them, or

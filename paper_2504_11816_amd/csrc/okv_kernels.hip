@@ -124,7 +124,7 @@ struct AttnArgs {
   float *part_ml;
   const int32_t *block_table, *chunk_prefix;
   const int4 *item_desc;           // [n_items] (sequence, first key, one past last key, flags)
-  const int32_t *n_groups_dev;     // NULL, or where the number of groups is to be read (n_groups is then ignored)
+  const int32_t *plan_dev;         // NULL, or where the plan is to be read (n_groups is then the most there may be)
   const int32_t *lens;             // the batch's lengths, for a launch that finds its shares from them (else NULL)
   const PairHead *pair_head;       // what every (stretch, KV head) pair starts with: pair p is wavefront p's; or
                                    // NULL: group j is item j of the launch
@@ -138,6 +138,7 @@ struct AttnArgs {
   int32_t mirror_is_tail;          // pool_mirror is the layer's tail slots: block (2 b + (block index & 1)) of it
   int32_t B, n_cls;                // merge: chunk_prefix is [n_cls][B] (+ 1)
   int32_t min_span;                // kFromLens: shortest stretch, in tiles
+  int64_t keep_tiles;              // plan_dev: up to this many tiles in the batch the loads keep the keys cached
   float scale_log2e;
 };
 
@@ -337,24 +338,27 @@ __device__ __forceinline__ void tile_update_pair(const half8_t (&qb)[2], float &
 // keep a work list in.  Partial results of sequence b in stretch j go to slot b + j.
 constexpr int kLensBatch = 64;
 struct LensPlan {
-  int n, tiles, before;      // this lane's sequence: keys, 16-key tiles, tiles of the sequences before it
+  int n, before;             // this lane's sequence: keys, 16-key tiles of the sequences before it
   int total, span, n_groups; // tiles of the batch, tiles per stretch, stretches
+  int n_items;               // pieces the sequences are cut into: one per stretch and one per sequence that begins in mid-stretch
 };
+__device__ __forceinline__ int tiles_in(const int n) { return (n + 15) >> 4; }
 __device__ __forceinline__ LensPlan plan_from_lens(const int32_t *lens, const int B, const int max_groups, const int min_span, const int lane) {
   LensPlan p;
-  p.n = lane < B ? lens[lane] : 0;
-  p.tiles = min(max((p.n >> 4) + ((p.n & 15) != 0), 0), 1 << 24);          // (a length no sequence can have stays within 32 bits)
-  int sum = p.tiles;
+  p.n = lane < B ? min(max(lens[lane], 0), 1 << 28) : 0;                  // (a length no sequence can have stays within 32 bits)
+  const int tiles = tiles_in(p.n);
+  int sum = tiles;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     const int up = __shfl_up(sum, off);
     if (lane >= off) sum += up;
   }
-  p.before = sum - p.tiles;
+  p.before = sum - tiles;
   p.total = __builtin_amdgcn_readlane(sum, 63);
   const SpanPlanOf<int32_t> plan = span_plan<int32_t>(p.total, max_groups, min_span);
   p.span = __builtin_amdgcn_readfirstlane(plan.span);
   p.n_groups = __builtin_amdgcn_readfirstlane(plan.n_groups);
+  p.n_items = p.n_groups + __builtin_popcountll(__ballot(p.n > 0 && p.before % p.span != 0));
   return p;
 }
 
@@ -408,40 +412,24 @@ struct Unit {
 // chain of tiles per wavefront, each a round trip to memory and through LDS; NS wavefronts shorten the chain without
 // cutting the keys any finer, so without more partial results or a merge (see waves_per_pair for when).
 //
-// SRC = kFromLens (with NS > 1, batches of at most kLensBatch): `pair_head` is the device array of lengths and n_groups the
-// most stretches there may be; the pair's items follow from the lengths (plan_from_lens).
+// SRC = kFromLens (batches of at most kLensBatch): the pair's items follow from the lengths (plan_from_lens).
+//
+// The body of a wavefront, for the kernels below that find its pair and, by kFromHeads, that pair's record `w`: `wave` is its place
+// in the workgroup's LDS and `sub` which of the pair's wavefronts it is.
+template <int D>
+constexpr int lds_region() { return 2 * lds_tiles<D>() * lds_tile_bytes<D>(); }       // LDS of a wavefront
+
 template <int D, bool PAGED, int PIPE, int SRC, bool NT, int NS>
-__global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_split_mfma_kernel(
-    const PairHead *pair_head, const uint16_t *pool, const uint16_t *q, const int32_t *n_groups_dev, const int32_t n_groups,
-    const int32_t G, const int32_t H, const int32_t R, const int32_t v_tiles, const AttnArgs a) {
-  static_assert(NS == 1 ? SRC != kFromLens : SRC != kFromItems, "several wavefronts per pair need a pair per workgroup");
-  constexpr int kRegion = 2 * lds_tiles<D>() * lds_tile_bytes<D>();     // LDS of a wavefront
-  static_assert(kRegion >= D / 16 * 1024 + 512, "a wavefront's sums, maxima and weights must fit its tiles' place");
-  __shared__ __attribute__((aligned(16))) char lds_all[NS > 1 ? NS : kWavesPerBlock][kRegion];
+__device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()], const uint32_t wave, const int sub, uint32_t pair,
+                                                const uint32_t n_pairs, const int32x8_t w, const LensPlan &lp, const uint16_t *pool,
+                                                const uint16_t *q, const int32_t G, const int32_t H, const int32_t R,
+                                                const int32_t v_tiles, const AttnArgs &a) {
+  static_assert(NS == 1 || SRC != kFromItems, "several wavefronts per pair need a pair per workgroup");
+  static_assert(lds_region<D>() >= D / 16 * 1024 + 512, "a wavefront's sums, maxima and weights must fit its tiles' place");
   constexpr int LPR = D / 8, RPL = 64 / LPR, LPT = D / 32;
+  constexpr bool by_head = SRC == kFromHeads, by_lens = SRC == kFromLens;
   const int lane = threadIdx.x & 63;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t n_waves = gridDim.x * kWavesPerBlock;
-  const int sub = NS > 1 ? (int)wave : 0;                // which of the pair's wavefronts this is
-  uint32_t pair = NS > 1 ? blockIdx.x : blockIdx.x * kWavesPerBlock + wave;    // of the unit N below
-  // With a table of heads every (stretch, KV head) pair has a wavefront of its own and its head says what
-  // the pair starts with; otherwise pairs are dealt out round robin.  The number of groups is a launch
-  // argument, or (for callers that do not know the batch's lengths on the host) what the bookkeeping kernel
-  // left in device memory.
-  //
-  // The parameters in front of `a` are the ones the first loads need: the build asks for the leading kernel
-  // arguments to be in scalar registers when a wavefront starts, so the pair's record can be asked for at
-  // once, and the first tiles as soon as it is there.
-  constexpr bool by_head = SRC == kFromHeads;            // (pair_head is not NULL then)
-  constexpr bool by_lens = SRC == kFromLens;
-  int32x8_t w = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (by_head) w = *(const_head_ptr)(uintptr_t)(pair_head + pair);
-  LensPlan lp = {};
-  if (by_lens) lp = plan_from_lens(reinterpret_cast<const int32_t *>(pair_head), a.B, n_groups, a.min_span, lane);
-  const uint32_t n_pairs = (by_lens ? (uint32_t)lp.n_groups : n_groups_dev ? (uint32_t)((const_i32_ptr)(uintptr_t)n_groups_dev)[0]
-                                                                          : (uint32_t)n_groups) * (uint32_t)G;
-  asm volatile("" ::"s"(w[0]), "s"(n_pairs));           // (both asked for before either is waited for)
-  if (pair >= n_pairs) return;
   PairHead head = {};
   if (by_head) {
     head.item = w[0], head.count = w[1], head.b = w[2], head.lo = w[3], head.hi = w[4], head.flags_g = w[5];
@@ -479,7 +467,7 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
   int item, item_end;
   int first_tile = 0, end_tile = 0, stretch = 0;
   auto next_with_keys = [&](int after) -> int {          // first sequence behind `after` with tiles in front of end_tile
-    const uint64_t mask = __ballot(lp.tiles > 0 && lp.before < end_tile && lp.before + lp.tiles > first_tile && lane > after);
+    const uint64_t mask = __ballot(lp.n > 0 && lp.before < end_tile && lp.before + tiles_in(lp.n) > first_tile && lane > after);
     return mask ? (int)__builtin_ctzll(mask) : 64;
   };
   if (by_lens) {
@@ -536,10 +524,10 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
   uint4 k_row = make_uint4(0u, 0u, 0u, 0u), v_row = k_row;
   C.it = C.g = C.b = C.lo = C.hi = C.flags = 0;
   auto unit_from_lens = [&](int b) {                     // N: what of sequence b lies in the stretch
-    const int before = __builtin_amdgcn_readlane(lp.before, b), tiles = __builtin_amdgcn_readlane(lp.tiles, b);
+    const int before = __builtin_amdgcn_readlane(lp.before, b), n = __builtin_amdgcn_readlane(lp.n, b), tiles = tiles_in(n);
     const int from = max(first_tile - before, 0), to = min(end_tile - before, tiles);
     N.it = b + stretch, N.g = (int)(pair % (uint32_t)G), N.b = b;
-    N.lo = from << 4, N.hi = to == tiles ? __builtin_amdgcn_readlane(lp.n, b) : to << 4;
+    N.lo = from << 4, N.hi = to == tiles ? n : to << 4;
     N.flags = (to == tiles ? kItemLast : 0) | (to == tiles && from == 0 ? kItemWhole : 0);
 #pragma unroll
     for (int i = 0; i < PIPE; ++i) N.blk0[i] = blk_of(b, min(from + sub + i * NS, to - 1));
@@ -762,6 +750,93 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
   }
 }
 
+// Tiles in flight per wavefront.  At d = 128 what counts is bytes: about 8 KiB per wavefront (one tile) times
+// a thousand wavefronts is where the memory system runs best (6.4-6.7 TB/s); twice that measured 5.9-6.1.  At
+// d = 64 a tile is half the bytes for the same chain of waits (LDS round trip, scores, softmax, weighted sum),
+// and that chain, not the memory system, sets the pace: with every tile reduced on its own, two tiles in
+// flight (8 KiB) ran at 5.3-5.4 TB/s (32 x 64 heads, batch 64, context 2048), four at 5.9, six at 6.1, eight
+// at 6.2; launches of a few dozen microseconds gained less and the shortest lost to the longer loop body from
+// six on (11.3 us with two, 11.7 with four, 12.6 with six, 13.9 with eight): four, which tile_update_pair
+// reduces two at a time (6.25 TB/s).
+// With several wavefronts per pair two tiles each are as many bytes per compute unit, and four are slower (32 x 64 heads,
+// 24 ragged sequences of 190..1150 keys: 29.2 us with two, 30.7 with four); at d = 128 two tiles instead of one likewise
+// (32 / 8 heads, 128 ragged sequences: 195 -> 200 us; one sequence of 2048 keys, 32 heads: 15.4 -> 15.7).
+template <int D, int NS>
+constexpr int base_depth() {
+  return D == 64 ? (NS > 1 ? 2 : 4) : 1;
+}
+
+// The launch of a context: the host knows the plan, so the wavefronts per pair are the kernel's, and a workgroup is NS
+// wavefronts of one pair or kWavesPerBlock pairs of one wavefront each.
+//
+// The parameters in front of `a` are the ones the first loads need: the build asks for the leading kernel
+// arguments to be in scalar registers when a wavefront starts, so the pair's record can be asked for at
+// once, and the first tiles as soon as it is there.
+template <int D, bool PAGED, int PIPE, int SRC, bool NT, int NS>
+__global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_split_mfma_kernel(
+    const PairHead *pair_head, const uint16_t *pool, const uint16_t *q, const int32_t n_groups, const int32_t G, const int32_t H,
+    const int32_t R, const int32_t v_tiles, const AttnArgs a) {
+  static_assert(SRC != kFromLens, "see attn_split_planned_kernel");
+  __shared__ __attribute__((aligned(16))) char lds_all[NS > 1 ? NS : kWavesPerBlock][lds_region<D>()];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t pair = NS > 1 ? blockIdx.x : blockIdx.x * kWavesPerBlock + wave, n_pairs = (uint32_t)n_groups * (uint32_t)G;
+  int32x8_t w = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (SRC == kFromHeads) w = *(const_head_ptr)(uintptr_t)(pair_head + pair);
+  if (pair >= n_pairs) return;
+  attn_split_body<D, PAGED, PIPE, SRC, NT, NS>(lds_all, wave, NS > 1 ? (int)wave : 0, pair, n_pairs, w, LensPlan{}, pool, q, G, H, R, v_tiles, a);
+}
+
+// The launch of the entry point that knows no lengths on the host: the plan comes from the lengths (kFromLens) or from what
+// the bookkeeping kernel left (kFromHeads), and with it the number of wavefronts per pair, by the rule a context goes by, so
+// that both sum in the same order.  A workgroup has as many wavefronts as a pair can be given; those past the number chosen
+// leave before the first barrier (which waits for the wavefronts that are still there), or, with one per pair, take a pair
+// each.  LARGE: the keys may not fit the memory-side cache; whether they do is seen from the plan as well.  (Room for three
+// wavefronts on a SIMD, 168 registers: with 170 the workgroups of two wavefronts that leave come in late, 64 x 400 keys, 32 / 8
+// heads 25 -> 29.5 us a call.)
+template <int D, bool PAGED, int SRC, bool LARGE>
+__global__ __launch_bounds__(most_waves_per_pair(D) * 64) __attribute__((amdgpu_waves_per_eu(SRC == kFromLens && D == 128 ? 3 : 1))) void attn_split_planned_kernel(
+    const void *source, const uint16_t *pool, const uint16_t *q, const int32_t *plan_dev, const int32_t most_groups, const int32_t G,
+    const int32_t H, const int32_t R, const int32_t v_tiles, const AttnArgs a) {
+  static_assert(SRC != kFromItems, "there is no plan then");
+  constexpr int W = most_waves_per_pair(D);
+  __shared__ __attribute__((aligned(16))) char lds_all[W][lds_region<D>()];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t alone = blockIdx.x * W + wave;          // the pair of this wavefront if it has one to itself
+  int32x8_t w = {0, 0, 0, 0, 0, 0, 0, 0}, w_alone = w;
+  LensPlan lp = {};
+  int32_t n_groups, n_items;
+  int64_t span;
+  if constexpr (SRC == kFromLens) {
+    lp = plan_from_lens(static_cast<const int32_t *>(source), a.B, most_groups, a.min_span, threadIdx.x & 63);
+    n_groups = lp.n_groups, n_items = lp.n_items, span = lp.span;
+  } else {
+    // both records this wavefront may want and the plan, asked for together (there are records for every pair there may be)
+    const PairHead *heads = static_cast<const PairHead *>(source);
+    w = *(const_head_ptr)(uintptr_t)(heads + blockIdx.x);
+    w_alone = *(const_head_ptr)(uintptr_t)(heads + min(alone, (uint32_t)most_groups * (uint32_t)G - 1));
+    const const_i32_ptr plan = (const_i32_ptr)(uintptr_t)plan_dev;
+    n_groups = plan[0], n_items = plan[1], span = plan[2] | (int64_t)plan[3] << 31;
+    asm volatile("" ::"s"(w[0]), "s"(w_alone[0]), "s"(n_groups));
+  }
+  const int32_t ns = waves_per_pair(D, G, n_groups, span, n_items);
+  const uint32_t n_pairs = (uint32_t)n_groups * (uint32_t)G;
+  auto run = [&](auto nt, auto waves) {
+    constexpr int NS = decltype(waves)::value;
+    if (NS > 1 && wave >= NS) return;
+    const uint32_t pair = NS > 1 ? blockIdx.x : alone;
+    if (pair >= n_pairs) return;
+    attn_split_body<D, PAGED, base_depth<D, NS>(), SRC, decltype(nt)::value, NS>(lds_all, wave, NS > 1 ? (int)wave : 0, pair, n_pairs,
+                                                                                 NS > 1 ? w : w_alone, lp, pool, q, G, H, R, v_tiles, a);
+  };
+  auto pick = [&](auto nt) {
+    if (W == 4 && ns == 4) return run(nt, std::integral_constant<int, W>{});
+    if (ns == 2) return run(nt, std::integral_constant<int, 2>{});
+    run(nt, std::integral_constant<int, 1>{});
+  };
+  if (LARGE && span * n_groups > a.keep_tiles) pick(std::integral_constant<bool, LARGE>{});
+  else pick(std::integral_constant<bool, false>{});
+}
+
 // out[b][h] = sum_c o_c 2^(m_c - M) / sum_c l_c 2^(m_c - M) over the items c of sequence b.
 // One wavefront per (b, h).  The items of a sequence are one contiguous range of the list per
 // block class.  Lane c first fetches (m_c, l_c) of item c, so the maxima and weights of up to
@@ -784,7 +859,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
   int first0, cnt0;
   if (LENS) {
     const LensPlan lp = plan_from_lens(chunk_prefix, B, a.n_groups, a.min_span, lane);
-    const int before = __builtin_amdgcn_readlane(lp.before, b), tiles = __builtin_amdgcn_readlane(lp.tiles, b);
+    const int before = __builtin_amdgcn_readlane(lp.before, b), tiles = tiles_in(__builtin_amdgcn_readlane(lp.n, b));
     const int j0 = before / lp.span, j1 = (before + tiles - 1) / lp.span;
     first0 = b + j0, cnt0 = tiles > 0 ? j1 - j0 + 1 : 0;
   } else {
@@ -871,39 +946,25 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
   }
 }
 
-// Tiles in flight per wavefront.  At d = 128 what counts is bytes: about 8 KiB per wavefront (one tile) times
-// a thousand wavefronts is where the memory system runs best (6.4-6.7 TB/s); twice that measured 5.9-6.1.  At
-// d = 64 a tile is half the bytes for the same chain of waits (LDS round trip, scores, softmax, weighted sum),
-// and that chain, not the memory system, sets the pace: with every tile reduced on its own, two tiles in
-// flight (8 KiB) ran at 5.3-5.4 TB/s (32 x 64 heads, batch 64, context 2048), four at 5.9, six at 6.1, eight
-// at 6.2; launches of a few dozen microseconds gained less and the shortest lost to the longer loop body from
-// six on (11.3 us with two, 11.7 with four, 12.6 with six, 13.9 with eight): four, which tile_update_pair
-// reduces two at a time (6.25 TB/s).
-// With several wavefronts per pair two tiles each are as many bytes per compute unit, and four are slower (32 x 64 heads,
-// 24 ragged sequences of 190..1150 keys: 29.2 us with two, 30.7 with four); at d = 128 two tiles instead of one likewise
-// (32 / 8 heads, 128 ragged sequences: 195 -> 200 us; one sequence of 2048 keys, 32 heads: 15.4 -> 15.7).
-template <int D, int NS>
-constexpr int base_depth() {
-  return D == 64 ? (NS > 1 ? 2 : 4) : 1;
-}
-
 template <int D, bool PAGED, int SRC, bool NT, int NS>
 void launch_split_as(const AttnArgs &args, dim3 grid, hipStream_t stream) {
   hipLaunchKernelGGL((attn_split_mfma_kernel<D, PAGED, base_depth<D, NS>(), SRC, NT, NS>), grid, dim3((NS > 1 ? NS : kWavesPerBlock) * 64), 0,
-                     stream, SRC == kFromLens ? reinterpret_cast<const PairHead *>(args.lens) : args.pair_head, args.pool, args.q,
-                     args.n_groups_dev, args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args);
+                     stream, args.pair_head, args.pool, args.q, args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args);
 }
 
-// (D = 64 knows one or two wavefronts per pair, see waves_per_pair; launches from the lengths are small ones: never one
-// wavefront per pair, nor more keys than the memory-side cache holds)
+template <int D, bool PAGED, int SRC, bool LARGE>
+void launch_planned(const AttnArgs &args, const void *source, dim3 grid, hipStream_t stream) {
+  hipLaunchKernelGGL((attn_split_planned_kernel<D, PAGED, SRC, LARGE>), grid, dim3(most_waves_per_pair(D) * 64), 0, stream, source,
+                     args.pool, args.q, args.plan_dev, args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args);
+}
+
+// (launches from the lengths are small ones: never more keys than the memory-side cache holds)
 template <int D, bool PAGED, bool NT>
 void launch_split_kept(const AttnArgs &args, int waves, dim3 grid, hipStream_t stream) {
   if constexpr (!NT) {
-    if constexpr (D == 128) {
-      if (args.lens && waves == 4) return launch_split_as<D, PAGED, kFromLens, NT, 4>(args, grid, stream);
-    }
-    if (args.lens) return launch_split_as<D, PAGED, kFromLens, NT, 2>(args, grid, stream);
+    if (args.lens) return launch_planned<D, PAGED, kFromLens, NT>(args, args.lens, grid, stream);
   }
+  if (args.plan_dev) return launch_planned<D, PAGED, kFromHeads, NT>(args, args.pair_head, grid, stream);
   if (!args.pair_head) return launch_split_as<D, PAGED, kFromItems, NT, 1>(args, grid, stream);
   if constexpr (D == 128) {
     if (waves == 4) return launch_split_as<D, PAGED, kFromHeads, NT, 4>(args, grid, stream);
@@ -940,10 +1001,11 @@ AttnArgs make_args(const AttnLaunch &a) {
   args.block_table = a.batch.block_table;
   args.chunk_prefix = a.batch.chunk_prefix;
   args.item_desc = a.batch.item_desc;
-  args.n_groups_dev = a.n_groups_dev;
+  args.plan_dev = a.plan_dev;
   args.pair_head = static_cast<const PairHead *>(a.pair_head);
   args.lens = a.from_lens ? a.batch.ctx_lens : nullptr;
   args.min_span = a.min_span;
+  args.keep_tiles = kKeepCachedBytes / 2 / (16 * 4 * (int64_t)s.G * s.D);
   args.n_groups = a.pair_head || a.from_lens ? a.n_groups : a.item_count;
   args.H = s.H;
   args.G = s.G;
@@ -977,14 +1039,15 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream, hipEvent_
   // persistent launch: no more wavefronts than there are (group, KV head) pairs, no more than a.max_waves
   const int64_t want = ((int64_t)args.n_groups * s.G + kWavesPerBlock - 1) / kWavesPerBlock;
   const int64_t cap = std::max<int64_t>(1, a.max_waves / kWavesPerBlock);
-  const int waves = a.pair_head || a.from_lens ? a.waves_per_pair : 1;
-  if (a.from_lens && (waves < 2 || !a.keep_cached || a.pair_head || a.batch.B > kLensBatch ||
-                      a.n_groups < 1 || a.grid_groups < 1 || a.min_span < 1))
+  const int waves = a.pair_head && !a.plan_dev ? a.waves_per_pair : 1;
+  if (a.from_lens && (!a.keep_cached || a.pair_head || a.plan_dev || a.batch.B > kLensBatch || a.n_groups < 1 || a.grid_groups < 1 ||
+                      a.min_span < 1))
     return hipErrorInvalidValue;
+  if (a.plan_dev && !a.pair_head) return hipErrorInvalidValue;
   if (waves != 1 && waves != 2 && !(waves == 4 && s.D == 128)) return hipErrorInvalidValue;
-  const int64_t pairs = (a.n_groups_dev ? cap : std::min(want, cap)) * kWavesPerBlock;      // that the grid covers
+  // (a launch that finds its plan itself has a workgroup for every pair there may be)
   dim3 grid((unsigned)(a.from_lens ? (int64_t)a.grid_groups * s.G
-                       : waves > 1 ? std::min<int64_t>(pairs, (int64_t)args.n_groups * s.G) : pairs / kWavesPerBlock));
+                       : waves > 1 || a.plan_dev ? (int64_t)args.n_groups * s.G : std::min(want, cap)));
   // (stretches come with a table of heads, which needs a wavefront per (stretch, KV head) pair and a pool that
   // holds the blocks as the table numbers them)
   if (a.pair_head && (want > cap || a.id_base != 0 || a.item_first != 0)) return hipErrorInvalidValue;

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from paper_2504_11816_amd import binding
+from paper_2504_11816_amd.harness import Stack
 
 from gpu_util import build_stack, make_inputs, run_and_check
 
@@ -43,4 +44,54 @@ def test_every_output(what, H, G, d, T, B, cap):
                                        ctx_lens=lens, q=q[0], out=got, k_new=k[0], v_new=v[0])
         torch.cuda.synchronize()
         assert np.array_equal(got.cpu().numpy().view(np.uint8), out[0].cpu().numpy().view(np.uint8))
+        st.close()
+
+
+# room for longer sequences than there are: (lengths before the step, capacities of the contexts, capacity the entry point
+# that allocates nothing is told)
+@pytest.mark.parametrize("what,H,G,d,B,lens,caps,told", [
+    ("d128, 32 heads", 32, 32, 128, 32, (500, 630), (640, 656, 4096), (640, 1040, 8192)),
+    ("d128, few pairs", 8, 8, 128, 4, (200, 300), (304, 4096, 16384), (304, 8192, 32768)),
+    ("d128, 65 sequences", 8, 2, 128, 65, (40, 500), (512, 8192), (512, 32768)),
+    ("d64", 32, 32, 64, 24, (190, 1150), (1168, 8192), (1168, 8192, 32768)),
+    ("d64, 40 sequences", 16, 2, 64, 40, (1, 90), (96, 16384), (96, 16384, 1 << 20))])
+def test_the_capacity_changes_no_bit(what, H, G, d, B, lens, caps, told):
+    rng = np.random.Generator(np.random.PCG64(17))
+    ctx = rng.integers(lens[0], lens[1], size=B).astype(np.int32)
+    blocks = int(((ctx + 1 + 15) // 16).sum())
+    ids = rng.permutation(blocks).astype(np.int32)
+    need = (ctx + 1 + 15) // 16
+
+    def table_of(cols):
+        t = np.full((B, cols), -1, dtype=np.int32)
+        at = 0
+        for b in range(B):
+            t[b, :need[b]] = ids[at:at + need[b]]
+            at += need[b]
+        return t
+
+    first = None
+    for cap in caps:
+        print(f"{what}: context of capacity {cap}", flush=True)
+        st = Stack(L=1, H=H, G=G, d=d, B=B, T=16, cap_tokens=cap, blocks_per_layer=blocks, workspace_items=4 * B + 2048)
+        st.fill_pool(0, 5)
+        st.set_batch(ctx, table_of(st.max_blocks))
+        q, k, v, out = make_inputs(st, 79, 0, st.device)
+        st.step(q, k, v, out)
+        st.synchronize()
+        got = out[0].cpu().numpy().view(np.uint16)
+        first = got if first is None else first
+        assert np.array_equal(got, first), f"capacity {cap}"
+        if cap == caps[-1]:
+            now = torch.tensor(ctx + 1, dtype=torch.int32, device=st.device)
+            for t in told:
+                print(f"{what}: told of a capacity of {t}", flush=True)
+                again = torch.full_like(out[0], float("nan"))
+                table = torch.tensor(table_of(t // 16), dtype=torch.int32, device=st.device)
+                torch.cuda.synchronize()
+                binding.okv_decode_attn_static(n_q_heads=H, n_kv_heads=G, head_dim=d, block_tokens=16, max_blocks_per_seq=t // 16,
+                                               max_ctx=0, out_dtype=0, B=B, pool=st.dev_part[0], block_table=table, ctx_lens=now,
+                                               q=q[0], out=again, k_new=k[0], v_new=v[0])
+                torch.cuda.synchronize()
+                assert np.array_equal(again.cpu().numpy().view(np.uint16), first), f"told {t}"
         st.close()
