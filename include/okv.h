@@ -241,6 +241,11 @@ int okv_plan_block_split(int64_t n_blocks, int64_t coff_num, int64_t coff_den,
 int okv_equal_stretches(const int32_t *ctx_lens, int32_t B, int32_t max_groups, int32_t *items, int64_t max_items,
                         int64_t *n_items, int32_t *group_first, int32_t *n_groups, int64_t *span_tiles);
 
+/* Wavefronts that share a (stretch, KV head) pair of such a launch: 1, 2 or 4, by the cut that
+ * okv_equal_stretches makes of the lengths (with the row the step stores) and by nothing else, so that a batch is
+ * summed in the same order whatever the capacities.  Pure host function; OKV_EINVAL for a bad argument. */
+int32_t okv_waves_per_pair(int32_t head_dim, int32_t n_kv_heads, int32_t n_groups, int64_t span_tiles, int64_t n_items);
+
 /* The order of operations the copy pipeline enqueues, without a GPU (the runtime
  * walks the same scheduler).
  *   host_chunks   HOST int32 [n_layers]: streamed chunks of each layer (whole-layer

@@ -23,7 +23,7 @@ EXPORTS = [
     "okv_worklist_classes", "okv_pair_heads", "okv_prefill_begin", "kv_append_bulk", "okv_prefill_release", "okv_prefill_end", "okv_prefill_plan",
     "okv_measure_d2h",
     "okv_profile_enable", "okv_profile_read", "okv_measure_h2d", "okv_time_copies", "okv_probe_copy",
-    "okv_probe_read", "okv_equal_stretches", "okv_decode_attn_static",
+    "okv_probe_read", "okv_equal_stretches", "okv_waves_per_pair", "okv_decode_attn_static",
 ]
 
 
@@ -140,6 +140,7 @@ def lib():
             "okv_probe_read": (ctypes.c_int, [P, I64, P, P]),
             "okv_equal_stretches": (ctypes.c_int, [P, I32, I32, P, I64, ctypes.POINTER(I64), P, ctypes.POINTER(I32),
                                                    ctypes.POINTER(I64)]),
+            "okv_waves_per_pair": (I32, [I32, I32, I32, I64, I64]),
             "okv_decode_attn_static": (ctypes.c_int, [ctypes.POINTER(OkvStaticAttn)]),
         }
         for name, (res, args) in sig.items():
@@ -220,6 +221,14 @@ def okv_equal_stretches(ctx_lens, max_groups):
     _check(lib().okv_equal_stretches(_ptr(ctx_lens), B, max_groups, _ptr(items), max_items, ctypes.byref(n), _ptr(first),
                                      ctypes.byref(groups), ctypes.byref(span)))
     return items[:n.value].copy(), first[:groups.value + 1].copy(), span.value
+
+
+def okv_waves_per_pair(head_dim, n_kv_heads, ctx_lens, max_groups):
+    """Wavefronts per (stretch, KV head) pair for a batch of these lengths."""
+    items, first, span = okv_equal_stretches(ctx_lens, max_groups)
+    n = lib().okv_waves_per_pair(head_dim, n_kv_heads, len(first) - 1, span, len(items))
+    _check(min(n, 0))
+    return n
 
 
 def okv_decode_attn_static(*, n_q_heads, n_kv_heads, head_dim, block_tokens, max_blocks_per_seq, max_ctx, out_dtype, B, pool,

@@ -786,6 +786,12 @@ int okv_equal_stretches(const int32_t *ctx_lens, int32_t B, int32_t max_groups, 
   return OKV_OK;
 }
 
+int32_t okv_waves_per_pair(int32_t head_dim, int32_t n_kv_heads, int32_t n_groups, int64_t span_tiles, int64_t n_items) {
+  if ((head_dim != 64 && head_dim != 128) || n_kv_heads < 1 || n_groups < 0 || span_tiles < 1 || n_items < n_groups || n_items > INT32_MAX)
+    return fail(nullptr, OKV_EINVAL, "okv_waves_per_pair: bad argument");
+  return okv::waves_per_pair(head_dim, n_kv_heads, n_groups, span_tiles, (int32_t)n_items);
+}
+
 int32_t okv_slab_tiles(int32_t n_kv_heads, int32_t head_dim, int32_t slice_tokens) {
   if (n_kv_heads < 1 || (head_dim != 64 && head_dim != 128) || slice_tokens < 16 || slice_tokens % 16)
     return fail(nullptr, OKV_EINVAL, "okv_slab_tiles: bad argument");

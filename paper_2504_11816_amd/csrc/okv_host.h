@@ -180,21 +180,31 @@ __host__ __device__ inline SpanPlanOf<I> span_plan(I total_tiles, int32_t max_gr
 }
 
 // Wavefronts that share a (stretch, KV head) pair of an attention launch with equal stretches: 1, 2 or 4.  More of them
-// shorten the chain of tiles per wavefront, which is what short launches and short items cost; on long launches of
-// uncut sequences at d = 128 one wavefront per pair already draws what the memory gives, and two are slower.  Measured on
-// MI355X, us a layer with 1 and 2 wavefronts (4 in brackets):
-//   d = 64    24 ragged sequences of 190..1150 keys, 32 heads: 32.0, 29.2 (31.4); 16 x 300 keys, 12 heads: 14.8, 12.4
-//             (12.8); 64 x 1024, 32 heads: 95.8, 92.8; 64 x 1500 contiguous: 129, 133-142
-//   d = 128   4 x 256 keys, 8 heads: 14.9, 12.3 (10.3); one sequence of 2048, 32 heads: 17.9, 15.4 (14.6); 32 x 1100, 2 heads:
-//             19.7, 16.9 (16.4); 32 x 660, 128 / 8 heads: 29.8, 27.4 (31.1); 64 x 2048, 64 / 8 heads: 99.9, 97.4; 128 x 290,
-//             32 / 8 heads: 37.6, 35.6; 32 x 512, 32 heads: 48.4, 48.9; 32 x 768, 32 heads: 64, 65-71
+// shorten the chain of tiles per wavefront, which is what short launches and short items cost; in a long run of tiles
+// one wavefront per pair already draws what the memory gives, and the joining of the sums is on top.  So the number
+// follows the tiles per stretch, and where the line lies follows how many items begin in mid-stretch: few where every
+// stretch is one item, as when a long sequence fills several stretches or equal sequences one each.  Measured on MI355X, us a
+// layer with 1 and 2 wavefronts (4 in brackets); NT: keys of more layers than the memory-side cache holds, with nontemporal
+// loads; kept: one layer that stays in it, with ordinary loads:
+//   d = 128   few pairs (4 wavefronts up to 600, 2 up to 900): 4 x 256 keys, 8 heads NT 14.5, 12.4 (11.2); one sequence of 2040, 32
+//             heads, 512 pairs 16.7, 14.5 (13.8), kept 16.7, 14.1 (13.3); 16 x 600, 8 heads, 608 pairs 17.8, 15.1 (15.9), kept 17.2,
+//             15.1 (16.0); 8 ragged sequences, 40 heads, 760 pairs 19.0, 16.8 (16.9); 1024 pairs, 8 tiles 14.5, 14.2, kept 13.6, 14.0
+//             a stretch an item: 32 sequences, 32 heads, 16 tiles NT 23.9, 24.5, kept 22.5, 23.7; 32 tiles 42.8, 44.8 and 40.7,
+//             43.0; 40 tiles NT 52.3, 55.4
+//             more items (2 up to 16 tiles): 100 ragged sequences, 32 / 8 heads, 13 tiles NT 27.6, 26.1, kept 26.3, 25.8; 24
+//             ragged, 32 heads, 13 tiles NT 25.7, 25.0, kept 24.0, 24.7; 32 ragged, 30 tiles NT 46.2, 47.5, kept 43.5, 45.9
+//   d = 64    a stretch an item (up to 24 tiles): 32 sequences, 32 heads, 24 tiles NT 20.0, 19.8, kept 19.0, 18.9; 48 tiles
+//             34.7, 35.1 and 32.2, 33.3; 64 tiles 44.4, 45.6 and 42.3, 42.9
+//             more items (up to 112 tiles): 24 ragged sequences, 32 heads, 32 tiles NT 33.2, 30.2, kept 31.4, 29.7; 95 tiles 71.8, 71.1
+//             and 74.8, 74.0; 127 tiles 90.7, 91.0 and 94.8, 96.2; 100 ragged, 32 / 8 heads, 83 tiles NT 66.8, 62.6
 // The choice decides the order of summation, and every entry point has to sum a batch in the same order.  So it follows
 // from the plan of the lengths alone, which each of them has: the host of a context, the bookkeeping kernel's record, and
 // a kernel that reads the lengths itself; capacities, the number of layers and where they lie have no part in it.
 __host__ __device__ inline int32_t waves_per_pair(int32_t D, int32_t G, int32_t n_groups, int64_t span, int32_t n_items) {
-  if (D == 64) return span <= 128 ? 2 : 1;
-  if ((int64_t)n_groups * G <= 600) return 4;
-  return span <= (n_items == n_groups ? 40 : 96) ? 2 : 1;
+  const bool many_items = 2 * (n_items - n_groups) >= n_groups;
+  if (D == 64) return span <= (many_items ? 112 : 24) ? 2 : 1;
+  const int64_t pairs = (int64_t)n_groups * G;
+  return pairs <= 600 ? 4 : pairs <= 900 || (many_items && span <= 16) ? 2 : 1;
 }
 // The most there can be, which is what a launch is sized for where the host does not know the lengths.
 constexpr int32_t most_waves_per_pair(int32_t D) { return D == 64 ? 2 : 4; }

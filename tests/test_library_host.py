@@ -263,6 +263,22 @@ def test_equal_stretches_match_the_oracle_walk():
     assert e.value.code == binding.OKV_EINVAL
 
 
+def test_wavefronts_per_pair_are_what_measured_faster():
+    # 1024 wavefronts a launch; (head dimension, KV heads, lengths) and the number that measured faster by more than 1.5 %
+    # with the keys streamed and no slower by more with the keys cached
+    rng = np.random.default_rng(3)
+    ragged = lambda n, mean: rng.integers(mean // 4, mean * 7 // 4, size=n)  # noqa: E731
+    for d, G, lens, want in [
+            (128, 8, [256] * 4, 4), (128, 32, [1024], 4), (128, 8, [512] * 8, 4), (128, 8, [600] * 16, 2), (128, 32, [2040], 4), (128, 32, [2800], 2), (128, 40, ragged(8, 340), 2),
+            (128, 32, [80] * 32, 2), (128, 32, [256] * 32, 1), (128, 32, [512] * 32, 1), (128, 32, [640] * 32, 1), (128, 32, [768] * 32, 1),
+            (128, 8, [512] * 128, 1), (128, 32, [16 * 32 * 24], 1), (128, 8, ragged(100, 260), 2), (128, 32, ragged(32, 720), 1),
+            (128, 8, ragged(128, 2304), 1), (64, 32, [256] * 32, 2), (64, 32, [1024] * 32, 1), (64, 32, [768] * 32, 1),
+            (64, 32, ragged(24, 670), 2), (64, 8, ragged(100, 1700), 2), (64, 32, ragged(24, 4000), 1), (64, 8, [256] * 4, 2)]:
+        assert binding.okv_waves_per_pair(d, G, np.asarray(lens), 1024 // G) == want, (d, G, list(lens)[:4])
+    for bad in ((96, 8, 4, 8, 4), (128, 0, 4, 8, 4), (128, 8, 4, 0, 4), (128, 8, 4, 8, 3)):
+        assert binding.lib().okv_waves_per_pair(*bad) == binding.OKV_EINVAL
+
+
 def test_static_entry_point_rejects_bad_arguments_without_a_gpu():
     # shape and size checks come before any GPU call
     base = dict(n_q_heads=32, n_kv_heads=8, head_dim=128, block_tokens=16, max_blocks_per_seq=8, max_ctx=0, out_dtype=0, B=4,
