@@ -498,9 +498,14 @@ struct TileShape {
   static_assert(WD * 2 * FN + (WD - 1) * kLoads <= 63, "the wait for a stage must fit the load counter");
 };
 
-// One 16-byte-per-lane load from `base` + off straight into LDS: lane l's bytes land at lds + 16 l.
+// One 16-byte-per-lane load from `base` + off straight into LDS: lane l's bytes land at lds + 16 l.  The place goes through m0,
+// which an asm statement cannot be said to change (the compiler reserves it): it is left as it was found.
 __device__ __forceinline__ void load_to_lds(const void *base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+  uint32_t found;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+               : "=&s"(found)
+               : "s"(lds), "v"(off), "s"(base)
+               : "memory");
 }
 
 template <int FM, int FN, int WM, int WN, int WD>

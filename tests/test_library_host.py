@@ -77,6 +77,20 @@ def test_cuts_of_the_product_kernels_follow_the_launch_model():
             assert c >= 1 and (n_in // chunk) % c == 0 and (c == 1 or n_in // chunk // c >= 2)
 
 
+def test_inline_assembly_leaves_m0_as_it_found_it():
+    # m0 is reserved: a clobber cannot name it, so a statement that writes it saves it first and puts it back last
+    csrc = os.path.join(ROOT, "paper_2504_11816_amd", "csrc")
+    writers = 0
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        for body in re.findall(r'asm volatile\(((?:\s*"(?:[^"\\]|\\.)*")+)', text):
+            lines = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', body)).replace("\\t", "").split("\\n")
+            if any(re.match(r"s_\w+ m0,", line) for line in lines):
+                writers += 1
+                assert lines[0] == "s_mov_b32 %0, m0" and lines[-1] == "s_mov_b32 m0, %0", (name, lines)
+    assert writers
+
+
 def test_plan_matches_oracle_brute_force():
     for L in range(1, 65):
         for den in range(1, 33):
