@@ -948,9 +948,10 @@ constexpr TileForm kTileForms[] = {{256, 256, 1.55, false}, {256, 192, 1.24, fal
                                    {96, 128, 0.41, true},   {64, 128, 0.40, true},   {64, 64, 0.22, true},    {32, 64, 0.17, true}};
 constexpr int kTileFormCount = sizeof(kTileForms) / sizeof(kTileForms[0]);
 
-template <int FM, int FN, int WM, int WN, int WD>
+template <int F, int FM, int FN, int WM, int WN, int WD>
 void launch_tile_as(const LinearArgs &a, hipStream_t stream) {
   using S = TileShape<FM, FN, WM, WN, WD>;
+  static_assert(kTileForms[F].rows == S::kRows && kTileForms[F].cols == S::kCols, "the model's form is the kernel's");
   const int m_tiles = (a.m + S::kRows - 1) / S::kRows, groups = (a.n_out + S::kCols - 1) / S::kCols;
   hipLaunchKernelGGL((linear_tile_kernel<FM, FN, WM, WN, WD>), dim3(m_tiles * groups * a.splits), dim3(S::kThreads), 0, stream, a.w, a.x,
                      a.n_kb, a.splits, a.n_in, a.m, a.n_tiles, m_tiles, groups, a);
@@ -958,14 +959,14 @@ void launch_tile_as(const LinearArgs &a, hipStream_t stream) {
 
 hipError_t launch_linear_tile(const LinearArgs &a, int form, hipStream_t stream) {
   switch (form) {
-    case 0: launch_tile_as<8, 4, 2, 4, 2>(a, stream); break;
-    case 1: launch_tile_as<8, 3, 2, 4, 2>(a, stream); break;
-    case 2: launch_tile_as<8, 2, 1, 8, 2>(a, stream); break;
-    case 3: launch_tile_as<8, 2, 1, 4, 4>(a, stream); break;
-    case 4: launch_tile_as<6, 2, 1, 4, 4>(a, stream); break;
-    case 5: launch_tile_as<4, 2, 1, 4, 4>(a, stream); break;
-    case 6: launch_tile_as<4, 1, 1, 4, 4>(a, stream); break;
-    case 7: launch_tile_as<2, 1, 1, 4, 4>(a, stream); break;
+    case 0: launch_tile_as<0, 8, 4, 2, 4, 2>(a, stream); break;
+    case 1: launch_tile_as<1, 8, 3, 2, 4, 2>(a, stream); break;
+    case 2: launch_tile_as<2, 8, 2, 1, 8, 2>(a, stream); break;
+    case 3: launch_tile_as<3, 8, 2, 1, 4, 4>(a, stream); break;
+    case 4: launch_tile_as<4, 6, 2, 1, 4, 4>(a, stream); break;
+    case 5: launch_tile_as<5, 4, 2, 1, 4, 4>(a, stream); break;
+    case 6: launch_tile_as<6, 4, 1, 1, 4, 4>(a, stream); break;
+    case 7: launch_tile_as<7, 2, 1, 1, 4, 4>(a, stream); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();
