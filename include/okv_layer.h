@@ -93,8 +93,14 @@ int okv_linear_layernorm(const void *x, const void *w_packed, const void *bias,
                          int32_t relu, void *workspace, int64_t workspace_bytes, void *stream);
 
 /* Bytes of workspace okv_linear wants for this shape on the current device (0 if it
- * would not use one); < 0 on a bad shape. */
+ * would not use one); < 0 on a bad shape.  It is an fp32 copy of the result per cut of the inputs, at most 8:
+ * 67 MB for 1024 rows of 4096 x 16384 (four cuts).  Less is accepted: fewer cuts, then none. */
 int64_t okv_linear_workspace_bytes(int32_t m, int32_t n_out, int32_t n_in);
+
+/* What okv_linear runs for this shape with that much workspace on the current device:
+ *   plan   HOST int32 [4]: kernel (0 the simple one, 1 the staged one, 2 tiles of rows x features), rows and
+ *          features of a workgroup, cuts of the inputs */
+int okv_linear_plan(int32_t m, int32_t n_out, int32_t n_in, int64_t workspace_bytes, int32_t *plan);
 
 /* out[i] = (x[i] - mean_i) / sqrt(var_i + eps) * gamma + beta for each of m rows of h
  * numbers (population variance; statistics in fp32).

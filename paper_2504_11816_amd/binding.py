@@ -28,7 +28,7 @@ EXPORTS = [
 
 
 # every symbol include/okv_layer.h declares (same library)
-LAYER_EXPORTS = ["okv_pack_linear_weight", "okv_linear", "okv_linear_qkv", "okv_linear_layernorm", "okv_linear_workspace_bytes", "okv_layernorm",
+LAYER_EXPORTS = ["okv_pack_linear_weight", "okv_linear", "okv_linear_qkv", "okv_linear_layernorm", "okv_linear_workspace_bytes", "okv_linear_plan", "okv_layernorm",
                  "okv_decoder_scratch_bytes", "okv_decoder_step"]
 
 
@@ -132,6 +132,7 @@ def lib():
             "okv_pack_linear_weight": (ctypes.c_int, [P, P, I32, I32, P]),
             "okv_linear": (ctypes.c_int, [P, P, P, P, ctypes.POINTER(P), I32, I32, I32, I32, I32, P, I64, P]),
             "okv_linear_workspace_bytes": (I64, [I32, I32, I32]),
+            "okv_linear_plan": (ctypes.c_int, [I32, I32, I32, I64, P]),
             "okv_linear_qkv": (ctypes.c_int, [P, P, P, P, P, P, I32, I32, I32, I32, P, I64, P]),
             "okv_linear_layernorm": (ctypes.c_int, [P, P, P, P, P, P, P, ctypes.c_float, P, I32, I32, I32, I32, P, I64, P]),
             "okv_layernorm": (ctypes.c_int, [P, P, P, P, I32, I32, ctypes.c_float, P]),
@@ -354,6 +355,14 @@ def okv_linear_workspace_bytes(m, n_out, n_in):
     if r < 0:
         _check(int(r))
     return int(r)
+
+
+def okv_linear_plan(m, n_out, n_in, workspace_bytes=None):
+    """-> (kernel, rows, features, cuts): 0 simple, 1 staged, 2 tiles; by default with the workspace the shape wants."""
+    plan = (ctypes.c_int32 * 4)()
+    nbytes = okv_linear_workspace_bytes(m, n_out, n_in) if workspace_bytes is None else workspace_bytes
+    _check(lib().okv_linear_plan(m, n_out, n_in, nbytes, plan))
+    return tuple(plan)
 
 
 def okv_layernorm(x, gamma, beta, out, m, h, eps=1e-5, stream=0):

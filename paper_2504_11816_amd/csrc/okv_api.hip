@@ -1806,6 +1806,14 @@ int64_t okv_linear_workspace_bytes(int32_t m, int32_t n_out, int32_t n_in) {
   return okv::linear_workspace_bytes(m, n_out, n_in, device_cus());
 }
 
+int okv_linear_plan(int32_t m, int32_t n_out, int32_t n_in, int64_t workspace_bytes, int32_t *plan) {
+  if (m < 1 || m > OKV_LINEAR_MAX_BATCH || n_out < 16 || n_out % 16 || n_in < 32 || n_in % 32 || workspace_bytes < 0 || !plan)
+    return fail(nullptr, OKV_EINVAL, "okv_linear_plan: bad argument");
+  const okv::LinearRoute r = okv::linear_route(m, n_out, n_in, device_cus(), workspace_bytes);
+  plan[0] = r.kernel, plan[1] = r.rows, plan[2] = r.cols, plan[3] = r.cuts;
+  return OKV_OK;
+}
+
 namespace {
 int linear_impl(const void *x, const void *w_packed, const void *bias, const void *residual, void *const *out, int32_t n_seg,
                 int32_t m, int32_t n_out, int32_t n_in, int32_t relu, void *workspace, int64_t workspace_bytes,

@@ -977,7 +977,7 @@ hipError_t launch_linear_tile(const LinearArgs &a, int form, hipStream_t stream)
 
 // Which kernel a product runs and how its input dimension is cut, with the time a small model of the launch gives it.
 struct LinearPlan {
-  enum Kind { kSimple, kStaged, kTile } kind;
+  enum Kind { kSimple = 0, kStaged = 1, kTile = 2 } kind;
   int waves, cuts, form;
   double us;
 };
@@ -1078,6 +1078,13 @@ int64_t linear_workspace_bytes(int32_t m, int32_t n_out, int32_t n_in, int32_t n
   const LinearPlan plan = choose_linear(m, n_out, n_in, n_cus, m > OKV_LINEAR_MAX_ROWS || staged_plan(m, n_out, n_in, n_cus).cuts ? INT64_MAX : 0);
   // a single cut of the staged kernel still goes through a share when a layer norm follows
   return plan.kind == LinearPlan::kStaged || plan.cuts > 1 ? (int64_t)plan.cuts * m * n_out * 4 : 0;
+}
+
+LinearRoute linear_route(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
+  const LinearPlan plan = choose_linear(m, n_out, n_in, n_cus, workspace_bytes);
+  if (plan.kind == LinearPlan::kSimple) return {plan.kind, (m + 15) / 16 * 16, 16, 1};
+  if (plan.kind == LinearPlan::kStaged) return {plan.kind, (m + 15) / 16 * 16, 16 * plan.waves, plan.cuts};
+  return {plan.kind, kTileForms[plan.form].rows, kTileForms[plan.form].cols, plan.cuts};
 }
 
 hipError_t launch_linear(const LinearLaunch &l, hipStream_t stream) {

@@ -3,7 +3,7 @@ than a tile, features that do not fill a tile, one block of inputs, an odd numbe
 fewer stages than are in flight, cuts of the inputs and none for want of a workspace, every epilogue.
 
 Tolerance as for the other products: |gpu - oracle| <= 2e-3 + 2e-3 |oracle| (fp16 inputs exact in fp32, fp32
-sums of at most 8192 terms here, one rounding to fp16 of results of size O(1..8))."""
+sums of at most 16352 terms here, one rounding to fp16 of results of size O(1..8))."""
 import numpy as np
 import pytest
 import torch
@@ -58,6 +58,27 @@ def test_tile_product_epilogues(m, n_out, n_in):
     product(m, n_out, n_in, 4, n_seg=2, relu=True, bias=False)
 
 
+# every form (rows x features of a workgroup) with more stages than two rounds of those in flight, an odd number of
+# blocks of 32 inputs, rows and features that do not fill the last tile, uncut and cut
+@pytest.mark.parametrize("form,cuts,m,n_out,n_in", [
+    ((32, 64), 1, 97, 208, 544), ((32, 64), 7, 257, 208, 4128), ((64, 64), 1, 97, 4112, 544), ((64, 64), 5, 129, 1040, 3104),
+    ((64, 128), 1, 257, 6160, 544), ((96, 128), 1, 500, 4112, 544), ((96, 128), 7, 129, 2064, 4128), ((128, 128), 1, 2719, 1040, 544),
+    ((128, 128), 7, 500, 1040, 4128), ((128, 256), 1, 1000, 6160, 544), ((128, 256), 7, 193, 4112, 3104), ((256, 192), 1, 1500, 6160, 544),
+    ((256, 192), 2, 4051, 4112, 4128), ((256, 256), 1, 3000, 4112, 544), ((256, 256), 4, 1000, 4080, 16352)])
+def test_every_form_over_many_stages(form, cuts, m, n_out, n_in):
+    uncut = cuts == 1
+    assert binding.okv_linear_plan(m, n_out, n_in, 0 if uncut else None) == (2, *form, cuts)
+    product(m, n_out, n_in, 970 + m, relu=True, residual=True, workspace=not uncut)
+
+
+# weights too large to stay cached (32 MiB and more): up to 8 rows nontemporal loads
+@pytest.mark.parametrize("m", [1, 3, 8])
+def test_few_rows_of_a_large_matrix(m):
+    assert binding.okv_linear_plan(m, 4096, 4096)[0] == 0
+    product(m, 4096, 4096, 990 + m, residual=True, workspace=False)
+    product(m, 8208, 2080, 995 + m, relu=True, workspace=False)
+
+
 def test_tile_product_repeats_bit_for_bit_and_feeds_a_layer_norm():
     m, n_out, n_in = 400, 1024, 4096
     x = synth.randn_f16_torch((m, n_in), synth.stream_seed(5, 1), DEV)
@@ -68,6 +89,9 @@ def test_tile_product_repeats_bit_for_bit_and_feeds_a_layer_norm():
     ws = torch.empty(max(16, binding.okv_linear_workspace_bytes(m, n_out, n_in)), dtype=torch.uint8, device=DEV)
     first = torch.empty((m, n_out), dtype=torch.float16, device=DEV)
     binding.okv_linear(x, wp, None, None, first, m, n_out, n_in, False, 0, ws, ws.numel())
+    torch.cuda.synchronize()
+    want = dl.linear(x.double().cpu().numpy(), w.double().cpu().numpy(), None)
+    assert np.max(np.abs(first.double().cpu().numpy() - want) - 2e-3 * np.abs(want)) <= 2e-3
     for _ in range(10):
         y, z = torch.empty_like(first), torch.empty_like(first)
         binding.okv_linear_layernorm(x, wp, None, None, y, g, e, z, m, n_out, n_in, 1e-5, False, 0, ws, ws.numel())

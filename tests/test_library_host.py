@@ -75,6 +75,14 @@ def test_cuts_of_the_product_kernels_follow_the_launch_model():
             c = cuts(m, n_out, n_in)
             chunk = 256 if m <= 96 else 128
             assert c >= 1 and (n_in // chunk) % c == 0 and (c == 1 or n_in // chunk // c >= 2)
+            assert binding.okv_linear_plan(m, n_out, n_in)[::3] == (1, c)
+    # what runs fits the workspace there is, and more rows than the staged kernel takes run tiles
+    for m, n_out, n_in in ((1, 4096, 4096), (64, 1056, 4224), (192, 4096, 16384), (1024, 4096, 16384), (4096, 16, 1 << 20)):
+        for share in (0, 1, 2, 5, 8):
+            kernel, rows, cols, c = binding.okv_linear_plan(m, n_out, n_in, share * m * n_out * 4)
+            assert c <= max(share, 1) and kernel == (0 if m <= 8 else 2 if m > 192 else kernel) and rows >= 16 and cols >= 16
+    with pytest.raises(binding.OkvError):
+        binding.okv_linear_plan(4, 4096, 4096, -1)
 
 
 def test_inline_assembly_leaves_m0_as_it_found_it():
