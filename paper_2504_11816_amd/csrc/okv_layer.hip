@@ -994,8 +994,10 @@ struct LinearPlan {
 // workgroups per compute unit is not considered (longer-lived workgroups measured faster than more of them).
 // Examples on 256 compute units: 12288 x 4096 -> 3 wavefronts, no cut (256 workgroups); 6144 x 4096 -> 3
 // wavefronts, 2 cuts; 4096 x 4096 and 4096 x 16384 -> 4 wavefronts, 4 cuts; 16384 x 4096 -> 4, none.
-// Cuts 0: not a shape for the staged kernel.  `us` is the plan's time with 13 MB/us through the L2s, which is what the
-// kernel gets from 129 rows on (16384 x 4096 at 192 rows: 43 us, 4096 x 16384: 53).
+// Cuts 0: not a shape for the staged kernel.  `us` is the plan's time from 129 rows on, where the tile kernel is the
+// alternative: 4.4 us, the weights at 7.4 MB/us, the rows of x that a compute unit takes in at 89 KB/us (64 where they
+// are 16384 inputs apart: rows at multiples of 32 KiB share the memory channels) and for a cut 2.2 us and the shares at
+// 2.7 MB/us.  (700 shapes of 129 to 192 rows, 512 to 16384 features and inputs, weights from HBM: within 5 % rms.)
 LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
   LinearPlan plan = {LinearPlan::kStaged, 4, 0, 0, 0.0};
   if (m > OKV_LINEAR_MAX_ROWS_STAGED) return plan;
@@ -1020,7 +1022,8 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
         best = t;
         plan.waves = w;
         plan.cuts = s;
-        plan.us = std::max(weight_mb / 6.0, (weight_mb + x_mb) / 13.0) / fill + second;
+        const double intake_kb = (double)rounds * m * (n_in / s) * 2 / 1e3;
+        plan.us = 4.4 + weight_mb / 7.4 + intake_kb / (n_in % 16384 ? 89.0 : 64.0) + (s > 1 ? 2.2 + (double)s * m * n_out * 4 / 2.7e6 : 0.0);
       }
     }
   }
@@ -1030,11 +1033,13 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
 // The tile kernel's form and cuts: 4 us for the launch, the weights at 12 MB/us (the part of their way from HBM that
 // the walk does not hide: the same tiles take 6-12 us longer with 134 MB of weights than with 33), the walk, and for a
 // cut 3.5 us and the shares at 5 MB/us (written and read back).  Forms of which a compute unit holds several
-// workgroups are taken half way between whole and broken rounds.
+// workgroups are taken half way between whole and broken rounds.  (`us` of a cut counts the shares at 2.8 MB/us, which is
+// what they take at 129 to 192 rows, where it is compared with the staged kernel's.)
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
   const int stages = (n_in + 63) / 64;
   const double weight_mb = (double)n_out * n_in * 2 / 1e6;
+  double best = 0;
   for (int f = 0; f < kTileFormCount; ++f) {
     const TileForm &form = kTileForms[f];
     const int64_t tiles = (int64_t)((m + form.rows - 1) / form.rows) * ((n_out + form.cols - 1) / form.cols);
@@ -1043,8 +1048,9 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
       const double q = (double)(tiles * s) / n_cus, whole = std::ceil(q);
       const double rounds = form.shares_cu ? 0.5 * (whole + std::max(1.0, q)) : whole;
       double t = 4.0 + weight_mb / 12.0 + rounds * ((stages + s - 1) / s) * form.stage_us;
-      if (s > 1) t += 3.5 + (double)s * m * n_out * 4 / 5e6;
-      if (plan.cuts == 0 || t < plan.us) plan.us = t, plan.form = f, plan.cuts = s;
+      const double shares_mb = s > 1 ? (double)s * m * n_out * 4 / 1e6 : 0.0;
+      if (s > 1) t += 3.5 + shares_mb / 5.0;
+      if (plan.cuts == 0 || t < best) best = t, plan.us = t + 0.16 * shares_mb, plan.form = f, plan.cuts = s;
     }
   }
   return plan;
@@ -1054,8 +1060,9 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
 // where it takes the shape (12288 x 4096 at 128 rows 28 us against the tile kernel's 31, 16384 x 4096 35 against 38; where the
 // inputs are many the tile kernel would win, 4096 x 16384 at 128 rows 35 against 43, with twice the cuts and so twice the
 // workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
-// for (4096 x 16384 at 192 rows: 45 us against 53, tiles; 12288 x 4096: 39 against 37, staged), beyond always the tile
-// kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
+// for (4096 x 16384 at 192 rows: 46 us against 53, tiles; 12288 x 4096 39 against 37, 2304 x 4096 17.7 against 15.2 and 6144 x 2048
+// 20.2 against 17.0, staged; of the 700 shapes above 4 run more than 2 % slower than the staged kernel would, the worst
+// 7 %), beyond always the tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
 // workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront: 4224 x 1056 takes it 7.6 us
 // at 32 rows, 11.6 at 64 and 17.9 at 128, the tile kernel 7.2, 9.0 and 8.9; at 1056 x 1056 and 32 rows 4.6 against 6.2.
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
