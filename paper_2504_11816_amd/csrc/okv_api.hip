@@ -487,11 +487,10 @@ int exec_ops(okv_ctx *ctx, const std::vector<Op> &ops, const void *a0, const voi
   return OKV_OK;
 }
 
-// Recomputes split size, item count and merge flag from the host lengths and
-// rebuilds the device work list (adding `inc` to every device length first).
 // One or two small host arrays to the device, before whatever is enqueued on the compute stream next.  Called with that
 // stream drained, so the memory of the upload before this one is free again; it grows to the largest upload and goes
-// with the context.  Where it cannot be had (pinned memory is limited) the arrays are copied synchronously.
+// with the context.  Coherent: a kernel reads what the host wrote last, whatever its caches held of the upload before.
+// Where it cannot be had (pinned memory is limited) the arrays are copied synchronously.
 constexpr int64_t kUploadTileBytes = 1 << 20;              // of a prompt store's tile list, reserved when the context is made
 
 void reserve_upload(okv_ctx *ctx, int64_t need) {
@@ -500,7 +499,7 @@ void reserve_upload(okv_ctx *ctx, int64_t need) {
   ctx->h_up = nullptr;
   ctx->up_cap = 0;
   void *p = nullptr;
-  if (hipHostMalloc(&p, (size_t)need, hipHostMallocMapped) == hipSuccess) {
+  if (hipHostMalloc(&p, (size_t)need, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
     ctx->h_up = static_cast<char *>(p);
     ctx->up_cap = need;
   } else {
@@ -528,6 +527,8 @@ int upload_tables(okv_ctx *ctx, void *dst0, const void *src0, int64_t bytes0, vo
   return OKV_OK;
 }
 
+// Recomputes split size, item count and merge flag from the host lengths and
+// rebuilds the device work list (adding `inc` to every device length first).
 int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false) {
   int64_t keys = 0;
   for (int32_t b = 0; b < ctx->B; ++b) keys += ctx->h_ctx_lens[b];
