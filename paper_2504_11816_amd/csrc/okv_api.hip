@@ -2060,10 +2060,13 @@ int okv_decode_attn_static(const okv_static_attn *a) {
   l.part_ml = reinterpret_cast<float *>(base + lay.part_ml);
   l.out_fp32 = a->out_dtype;
   l.need_merge = 1;
-  // Neither the lengths nor the number of layers is known here.  A layer that holds half of the memory-side cache and more
-  // is taken for one of a stack that does not fit it; where the capacity leaves that open, the kernel goes by the lengths
-  // (by the capacity alone, 16 x 512 keys, 8 heads x 128, with room for 32768 took 21.2 us a call against 17.4).
-  l.keep_cached = (int64_t)a->B * cap_tokens_of(&c) * G * D * 4 <= okv::kKeepCachedBytes / 2;
+  // Neither the lengths nor the number of layers is known here.  A layer with room for more than a quarter of the
+  // memory-side cache is taken for one of a stack that does not fit it: beyond the cache the loads that do not keep the keys
+  // are 6 to 10 % faster (66 MB x 8 layers 23.7 -> 22.0 us a layer, 83 MB x 8 33.1 -> 30.4), within it 6 % faster to 4 %
+  // slower (50 MB x 1 26.2 -> 25.5, 80 MB x 2 23.4 -> 24.1, 20 MB x 4 24.0 -> 25.0), with one layer of 150 to 250 MB 2 to 7 %
+  // slower.
+  const int64_t cap_bytes = (int64_t)a->B * cap_tokens_of(&c) * G * D * 4;
+  l.keep_cached = cap_bytes <= okv::kKeepCachedBytes / 4;
   l.pair_head = pair_head;
   l.n_groups = max_groups;
   l.plan_dev = plan;                                     // the kernel reads how many stretches are in use
@@ -2071,11 +2074,11 @@ int okv_decode_attn_static(const okv_static_attn *a) {
   l.item_first = 0, l.item_count = (int32_t)max_items;
   l.id_base = l.mirror_base = 0;
   // Small batches go without the bookkeeping launch: the attention launch cuts the keys itself (8 heads x 64, batch 4,
-  // context 256: 15.1 us a call with it, 12.0 without).  Not where the stretches may be long or the keys may not fit the
-  // memory-side cache: those launches take dozens of microseconds, and the table of heads starts them sooner.
+  // context 256: 15.1 us a call with it, 12.0 without).  Not where the stretches may be long or the keys many: those launches
+  // take dozens of microseconds, and the table of heads starts them sooner.
   const int64_t cap_tiles = (cap_tokens_of(&c) + 15) / 16;
   const okv::SpanPlan at_cap = okv::span_plan(a->B * cap_tiles, max_groups, kMinSpanTiles);
-  l.from_lens = a->B <= 64 && l.keep_cached && at_cap.span <= kLensMaxSpan && cap_tiles <= (1 << 24);
+  l.from_lens = a->B <= 64 && cap_bytes <= okv::kKeepCachedBytes / 2 && at_cap.span <= kLensMaxSpan && cap_tiles <= (1 << 24);
   if (l.from_lens) {
     l.pair_head = nullptr;
     l.plan_dev = nullptr;

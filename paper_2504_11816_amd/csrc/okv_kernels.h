@@ -53,8 +53,8 @@ struct AttnLaunch {
   const void *pair_head = nullptr;        // device
   int32_t n_groups = 0;                   // stretches in use (with pair_head)
   // Where the host does not know the lengths, the launch finds the plan and its wavefronts per pair itself: from what
-  // launch_step_advance_spans left at plan_dev (with pair_head), or, for up to 64 sequences and keep_cached launches, from
-  // batch.ctx_lens with no work list at all (from_lens; the merge likewise): at most n_groups stretches of at least min_span
+  // launch_step_advance_spans left at plan_dev (with pair_head), or, for up to 64 sequences, from batch.ctx_lens with no
+  // work list at all (from_lens; the merge likewise): at most n_groups stretches of at least min_span
   // tiles, no more than grid_groups of them for the lengths there may be; the partial results need B + n_groups slots.
   const int32_t *plan_dev = nullptr;
   int32_t from_lens = 0, min_span = 0, grid_groups = 0;

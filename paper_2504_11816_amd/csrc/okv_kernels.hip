@@ -138,7 +138,6 @@ struct AttnArgs {
   int32_t mirror_is_tail;          // pool_mirror is the layer's tail slots: block (2 b + (block index & 1)) of it
   int32_t B, n_cls;                // merge: chunk_prefix is [n_cls][B] (+ 1)
   int32_t min_span;                // kFromLens: shortest stretch, in tiles
-  int64_t keep_tiles;              // plan_dev: up to this many tiles in the batch the loads keep the keys cached
   float scale_log2e;
 };
 
@@ -423,7 +422,7 @@ template <int D, bool PAGED, int PIPE, int SRC, bool NT, int NS>
 __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()], const uint32_t wave, const int sub, uint32_t pair,
                                                 const uint32_t n_pairs, const int32x8_t w, const LensPlan &lp, const uint16_t *pool,
                                                 const uint16_t *q, const int32_t G, const int32_t H, const int32_t R,
-                                                const int32_t v_tiles, const AttnArgs &a) {
+                                                const int32_t v_tiles, const AttnArgs a) {
   static_assert(NS == 1 || SRC != kFromItems, "several wavefronts per pair need a pair per workgroup");
   static_assert(lds_region<D>() >= D / 16 * 1024 + 512, "a wavefront's sums, maxima and weights must fit its tiles' place");
   constexpr int LPR = D / 8, RPL = 64 / LPR, LPT = D / 32;
@@ -789,19 +788,24 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
 // The launch of the entry point that knows no lengths on the host: the plan comes from the lengths (kFromLens) or from what
 // the bookkeeping kernel left (kFromHeads), and with it the number of wavefronts per pair, by the rule a context goes by, so
 // that both sum in the same order.  A workgroup has as many wavefronts as a pair can be given; those past the number chosen
-// leave before the first barrier (which waits for the wavefronts that are still there), or, with one per pair, take a pair
-// each.  LARGE: the keys may not fit the memory-side cache; whether they do is seen from the plan as well.  (Room for three
-// wavefronts on a SIMD, 168 registers: with 170 the workgroups of two wavefronts that leave come in late, 64 x 400 keys, 32 / 8
-// heads 25 -> 29.5 us a call.)
-template <int D, bool PAGED, int SRC, bool LARGE>
-__global__ __launch_bounds__(most_waves_per_pair(D) * 64) __attribute__((amdgpu_waves_per_eu(SRC == kFromLens && D == 128 ? 3 : 1))) void attn_split_planned_kernel(
+// leave before the first barrier (which waits for the wavefronts that are still there).  With one per pair the four of d = 128
+// take a pair each; at d = 64 a workgroup keeps to one pair (two in it land on the same SIMDs: 67 x 508..1017 keys, 40 heads 107
+// us a call against 102).  Room for three wavefronts on a SIMD (168 registers) matters at d = 128: with 170 the workgroups of two
+// wavefronts that leave come in late, 64 x 400 keys, 32 / 8 heads 25 -> 29.5 us a call.
+//
+// a1, a2, a4: the same arguments once more for each number of wavefronts.  With one copy the compiler fetches what all three
+// bodies read in front of the choice, and the first tiles wait for that round trip (81 x 10..83 keys, 40 heads x 128 35.0 us a
+// call against 31.7).  (Contiguous pools at d = 64 stay with one: a body of its own arguments spills there.)
+template <int D, bool PAGED, int SRC, bool NT>
+__global__ __launch_bounds__(most_waves_per_pair(D) * 64) void attn_split_planned_kernel(
     const void *source, const uint16_t *pool, const uint16_t *q, const int32_t *plan_dev, const int32_t most_groups, const int32_t G,
-    const int32_t H, const int32_t R, const int32_t v_tiles, const AttnArgs a) {
+    const int32_t H, const int32_t R, const int32_t v_tiles, const AttnArgs a, const AttnArgs a1, const AttnArgs a2, const AttnArgs a4) {
   static_assert(SRC != kFromItems, "there is no plan then");
   constexpr int W = most_waves_per_pair(D);
+  constexpr bool kFour = W == kWavesPerBlock;            // a workgroup of wavefronts with a pair each
   __shared__ __attribute__((aligned(16))) char lds_all[W][lds_region<D>()];
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t alone = blockIdx.x * W + wave;          // the pair of this wavefront if it has one to itself
+  const uint32_t alone = kFour ? blockIdx.x * W + wave : blockIdx.x;       // the pair of this wavefront if it has one to itself
   int32x8_t w = {0, 0, 0, 0, 0, 0, 0, 0}, w_alone = w;
   LensPlan lp = {};
   int32_t n_groups, n_items;
@@ -820,21 +824,17 @@ __global__ __launch_bounds__(most_waves_per_pair(D) * 64) __attribute__((amdgpu_
   }
   const int32_t ns = waves_per_pair(D, G, n_groups, span, n_items);
   const uint32_t n_pairs = (uint32_t)n_groups * (uint32_t)G;
-  auto run = [&](auto nt, auto waves) {
+  auto run = [&](auto waves, const AttnArgs args) {
     constexpr int NS = decltype(waves)::value;
-    if (NS > 1 && wave >= NS) return;
+    if (wave >= (NS > 1 || !kFour ? NS : W)) return;
     const uint32_t pair = NS > 1 ? blockIdx.x : alone;
     if (pair >= n_pairs) return;
-    attn_split_body<D, PAGED, base_depth<D, NS>(), SRC, decltype(nt)::value, NS>(lds_all, wave, NS > 1 ? (int)wave : 0, pair, n_pairs,
-                                                                                 NS > 1 ? w : w_alone, lp, pool, q, G, H, R, v_tiles, a);
+    attn_split_body<D, PAGED, base_depth<D, NS>(), SRC, NT, NS>(lds_all, wave, NS > 1 ? (int)wave : 0, pair, n_pairs, NS > 1 ? w : w_alone, lp,
+                                                                pool, q, G, H, R, v_tiles, args);
   };
-  auto pick = [&](auto nt) {
-    if (W == 4 && ns == 4) return run(nt, std::integral_constant<int, W>{});
-    if (ns == 2) return run(nt, std::integral_constant<int, 2>{});
-    run(nt, std::integral_constant<int, 1>{});
-  };
-  if (LARGE && span * n_groups > a.keep_tiles) pick(std::integral_constant<bool, LARGE>{});
-  else pick(std::integral_constant<bool, false>{});
+  if (W == 4 && ns == 4) return run(std::integral_constant<int, W>{}, a4);
+  if (ns == 2) return run(std::integral_constant<int, 2>{}, PAGED || D == 128 ? a2 : a);
+  run(std::integral_constant<int, 1>{}, PAGED || D == 128 ? a1 : a);
 }
 
 // out[b][h] = sum_c o_c 2^(m_c - M) / sum_c l_c 2^(m_c - M) over the items c of sequence b.
@@ -952,18 +952,15 @@ void launch_split_as(const AttnArgs &args, dim3 grid, hipStream_t stream) {
                      stream, args.pair_head, args.pool, args.q, args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args);
 }
 
-template <int D, bool PAGED, int SRC, bool LARGE>
+template <int D, bool PAGED, int SRC, bool NT>
 void launch_planned(const AttnArgs &args, const void *source, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_split_planned_kernel<D, PAGED, SRC, LARGE>), grid, dim3(most_waves_per_pair(D) * 64), 0, stream, source,
-                     args.pool, args.q, args.plan_dev, args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args);
+  hipLaunchKernelGGL((attn_split_planned_kernel<D, PAGED, SRC, NT>), grid, dim3(most_waves_per_pair(D) * 64), 0, stream, source,
+                     args.pool, args.q, args.plan_dev, args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args, args, args, args);
 }
 
-// (launches from the lengths are small ones: never more keys than the memory-side cache holds)
 template <int D, bool PAGED, bool NT>
 void launch_split_kept(const AttnArgs &args, int waves, dim3 grid, hipStream_t stream) {
-  if constexpr (!NT) {
-    if (args.lens) return launch_planned<D, PAGED, kFromLens, NT>(args, args.lens, grid, stream);
-  }
+  if (args.lens) return launch_planned<D, PAGED, kFromLens, NT>(args, args.lens, grid, stream);
   if (args.plan_dev) return launch_planned<D, PAGED, kFromHeads, NT>(args, args.pair_head, grid, stream);
   if (!args.pair_head) return launch_split_as<D, PAGED, kFromItems, NT, 1>(args, grid, stream);
   if constexpr (D == 128) {
@@ -1005,7 +1002,6 @@ AttnArgs make_args(const AttnLaunch &a) {
   args.pair_head = static_cast<const PairHead *>(a.pair_head);
   args.lens = a.from_lens ? a.batch.ctx_lens : nullptr;
   args.min_span = a.min_span;
-  args.keep_tiles = kKeepCachedBytes / 2 / (16 * 4 * (int64_t)s.G * s.D);
   args.n_groups = a.pair_head || a.from_lens ? a.n_groups : a.item_count;
   args.H = s.H;
   args.G = s.G;
@@ -1040,7 +1036,7 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream, hipEvent_
   const int64_t want = ((int64_t)args.n_groups * s.G + kWavesPerBlock - 1) / kWavesPerBlock;
   const int64_t cap = std::max<int64_t>(1, a.max_waves / kWavesPerBlock);
   const int waves = a.pair_head && !a.plan_dev ? a.waves_per_pair : 1;
-  if (a.from_lens && (!a.keep_cached || a.pair_head || a.plan_dev || a.batch.B > kLensBatch || a.n_groups < 1 || a.grid_groups < 1 ||
+  if (a.from_lens && (a.pair_head || a.plan_dev || a.batch.B > kLensBatch || a.n_groups < 1 || a.grid_groups < 1 ||
                       a.min_span < 1))
     return hipErrorInvalidValue;
   if (a.plan_dev && !a.pair_head) return hipErrorInvalidValue;
