@@ -2062,9 +2062,10 @@ int okv_decode_attn_static(const okv_static_attn *a) {
   l.need_merge = 1;
   // Neither the lengths nor the number of layers is known here.  A layer with room for more than a quarter of the
   // memory-side cache is taken for one of a stack that does not fit it: beyond the cache the loads that do not keep the keys
-  // are 6 to 10 % faster (66 MB x 8 layers 23.7 -> 22.0 us a layer, 83 MB x 8 33.1 -> 30.4), within it 6 % faster to 4 %
-  // slower (50 MB x 1 26.2 -> 25.5, 80 MB x 2 23.4 -> 24.1, 20 MB x 4 24.0 -> 25.0), with one layer of 150 to 250 MB 2 to 7 %
-  // slower.
+  // are 6 to 10 % faster (66 MB x 8 layers 23.7 -> 22.0 us a layer, 83 MB x 8 33.1 -> 30.4, 105 MB x 8 30.0 -> 28.2).  One or
+  // two layers of 64 to 128 MB that stay in the cache go from 6 % faster to 11 % slower (83 MB x 1 29.0 -> 27.4, 105 MB x 2
+  // 25.2 -> 27.6).  Below a quarter a stack has to be deep to leave the cache, and what stays in it is up to 4 % faster kept
+  // (20 MB x 4 24.0 -> 25.0).
   const int64_t cap_bytes = (int64_t)a->B * cap_tokens_of(&c) * G * D * 4;
   l.keep_cached = cap_bytes <= okv::kKeepCachedBytes / 4;
   l.pair_head = pair_head;
