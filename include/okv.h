@@ -23,7 +23,9 @@
  *     q / k / v / out) and keeps it alive until okv_destroy; the library never
  *     frees or reallocates them.  The library itself allocates only small
  *     bookkeeping arrays (O(max_batch * max_blocks_per_seq) integers, as much pinned host
- *     memory to upload them from, a few events).
+ *     memory to upload them from, a few events) and, with two or more layers and none of
+ *     them on the host, up to 64 MiB (or two layers' worth, where that is more) of partial
+ *     results for okv_decode_step.
  *   - Work is enqueued on the two streams given at creation and the calls return
  *     without waiting for the GPU unless stated otherwise.  q / k_new / v_new / out
  *     may be reused once the work enqueued on the compute stream has finished.
@@ -364,15 +366,23 @@ int kv_append(okv_ctx *ctx, int32_t layer, const void *k_new, const void *v_new)
 int decode_attn(okv_ctx *ctx, int32_t layer, const void *q, void *out);
 
 /* One whole decode step in one call: okv_step_begin, then kv_append(l) and decode_attn(l)
- * for l = 0 .. L-1, then okv_step_end -- exactly those calls, made from inside the library,
- * for callers that have every layer's inputs ready (attention over a cache with no linear
- * layers in between, benchmarks) and do not want to cross the ABI 2 L + 2 times a step.
+ * for l = 0 .. L-1, then okv_step_end, for callers that have every layer's inputs ready
+ * (attention over a cache with no linear layers in between, benchmarks).  The results are those
+ * of the calls one by one, bit for bit.  Where every layer is in HBM and no layer's results or
+ * pool overlap what another layer reads or writes, the layers are attended together: a launch
+ * covers up to 32 of them (fewer where the batch is cut into pieces and their partial results
+ * would take more than 64 MiB, which the library allocates with the context); otherwise the calls
+ * are made one after the other, from inside the library.
  *   q, k_new, v_new, out  HOST arrays [n_layers] of DEVICE pointers, each as in kv_append /
  *                         decode_attn
  * Stops at the first error and returns its code; the step is then left open as the failing
  * call left it. */
 int okv_decode_step(okv_ctx *ctx, const void *const *q, const void *const *k_new,
                     const void *const *v_new, void *const *out);
+
+/* Layers that a launch of the last okv_decode_step on ctx covered at most (1: layer by layer; 0:
+ * no step yet). */
+int32_t okv_layers_per_launch(const okv_ctx *ctx);
 
 /* ---- storing prompts (the prefill side) ---------------------------------------------
  *

@@ -23,7 +23,7 @@ EXPORTS = [
     "okv_worklist_classes", "okv_pair_heads", "okv_prefill_begin", "kv_append_bulk", "okv_prefill_release", "okv_prefill_end", "okv_prefill_plan",
     "okv_measure_d2h",
     "okv_profile_enable", "okv_profile_read", "okv_measure_h2d", "okv_time_copies", "okv_probe_copy",
-    "okv_probe_read", "okv_equal_stretches", "okv_waves_per_pair", "okv_decode_attn_static",
+    "okv_probe_read", "okv_equal_stretches", "okv_waves_per_pair", "okv_decode_attn_static", "okv_layers_per_launch",
 ]
 
 
@@ -142,6 +142,7 @@ def lib():
             "okv_equal_stretches": (ctypes.c_int, [P, I32, I32, P, I64, ctypes.POINTER(I64), P, ctypes.POINTER(I32),
                                                    ctypes.POINTER(I64)]),
             "okv_waves_per_pair": (I32, [I32, I32, I32, I64, I64]),
+            "okv_layers_per_launch": (I32, [P]),
             "okv_decode_attn_static": (ctypes.c_int, [ctypes.POINTER(OkvStaticAttn)]),
         }
         for name, (res, args) in sig.items():
@@ -452,6 +453,10 @@ class Context:
         if not (len(q) == len(k) == len(v) == len(o) == self.cfg.n_layers):
             raise ValueError("one pointer per layer in each array")
         self._c(lib().okv_decode_step(self._h, q, k, v, o))
+
+    def okv_layers_per_launch(self):
+        """Layers that a launch of the last okv_decode_step covered at most."""
+        return lib().okv_layers_per_launch(self._h)
 
     @staticmethod
     def decoder_layers(layers):

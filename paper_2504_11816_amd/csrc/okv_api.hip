@@ -130,6 +130,11 @@ struct okv_ctx {
   bool keep_cached = true;               // the batch's keys and values of all layers fit the memory-side cache
   int64_t max_items = 0;
   float *part_o = nullptr, *part_ml = nullptr;
+  // okv_decode_step over several layers a launch: their partial results side by side, if the batch is cut at all
+  float *layer_parts = nullptr;
+  int64_t layer_parts_bytes = 0;
+  int32_t layers_per_launch = 0;         // of the last okv_decode_step
+  std::vector<okv::Buffer> step_buffers; // scratch of step_layers_together
 
   std::vector<int32_t> h_block_table, h_ctx_lens;
   int32_t B = 0, split = 0, split_override = 0, n_items = 0;
@@ -247,6 +252,10 @@ int32_t max_classes_of(const okv_config *c) {
   if (c->chunk_blocks <= 0) return 1;
   return 1 + (int32_t)((c->blocks_per_layer - c->resident_blocks + c->chunk_blocks - 1) / c->chunk_blocks);
 }
+
+// Of the partial results that okv_decode_step keeps for the layers of a launch (cfg4-sized batches, 4.2 MB a layer, then go 15
+// layers at a time), or those of two layers where that is more.
+constexpr int64_t kLayerPartsBytes = 64 << 20;
 
 int64_t bytes_per_item(const okv_config *c) { return (int64_t)c->n_q_heads * (c->head_dim + 2) * 4; }
 
@@ -386,6 +395,27 @@ void tail_mark_chunks(okv_ctx *ctx) {
   for (size_t u = 0; u < ctx->active_chunks.size(); ++u) ctx->patch_chunk[u] = by_chunk[(size_t)ctx->active_chunks[u]];
 }
 
+// The events around a split-K launch that is about to be enqueued, as okv_profile_enable asked for them (NULL: none here).
+int bracket_launch(okv_ctx *ctx, hipEvent_t *e0, hipEvent_t *e1) {
+  if (ctx->profile == 1 || (ctx->profile == 2 && !ctx->prof_open)) {
+    if (ctx->prof_used == ctx->prof_events.size()) {
+      hipEvent_t x, y;
+      OKV_HIP(ctx, hipEventCreate(&x));
+      OKV_HIP(ctx, hipEventCreate(&y));
+      ctx->prof_events.emplace_back(x, y);
+    }
+    *e0 = ctx->prof_events[ctx->prof_used].first;
+    if (ctx->profile == 1) {
+      *e1 = ctx->prof_events[ctx->prof_used].second;
+      ++ctx->prof_used;
+    } else {
+      ctx->prof_open = true;                             // okv_step_end records the closing event
+    }
+  }
+  if (ctx->profile) ++ctx->prof_launches;
+  return OKV_OK;
+}
+
 int exec_op(okv_ctx *ctx, const Op &op, const void *a0, const void *a1, void *out) {
   switch (op.kind) {
     case okv::OP_COPY: {
@@ -445,22 +475,7 @@ int exec_op(okv_ctx *ctx, const Op &op, const void *a0, const void *a1, void *ou
       }
       a.out = out;
       hipEvent_t e0 = nullptr, e1 = nullptr;
-      if (ctx->profile == 1 || (ctx->profile == 2 && !ctx->prof_open)) {
-        if (ctx->prof_used == ctx->prof_events.size()) {
-          hipEvent_t x, y;
-          OKV_HIP(ctx, hipEventCreate(&x));
-          OKV_HIP(ctx, hipEventCreate(&y));
-          ctx->prof_events.emplace_back(x, y);
-        }
-        e0 = ctx->prof_events[ctx->prof_used].first;
-        if (ctx->profile == 1) {
-          e1 = ctx->prof_events[ctx->prof_used].second;
-          ++ctx->prof_used;
-        } else {
-          ctx->prof_open = true;                         // okv_step_end records the closing event
-        }
-      }
-      if (ctx->profile) ++ctx->prof_launches;
+      if (int rc = bracket_launch(ctx, &e0, &e1)) return rc;
       OKV_HIP(ctx, okv::launch_decode_attn(a, ctx->compute, e0, e1));
       return OKV_OK;
     }
@@ -477,6 +492,37 @@ int exec_op(okv_ctx *ctx, const Op &op, const void *a0, const void *a1, void *ou
     }
   }
   return fail(ctx, OKV_ESTATE, "unknown pipeline op %d", op.kind);
+}
+
+// Layers of a step that one launch may cover: 1 unless every layer is in HBM, the work list is one of equal stretches, the
+// layers can be attended in any order and no bracket per launch is wanted.  As many as the launch's arguments hold and, where
+// sequences are cut, as there is room for partial results of.  (A bad pointer is left to the calls one by one to refuse.)
+int32_t step_layers_together(okv_ctx *ctx, const void *const *q, const void *const *k, const void *const *v, void *const *out) {
+  const int32_t L = ctx->cfg.n_layers;
+  if (L < 2 || ctx->any_host || ctx->by_class || !ctx->spans || ctx->profile == 1 || ctx->n_items < 1) return 1;
+  int64_t most = okv::kLayersPerLaunch;
+  if (ctx->need_merge) most = std::min(most, ctx->layer_parts_bytes / (ctx->n_items * bytes_per_item(&ctx->cfg)));
+  if (most < 2) return 1;
+  const okv::PoolShape &s = ctx->shape;
+  const uintptr_t q_bytes = (uintptr_t)ctx->B * s.H * s.D * 2, kv_bytes = (uintptr_t)ctx->B * s.G * s.D * 2;
+  const uintptr_t out_bytes = q_bytes * (ctx->cfg.out_dtype ? 2 : 1);
+  ctx->step_buffers.clear();
+  for (int32_t l = 0; l < L; ++l) {
+    const void *reads[3] = {q[l], k[l], v[l]};
+    for (const void *p : reads)
+      if (!p || !aligned16(p)) return 1;
+    if (!out[l] || !aligned16(out[l])) return 1;
+    auto add = [&](const void *p, uintptr_t bytes, bool written) {
+      ctx->step_buffers.push_back({reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes, l, written});
+    };
+    add(q[l], q_bytes, false);
+    add(k[l], kv_bytes, false);
+    add(v[l], kv_bytes, false);
+    add(out[l], out_bytes, true);
+    add(ctx->dev_pool[l], (uintptr_t)ctx->pool_bytes, true);
+  }
+  if (!okv::layers_independent(ctx->step_buffers)) return 1;
+  return (int32_t)std::min<int64_t>(most, L);
 }
 
 int exec_ops(okv_ctx *ctx, const std::vector<Op> &ops, const void *a0, const void *a1, void *out) {
@@ -944,6 +990,18 @@ int okv_create(const okv_config *cfg, okv_ctx **out) {
   OKV_TRY_CREATE(hipMalloc(&ctx->d_pair_head, (size_t)max_pairs(ctx->max_waves) * okv::kPairHeadBytes));
   OKV_TRY_CREATE(hipMemset(ctx->d_pair_head, 0, (size_t)max_pairs(ctx->max_waves) * okv::kPairHeadBytes));
   OKV_TRY_CREATE(hipMalloc(&ctx->d_plan, 4 * sizeof(int32_t)));
+  if (L >= 2 && !any_host && !by_class) {
+    // items of a batch cut into equal stretches: one per sequence and one more per cut
+    const int64_t most = std::min<int64_t>(max_items, (int64_t)cfg->max_batch + ctx->max_groups - 1) * per_item;
+    const int64_t want = std::min(std::min(L, okv::kLayersPerLaunch) * most, std::max(kLayerPartsBytes, 2 * most));
+    void *p = nullptr;
+    if (hipMalloc(&p, (size_t)want) == hipSuccess) {
+      ctx->layer_parts = static_cast<float *>(p);
+      ctx->layer_parts_bytes = want;
+    } else {
+      (void)hipGetLastError();                           // steps whose batch is cut then go layer by layer
+    }
+  }
   // What a batch's tables and an ordinary prompt's tiles are uploaded from is had here: allocating it (and growing it) in
   // the first calls made a new context's first batch and prompt 0.4 ms slower.
   const int64_t tiles = (int64_t)cfg->max_batch * (((int64_t)ctx->cap_tokens + 15) / 16) * (int64_t)sizeof(int4);
@@ -980,6 +1038,7 @@ int okv_destroy(okv_ctx *ctx) {
   (void)hipFree(ctx->d_item_desc);
   (void)hipFree(ctx->d_group_first);
   (void)hipFree(ctx->d_pair_head);
+  (void)hipFree(ctx->layer_parts);
   if (ctx->h_up) (void)hipHostFree(ctx->h_up);
   (void)hipFree(ctx->d_plan);
   (void)hipFree(ctx->d_items_dump);
@@ -1251,12 +1310,36 @@ int okv_decode_step(okv_ctx *ctx, const void *const *q, const void *const *k_new
   if (!ctx) return fail(nullptr, OKV_EINVAL, "ctx is NULL");
   if (!q || !k_new || !v_new || !out) return fail(ctx, OKV_EINVAL, "okv_decode_step: NULL pointer array");
   int rc = okv_step_begin(ctx);
-  for (int32_t l = 0; rc == OKV_OK && l < ctx->cfg.n_layers; ++l) {
+  if (rc != OKV_OK) return rc;
+  const int32_t together = step_layers_together(ctx, q, k_new, v_new, out), L = ctx->cfg.n_layers;
+  ctx->layers_per_launch = together;
+  for (int32_t l = 0; rc == OKV_OK && l < L; ++l) {
+    const int32_t n = std::min(together, L - l);
+    if (n > 1) {
+      okv::DecodeLayer at[okv::kLayersPerLaunch];
+      for (int32_t i = 0; i < n; ++i)
+        at[i] = {static_cast<const uint16_t *>(ctx->dev_pool[l + i]), static_cast<const uint16_t *>(q[l + i]),
+                 static_cast<const uint16_t *>(k_new[l + i]), static_cast<const uint16_t *>(v_new[l + i]), out[l + i]};
+      okv::AttnLaunch a = base_launch(ctx);
+      if (a.need_merge) {
+        a.part_o = ctx->layer_parts;
+        a.part_ml = a.part_o + (int64_t)n * ctx->n_items * a.shape.H * a.shape.D;
+      }
+      hipEvent_t e0 = nullptr, e1 = nullptr;
+      rc = bracket_launch(ctx, &e0, &e1);
+      if (rc == OKV_OK && e0) OKV_HIP(ctx, hipEventRecord(e0, ctx->compute));
+      if (rc == OKV_OK) OKV_HIP(ctx, okv::launch_decode_layers(a, at, n, ctx->compute));
+      l += n - 1;
+      ctx->next_layer = l + 1;
+      continue;
+    }
     rc = kv_append(ctx, l, k_new[l], v_new[l]);
     if (rc == OKV_OK) rc = decode_attn(ctx, l, q[l], out[l]);
   }
   return rc == OKV_OK ? okv_step_end(ctx) : rc;
 }
+
+int32_t okv_layers_per_launch(const okv_ctx *ctx) { return ctx ? ctx->layers_per_launch : OKV_EINVAL; }
 
 // ---- bulk store of prompts ------------------------------------------------------------
 

@@ -5,6 +5,7 @@
 
 #include <stdint.h>
 
+#include <algorithm>
 #include <vector>
 
 namespace okv {
@@ -208,6 +209,47 @@ __host__ __device__ inline int32_t waves_per_pair(int32_t D, int32_t G, int32_t 
 }
 // The most there can be, which is what a launch is sized for where the host does not know the lengths.
 constexpr int32_t most_waves_per_pair(int32_t D) { return D == 64 ? 2 : 4; }
+
+// Layers of a launch over several that are attended side by side, by wavefronts of their own; the others one after the other by the
+// same wavefronts.  Launches of one wavefront per pair at d = 128 have about as many wavefronts as the memory system runs best
+// with, and those go from layer to layer (us a step, one after the other / side by side: 8 layers of 32 x 776 keys, 32 heads 488 / 502;
+// 4 layers of 128 x 512..4096 keys, 32 / 8 heads 788 / 844; 128 x 500..2000, 64 / 8 heads 445 / 478; 32 x 300..1500, 40 heads 357 / 380).
+// The others are bound by the chain of tiles of a wavefront: side by side 8 layers of 8 x 512 keys, 8 heads 47 against 68, of
+// 40 x 20..90, 32 heads 95 against 120, of 16 x 100..300 101 against 108; at d = 64, 8 layers of 16 x 300..900, 8 heads 52 against 78, of 32 x 300,
+// 32 heads 120 against 120, 6 of 24 x 190..1150 135 against 142, 4 of 64 x 1000 344 against 351.
+inline int32_t layers_abreast(int32_t D, int32_t waves_per_pair, int32_t n_layers) { return D == 128 && waves_per_pair == 1 ? 1 : n_layers; }
+
+// Whether the layers of a step can be attended in any order: no layer writes (its results, its pool) where another reads or
+// writes.  Buffers as [first, last) addresses.
+struct Buffer {
+  uintptr_t first, last;
+  int32_t layer;
+  bool written;
+};
+inline bool layers_independent(std::vector<Buffer> &bufs) {
+  std::sort(bufs.begin(), bufs.end(), [](const Buffer &a, const Buffer &b) { return a.first < b.first; });
+  // how far written and read buffers reach so far, of the layer that reaches furthest and of the others
+  struct Reach {
+    uintptr_t far = 0, other = 0;
+    int32_t layer = -1;
+    void add(const Buffer &b) {
+      if (b.layer == layer) {
+        far = std::max(far, b.last);
+      } else if (b.last > far) {
+        other = far, far = b.last, layer = b.layer;
+      } else {
+        other = std::max(other, b.last);
+      }
+    }
+    uintptr_t past(int32_t of) const { return layer == of ? other : far; }   // the furthest end among the other layers'
+  } written, any;
+  for (const Buffer &b : bufs) {
+    if (b.first < (b.written ? any : written).past(b.layer)) return false;
+    any.add(b);
+    if (b.written) written.add(b);
+  }
+  return true;
+}
 
 // Pieces of a sequence whose tiles are [first, first + tiles) of the stream: it is cut at the multiples
 // of span strictly inside that range.  *k0 receives the first such multiple's index, so that piece c >= 1

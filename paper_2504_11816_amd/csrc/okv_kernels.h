@@ -29,6 +29,13 @@ struct BatchState {        // device arrays owned by the context
   int32_t n_cls;                // block classes: 1 unless a share of every layer's blocks is on the host
 };
 
+// What a layer brings to an attention launch that covers several (fp16 on the device, as in AttnLaunch).
+struct DecodeLayer {
+  const uint16_t *pool, *q, *k_new, *v_new;
+  void *out;
+};
+constexpr int kLayersPerLaunch = 32;     // a launch's arguments hold that many
+
 struct AttnLaunch {
   PoolShape shape;
   BatchState batch;
@@ -76,6 +83,11 @@ constexpr int64_t kKeepCachedBytes = 256000000;
 // Store of the step's K/V rows and split-K partial attention over the launch's items.
 hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream,
                               hipEvent_t ev_begin, hipEvent_t ev_end);
+
+// The same for n_layers (at most kLayersPerLaunch) layers in HBM at once, merge included: two launches whatever their number.
+// Of `a` everything but pool, q, k_new, v_new and out is the layers' own in common; the work list is one of equal stretches
+// (pair_head), and part_o / part_ml hold batch.n_items slots per layer, one layer after the other.
+hipError_t launch_decode_layers(const AttnLaunch &a, const DecodeLayer *layers, int32_t n_layers, hipStream_t stream);
 
 // Merge of the partial results of every sequence that has more than one item (reads
 // shape, batch, out, part_o, part_ml, out_fp32 of `a`).

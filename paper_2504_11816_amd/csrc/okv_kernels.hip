@@ -23,6 +23,7 @@
 #include "okv_kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #include "okv_host.h"
 
@@ -106,6 +107,15 @@ __device__ __forceinline__ uint4 load_kv(const uint4 *p) {
   if constexpr (NT) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)));
   else return *p;
 }
+
+// What differs between the layers of a launch that covers several of them: part of its arguments, so a look-up is a scalar load.
+struct LayerList {
+  int32_t count;
+  int32_t pair_shift;              // by how many pairs a wavefront's next layer is shifted against its last
+  int32_t slots;                   // partial results between one layer's and the next's (items x H)
+  DecodeLayer at[kLayersPerLaunch];
+};
+struct NoLayers {};
 
 template <int LPT>
 struct Tile {
@@ -415,15 +425,21 @@ struct Unit {
 //
 // The body of a wavefront, for the kernels below that find its pair and, by kFromHeads, that pair's record `w`: `wave` is its place
 // in the workgroup's LDS and `sub` which of the pair's wavefronts it is.
+//
+// Layers: the launch covers several layers (LayerList) with one work list: when its pair's items are done a wavefront goes on
+// with another pair of the layer gridDim.y further on, as it would with a next item, so its stream does not stop between layers
+// either.
 template <int D>
 constexpr int lds_region() { return 2 * lds_tiles<D>() * lds_tile_bytes<D>(); }       // LDS of a wavefront
 
-template <int D, bool PAGED, int PIPE, int SRC, bool NT, int NS>
+template <int D, bool PAGED, int PIPE, int SRC, bool NT, int NS, typename Layers = NoLayers>
 __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()], const uint32_t wave, const int sub, uint32_t pair,
                                                 const uint32_t n_pairs, const int32x8_t w, const LensPlan &lp, const uint16_t *pool,
                                                 const uint16_t *q, const int32_t G, const int32_t H, const int32_t R,
-                                                const int32_t v_tiles, const AttnArgs a) {
+                                                const int32_t v_tiles, const AttnArgs a, const Layers &layers = Layers()) {
+  constexpr bool LAYERS = std::is_same<Layers, LayerList>::value;
   static_assert(NS == 1 || SRC != kFromItems, "several wavefronts per pair need a pair per workgroup");
+  static_assert(!LAYERS || SRC == kFromHeads, "a launch over several layers starts from the table of heads");
   static_assert(lds_region<D>() >= D / 16 * 1024 + 512, "a wavefront's sums, maxima and weights must fit its tiles' place");
   constexpr int LPR = D / 8, RPL = 64 / LPR, LPT = D / 32;
   constexpr bool by_head = SRC == kFromHeads, by_lens = SRC == kFromLens;
@@ -439,6 +455,12 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
   const int row = lane / LPR, col = lane % LPR;
   const int quarter = lane >> 4, rho = lane & 15;
   char *ks = lds_all[wave], *vs = ks + lds_tiles<D>() * lds_tile_bytes<D>();
+  // `pool` and `q` are those of the layer the next loads are for, these of the unit being reduced (the same with one layer)
+  int layer = LAYERS ? (int)blockIdx.y : 0;
+  const uint16_t *k_new = a.k_new, *v_new = a.v_new;
+  uint16_t *pool_store = a.pool_store;
+  void *out = a.out;
+  float *part_o = a.part_o, *part_ml = a.part_ml;
 
   // Block id of a tile: a wavefront-uniform (scalar) load from the block table.  The table is read
   // through the constant address space: the kernel also stores (outputs, appended rows) and without
@@ -451,7 +473,7 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
     bi = bi < a.max_blocks ? bi : a.max_blocks - 1;
     return tbl[bi] - a.id_base;
   };
-  auto load_tile = [&](Tile<LPT> &t, const TileAddr &ta, int tile, int blk) {
+  auto load_tile = [&](Tile<LPT> &t, const uint16_t *pool, const TileAddr &ta, int tile, int blk) {
     const int64_t base = slab_base<PAGED>(ta, blk, tile);
     const uint4 *kp = reinterpret_cast<const uint4 *>(pool + base + ta.head_k) + lane;
     const uint4 *vp = reinterpret_cast<const uint4 *>(pool + base + ta.head_v) + lane;
@@ -503,7 +525,7 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
         for (int j = 0; j < LPT; ++j) buf[i].v[j] = load_kv<NT>(vp + j * 64);
       } else {
         const int tile = min((head.lo >> 4) + k, last0);
-        load_tile(buf[i], tile_addr<D>(G, a.gg, a.tcap, a.st_log2, g0), tile, blk_of(head.b, tile));
+        load_tile(buf[i], pool, tile_addr<D>(G, a.gg, a.tcap, a.st_log2, g0), tile, blk_of(head.b, tile));
       }
     }
     const uint4 *qp = reinterpret_cast<const uint4 *>(q + ((size_t)head.b * H + (size_t)(head.flags_g >> 8) * R + (rho < R ? rho : 0)) * D + 8 * quarter);
@@ -514,8 +536,8 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
   // All the other launch arguments are asked for here, in one batch of scalar loads (with a table of heads:
   // behind the first tile loads).  Left to itself the compiler fetches each where it is first used, which
   // makes three or four dependent round trips to the argument segment of them.
-  asm volatile("" ::"s"(gridDim.x), "s"(a.gg), "s"(a.st_log2), "s"(a.k_new), "s"(a.v_new), "s"(a.pool_store),
-               "s"(a.pool_mirror), "s"(a.out), "s"(a.part_o), "s"(a.part_ml), "s"(a.block_table), "s"(a.item_desc),
+  asm volatile("" ::"s"(gridDim.x), "s"(a.gg), "s"(a.st_log2), "s"(k_new), "s"(v_new), "s"(pool_store),
+               "s"(a.pool_mirror), "s"(out), "s"(part_o), "s"(part_ml), "s"(a.block_table), "s"(a.item_desc),
                "s"(a.log2_T), "s"(a.tcap), "s"(a.max_blocks), "s"(a.out_fp32), "s"(a.item_first),
                "s"(a.id_base), "s"(a.mirror_shift), "s"(a.mirror_is_tail), "s"(a.scale_log2e));
   float m = kNegBig, l = 0.f;
@@ -554,10 +576,10 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
     }
     // [A] the next unit's first tiles and its q
     // (with a table of heads a wavefront stays with one KV head: nothing to work out again)
-    const TileAddr ta_next = (by_head || by_lens) && live ? ta : tile_addr<D>(G, a.gg, a.tcap, a.st_log2, N.g);
+    const TileAddr ta_next = (by_head || by_lens) && !LAYERS && live ? ta : tile_addr<D>(G, a.gg, a.tcap, a.st_log2, N.g);
     if (has_next && (live || !by_head)) {
 #pragma unroll
-      for (int i = 0; i < PIPE; ++i) load_tile(buf[i], ta_next, min((N.lo >> 4) + sub + i * NS, (N.hi - 1) >> 4), N.blk0[i]);
+      for (int i = 0; i < PIPE; ++i) load_tile(buf[i], pool, ta_next, min((N.lo >> 4) + sub + i * NS, (N.hi - 1) >> 4), N.blk0[i]);
       // (lanes past the group's heads read head 0's piece, which is dropped where q is taken over: no branch
       // around each load)
       const uint4 *qp = reinterpret_cast<const uint4 *>(q + ((size_t)N.b * H + (size_t)N.g * R + (rho < R ? rho : 0)) * D + 8 * quarter);
@@ -614,9 +636,9 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
         const int h = C.g * R + rho;
         const float inv = seq_whole ? 1.0f / lt : 1.0f;
         const bool as_float = !seq_whole || a.out_fp32;
-        float *fdst = seq_whole ? reinterpret_cast<float *>(a.out) + ((size_t)C.b * H + h) * D
-                                : a.part_o + ((size_t)C.it * H + h) * D;
-        uint16_t *hdst = reinterpret_cast<uint16_t *>(a.out) + ((size_t)C.b * H + h) * D;
+        float *fdst = seq_whole ? reinterpret_cast<float *>(out) + ((size_t)C.b * H + h) * D
+                                : part_o + ((size_t)C.it * H + h) * D;
+        uint16_t *hdst = reinterpret_cast<uint16_t *>(out) + ((size_t)C.b * H + h) * D;
 #pragma unroll
         for (int u = 0; u < kShare; ++u) {
           float ot[8];
@@ -640,16 +662,16 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
           }
         }
         if (!seq_whole && quarter == 0 && sub == 0)
-          *reinterpret_cast<float2 *>(a.part_ml + ((size_t)C.it * H + h) * 2) = make_float2(m, lt);
+          *reinterpret_cast<float2 *>(part_ml + ((size_t)C.it * H + h) * 2) = make_float2(m, lt);
       }
       // The item that ends at the sequence's last key also stores this step's K/V rows (paper §II-A: keys
       // and values of every processed token are kept): row 0 of the load layout stores the K row, row 1 the V row.
       const int pos = C.hi - 1;
-      if (a.k_new != nullptr && (C.flags & kItemLast) && row < 2 && sub == 0) {
+      if (k_new != nullptr && (C.flags & kItemLast) && row < 2 && sub == 0) {
         const int blk = blk_of(C.b, pos >> 4);
         const int64_t in_slab = (row == 0 ? ta.head_k : ta.head_v) + (int64_t)(pos & 15) * D + col * 8;
         const uint4 val = row == 0 ? k_row : v_row;
-        *reinterpret_cast<uint4 *>(a.pool_store + slab_base<PAGED>(ta, blk, pos >> 4) + in_slab) = val;
+        *reinterpret_cast<uint4 *>(pool_store + slab_base<PAGED>(ta, blk, pos >> 4) + in_slab) = val;
         if (a.pool_mirror) {
           const int mblk = PAGED && a.mirror_is_tail ? 2 * C.b + ((pos >> a.log2_T) & 1) : blk + (PAGED ? a.mirror_shift : 0);
           *reinterpret_cast<uint4 *>(a.pool_mirror + slab_base<PAGED>(ta, mblk, pos >> 4) + in_slab) = val;
@@ -663,11 +685,29 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
     C = N;
     ta = ta_next;
     live = true;
+    if constexpr (LAYERS) {                              // what its results, its appended rows and its refills go by
+      k_new = layers.at[layer].k_new, v_new = layers.at[layer].v_new, out = layers.at[layer].out;
+      pool_store = const_cast<uint16_t *>(pool);
+      part_o = a.part_o + (size_t)layer * layers.slots * D;
+      part_ml = a.part_ml + (size_t)layer * layers.slots * 2;
+    }
+    const uint16_t *const pool_now = pool;
     if (by_lens) {
       item = next_with_keys(item);
       has_next = item < 64;
     } else if (item + 1 < item_end) {
       ++item;
+    } else if constexpr (LAYERS) {
+      layer += gridDim.y;
+      has_next = layer < layers.count;
+      if (has_next) {
+        pair += (uint32_t)layers.pair_shift;
+        if (pair >= n_pairs) pair -= n_pairs;
+        const const_i32_ptr hp = (const_i32_ptr)(uintptr_t)(a.pair_head + pair);
+        item = hp[0], item_end = item + hp[1];
+        N.g = hp[5] >> 8;
+        pool = layers.at[layer].pool, q = layers.at[layer].q;
+      }
     } else {
       pair += n_waves;
       has_next = !by_head && pair < n_pairs;             // by head: the wavefront's own stretch is all it has
@@ -678,7 +718,7 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
     if (by_lens) {
       if (has_next) unit_from_lens(item);
     } else if (has_next) {
-      N.g = by_head ? C.g : (int)(pair % (uint32_t)G);
+      if (!LAYERS) N.g = by_head ? C.g : (int)(pair % (uint32_t)G);
       N.it = a.item_first + item;
       const const_i32_ptr dp = (const_i32_ptr)(uintptr_t)(a.item_desc + N.it);
       N.b = dp[0], N.lo = dp[1], N.hi = dp[2], N.flags = dp[3];
@@ -689,11 +729,11 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
     // The rows to append are patched into the tile in registers, so the attention does not depend on
     // reading its own store back; the store itself is issued with the results ([B]).
     const int pos = hi - 1;
-    const bool appending = a.k_new != nullptr && (C.flags & kItemLast) != 0;
+    const bool appending = k_new != nullptr && (C.flags & kItemLast) != 0;
     if (appending) {
       const size_t at = ((size_t)b * G + C.g) * LPR + col;
-      k_row = reinterpret_cast<const uint4 *>(a.k_new)[at];
-      v_row = reinterpret_cast<const uint4 *>(a.v_new)[at];
+      k_row = reinterpret_cast<const uint4 *>(k_new)[at];
+      v_row = reinterpret_cast<const uint4 *>(v_new)[at];
     }
     half8_t qb[D / 32];
 #pragma unroll
@@ -740,7 +780,7 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
         }
         __builtin_amdgcn_sched_barrier(0);    // keep the refill behind the reduce that frees it,
         if (!last) {
-          load_tile(buf[i], ta, min(ti + PIPE * NS, last_tile), next_blk[i]);
+          load_tile(buf[i], pool_now, ta, min(ti + PIPE * NS, last_tile), next_blk[i]);
           next_blk[i] = blk_of(b, min(ti + 2 * PIPE * NS, last_tile));
         }
         __builtin_amdgcn_sched_barrier(0);    // and ahead of the next tile's reduce
@@ -783,6 +823,26 @@ __global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_spli
   if (SRC == kFromHeads) w = *(const_head_ptr)(uintptr_t)(pair_head + pair);
   if (pair >= n_pairs) return;
   attn_split_body<D, PAGED, PIPE, SRC, NT, NS>(lds_all, wave, NS > 1 ? (int)wave : 0, pair, n_pairs, w, LensPlan{}, pool, q, G, H, R, v_tiles, a);
+}
+
+// The same over several layers at once, for a step whose inputs are all there: workgroup (x, y) takes the layers y, y + gridDim.y, ...
+// one after the other (layers_abreast says how many go side by side).  What a launch costs besides its bytes -- being
+// dispatched, the first tiles with nothing in flight, the wavefronts' end times -- is paid once for all of them, and a launch
+// per layer with a merge behind each becomes two in all.  Bound by HBM where the launch is long (8 layers of 403 MB: 474 us,
+// 6.8 TB/s, against 61.0 us a layer), by the chain of tiles of a wavefront where it is not; a layer's share of a step of 6 layers,
+// 24 x 190..1150 keys, 32 heads x 64: 30.0 -> 22.4 us with the merge, 19 of it the bytes.
+template <int D, bool PAGED, bool NT, int NS>
+__global__ __launch_bounds__((NS > 1 ? NS : kWavesPerBlock) * 64) void attn_split_layers_kernel(
+    const PairHead *pair_head, const int32_t n_groups, const int32_t G, const int32_t H, const int32_t R, const int32_t v_tiles,
+    const AttnArgs a, const LayerList list) {
+  __shared__ __attribute__((aligned(16))) char lds_all[NS > 1 ? NS : kWavesPerBlock][lds_region<D>()];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t pair = NS > 1 ? blockIdx.x : blockIdx.x * kWavesPerBlock + wave, n_pairs = (uint32_t)n_groups * (uint32_t)G;
+  const int32x8_t w = *(const_head_ptr)(uintptr_t)(pair_head + pair);
+  const uint16_t *pool = list.at[blockIdx.y].pool, *q = list.at[blockIdx.y].q;
+  if (pair >= n_pairs) return;
+  attn_split_body<D, PAGED, base_depth<D, NS>(), kFromHeads, NT, NS>(lds_all, wave, NS > 1 ? (int)wave : 0, pair, n_pairs, w, LensPlan{}, pool,
+                                                                     q, G, H, R, v_tiles, a, list);
 }
 
 // The launch of the entry point that knows no lengths on the host: the plan comes from the lengths (kFromLens) or from what
@@ -846,15 +906,27 @@ __global__ __launch_bounds__(most_waves_per_pair(D) * 64) void attn_split_planne
 // a sequence in at most four pieces waits for two round trips (the item range, then everything) and not for three, and
 // four (b, h) pairs share a workgroup.
 // LENS: `chunk_prefix` is the device array of lengths instead, and a sequence's pieces are where plan_from_lens puts them.
-template <int D, bool LENS>
+// MergeOuts: the results of several layers (blockIdx.z), whose partial results follow one another.
+struct MergeOuts {
+  int32_t slots;                   // as in LayerList
+  void *at[kLayersPerLaunch];
+};
+template <int D, bool LENS, typename Outs>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_prefix, const float *part_ml, const float *part_o,
-                                                          const int32_t B, const int32_t n_cls, const int32_t H, const AttnArgs a) {
+                                                          const int32_t B, const int32_t n_cls, const int32_t H, const AttnArgs a,
+                                                          const Outs outs) {
   // (leading parameters: in scalar registers when the wavefront starts, so the first look-ups need no round trip
   // to the argument segment; most wavefronts of a launch find a sequence in one piece and leave at once)
   constexpr int EPT = D / 64;
   const int lane = threadIdx.x & 63;
   const int b = blockIdx.y, h = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (h >= H) return;
+  void *out = a.out;
+  if constexpr (std::is_same<Outs, MergeOuts>::value) {
+    out = outs.at[blockIdx.z];
+    part_o += (size_t)blockIdx.z * outs.slots * D;
+    part_ml += (size_t)blockIdx.z * outs.slots * 2;
+  }
   auto row_of = [&](int it) { return part_o + ((size_t)it * H + h) * D + lane * EPT; };
   int first0, cnt0;
   if (LENS) {
@@ -940,9 +1012,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
     if (a.out_fp32)
-      reinterpret_cast<float *>(a.out)[at + e] = acc[e] * inv;
+      reinterpret_cast<float *>(out)[at + e] = acc[e] * inv;
     else
-      reinterpret_cast<_Float16 *>(a.out)[at + e] = (_Float16)(acc[e] * inv);
+      reinterpret_cast<_Float16 *>(out)[at + e] = (_Float16)(acc[e] * inv);
   }
 }
 
@@ -950,6 +1022,31 @@ template <int D, bool PAGED, int SRC, bool NT, int NS>
 void launch_split_as(const AttnArgs &args, dim3 grid, hipStream_t stream) {
   hipLaunchKernelGGL((attn_split_mfma_kernel<D, PAGED, base_depth<D, NS>(), SRC, NT, NS>), grid, dim3((NS > 1 ? NS : kWavesPerBlock) * 64), 0,
                      stream, args.pair_head, args.pool, args.q, args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args);
+}
+
+template <int D, bool PAGED, bool NT, int NS>
+void launch_layers_as(const AttnArgs &args, const LayerList &list, dim3 grid, hipStream_t stream) {
+  hipLaunchKernelGGL((attn_split_layers_kernel<D, PAGED, NT, NS>), grid, dim3((NS > 1 ? NS : kWavesPerBlock) * 64), 0, stream, args.pair_head,
+                     args.n_groups, args.G, args.H, args.R, args.gg << args.st_log2, args, list);
+}
+
+template <int D, bool PAGED, bool NT>
+void launch_layers_kept(const AttnArgs &args, const LayerList &list, int waves, dim3 grid, hipStream_t stream) {
+  if constexpr (D == 128) {
+    if (waves == 4) return launch_layers_as<D, PAGED, NT, 4>(args, list, grid, stream);
+  }
+  if (waves == 2) return launch_layers_as<D, PAGED, NT, 2>(args, list, grid, stream);
+  launch_layers_as<D, PAGED, NT, 1>(args, list, grid, stream);
+}
+
+template <int D>
+void launch_layers(const AttnArgs &args, const LayerList &list, bool paged, bool keep, int waves, dim3 grid, hipStream_t stream) {
+  if (paged)
+    keep ? launch_layers_kept<D, true, false>(args, list, waves, grid, stream)
+         : launch_layers_kept<D, true, true>(args, list, waves, grid, stream);
+  else
+    keep ? launch_layers_kept<D, false, false>(args, list, waves, grid, stream)
+         : launch_layers_kept<D, false, true>(args, list, waves, grid, stream);
 }
 
 template <int D, bool PAGED, int SRC, bool NT>
@@ -1062,23 +1159,59 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream, hipEvent_
   return hipSuccess;
 }
 
+hipError_t launch_decode_layers(const AttnLaunch &a, const DecodeLayer *layers, int32_t n_layers, hipStream_t stream) {
+  const PoolShape &s = a.shape;
+  const int R = s.G > 0 ? s.H / s.G : 0, waves = a.waves_per_pair;
+  if (n_layers < 1 || n_layers > kLayersPerLaunch || !a.pair_head || a.plan_dev || a.from_lens || a.pool_mirror || a.id_base != 0 ||
+      a.item_first != 0 || a.item_count <= 0 || a.item_count != a.batch.n_items || R < 1 || R > 16 || R * s.G != s.H ||
+      (s.D != 64 && s.D != 128) || (waves != 1 && waves != 2 && !(waves == 4 && s.D == 128)))
+    return hipErrorInvalidValue;
+  const AttnArgs args = make_args(a);
+  const int64_t pairs = (int64_t)a.n_groups * s.G, groups = (pairs + kWavesPerBlock - 1) / kWavesPerBlock;
+  if (groups > std::max<int64_t>(1, a.max_waves / kWavesPerBlock)) return hipErrorInvalidValue;
+  // a wavefront's next layer is that of the pair 0.382 of the stretches further on: stretches have the same number of tiles and
+  // not of pieces, and one that takes longer is then no wavefront's in every layer (128 x 512..4096 keys, 32 / 8 heads 791 -> 784 us a
+  // step of 4 layers, uniform lengths the same)
+  LayerList list = {};
+  list.count = n_layers, list.slots = a.batch.n_items * s.H, list.pair_shift = (int32_t)(0.382 * a.n_groups) * s.G;
+  for (int32_t l = 0; l < n_layers; ++l) list.at[l] = layers[l];
+  const dim3 grid((unsigned)(waves > 1 ? pairs : groups), (unsigned)layers_abreast(s.D, waves, n_layers));
+  if (s.D == 128)
+    launch_layers<128>(args, list, s.paged != 0, a.keep_cached != 0, waves, grid, stream);
+  else
+    launch_layers<64>(args, list, s.paged != 0, a.keep_cached != 0, waves, grid, stream);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !a.need_merge) return e;
+  MergeOuts outs = {};
+  outs.slots = list.slots;
+  for (int32_t l = 0; l < n_layers; ++l) outs.at[l] = layers[l].out;
+  const dim3 mgrid((s.H + 3) / 4, a.batch.B, n_layers);
+  if (s.D == 128)
+    hipLaunchKernelGGL((attn_merge_kernel<128, false, MergeOuts>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o,
+                       args.B, 1, args.H, args, outs);
+  else
+    hipLaunchKernelGGL((attn_merge_kernel<64, false, MergeOuts>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o,
+                       args.B, 1, args.H, args, outs);
+  return hipGetLastError();
+}
+
 hipError_t launch_merge(const AttnLaunch &a, hipStream_t stream) {
   const PoolShape &s = a.shape;
   const AttnArgs args = make_args(a);
   dim3 mgrid((s.H + 3) / 4, a.batch.B);
   if (args.lens) {
     if (s.D == 128)
-      hipLaunchKernelGGL((attn_merge_kernel<128, true>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args);
+      hipLaunchKernelGGL((attn_merge_kernel<128, true, NoLayers>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args, NoLayers{});
     else if (s.D == 64)
-      hipLaunchKernelGGL((attn_merge_kernel<64, true>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args);
+      hipLaunchKernelGGL((attn_merge_kernel<64, true, NoLayers>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args, NoLayers{});
     else
       return hipErrorInvalidValue;
     return hipGetLastError();
   }
   if (s.D == 128)
-    hipLaunchKernelGGL((attn_merge_kernel<128, false>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args);
+    hipLaunchKernelGGL((attn_merge_kernel<128, false, NoLayers>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args, NoLayers{});
   else if (s.D == 64)
-    hipLaunchKernelGGL((attn_merge_kernel<64, false>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args);
+    hipLaunchKernelGGL((attn_merge_kernel<64, false, NoLayers>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args, NoLayers{});
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

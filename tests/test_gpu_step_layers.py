@@ -1,0 +1,90 @@
+"""okv_decode_step over layers that are attended together: every output, every pool and the lengths bit for bit those of the
+calls layer by layer (which other tests hold against the fp64 oracle), over head counts with one, two and four wavefronts per
+pair, batches that are cut and batches that are not, more layers than a launch takes and than there is room for partial
+results of; and steps whose buffers make a layer depend on another, which are taken layer by layer."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import build_stack, make_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def bits(t):
+    return t.cpu().numpy().view(np.uint8)
+
+
+def same_steps(n_steps, together, **kw):
+    sts = [build_stack(**kw) for _ in range(2)]
+    L = kw["L"]
+    for step in range(n_steps):
+        q, k, v, one = make_inputs(sts[0], 813, step, sts[0].device)
+        two = [torch.full_like(o, float("nan")) for o in one]
+        sts[0].step(q, k, v, one)
+        sts[1].step_bound(sts[1].bind_step(q, k, v, two))
+        for st in sts:
+            st.synchronize()
+        assert sts[1].ctx.okv_layers_per_launch() in (together if isinstance(together, tuple) else (together,))
+        for l in range(L):
+            np.testing.assert_array_equal(bits(one[l]), bits(two[l]), err_msg=f"step {step} layer {l}")
+    for l in range(L):
+        np.testing.assert_array_equal(sts[0].read_pool(l).view(np.uint16), sts[1].read_pool(l).view(np.uint16))
+    assert sts[0].ctx.okv_get_ctx_lens().tolist() == sts[1].ctx.okv_get_ctx_lens().tolist()
+    for st in sts:
+        st.close()
+
+
+RAGGED = [1, 15, 16, 17, 31, 33, 200, 47, 0, 64, 129, 500]
+
+
+@pytest.mark.parametrize("L,H,G,d,T,ctx,out_dtype,together", [
+    (2, 8, 8, 128, 16, RAGGED, 0, 2), (3, 8, 2, 64, 16, RAGGED, 1, 3), (5, 12, 12, 64, 0, RAGGED, 0, 5),
+    (4, 16, 1, 128, 0, [700], 1, 4), (3, 64, 64, 128, 16, [33 + 3 * b for b in range(20)], 0, 3),       # one wavefront per pair
+    (3, 32, 32, 128, 64, [180 + b for b in range(24)], 0, 3), (3, 32, 32, 64, 0, [1500, 1800], 1, 3),
+    (2, 32, 32, 128, 0, [400] * 32, 0, 2),                       # a stretch a sequence: nothing to merge
+    (35, 4, 2, 64, 16, [100, 40], 0, 32),                        # more layers than a launch takes
+    (6, 128, 8, 128, 16, [90 + b % 7 for b in range(160)], 0, (3, 4)),    # room for the pieces of three or four layers
+])
+def test_same_bits_as_layer_by_layer(L, H, G, d, T, ctx, out_dtype, together):
+    print(f"L={L} H={H} G={G} d={d} T={T} B={len(ctx)} out={out_dtype}", flush=True)
+    same_steps(3, together, L=L, H=H, G=G, d=d, T=T, ctx_before=ctx, cap_tokens=max(ctx) // 64 * 64 + 128, out_dtype=out_dtype, seed=811)
+
+
+def test_a_split_size_or_host_layers_go_layer_by_layer():
+    same_steps(2, 1, L=3, H=4, G=4, d=64, T=16, ctx_before=[70, 200], cap_tokens=256, split_tokens=64, seed=3)
+    same_steps(2, 1, L=3, H=4, G=4, d=64, T=16, ctx_before=[70, 200], cap_tokens=256, on_host=[0, 1, 0], seed=3)
+    same_steps(1, 1, L=1, H=4, G=4, d=64, T=16, ctx_before=[70, 200], cap_tokens=256, seed=3)
+
+
+@pytest.mark.parametrize("how", ["one output", "output is the next query", "overlapping outputs", "output over later rows", "distinct"])
+def test_buffers_that_order_the_layers(how):
+    print(how, flush=True)
+    L, H, d, ctx = 4, 8, 64, [100, 37, 300]
+    kw = dict(L=L, H=H, G=H, d=d, T=16, ctx_before=ctx, cap_tokens=320, seed=17)
+    got = []
+    for together in (False, True):
+        st = build_stack(**kw)
+        q, k, v, out = make_inputs(st, 19, 0, st.device)
+        n = q[0].numel()
+        room = torch.zeros(4 * L * n, dtype=torch.float16, device=st.device)
+        if how == "one output":
+            out = [out[0]] * L
+        elif how == "output is the next query":
+            out = q[1:] + [out[0]]
+        elif how == "overlapping outputs":
+            out = [room[l * n // 2:][:n].view_as(q[0]) for l in range(L)]
+        elif how == "output over later rows":
+            out[0] = k[3]
+        torch.cuda.synchronize()
+        if together:
+            st.step_bound(st.bind_step(q, k, v, out))
+            st.synchronize()
+            assert st.ctx.okv_layers_per_launch() == (L if how == "distinct" else 1)
+        else:
+            st.step(q, k, v, out)
+            st.synchronize()
+        got.append([bits(t).copy() for t in out + q + k + v] + [st.read_pool(l).view(np.uint8) for l in range(L)])
+        st.close()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
