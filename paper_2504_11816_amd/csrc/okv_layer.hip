@@ -41,6 +41,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace okv {
 
@@ -463,7 +464,7 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
 // wavefronts a 16 FM x 16 FN piece each, so an operand read from LDS serves FN products and a weight FM.
 //
 //   * x goes through LDS, 64 inputs at a time (a stage), fetched by the load that writes LDS directly (16 bytes per
-//     lane, no registers), whole 128-byte lines of 8 rows per instruction; the weights go from memory straight into
+//     lane, no registers), whole 128-byte lines of 8 rows an instruction; the weights go from memory straight into
 //     the registers of the wavefronts that use them: packed, one load is one operand of the matrix instruction;
 //   * the direct loads are written as assembly because the compiler, which cannot tell the stage being
 //     written from the one being read, waits for all of them in front of every LDS read otherwise.  It does not
@@ -471,20 +472,16 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
 //   * loads retire in order, so a stage of x needs no more lead than the weights have: WD stages of both are in
 //     flight (WD + 1 LDS buffers).
 //
-// Measured (weights from HBM), before = launches of at most 192 rows of the staged kernel, each reading the weights
-// again: 1024 rows x 16384 x 4096 221 -> 114 us (1.2 PFLOP/s; the library's fp16 product of 8192 x 8192 x 8192 runs at
-// 1.49), 12288 x 4096 166 -> 92, 4096 x 4096 98 -> 41, 4096 x 16384 291 -> 130 with its share reduction; 512 rows 116 -> 68,
-// 89 -> 61, 50 -> 31, 146 -> 77.  What bounds it: with every operand in the L2s (timing builds) the same walk takes
-// 105 of the 114 us, with x packed nothing less; reading LDS a step ahead of the matrix instructions, or two
-// fragments at a time, was slower, two stages in flight instead of one 8-15 % faster.
-// The small tiles follow the bytes a compute unit takes in, about 62 KB/us with the weights coming from HBM and 77 from
-// its L2, alone on the chip as well (a stage of 96 x 128, 28 KiB: 0.47 and 0.365 us, where its matrix instructions take 0.16):
-// two or three teams of wavefronts along the inputs, or the next half stage read from LDS early, change nothing.
+// Measured (weights from HBM, warm clocks): 1024 rows x 4096 x 4096 42 us, 512 x 16384 x 4096 68, 192 x 16384 x 4096 41 (96 x
+// 128).  What bounds the small tiles: a compute unit takes in 58 KB/us once weights from HBM are among its loads, whatever the
+// mix, the depth or the wavefronts (a probe of nothing but loads: 54 from HBM alone, 130 to 150 from its L2 alone; the L1 answers
+// in order).  Two or three teams of wavefronts along the inputs, or the next half stage read from LDS early, change nothing.
 //
-// LDS layout of a stage: 16 rows x 64 inputs (8 pieces of 16 bytes a row) are 128 units.  Row rr, piece p = 2 v + ql
-// sits at unit 64 (rr & 1) + 16 (2 (v >> 1) + ql) + (rr + v) % 16: an instruction's 64 units are the eight even (odd)
-// rows with all their pieces, and an operand read (lane 16 q + rr takes piece 4 i + q of row rr) meets every
-// bank once in each of the groups of 16 lanes that the LDS serves together (see linear_lds_kernel).
+// LDS layout of a stage: row r has its 8 pieces of 16 bytes in units 8 r .. 8 r + 7, piece p in unit 8 r + (p ^ (r / 2) % 8).
+// An instruction of 64 lanes brings eight whole rows, eight lanes a line, and an operand read (lane 16 q + rr takes piece
+// 4 i + q of row rr) meets every bank once in each of the groups of 16 lanes that the LDS serves together (see
+// linear_lds_kernel).  (With the lanes of a quad on two rows x alone came in at 65 KB/us a unit; now 115.  384 rows of a
+// 4096-wide layer 226 -> 219 us, 1024 rows of a 2048-wide one 88 -> 86.)
 template <int FM, int FN, int WM, int WN, int WD>
 struct TileShape {
   static constexpr int kThreads = WM * WN * 64, kRows = 16 * FM * WM, kCols = 16 * FN * WN;
@@ -534,28 +531,26 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
     return stage0 + (t >= n_stages ? t - n_stages : t);
   };
 
-  // staging: this wavefront's instructions are kLoads * wave + j; instruction 2 f + t holds rows of parity t of fragment f
+  // staging: this wavefront's instructions are kLoads * wave + j, eight rows each
   const int row0 = mt * S::kRows, last_row = m - 1 - row0;
   const uint32_t row_bytes = (uint32_t)n_in * 2;
   uint32_t xoff[S::kLoads];
-  const uint32_t second = lane >> 5 ? 64 : 0;            // this lane fetches of the stage's second 32 inputs
+  uint32_t second[S::kLoads];
 #pragma unroll
   for (int j = 0; j < S::kLoads; ++j) {
-    const int ii = wave * S::kLoads + j, f = ii >> 1, t = ii & 1;
-    const int bank = lane & 15, ql = (lane >> 4) & 1;
-    const int v = 2 * (lane >> 5) + ((bank - t) & 1);
-    const int rr = (bank - v) & 15;
-    xoff[j] = (uint32_t)min(16 * f + rr, last_row) * row_bytes + (uint32_t)(2 * v + ql) * 16;   // rows past the batch: the last again
+    const int r = (wave * S::kLoads + j) * 8 + (lane >> 3), piece = (lane & 7) ^ ((r >> 1) & 7);
+    xoff[j] = (uint32_t)min(r, last_row) * row_bytes + (uint32_t)piece * 16;   // rows past the batch: the last again
+    second[j] = piece & 4 ? 64 : 0;                      // this lane fetches of the stage's second 32 inputs
   }
   const char *xbase = reinterpret_cast<const char *>(x) + (size_t)row0 * row_bytes;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds);
   auto stage_x = [&](int s, int buf) {
     const int st = stage_at(s);
     const char *src = xbase + (size_t)st * 128;
-    const uint32_t back = st == half_stage ? second : 0;       // a half-full stage: its first half twice (the second is never used)
     const uint32_t dst = lds0 + (uint32_t)buf * S::kStageBytes + (uint32_t)(wave * S::kLoads) * 1024;
 #pragma unroll
-    for (int j = 0; j < S::kLoads; ++j) load_to_lds(src, xoff[j] - back, dst + j * 1024);
+    for (int j = 0; j < S::kLoads; ++j)                  // (a half-full stage: its first half twice, the second is never used)
+      load_to_lds(src, xoff[j] - (st == half_stage ? second[j] : 0), dst + j * 1024);
   };
   // weights: FN runs of 1 KiB per 32 inputs (a tile past the last one streams the last one and is never stored)
   const int tile0 = (group * WN + wn) * FN;
@@ -571,7 +566,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
   const int rr = lane & 15, q = lane >> 4;
   int xunit[2];                                          // where this lane's piece of 32 inputs i of fragment 0 sits in a stage
 #pragma unroll
-  for (int i = 0; i < 2; ++i) xunit[i] = 64 * (rr & 1) + 16 * (2 * i + (q & 1)) + ((rr + 2 * i + (q >> 1)) & 15);
+  for (int i = 0; i < 2; ++i) xunit[i] = 8 * rr + ((4 * i + q) ^ ((rr >> 1) & 7));
 
   floatx4 acc[FM][FN];
 #pragma unroll
@@ -659,6 +654,225 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
     for (int k = 0; k < FN; ++k) {
       const int o = k * 64 + lane, r = o / (2 * FN), pc = o % (2 * FN);
       const int mrow = row0 + (wm * FM + 2 * c) * 16 + r, n = tile0 * 16 + pc * 8;
+      const float4 *t = reinterpret_cast<const float4 *>(mine + r * S::kOutStride + pc * 8);
+      const float4 t0 = t[0], t1 = t[1];
+      if (mrow >= m || n >= a.n_out) continue;
+      if (to_shares) {
+        float4 *dst = reinterpret_cast<float4 *>(a.shares + ((size_t)cut * m + mrow) * a.n_out + n);
+        dst[0] = t0;
+        dst[1] = t1;
+      } else {
+        store_eight(a, mrow, n, t0, t1);
+      }
+    }
+  }
+}
+
+// ---- the largest tiles: weights through LDS as well ----------------------------------------------
+//
+// With two rows of wavefronts the kernel above loads every weight twice, which with 256 x 256 or 192 x 128 tiles is a third to two
+// fifths of all a compute unit takes in.  Here the weights go through LDS like x, half a stage (32 inputs, one operand of the
+// matrix instruction, 1 KiB a piece) at a time, and every byte comes in once.  Nothing in the walk loads into registers, so the
+// waits written here are the only ones and are exact.  A wavefront reads FM / 2 fragments of x ahead of its matrix instructions
+// and the next half stage's weights under them; one barrier per half stage, in its middle: behind it the next half stage is in
+// LDS and the buffers of the one before are free, so the reads ahead go on across half stages.
+//
+// What bounds it: 256 x 256 the matrix cores and LDS beside them (1024 rows x 16384 x 4096 1.2 PFLOP/s; with nothing loaded
+// 1.45), 192 x 128 what a compute unit takes in.  us, the kernel above with the same tiles -> this one: 256 x 256, 1024 x 16384 x 4096
+// 119 -> 114.5 and 4096 x 16384 in four cuts 136 -> 129; 192 x 128, 384 x 12288 x 4096 54 -> 49 (96 x 128 above: 59), 192 x 4096 x 16384
+// in eight cuts 45 -> 40.  Not for the other forms: 128 x 256 is 4 % slower so, 128 x 128 9 %, the smallest 10 %, whose walk is
+// the latency of a half stage (two barriers a stage); 256 x 192, whose pieces do not come out even, 2 %.  Four wavefronts of 128 x 128,
+// whole stages of weights, nontemporal weights and more stages in flight change nothing.
+template <int FM, int FN, int WM, int WN, int NX>
+struct WideShape {
+  static constexpr int kWaves = WM * WN, kThreads = kWaves * 64, kRows = 16 * FM * WM, kCols = 16 * FN * WN;
+  static constexpr int kXBuffers = NX, kWBuffers = 2 * NX - 2;        // stages of x, half stages of weights
+  static constexpr int kXBytes = kRows * 128, kWBytes = kCols * 64;
+  static constexpr int kAhead = FM / 2;                  // fragments of x a wavefront reads ahead; the barrier is as far into a half stage
+  // loads of a wavefront: LX per stage of x; of the half stage's FN WN pieces of weights LW, and one less where the
+  // pieces do not come out even and the wavefront is past the first kMore
+  static constexpr int LX = kRows / 8 / kWaves, LW = (FN * WN + kWaves - 1) / kWaves, kMore = FN * WN - (LW - 1) * kWaves;
+  // How many loads a wavefront with lw pieces may have outstanding for the next half stage to have landed: those issued after its last one,
+  // which are kWBuffers - 3 half stages of weights and the stages of x among them (one more in front of an odd half)
+  static constexpr int outstanding(int lw, int odd) { return (kWBuffers - 3) * lw + (kWBuffers - (odd ? 2 : 4)) / 2 * LX; }
+  static constexpr int first(int lw) { return (kWBuffers - 2) * lw + (kXBuffers - 2) * LX; }        // and in front of the first half stage
+  static constexpr int kOutStride = 16 * FN + 4;         // floats between two rows of a wavefront's results in LDS
+  static constexpr int kOutBytes = kWaves * 32 * kOutStride * 4;
+  static constexpr int kStageBytes = kXBuffers * kXBytes + kWBuffers * kWBytes;
+  static constexpr int kLds = kStageBytes > kOutBytes ? kStageBytes : kOutBytes;
+  static_assert(FM % 2 == 0 && NX >= 3 && kRows % (8 * kWaves) == 0, "fragments and staging instructions come out even");
+  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+  static_assert(outstanding(LW, 1) <= 63 && first(LW) <= 63, "the wait for a half stage must fit the load counter");
+};
+
+// A barrier that does not wait for this wavefront's reads from LDS (__syncthreads does): what they read is not overwritten behind it.
+__device__ __forceinline__ void barrier_leaving_reads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <int FM, int FN, int WM, int WN, int NX>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1, 2))) void linear_wide_kernel(
+    const uint4 *w, const uint4 *x, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
+    const int32_t n_tiles, const int32_t m_tiles, const int32_t n_groups, const LinearArgs a) {
+  using S = WideShape<FM, FN, WM, WN, NX>;
+  constexpr int kXB = S::kXBuffers, kWB = S::kWBuffers, kAhead = S::kAhead;
+  __shared__ __attribute__((aligned(1024))) char lds[S::kLds];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  // Workgroups are dealt to the 8 XCDs in rotation; tiles that share weights (all row tiles of a feature group)
+  // and neighbouring groups are put on the same XCD, whose L2 then reads them from memory once.
+  const int total = gridDim.x, xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
+  const int tile = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
+  const int mt = tile % m_tiles, group = (tile / m_tiles) % n_groups, cut = tile / (m_tiles * n_groups);
+  // This workgroup's stages of 64 inputs.  Where the inputs are an odd number of blocks of 32, the very last stage is
+  // half full: it is the last one walked by the cut that has it (no shift of the walk then).
+  const int all_stages = (n_kb + 1) >> 1, stage0 = (int)((int64_t)cut * all_stages / splits);
+  const int n_stages = (int)((int64_t)(cut + 1) * all_stages / splits) - stage0;
+  const int half_stage = n_kb & 1 ? all_stages - 1 : -1;
+  const int full_stages = n_stages - (stage0 + n_stages - 1 == half_stage ? 1 : 0);
+  const int rot = m_tiles == 1 && half_stage < 0 ? (int)(((unsigned)group * 5u + (unsigned)cut * 3u) % (unsigned)n_stages) : 0;
+  auto stage_at = [&](int s) {                           // position in this workgroup's walk -> stage; past the end: the last again
+    const int t = min(s, n_stages - 1) + rot;
+    return stage0 + (t >= n_stages ? t - n_stages : t);
+  };
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds);
+  constexpr uint32_t kW0 = kXB * S::kXBytes;             // where the weights begin
+
+  // x: this wavefront's instructions are LX * wave + j, eight rows each
+  const int row0 = mt * S::kRows, last_row = m - 1 - row0;
+  const uint32_t row_bytes = (uint32_t)n_in * 2;
+  uint32_t xoff[S::LX], second[S::LX];
+#pragma unroll
+  for (int j = 0; j < S::LX; ++j) {
+    const int r = (wave * S::LX + j) * 8 + (lane >> 3), piece = (lane & 7) ^ ((r >> 1) & 7);
+    xoff[j] = (uint32_t)min(r, last_row) * row_bytes + (uint32_t)piece * 16;   // rows past the batch: the last again
+    second[j] = piece & 4 ? 64 : 0;                      // this lane fetches of the stage's second 32 inputs
+  }
+  const char *xbase = reinterpret_cast<const char *>(x) + (size_t)row0 * row_bytes;
+  auto stage_x = [&](int s, int buf) {
+    const int st = stage_at(s);
+    const char *src = xbase + (size_t)st * 128;
+    const uint32_t dst = lds0 + (uint32_t)buf * S::kXBytes + (uint32_t)(wave * S::LX) * 1024;
+#pragma unroll
+    for (int j = 0; j < S::LX; ++j)                      // (a half-full stage: its first half twice, the second is never used)
+      load_to_lds(src, xoff[j] - (st == half_stage ? second[j] : 0), dst + j * 1024);
+  };
+  // weights: instructions wave, wave + kWaves, ... of a half stage, a tile each (past the last one: the last again, never stored)
+  const int tile0 = group * (FN * WN);
+  uint32_t woff[S::LW];
+#pragma unroll
+  for (int j = 0; j < S::LW; ++j)
+    woff[j] = (uint32_t)min(wave + j * S::kWaves, n_tiles - 1 - tile0) * (uint32_t)n_kb * 1024 + lane * 16;
+  const char *wbase = reinterpret_cast<const char *>(w) + (size_t)tile0 * n_kb * 1024;
+  const bool more = S::kMore == S::kWaves || wave < S::kMore;          // has LW pieces of a half stage
+  auto stage_w = [&](int h, int buf) {
+    const char *src = wbase + (size_t)min(2 * stage_at(h >> 1) + (h & 1), n_kb - 1) * 1024;
+    const uint32_t dst = lds0 + kW0 + (uint32_t)buf * S::kWBytes + (uint32_t)wave * 1024;
+#pragma unroll
+    for (int j = 0; j < S::LW; ++j)
+      if (j < S::LW - 1 || more) load_to_lds(src, woff[j], dst + j * S::kWaves * 1024);
+  };
+  auto landed = [&](auto odd) {                          // the next half stage: this wavefront's share of it
+    constexpr int O = decltype(odd)::value;
+    if (more) __builtin_amdgcn_s_waitcnt(vmcnt_only(S::outstanding(S::LW, O)));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_only(S::outstanding(S::LW - 1, O)));
+  };
+
+  const int rr = lane & 15, q = lane >> 4;
+  uint32_t xunit[2];                                     // where this lane's piece of 32 inputs i of fragment 0 sits in a stage
+#pragma unroll
+  for (int i = 0; i < 2; ++i) xunit[i] = 16 * (wm * FM * 128 + 8 * rr + ((4 * i + q) ^ ((rr >> 1) & 7)));
+  const uint32_t wunit = kW0 + (uint32_t)(wn * FN) * 1024 + lane * 16;
+  auto read_x = [&](int buf, int j) -> uint4 {           // fragment j % FM of half j / FM
+    return *reinterpret_cast<const uint4 *>(lds + (uint32_t)buf * S::kXBytes + xunit[j / FM] + (j % FM) * 2048);
+  };
+  auto read_w = [&](int buf, int fn) -> uint4 {
+    return *reinterpret_cast<const uint4 *>(lds + (uint32_t)buf * S::kWBytes + wunit + fn * 1024);
+  };
+  floatx4 acc[FM][FN];
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = floatx4{0.f, 0.f, 0.f, 0.f};
+  uint4 xf[kAhead], wf[2][FN];                           // fragments of x read ahead (fragment j in j % kAhead), weights of two halves
+
+#pragma unroll
+  for (int h = 0; h < kWB - 1; ++h) {                    // (in the order the walk goes on in)
+    if (h == 0) stage_x(0, 0);
+    if (h % 2 == 1) stage_x((h + 1) / 2, (h + 1) / 2);
+    stage_w(h, h);
+  }
+  if (more) __builtin_amdgcn_s_waitcnt(vmcnt_only(S::first(S::LW)));
+  else __builtin_amdgcn_s_waitcnt(vmcnt_only(S::first(S::LW - 1)));
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) xf[j] = read_x(0, j);
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn) wf[0][fn] = read_w(0, fn);
+  int xb = 0, xfill = kXB - 1, wnext = 1, wfill = kWB - 1;     // buffers: this stage, to fill; the next half's weights, to fill
+  for (int s = 0; s < full_stages; ++s) {
+    const int xn = xb + 1 == kXB ? 0 : xb + 1;
+    auto half = [&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+#pragma unroll
+      for (int j0 = 0; j0 < FM; ++j0) {
+        if (j0 == kAhead) {
+          __builtin_amdgcn_sched_barrier(0);
+          landed(i_);
+          barrier_leaving_reads();
+          __builtin_amdgcn_sched_barrier(0);
+          if (i == 0) {
+            stage_x(s + kXB - 1, xfill);
+            xfill = xfill + 1 == kXB ? 0 : xfill + 1;
+          }
+          stage_w(2 * s + i + kWB - 1, wfill);
+          wfill = wfill + 1 == kWB ? 0 : wfill + 1;
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const int j = i * FM + j0;
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn) acc[j0][fn] = mfma32(wf[i][fn], xf[j % kAhead], acc[j0][fn]);
+        xf[j % kAhead] = j + kAhead < 2 * FM ? read_x(xb, j + kAhead) : read_x(xn, j + kAhead - 2 * FM);
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn)
+          if (j0 >= kAhead && fn * (FM - kAhead) / FN == j0 - kAhead) wf[i ^ 1][fn] = read_w(wnext, fn);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wnext = wnext + 1 == kWB ? 0 : wnext + 1;
+    };
+    half(std::integral_constant<int, 0>{});
+    half(std::integral_constant<int, 1>{});
+    xb = xn;
+  }
+  if (full_stages < n_stages) {                          // a half-full last stage: in LDS already, as its first fragments are in registers
+#pragma unroll
+    for (int j = 0; j < FM; ++j) {
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn) acc[j][fn] = mfma32(wf[0][fn], xf[j % kAhead], acc[j][fn]);
+      if (j + kAhead < FM) xf[j % kAhead] = read_x(xb, j + kAhead);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(0));             // nothing may still be on its way into LDS
+  __syncthreads();
+
+  // Results: acc[fm][fn][r] is row 16 fm + lane % 16, feature 16 fn + 4 (lane / 16) + r of the wavefront's piece.  They pass
+  // through LDS that belongs to the wavefront, 32 rows at a time, and leave as 16-byte pieces of whole rows.
+  float *mine = reinterpret_cast<float *>(lds) + wave * 32 * S::kOutStride;
+  const bool to_shares = splits > 1 || a.to_shares;
+#pragma unroll
+  for (int c = 0; c < FM / 2; ++c) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn)
+        *reinterpret_cast<floatx4 *>(mine + (16 * h + rr) * S::kOutStride + 16 * fn + 4 * q) = acc[2 * c + h][fn];
+#pragma unroll
+    for (int k = 0; k < FN; ++k) {
+      const int o = k * 64 + lane, r = o / (2 * FN), pc = o % (2 * FN);
+      const int mrow = row0 + (wm * FM + 2 * c) * 16 + r, n = (tile0 + wn * FN) * 16 + pc * 8;
       const float4 *t = reinterpret_cast<const float4 *>(mine + r * S::kOutStride + pc * 8);
       const float4 t0 = t[0], t1 = t[1];
       if (mrow >= m || n >= a.n_out) continue;
@@ -933,19 +1147,21 @@ hipError_t launch_linear_mf(const LinearArgs &args, int n_tiles, bool fast, int 
   return hipGetLastError();
 }
 
-// The forms linear_tile_kernel is built in, with what a stage of 64 inputs takes a workgroup when every compute unit
-// has one (us, measured on MI355X with the weights coming from HBM: 1024 rows x 16384 x 4096 for 256 x 256, 1024 x 12288 x
-// 4096 for 256 x 192, 512 x 16384 x 4096 for 128 x 256, 1024 x 4096 x 4096 for 128 x 128, 4224- and 1056-wide
-// products for the small ones), and whether a compute unit has room for more than one.  Wavefronts side by side in
-// the rows (2 x 4) load every weight twice, which the widest forms need to keep their accumulators in registers; at 128
-// rows and below one row of wavefronts measured faster (128 x 128 at 1024 x 4096 x 4096: 41 us as 1 x 4, 47 as 2 x 2).
+// The forms linear_tile_kernel and linear_wide_kernel (256 x 256, 192 x 128) are built in, with what a stage of 64 inputs takes a
+// workgroup when every compute unit has one (us, MI355X, weights from HBM) and whether a compute unit has room for more.
+// Fitted, with the constants of tile_plan, to 260 shapes of 129 to 1024 rows, 512 to 20480 features and inputs, every form and
+// cut within 30 % of the best timed on each: what they choose is 1.5 % slower than the fastest on average, 25 % at worst.
+// Wavefronts side by side in the rows (2 x 4) load every weight twice in linear_tile_kernel, which 256 x 192 needs to keep its
+// accumulators in registers; at 128 rows and below one row of wavefronts measured faster (128 x 128 at 1024 x 4096 x 4096: 41 us as 1 x 4,
+// 47 as 2 x 2).
 struct TileForm {
   int rows, cols;
   double stage_us;
   bool shares_cu;
 };
-constexpr TileForm kTileForms[] = {{256, 256, 1.55, false}, {256, 192, 1.24, false}, {128, 256, 0.83, false}, {128, 128, 0.52, true},
-                                   {96, 128, 0.41, true},   {64, 128, 0.40, true},   {64, 64, 0.22, true},    {32, 64, 0.17, true}};
+constexpr TileForm kTileForms[] = {{256, 256, 1.442, false}, {256, 192, 1.23, false}, {128, 256, 0.825, false}, {192, 128, 0.7245, false}, {128, 128, 0.5305, true},
+                                   {96, 128, 0.416, true},   {64, 128, 0.374, true},  {64, 64, 0.2256, true},   {32, 64, 0.164, true}};
+constexpr int kWideRows = 1024;          // rows up to which 192 x 128 was timed and is taken
 constexpr int kTileFormCount = sizeof(kTileForms) / sizeof(kTileForms[0]);
 
 template <int F, int FM, int FN, int WM, int WN, int WD>
@@ -957,16 +1173,26 @@ void launch_tile_as(const LinearArgs &a, hipStream_t stream) {
                      a.n_kb, a.splits, a.n_in, a.m, a.n_tiles, m_tiles, groups, a);
 }
 
+template <int F, int FM, int FN, int WM, int WN, int NX>
+void launch_wide_as(const LinearArgs &a, hipStream_t stream) {
+  using S = WideShape<FM, FN, WM, WN, NX>;
+  static_assert(kTileForms[F].rows == S::kRows && kTileForms[F].cols == S::kCols, "the model's form is the kernel's");
+  const int m_tiles = (a.m + S::kRows - 1) / S::kRows, groups = (a.n_out + S::kCols - 1) / S::kCols;
+  hipLaunchKernelGGL((linear_wide_kernel<FM, FN, WM, WN, NX>), dim3(m_tiles * groups * a.splits), dim3(S::kThreads), 0, stream, a.w, a.x,
+                     a.n_kb, a.splits, a.n_in, a.m, a.n_tiles, m_tiles, groups, a);
+}
+
 hipError_t launch_linear_tile(const LinearArgs &a, int form, hipStream_t stream) {
   switch (form) {
-    case 0: launch_tile_as<0, 8, 4, 2, 4, 2>(a, stream); break;
+    case 0: launch_wide_as<0, 8, 4, 2, 4, 3>(a, stream); break;
     case 1: launch_tile_as<1, 8, 3, 2, 4, 2>(a, stream); break;
     case 2: launch_tile_as<2, 8, 2, 1, 8, 2>(a, stream); break;
-    case 3: launch_tile_as<3, 8, 2, 1, 4, 4>(a, stream); break;
-    case 4: launch_tile_as<4, 6, 2, 1, 4, 4>(a, stream); break;
-    case 5: launch_tile_as<5, 4, 2, 1, 4, 4>(a, stream); break;
-    case 6: launch_tile_as<6, 4, 1, 1, 4, 4>(a, stream); break;
-    case 7: launch_tile_as<7, 2, 1, 1, 4, 4>(a, stream); break;
+    case 3: launch_wide_as<3, 6, 2, 2, 4, 4>(a, stream); break;
+    case 4: launch_tile_as<4, 8, 2, 1, 4, 4>(a, stream); break;
+    case 5: launch_tile_as<5, 6, 2, 1, 4, 4>(a, stream); break;
+    case 6: launch_tile_as<6, 4, 2, 1, 4, 4>(a, stream); break;
+    case 7: launch_tile_as<7, 4, 1, 1, 4, 4>(a, stream); break;
+    case 8: launch_tile_as<8, 2, 1, 1, 4, 4>(a, stream); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();
@@ -995,9 +1221,9 @@ struct LinearPlan {
 // Examples on 256 compute units: 12288 x 4096 -> 3 wavefronts, no cut (256 workgroups); 6144 x 4096 -> 3
 // wavefronts, 2 cuts; 4096 x 4096 and 4096 x 16384 -> 4 wavefronts, 4 cuts; 16384 x 4096 -> 4, none.
 // Cuts 0: not a shape for the staged kernel.  `us` is the plan's time from 129 rows on, where the tile kernel is the
-// alternative: 4.4 us, the weights at 7.4 MB/us, the rows of x that a compute unit takes in at 89 KB/us (64 where they
-// are 16384 inputs apart: rows at multiples of 32 KiB share the memory channels) and for a cut 2.2 us and the shares at
-// 2.7 MB/us.  (700 shapes of 129 to 192 rows, 512 to 16384 features and inputs, weights from HBM: within 5 % rms.)
+// alternative: 3.9 us, the weights at 7.7 MB/us, the rows of x that a compute unit takes in at 71.5 KB/us (60 where they
+// are 16384 inputs apart: rows at multiples of 32 KiB share the memory channels) and for a cut 2.5 us and the shares at
+// 4.4 MB/us.  (60 shapes of 129 to 192 rows, 512 to 20480 features and inputs, weights from HBM, warm clocks: within 4.6 % rms.)
 LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
   LinearPlan plan = {LinearPlan::kStaged, 4, 0, 0, 0.0};
   if (m > OKV_LINEAR_MAX_ROWS_STAGED) return plan;
@@ -1023,17 +1249,17 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
         plan.waves = w;
         plan.cuts = s;
         const double intake_kb = (double)rounds * m * (n_in / s) * 2 / 1e3;
-        plan.us = 4.4 + weight_mb / 7.4 + intake_kb / (n_in % 16384 ? 89.0 : 64.0) + (s > 1 ? 2.2 + (double)s * m * n_out * 4 / 2.7e6 : 0.0);
+        plan.us = 3.9 + weight_mb / 7.7 + intake_kb / (n_in % 16384 ? 71.5 : 60.0) + (s > 1 ? 2.5 + (double)s * m * n_out * 4 / 4.4e6 : 0.0);
       }
     }
   }
   return plan;
 }
 
-// The tile kernel's form and cuts: 4 us for the launch, the weights at 12 MB/us (the part of their way from HBM that
-// the walk does not hide: the same tiles take 6-12 us longer with 134 MB of weights than with 33), the walk, and for a
-// cut 3.5 us and the shares at 5 MB/us (written and read back).  Forms of which a compute unit holds several
-// workgroups are taken half way between whole and broken rounds.  (`us` of a cut counts the shares at 2.8 MB/us, which is
+// The tile kernels' form and cuts: 4 us for the launch, the weights at 19.4 MB/us (the part of their way from HBM that
+// the walk does not hide), the walk, and for a cut 2.8 us and the shares at 4.7 MB/us (written and read back); a launch that
+// leaves compute units idle walks up to 8 % faster, and a cut has to be worth 1 %.  Forms of which a compute unit holds several
+// workgroups are taken half way between whole and broken rounds.  (`us` of a cut counts the shares at 3.4 MB/us, which is
 // what they take at 129 to 192 rows, where it is compared with the staged kernel's.)
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
@@ -1042,15 +1268,17 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
   double best = 0;
   for (int f = 0; f < kTileFormCount; ++f) {
     const TileForm &form = kTileForms[f];
+    if (form.rows == 192 && m > kWideRows) continue;
     const int64_t tiles = (int64_t)((m + form.rows - 1) / form.rows) * ((n_out + form.cols - 1) / form.cols);
     for (int s = 1; s <= 8; ++s) {
       if (s > 1 && (stages / s < 4 || (int64_t)s * m * n_out * 4 > workspace_bytes)) break;
       const double q = (double)(tiles * s) / n_cus, whole = std::ceil(q);
       const double rounds = form.shares_cu ? 0.5 * (whole + std::max(1.0, q)) : whole;
-      double t = 4.0 + weight_mb / 12.0 + rounds * ((stages + s - 1) / s) * form.stage_us;
+      double t = 4.0 + weight_mb / 19.4 + rounds * ((stages + s - 1) / s) * form.stage_us * (1.0 - 0.08 * (1.0 - std::min(1.0, q)));
       const double shares_mb = s > 1 ? (double)s * m * n_out * 4 / 1e6 : 0.0;
-      if (s > 1) t += 3.5 + shares_mb / 5.0;
-      if (plan.cuts == 0 || t < best) best = t, plan.us = t + 0.16 * shares_mb, plan.form = f, plan.cuts = s;
+      if (s > 1) t += 2.8 + shares_mb / 4.7;
+      const double us = t + 0.084 * shares_mb, counts = m <= OKV_LINEAR_MAX_ROWS_STAGED ? us : t, worth = s > 1 ? counts + 0.01 * t : counts;
+      if (plan.cuts == 0 || worth < best) best = worth, plan.us = us, plan.form = f, plan.cuts = s;
     }
   }
   return plan;
@@ -1060,9 +1288,8 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
 // where it takes the shape (12288 x 4096 at 128 rows 28 us against the tile kernel's 31, 16384 x 4096 35 against 38; where the
 // inputs are many the tile kernel would win, 4096 x 16384 at 128 rows 35 against 43, with twice the cuts and so twice the
 // workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
-// for (4096 x 16384 at 192 rows: 46 us against 53, tiles; 12288 x 4096 39 against 37, 2304 x 4096 17.7 against 15.2 and 6144 x 2048
-// 20.2 against 17.0, staged; of the 700 shapes above 4 run more than 2 % slower than the staged kernel would, the worst
-// 7 %), beyond always the tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
+// for (at 192 rows 4096 x 16384 40 us against 53 and 16384 x 4096 41 against 44, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
+// 20.2 against 17.0, staged), beyond always a tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
 // workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront: 4224 x 1056 takes it 7.6 us
 // at 32 rows, 11.6 at 64 and 17.9 at 128, the tile kernel 7.2, 9.0 and 8.9; at 1056 x 1056 and 32 rows 4.6 against 6.2.
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
@@ -1072,7 +1299,7 @@ LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, 
   const bool staged_runs = staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes);
   if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return staged;
   const LinearPlan tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
-  if (staged_runs) return tile.us < 0.95 * staged.us ? tile : staged;
+  if (staged_runs) return tile.us < 0.955 * staged.us ? tile : staged;
   if (m > OKV_LINEAR_MAX_ROWS) return tile;
   const double simple_us = 2.0 + n_in / 128.0 * (0.09 + 0.12 * ((m + 15) / 16)) * std::max(1.0, n_out / 16 / (0.5 * n_cus));
   return tile.us < simple_us ? tile : simple;
