@@ -35,7 +35,8 @@
 //   * up to 8 rows, and some shapes the fast kernel does not take (input dimension not a multiple
 //     of 256), run the simple kernel: a workgroup per 16 features, its wavefronts split the
 //     inputs and add up through LDS, x by gather;
-//   * with hundreds of rows the matrix cores and what feeds them bound the product: linear_tile_kernel.
+//   * with hundreds of rows the matrix cores and what feeds them bound the product: linear_tile_kernel, and
+//     linear_wide_kernel for the largest tiles.
 #include "okv_kernels.h"
 #include "okv_layer.h"
 
@@ -73,51 +74,84 @@ constexpr int lin_depth() {
 struct LinearArgs {
   const uint4 *x;          // [m][n_in] fp16, as 16-byte pieces
   const uint4 *w;          // packed weights
-  const _Float16 *bias, *residual;
+  // (the next twelve, what Sink takes, in the order in which they come by eight and four words: a load of three words is
+  // one of four, and the wavefront then waits for it before it uses the fourth register again)
   _Float16 *out[3];
-  int32_t m, n_in, n_kb, relu;
+  const _Float16 *residual;
+  float *shares;                    // several cuts or a layer norm to follow: [splits][m][n_out] fp32
+  int32_t n_out, to_shares;         // the kernel writes shares
   int32_t seg0_cols, seg_cols;      // width of the first output tensor, of the others (multiples of 16)
-  int32_t n_tiles, n_out, splits;   // fast path: 16-feature tiles, cuts of the input dimension
-  float *shares;                    // fast path, splits > 1 or a layer norm to follow: [splits][m][n_out] fp32
-  int32_t to_shares;                // fast path: write the share even when there is a single cut
+  int32_t relu, m;
+  const _Float16 *bias;
+  int32_t n_in, n_kb, n_tiles, splits;   // blocks of 32 inputs, 16-feature tiles, cuts of the input dimension
   const _Float16 *ln_gamma, *ln_beta;
   _Float16 *ln_out;                 // layer norm of the result, or NULL
   float ln_eps;
 };
 
-// Feature n of row mrow lands in output tensor `seg` at element `at` (the tensors are [m][their width]).
-__device__ __forceinline__ void seg_of(const LinearArgs &a, int mrow, int n, int &seg, size_t &at) {
-  if (n < a.seg0_cols) {
-    seg = 0;
-    at = (size_t)mrow * a.seg0_cols + n;
-  } else {
-    const int r = n - a.seg0_cols;
-    seg = 1 + r / a.seg_cols;
-    at = (size_t)mrow * a.seg_cols + (r - (seg - 1) * a.seg_cols);
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+
+// Where a product's results go and what is added to them: the part of the arguments that the end of a kernel needs.
+//
+// The end of a product kernel is a chain of waits that nothing hides: every workgroup is there at the same time and has
+// nothing else to do.  So these arguments are read while the first weights are on their way (`arrive`, without which the
+// compiler reads them where they are used, after the last barrier), the output tensor is chosen by comparisons (an indexed
+// pointer becomes a load), and the bias and the residual of all of a thread's results are asked for together before the first is
+// stored (a load behind a store waits for that store).  us before -> now: 1024 rows x 4096 x 4096 with a residual 50.3 -> 43.3, 192
+// x 16384 x 4096 46.0 -> 44.5, 4 x 4096 x 4096 7.5 -> 7.0; the products of 8 layers 1056 wide at 64 rows 311 -> 281, 768 wide at 512
+// rows 310 -> 283; the kernels that add the shares up, 1024 rows x 4096 in four cuts 15.9 -> 13.5.
+struct Sink {
+  uint64_t out0, out1, out2, residual, shares;
+  int32_t n_out, to_shares, seg0_cols, seg_cols, relu, m;
+
+  __device__ __forceinline__ explicit Sink(const LinearArgs &a)
+      : out0((uint64_t)a.out[0]), out1((uint64_t)a.out[1]), out2((uint64_t)a.out[2]), residual((uint64_t)a.residual), shares((uint64_t)a.shares),
+        n_out(a.n_out), to_shares(a.to_shares), seg0_cols(a.seg0_cols), seg_cols(a.seg_cols), relu(a.relu), m(a.m) {}
+  __device__ __forceinline__ void arrive() const {
+    asm volatile("" ::"s"(out0), "s"(out1), "s"(out2), "s"(residual), "s"(seg0_cols), "s"(seg_cols), "s"(relu), "s"(m));
   }
+  __device__ __forceinline__ void shares_arrive() const { asm volatile("" ::"s"(shares), "s"(n_out), "s"(to_shares)); }
+  // Feature n of row mrow lands in the output tensor at `out`, at byte `at` (the tensors are [m][their width]).
+  __device__ __forceinline__ void place(int mrow, int n, uint64_t &out, uint64_t &at) const {
+    const int r = n - seg0_cols;
+    const bool first = r < 0, third = r >= seg_cols;
+    out = first ? out0 : third ? out2 : out1;
+    at = 2 * ((uint64_t)mrow * (uint32_t)(first ? seg0_cols : seg_cols) + (uint32_t)(first ? n : third ? r - seg_cols : r));
+  }
+};
+
+template <class T>
+__device__ __forceinline__ T load_at(uint64_t p) {
+  return *(const __attribute__((address_space(1))) T *)p;
+}
+template <class T>
+__device__ __forceinline__ void store_at(uint64_t p, T v) {
+  *(__attribute__((address_space(1))) T *)p = v;
 }
 
 // Epilogue for eight neighbouring features n .. n + 7 of row mrow: bias, ReLU, residual, one rounding, one 16-byte store.
-// (Feature counts and segment widths are multiples of 16, so a group of eight never straddles a segment.)
-__device__ __forceinline__ void store_eight(const LinearArgs &a, int mrow, int n, const float4 t0, const float4 t1) {
-  const float v[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
-  int seg;
-  size_t at;
-  seg_of(a, mrow, n, seg, at);
-  uint4 bb = make_uint4(0u, 0u, 0u, 0u), rb = bb;
-  if (a.bias) bb = *reinterpret_cast<const uint4 *>(a.bias + n);
-  if (a.residual) rb = *reinterpret_cast<const uint4 *>(a.residual + at);
-  const _Float16 *bp = reinterpret_cast<const _Float16 *>(&bb), *rp = reinterpret_cast<const _Float16 *>(&rb);
-  uint4 yo;
-  _Float16 *yp = reinterpret_cast<_Float16 *>(&yo);
+// (Feature counts and segment widths are multiples of 16, so a group of eight never straddles a segment.)  The residual is
+// asked for by residual_eight, before.
+__device__ __forceinline__ u32x4_t residual_eight(const Sink &sink, int mrow, int n) {
+  if (!sink.residual) return u32x4_t{0u, 0u, 0u, 0u};
+  uint64_t out, at;
+  sink.place(mrow, n, out, at);
+  return load_at<u32x4_t>(sink.residual + at);
+}
+__device__ __forceinline__ void store_eight(const Sink &sink, int mrow, int n, const floatx4 t0, const floatx4 t1, const half8 bias, const half8 residual) {
+  const float v[8] = {t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
+  half8 yo;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    float y = v[e] + (float)bp[e];
-    if (a.relu) y = fmaxf(y, 0.f);
-    y += (float)rp[e];
-    yp[e] = (_Float16)y;
+    float y = v[e] + (float)bias[e];
+    if (sink.relu) y = fmaxf(y, 0.f);
+    y += (float)residual[e];
+    yo[e] = (_Float16)y;
   }
-  *reinterpret_cast<uint4 *>(a.out[seg] + at) = yo;
+  uint64_t out, at;
+  sink.place(mrow, n, out, at);
+  store_at(out + at, __builtin_bit_cast(u32x4_t, yo));
 }
 
 __device__ __forceinline__ floatx4 mfma16(const uint2 a, const uint2 b, floatx4 c) {
@@ -137,7 +171,6 @@ __device__ __forceinline__ floatx4 mfma32(const uint4 a, const uint4 b, floatx4 
 // 23.8.)  Not for matrices below these sizes, which a small model may keep cached (2048 x 2048 at 4 rows: 3.8 us kept, 4.6
 // not), nor beyond 128 rows, where row tiles share a weight or the time follows x (4096 x 16384 at 192 rows: 48.9 -> 50.9;
 // 33 MB matrices lose from 64 rows on: 4096 x 4096 at 128 rows 15.9 -> 17.9).
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 template <bool NT>
 __device__ __forceinline__ uint4 load_weight(const uint4 *p) {
   if constexpr (NT) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)));
@@ -146,8 +179,9 @@ __device__ __forceinline__ uint4 load_weight(const uint4 *p) {
 constexpr int64_t kStreamSimpleBytes = 32 << 20, kStreamStagedBytes = 64 << 20;
 
 template <int MF, bool NT>
-__global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, const uint4 *x, const int32_t n_kb,
-                                                                   const int32_t n_in, const int32_t m, const LinearArgs a) {
+__global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, const uint4 *x, const _Float16 *bias,
+                                                                   const int32_t n_kb, const int32_t n_in, const int32_t m,
+                                                                   const LinearArgs a) {
   // (leading parameters: in scalar registers when the wavefront starts, see linear_lds_kernel)
   constexpr int D = lin_depth<MF>();
   __shared__ floatx4 part[kLinWaves][MF][64];
@@ -193,6 +227,21 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
       acc[f] = mfma16(make_uint2(x.z, x.w), make_uint2(w.z, w.w), acc[f]);
     }
   };
+  // This thread's results are feature threadIdx.x % 16 of rows threadIdx.x / 16 + 16 f: what is added to them, asked for
+  // behind the first weights.
+  const Sink sink(a);
+  _Float16 add_bias = 0, add_residual[MF];
+  const int out_row = (int)threadIdx.x >> 4, out_feature = ntile * 16 + ((int)threadIdx.x & 15);
+  uint64_t out, at;
+  auto fetch_rest = [&]() {
+    sink.arrive();
+    if (bias) add_bias = bias[out_feature];
+#pragma unroll
+    for (int f = 0; f < MF; ++f) {
+      sink.place(min(16 * f + out_row, m - 1), out_feature, out, at);
+      add_residual[f] = sink.residual ? load_at<_Float16>(sink.residual + at) : (_Float16)0;
+    }
+  };
   int k = 0;
   if (nk >= 2 * D) {
 #pragma unroll
@@ -200,6 +249,8 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
       load(i, i);
       __builtin_amdgcn_sched_barrier(0);    // oldest first: the loop waits for the loads in this order
     }
+    fetch_rest();
+    __builtin_amdgcn_sched_barrier(0);
     for (; k + 2 * D <= nk; k += D) {                          // steady state: no conditional loads
 #pragma unroll
       for (int i = 0; i < D; ++i) {
@@ -213,6 +264,7 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
 #pragma unroll
     for (int i = 0; i < D; ++i)
       if (i < nk) load(i, i);
+    fetch_rest();
   }
   // drain: at most 2 D - 1 blocks are left, the first D of them in flight
 #pragma unroll
@@ -230,21 +282,20 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
 #pragma unroll
   for (int f = 0; f < MF; ++f) part[wave][f][lane] = acc[f];
   __syncthreads();
-  for (int o = threadIdx.x; o < MF * 256; o += kLinWaves * 64) {
-    const int mrow = o >> 4, j = o & 15;
-    if (mrow >= m) continue;
-    const int f = mrow >> 4, src_lane = j + 16 * ((mrow & 15) >> 2), r = mrow & 3;
+  static_assert(kLinWaves * 64 == 256, "a row fragment of results, 16 rows x 16 features, per pass of the workgroup");
+#pragma unroll
+  for (int f = 0; f < MF; ++f) {
+    const int mrow = 16 * f + out_row;
+    if (mrow >= m) break;
+    const int src_lane = (threadIdx.x & 15) + 16 * (out_row >> 2), r = out_row & 3;
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < kLinWaves; ++w) v += part[w][f][src_lane][r];
-    const int n = ntile * 16 + j;
-    if (a.bias) v += (float)a.bias[n];
-    if (a.relu) v = fmaxf(v, 0.f);
-    int seg;
-    size_t at;
-    seg_of(a, mrow, n, seg, at);
-    if (a.residual) v += (float)a.residual[at];
-    a.out[seg][at] = (_Float16)v;
+    if (bias) v += (float)add_bias;
+    if (sink.relu) v = fmaxf(v, 0.f);
+    if (sink.residual) v += (float)add_residual[f];
+    sink.place(mrow, out_feature, out, at);
+    store_at(out + at, (_Float16)v);
   }
 }
 
@@ -276,7 +327,7 @@ constexpr int vmcnt_only(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >
 // at the occupancy the launch bounds allow and capped the kernel at 64.
 template <int MF, int NW, bool NT>
 __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_waves_per_eu(1, MF > 8 ? 2 : 4))) void linear_lds_kernel(
-    const uint4 *w, const uint4 *x, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
+    const uint4 *w, const uint4 *x, const _Float16 *bias, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
     const int32_t n_tiles, const LinearArgs a) {
   // (the parameters in front of `a` are what the first loads need: the build has the leading kernel arguments
   // arrive in scalar registers with the wavefront, so the weight stream starts without a round trip to the
@@ -313,6 +364,8 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
   // memory channels at a time (16384 x 4096 at 32 rows, weights from HBM: 31.7 us without, 28.8 with).
   const int rot = (int)(((unsigned)group * 5u + (unsigned)cut * 3u) % (unsigned)n_chunks);
   auto rotc = [&](int c) { int cc = c + rot; return cc >= n_chunks ? cc - n_chunks : cc; };
+  const Sink sink(a);
+  _Float16 add_bias;                                     // of this lane's feature (without a bias: anything)
 
   if (wave >= NW) {
     // The staging wavefront.  Its loads have a counter of their own, so waiting for them never
@@ -354,6 +407,8 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
 #pragma unroll
     for (int j = 0; j < LEAD; ++j)
       if (j < n_chunks) stage(rotc(j), j);
+    sink.arrive();
+    sink.shares_arrive();
     landed(0);
     __builtin_amdgcn_s_barrier();
     int buf = LEAD;
@@ -388,6 +443,9 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
         wbuf[u][i] = load_weight<NT>(wp + ((size_t)ahead(u) * C + i) * 64);
         __builtin_amdgcn_sched_barrier(0);
       }
+    add_bias = bias ? bias[(ntile < n_tiles ? ntile : 0) * 16 + rr] : *reinterpret_cast<const _Float16 *>(w);
+    sink.arrive();
+    sink.shares_arrive();
     __syncthreads();
     int buf = 0;
     for (int c0 = 0; c0 < n_chunks; c0 += WD) {
@@ -422,37 +480,44 @@ __global__ __launch_bounds__((NW + lin_stagers(MF)) * 64) __attribute__((amdgpu_
     }
   }
 
-  // this workgroup's share of the tile [16 MF][128] in LDS (all reads of xs are behind the barrier above):
-  // result element (row 16 f + 4 (lane / 16) + r, feature 16 wave + lane % 16) sits in acc[f][r]
+  // this workgroup's share of the tile [16 MF][kTileCols] in LDS (all reads of xs are behind the barrier above), with the bias
+  // where it is the whole sum: result element (row 16 f + 4 (lane / 16) + r, feature 16 wave + lane % 16) sits in acc[f][r]
   float *tile = reinterpret_cast<float *>(&xs[0][0][0]);
   if (wave < NW) {
+    const float add = sink.to_shares || !bias ? 0.f : (float)add_bias;
 #pragma unroll
     for (int f = 0; f < MF; ++f)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) tile[(f * 16 + 4 * (lane >> 4) + r) * kTileCols + wave * 16 + (lane & 15)] = acc[f][r];
+      for (int r = 0; r < 4; ++r) tile[(f * 16 + 4 * (lane >> 4) + r) * kTileCols + wave * 16 + (lane & 15)] = acc[f][r] + add;
   }
-  __syncthreads();
   // eight neighbouring features of a row per thread (feature counts and segment widths are multiples of 16, so
   // a group of eight never straddles a segment and every access below is one aligned 16-byte piece)
   const int n0 = group * kTileCols;
   constexpr int VPR = kTileCols / 8;
-  if (splits > 1 || a.to_shares) {                   // this cut's share; a second kernel adds them up
-    float *mine = a.shares + (size_t)cut * m * a.n_out;
-    for (int o = tid; o < m * VPR; o += kFastThreads) {
-      const int mrow = o / VPR, n = n0 + 8 * (o % VPR);
-      if (n >= a.n_out) continue;
-      const float4 *t = reinterpret_cast<const float4 *>(tile + mrow * kTileCols + 8 * (o % VPR));
-      float4 *dst = reinterpret_cast<float4 *>(mine + (size_t)mrow * a.n_out + n);
-      dst[0] = t[0];
-      dst[1] = t[1];
+  if (sink.to_shares) {                              // this cut's share; a second kernel adds them up
+    __syncthreads();
+    const uint64_t mine = sink.shares + (uint64_t)cut * m * sink.n_out * 4;
+    for (int o = tid; o < 2 * m * VPR; o += kFastThreads) {          // neighbouring threads, neighbouring 16 bytes
+      const int mrow = o / (2 * VPR), n = n0 + 4 * (o % (2 * VPR));
+      if (n < sink.n_out) store_at(mine + ((uint64_t)mrow * sink.n_out + n) * 4, *reinterpret_cast<const floatx4 *>(tile + 4 * o));
     }
     return;
   }
-  for (int o = tid; o < m * VPR; o += kFastThreads) {
-    const int mrow = o / VPR, n = n0 + 8 * (o % VPR);
-    if (n >= a.n_out) continue;
-    const float4 *t = reinterpret_cast<const float4 *>(tile + mrow * kTileCols + 8 * (o % VPR));
-    store_eight(a, mrow, n, t[0], t[1]);
+  constexpr int kPasses = (16 * MF * VPR + kFastThreads - 1) / kFastThreads;
+  u32x4_t residual[kPasses];
+#pragma unroll
+  for (int k = 0; k < kPasses; ++k) {
+    const int o = tid + k * kFastThreads, n = n0 + 8 * (o % VPR);
+    residual[k] = residual_eight(sink, min(o / VPR, m - 1), n < sink.n_out ? n : 0);
+  }
+  __syncthreads();
+  const half8 no_bias = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < kPasses; ++k) {
+    const int o = tid + k * kFastThreads, mrow = o / VPR, n = n0 + 8 * (o % VPR);
+    if (mrow >= m || n >= sink.n_out) continue;
+    const floatx4 *t = reinterpret_cast<const floatx4 *>(tile + mrow * kTileCols + 8 * (o % VPR));
+    store_eight(sink, mrow, n, t[0], t[1], no_bias, __builtin_bit_cast(half8, residual[k]));
   }
 }
 
@@ -507,7 +572,7 @@ __device__ __forceinline__ void load_to_lds(const void *base, uint32_t off, uint
 
 template <int FM, int FN, int WM, int WN, int WD>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1, 2))) void linear_tile_kernel(
-    const uint4 *w, const uint4 *x, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
+    const uint4 *w, const uint4 *x, const _Float16 *bias, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
     const int32_t n_tiles, const int32_t m_tiles, const int32_t n_groups, const LinearArgs a) {
   using S = TileShape<FM, FN, WM, WN, WD>;
   __shared__ __attribute__((aligned(1024))) char lds[S::kLds];
@@ -516,13 +581,13 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
   const int wm = wave / WN, wn = wave % WN;
   // Workgroups are dealt to the 8 XCDs in rotation; tiles that share weights (all row tiles of a feature group)
   // and neighbouring groups are put on the same XCD, whose L2 then reads them from memory once.
-  const int total = gridDim.x, xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
+  const int total = m_tiles * n_groups * splits, xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
   const int tile = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
   const int mt = tile % m_tiles, group = (tile / m_tiles) % n_groups, cut = tile / (m_tiles * n_groups);
   // This workgroup's stages of 64 inputs.  Where the inputs are an odd number of blocks of 32, the very last stage is
   // half full: it is the last one walked by the cut that has it (no shift of the walk then).
-  const int all_stages = (n_kb + 1) >> 1, stage0 = (int)((int64_t)cut * all_stages / splits);
-  const int n_stages = (int)((int64_t)(cut + 1) * all_stages / splits) - stage0;
+  const int all_stages = (n_kb + 1) >> 1, stage0 = (int)((unsigned)(cut * all_stages) / (unsigned)splits);
+  const int n_stages = (int)((unsigned)((cut + 1) * all_stages) / (unsigned)splits) - stage0;
   const int half_stage = n_kb & 1 ? all_stages - 1 : -1;
   const int full_stages = n_stages - (stage0 + n_stages - 1 == half_stage ? 1 : 0);
   const int rot = m_tiles == 1 && half_stage < 0 ? (int)(((unsigned)group * 5u + (unsigned)cut * 3u) % (unsigned)n_stages) : 0;
@@ -595,6 +660,9 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
     for (int i = 0; i < 2; ++i) load_w(wbuf[u][i], u, i);
     __builtin_amdgcn_sched_barrier(0);
   }
+  const Sink sink(a);
+  sink.arrive();
+  sink.shares_arrive();
   // a stage of x has landed once no more loads are outstanding than were issued after it
   constexpr int kInFlight = WD * 2 * FN + (WD - 1) * S::kLoads;
   __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight));
@@ -642,29 +710,59 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
   // Results: acc[fm][fn][r] is row 16 fm + lane % 16, feature 16 fn + 4 (lane / 16) + r of the wavefront's piece.  They pass
   // through LDS that belongs to the wavefront, 32 rows at a time, and leave as 16-byte pieces of whole rows.
   float *mine = reinterpret_cast<float *>(lds) + wave * 32 * S::kOutStride;
-  const bool to_shares = splits > 1 || a.to_shares;
-#pragma unroll
-  for (int c = 0; c < FM / 2; ++c) {
+  const int out_row = row0 + wm * FM * 16, out_feature = tile0 * 16;
+  auto turn = [&](int c) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn)
         *reinterpret_cast<floatx4 *>(mine + (16 * h + rr) * S::kOutStride + 16 * fn + 4 * q) = acc[2 * c + h][fn];
+  };
+  auto piece = [&](int c, int k, int &mrow, int &n, floatx4 &t0, floatx4 &t1) {
+    const int o = k * 64 + lane, r = o / (2 * FN), pc = o % (2 * FN);
+    mrow = out_row + 32 * c + r, n = out_feature + pc * 8;
+    const floatx4 *t = reinterpret_cast<const floatx4 *>(mine + r * S::kOutStride + pc * 8);
+    t0 = t[0], t1 = t[1];
+    return mrow < m && n < sink.n_out;
+  };
+  int mrow, n;
+  floatx4 t0, t1;
+  if (sink.to_shares) {
 #pragma unroll
-    for (int k = 0; k < FN; ++k) {
-      const int o = k * 64 + lane, r = o / (2 * FN), pc = o % (2 * FN);
-      const int mrow = row0 + (wm * FM + 2 * c) * 16 + r, n = tile0 * 16 + pc * 8;
-      const float4 *t = reinterpret_cast<const float4 *>(mine + r * S::kOutStride + pc * 8);
-      const float4 t0 = t[0], t1 = t[1];
-      if (mrow >= m || n >= a.n_out) continue;
-      if (to_shares) {
-        float4 *dst = reinterpret_cast<float4 *>(a.shares + ((size_t)cut * m + mrow) * a.n_out + n);
-        dst[0] = t0;
-        dst[1] = t1;
-      } else {
-        store_eight(a, mrow, n, t0, t1);
+    for (int c = 0; c < FM / 2; ++c) {
+      turn(c);
+#pragma unroll
+      for (int k = 0; k < 2 * FN; ++k) {                 // neighbouring lanes, neighbouring 16 bytes
+        const int o = k * 64 + lane, r = o / (4 * FN), pc = o % (4 * FN);
+        const int mrow = out_row + 32 * c + r, n = out_feature + pc * 4;
+        const floatx4 t = *reinterpret_cast<const floatx4 *>(mine + r * S::kOutStride + pc * 4);
+        if (mrow < m && n < sink.n_out) store_at(sink.shares + (((uint64_t)cut * m + mrow) * sink.n_out + n) * 4, t);
       }
     }
+    return;
+  }
+  u32x4_t add_bias[FN] = {}, residual[FM / 2][FN] = {};
+#pragma unroll
+  for (int k = 0; k < FN; ++k) {
+    const int o = k * 64 + lane, r = o / (2 * FN), at = out_feature + o % (2 * FN) * 8, n = at < sink.n_out ? at : 0;
+    if (bias) add_bias[k] = load_at<u32x4_t>((uint64_t)(bias + n));
+#pragma unroll
+    for (int c = 0; c < FM / 2; ++c) residual[c][k] = residual_eight(sink, min(out_row + 32 * c + r, m - 1), n);
+  }
+  turn(0);
+#pragma unroll
+  for (int k = 0; k < FN; ++k) {                         // one wait for all of them, here: behind a store it would be one for the store
+    asm volatile("" : "+v"(add_bias[k]));
+#pragma unroll
+    for (int c = 0; c < FM / 2; ++c) asm volatile("" : "+v"(residual[c][k]));
+  }
+#pragma unroll
+  for (int c = 0; c < FM / 2; ++c) {
+    if (c > 0) turn(c);
+#pragma unroll
+    for (int k = 0; k < FN; ++k)
+      if (piece(c, k, mrow, n, t0, t1))
+        store_eight(sink, mrow, n, t0, t1, __builtin_bit_cast(half8, add_bias[k]), __builtin_bit_cast(half8, residual[c][k]));
   }
 }
 
@@ -714,7 +812,7 @@ __device__ __forceinline__ void barrier_leaving_reads() {
 
 template <int FM, int FN, int WM, int WN, int NX>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1, 2))) void linear_wide_kernel(
-    const uint4 *w, const uint4 *x, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
+    const uint4 *w, const uint4 *x, const _Float16 *bias, const int32_t n_kb, const int32_t splits, const int32_t n_in, const int32_t m,
     const int32_t n_tiles, const int32_t m_tiles, const int32_t n_groups, const LinearArgs a) {
   using S = WideShape<FM, FN, WM, WN, NX>;
   constexpr int kXB = S::kXBuffers, kWB = S::kWBuffers, kAhead = S::kAhead;
@@ -724,13 +822,13 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
   const int wm = wave / WN, wn = wave % WN;
   // Workgroups are dealt to the 8 XCDs in rotation; tiles that share weights (all row tiles of a feature group)
   // and neighbouring groups are put on the same XCD, whose L2 then reads them from memory once.
-  const int total = gridDim.x, xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
+  const int total = m_tiles * n_groups * splits, xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
   const int tile = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
   const int mt = tile % m_tiles, group = (tile / m_tiles) % n_groups, cut = tile / (m_tiles * n_groups);
   // This workgroup's stages of 64 inputs.  Where the inputs are an odd number of blocks of 32, the very last stage is
   // half full: it is the last one walked by the cut that has it (no shift of the walk then).
-  const int all_stages = (n_kb + 1) >> 1, stage0 = (int)((int64_t)cut * all_stages / splits);
-  const int n_stages = (int)((int64_t)(cut + 1) * all_stages / splits) - stage0;
+  const int all_stages = (n_kb + 1) >> 1, stage0 = (int)((unsigned)(cut * all_stages) / (unsigned)splits);
+  const int n_stages = (int)((unsigned)((cut + 1) * all_stages) / (unsigned)splits) - stage0;
   const int half_stage = n_kb & 1 ? all_stages - 1 : -1;
   const int full_stages = n_stages - (stage0 + n_stages - 1 == half_stage ? 1 : 0);
   const int rot = m_tiles == 1 && half_stage < 0 ? (int)(((unsigned)group * 5u + (unsigned)cut * 3u) % (unsigned)n_stages) : 0;
@@ -805,6 +903,9 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
     if (h % 2 == 1) stage_x((h + 1) / 2, (h + 1) / 2);
     stage_w(h, h);
   }
+  const Sink sink(a);
+  sink.arrive();
+  sink.shares_arrive();
   if (more) __builtin_amdgcn_s_waitcnt(vmcnt_only(S::first(S::LW)));
   else __builtin_amdgcn_s_waitcnt(vmcnt_only(S::first(S::LW - 1)));
   __syncthreads();
@@ -861,29 +962,59 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
   // Results: acc[fm][fn][r] is row 16 fm + lane % 16, feature 16 fn + 4 (lane / 16) + r of the wavefront's piece.  They pass
   // through LDS that belongs to the wavefront, 32 rows at a time, and leave as 16-byte pieces of whole rows.
   float *mine = reinterpret_cast<float *>(lds) + wave * 32 * S::kOutStride;
-  const bool to_shares = splits > 1 || a.to_shares;
-#pragma unroll
-  for (int c = 0; c < FM / 2; ++c) {
+  const int out_row = row0 + wm * FM * 16, out_feature = (tile0 + wn * FN) * 16;
+  auto turn = [&](int c) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn)
         *reinterpret_cast<floatx4 *>(mine + (16 * h + rr) * S::kOutStride + 16 * fn + 4 * q) = acc[2 * c + h][fn];
+  };
+  auto piece = [&](int c, int k, int &mrow, int &n, floatx4 &t0, floatx4 &t1) {
+    const int o = k * 64 + lane, r = o / (2 * FN), pc = o % (2 * FN);
+    mrow = out_row + 32 * c + r, n = out_feature + pc * 8;
+    const floatx4 *t = reinterpret_cast<const floatx4 *>(mine + r * S::kOutStride + pc * 8);
+    t0 = t[0], t1 = t[1];
+    return mrow < m && n < sink.n_out;
+  };
+  int mrow, n;
+  floatx4 t0, t1;
+  if (sink.to_shares) {
 #pragma unroll
-    for (int k = 0; k < FN; ++k) {
-      const int o = k * 64 + lane, r = o / (2 * FN), pc = o % (2 * FN);
-      const int mrow = row0 + (wm * FM + 2 * c) * 16 + r, n = (tile0 + wn * FN) * 16 + pc * 8;
-      const float4 *t = reinterpret_cast<const float4 *>(mine + r * S::kOutStride + pc * 8);
-      const float4 t0 = t[0], t1 = t[1];
-      if (mrow >= m || n >= a.n_out) continue;
-      if (to_shares) {
-        float4 *dst = reinterpret_cast<float4 *>(a.shares + ((size_t)cut * m + mrow) * a.n_out + n);
-        dst[0] = t0;
-        dst[1] = t1;
-      } else {
-        store_eight(a, mrow, n, t0, t1);
+    for (int c = 0; c < FM / 2; ++c) {
+      turn(c);
+#pragma unroll
+      for (int k = 0; k < 2 * FN; ++k) {                 // neighbouring lanes, neighbouring 16 bytes
+        const int o = k * 64 + lane, r = o / (4 * FN), pc = o % (4 * FN);
+        const int mrow = out_row + 32 * c + r, n = out_feature + pc * 4;
+        const floatx4 t = *reinterpret_cast<const floatx4 *>(mine + r * S::kOutStride + pc * 4);
+        if (mrow < m && n < sink.n_out) store_at(sink.shares + (((uint64_t)cut * m + mrow) * sink.n_out + n) * 4, t);
       }
     }
+    return;
+  }
+  u32x4_t add_bias[FN] = {}, residual[FM / 2][FN] = {};
+#pragma unroll
+  for (int k = 0; k < FN; ++k) {
+    const int o = k * 64 + lane, r = o / (2 * FN), at = out_feature + o % (2 * FN) * 8, n = at < sink.n_out ? at : 0;
+    if (bias) add_bias[k] = load_at<u32x4_t>((uint64_t)(bias + n));
+#pragma unroll
+    for (int c = 0; c < FM / 2; ++c) residual[c][k] = residual_eight(sink, min(out_row + 32 * c + r, m - 1), n);
+  }
+  turn(0);
+#pragma unroll
+  for (int k = 0; k < FN; ++k) {                         // one wait for all of them, here: behind a store it would be one for the store
+    asm volatile("" : "+v"(add_bias[k]));
+#pragma unroll
+    for (int c = 0; c < FM / 2; ++c) asm volatile("" : "+v"(residual[c][k]));
+  }
+#pragma unroll
+  for (int c = 0; c < FM / 2; ++c) {
+    if (c > 0) turn(c);
+#pragma unroll
+    for (int k = 0; k < FN; ++k)
+      if (piece(c, k, mrow, n, t0, t1))
+        store_eight(sink, mrow, n, t0, t1, __builtin_bit_cast(half8, add_bias[k]), __builtin_bit_cast(half8, residual[c][k]));
   }
 }
 
@@ -891,52 +1022,52 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
 // workgroup per 256 consecutive features of a row.  A launch of its own rather than a hand-over inside
 // the product kernel: a workgroup that reads what other workgroups wrote needs device-wide fences, and on
 // this GPU those write back and invalidate the L2 caches (measured: 75 us instead of 11 for a 32 MiB matrix).
-__global__ __launch_bounds__(256) void reduce_epilogue_kernel(const float *shares, const int32_t n_out, const int32_t splits,
-                                                                 const int32_t m, const LinearArgs a) {
+__global__ __launch_bounds__(256) void reduce_epilogue_kernel(const float *shares, const _Float16 *bias, const _Float16 *residual,
+                                                                 const int32_t n_out, const int32_t splits, const int32_t m,
+                                                                 const int32_t seg0_cols, const int32_t seg_cols, const LinearArgs a) {
   // four neighbouring features per thread; the shares are fetched four cuts at a time with loads that do not
   // depend on one another (past the last cut the last is read again and left out of the sum: not added with
   // weight 0, which would make a NaN of an infinity), so a thread waits for one round trip, not for one per cut
   const int n = (blockIdx.x * 256 + threadIdx.x) * 4, mrow = blockIdx.y;
   if (n >= n_out) return;
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  const Sink sink(a);
+  floatx4 v = {0.f, 0.f, 0.f, 0.f};
+  half4 add_bias, add_residual;
+  const int r = n - seg0_cols;                           // a segment is a multiple of 16 features wide
+  const bool first = r < 0, third = r >= seg_cols;
+  const uint64_t at = 2 * ((uint64_t)mrow * (uint32_t)(first ? seg0_cols : seg_cols) + (uint32_t)(first ? n : third ? r - seg_cols : r));
   for (int s2 = 0; s2 < splits; s2 += 4) {
-    float4 part[4];
+    floatx4 part[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int sj = s2 + j < splits ? s2 + j : splits - 1;
-      part[j] = *reinterpret_cast<const float4 *>(shares + ((size_t)sj * m + mrow) * n_out + n);
+      part[j] = *reinterpret_cast<const floatx4 *>(shares + ((size_t)sj * m + mrow) * n_out + n);
+    }
+    if (s2 == 0) {                                       // behind the first shares, not behind their sum
+      __builtin_amdgcn_sched_barrier(0);
+      // (without them, whatever else can be read: a branch around a load waits for it where the paths meet)
+      add_bias = load_at<half4>(bias ? (uint64_t)(bias + n) : (uint64_t)shares);
+      add_residual = load_at<half4>(residual ? (uint64_t)residual + at : (uint64_t)shares);
+      sink.arrive();
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const bool in = s2 + j < splits;
-      v.x += in ? part[j].x : 0.f, v.y += in ? part[j].y : 0.f, v.z += in ? part[j].z : 0.f, v.w += in ? part[j].w : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += in ? part[j][e] : 0.f;
     }
   }
-  int seg;                                                             // a segment is a multiple of 16 features wide
-  size_t at;
-  seg_of(a, mrow, n, seg, at);
-  float y[4] = {v.x, v.y, v.z, v.w};
-  if (a.bias) {
-    const uint2 b = *reinterpret_cast<const uint2 *>(a.bias + n);
-    const _Float16 *bp = reinterpret_cast<const _Float16 *>(&b);
+  half4 o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] += (float)bp[e];
+  for (int e = 0; e < 4; ++e) {
+    float y = v[e];
+    if (bias) y += (float)add_bias[e];
+    if (sink.relu) y = fmaxf(y, 0.f);
+    if (residual) y += (float)add_residual[e];
+    o[e] = (_Float16)y;
   }
-  if (a.relu) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = fmaxf(y[e], 0.f);
-  }
-  if (a.residual) {
-    const uint2 r = *reinterpret_cast<const uint2 *>(a.residual + at);
-    const _Float16 *rp = reinterpret_cast<const _Float16 *>(&r);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] += (float)rp[e];
-  }
-  uint2 o;
-  _Float16 *op = reinterpret_cast<_Float16 *>(&o);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) op[e] = (_Float16)y[e];
-  *reinterpret_cast<uint2 *>(a.out[seg] + at) = o;
+  store_at((first ? sink.out0 : third ? sink.out2 : sink.out1) + at, o);
 }
 
 // dst piece (block (nt, kb), lane) = src[16 nt + lane % 16][32 kb + 8 (lane / 16) .. + 7]
@@ -1021,13 +1152,18 @@ __global__ __launch_bounds__(kLnMaxThreads) void layernorm_kernel(const uint4 *x
 // the row whenever a product feeds a layer norm (output projection -> second norm, feed-forward
 // -> the next layer's first norm).
 template <int PPT>
-__global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const float *shares, const int32_t n_out, const int32_t splits,
-                                                                           const int32_t m, const LinearArgs a) {
-  // (leading parameters: in scalar registers when the wavefront starts, so the shares are asked for at once)
+__global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const float *shares, const _Float16 *bias, const _Float16 *residual,
+                                                                           const _Float16 *gamma, const _Float16 *beta, const int32_t n_out,
+                                                                           const int32_t splits, const int32_t m, const LinearArgs a) {
+  // (leading parameters: in scalar registers when the wavefront starts, so everything is asked for at once)
   __shared__ float scratch[kLnMaxThreads / 64];
   const int h = n_out, pieces = h >> 3, mrow = blockIdx.x;
+  const Sink sink(a);
   float v[PPT][8];
   float s = 0.f;
+  // the bias, the residual, gamma and beta are fetched behind the first shares: not behind the sums nor behind the reductions,
+  // whose barriers would otherwise stand between these loads and what they do not depend on
+  uint4 gam[PPT], bet[PPT];
 #pragma unroll
   for (int i = 0; i < PPT; ++i) {
     const int p = threadIdx.x + i * blockDim.x;
@@ -1035,6 +1171,8 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
       float acc[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+      u32x4_t rb, bb;
+      const uint64_t at = ((uint64_t)mrow * h + p * 8) * 2;
       for (int s2 = 0; s2 < splits; s2 += 4) {             // four cuts at a time, loads independent of one another
         float4 lo[4], hi[4];
 #pragma unroll
@@ -1043,6 +1181,15 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
           const float4 *sp = reinterpret_cast<const float4 *>(shares + ((size_t)sj * m + mrow) * h + p * 8);
           lo[j] = sp[0], hi[j] = sp[1];
         }
+        if (s2 == 0) {
+          __builtin_amdgcn_sched_barrier(0);
+          // (without them, gamma: a branch around a load waits for it where the paths meet)
+          bb = load_at<u32x4_t>((uint64_t)(bias ? bias : gamma) + p * 16);
+          rb = load_at<u32x4_t>(residual ? (uint64_t)residual + at : (uint64_t)gamma + p * 16);
+          gam[i] = reinterpret_cast<const uint4 *>(gamma)[p], bet[i] = reinterpret_cast<const uint4 *>(beta)[p];
+          if (i == 0) sink.arrive();
+          __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const bool in = s2 + j < splits;
@@ -1050,31 +1197,21 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
           acc[4] += in ? hi[j].x : 0.f, acc[5] += in ? hi[j].y : 0.f, acc[6] += in ? hi[j].z : 0.f, acc[7] += in ? hi[j].w : 0.f;
         }
       }
-      uint4 rb = make_uint4(0u, 0u, 0u, 0u), bb = rb;
-      if (a.bias) bb = reinterpret_cast<const uint4 *>(a.bias)[p];
-      if (a.residual) rb = reinterpret_cast<const uint4 *>(a.residual + (size_t)mrow * h)[p];
-      const _Float16 *bp = reinterpret_cast<const _Float16 *>(&bb), *rp = reinterpret_cast<const _Float16 *>(&rb);
+      const u32x4_t none = {0u, 0u, 0u, 0u};
+      const half8 bp = __builtin_bit_cast(half8, bias ? bb : none), rp = __builtin_bit_cast(half8, residual ? rb : none);
       uint4 yo;
       _Float16 *yp = reinterpret_cast<_Float16 *>(&yo);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         float y = acc[e] + (float)bp[e];
-        if (a.relu) y = fmaxf(y, 0.f);
+        if (sink.relu) y = fmaxf(y, 0.f);
         y += (float)rp[e];
         yp[e] = (_Float16)y;                               // the norm sees the row as it is stored
         v[i][e] = (float)yp[e];
         s += v[i][e];
       }
-      reinterpret_cast<uint4 *>(a.out[0] + (size_t)mrow * h)[p] = yo;
+      store_at(sink.out0 + at, __builtin_bit_cast(u32x4_t, yo));
     }
-  }
-  // gamma and beta are fetched before the reductions, whose barriers would otherwise stand between these
-  // loads and the statistics they do not depend on
-  uint4 gam[PPT], bet[PPT];
-#pragma unroll
-  for (int i = 0; i < PPT; ++i) {
-    const int p = threadIdx.x + i * blockDim.x;
-    if (p < pieces) gam[i] = reinterpret_cast<const uint4 *>(a.ln_gamma)[p], bet[i] = reinterpret_cast<const uint4 *>(a.ln_beta)[p];
   }
   const float mean = block_sum(s, scratch) / (float)h;
   float q = 0.f;
@@ -1102,20 +1239,20 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
 // The kernel that adds the cuts' shares up (and takes the layer norm of the sums, if asked to).
 void launch_reduce(const LinearArgs &args, hipStream_t stream) {
   if (args.ln_out && (args.n_out >> 3) <= kLnMaxThreads)
-    hipLaunchKernelGGL(reduce_layernorm_kernel<1>, dim3(args.m), dim3(ln_threads(args.n_out)), 0, stream, args.shares, args.n_out,
-                       args.splits, args.m, args);
+    hipLaunchKernelGGL(reduce_layernorm_kernel<1>, dim3(args.m), dim3(ln_threads(args.n_out)), 0, stream, args.shares, args.bias,
+                       args.residual, args.ln_gamma, args.ln_beta, args.n_out, args.splits, args.m, args);
   else if (args.ln_out)
-    hipLaunchKernelGGL(reduce_layernorm_kernel<2>, dim3(args.m), dim3(ln_threads(args.n_out)), 0, stream, args.shares, args.n_out,
-                       args.splits, args.m, args);
+    hipLaunchKernelGGL(reduce_layernorm_kernel<2>, dim3(args.m), dim3(ln_threads(args.n_out)), 0, stream, args.shares, args.bias,
+                       args.residual, args.ln_gamma, args.ln_beta, args.n_out, args.splits, args.m, args);
   else
     hipLaunchKernelGGL(reduce_epilogue_kernel, dim3((args.n_out + 1023) / 1024, args.m), dim3(256), 0, stream, args.shares,
-                       args.n_out, args.splits, args.m, args);
+                       args.bias, args.residual, args.n_out, args.splits, args.m, args.seg0_cols, args.seg_cols, args);
 }
 
 template <int MF, int NW, bool NT>
 void launch_staged_as(const LinearArgs &args, int n_tiles, hipStream_t stream) {
   hipLaunchKernelGGL((linear_lds_kernel<MF, NW, NT>), dim3((n_tiles + NW - 1) / NW, args.splits), dim3((NW + lin_stagers(MF)) * 64), 0, stream,
-                     args.w, args.x, args.n_kb, args.splits, args.n_in, args.m, args.n_tiles, args);
+                     args.w, args.x, args.bias, args.n_kb, args.splits, args.n_in, args.m, args.n_tiles, args);
 }
 
 template <int MF, int NW>
@@ -1130,16 +1267,16 @@ template <int MF>
 hipError_t launch_linear_mf(const LinearArgs &args, int n_tiles, bool fast, int fast_waves, hipStream_t stream) {
   if (fast) {
     fast_waves == 3 ? launch_staged<MF, 3>(args, n_tiles, stream) : launch_staged<MF, 4>(args, n_tiles, stream);
-    if (args.splits > 1 || args.to_shares) {
+    if (args.to_shares) {
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       launch_reduce(args, stream);
     }
   } else if constexpr (MF <= OKV_LINEAR_MAX_ROWS / 16) {
     const bool stream_w = MF == 1 && args.m <= OKV_LIN_SIMPLE_ROWS && (int64_t)args.n_out * args.n_in * 2 >= kStreamSimpleBytes;
-    if (stream_w) hipLaunchKernelGGL((linear_kernel<1, true>), dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.n_kb,
+    if (stream_w) hipLaunchKernelGGL((linear_kernel<1, true>), dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.bias, args.n_kb,
                                      args.n_in, args.m, args);
-    else hipLaunchKernelGGL((linear_kernel<MF, false>), dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.n_kb, args.n_in,
+    else hipLaunchKernelGGL((linear_kernel<MF, false>), dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.bias, args.n_kb, args.n_in,
                             args.m, args);
   } else {
     return hipErrorInvalidValue;                       // more than OKV_LINEAR_MAX_ROWS rows: the staged or the tile kernel only
@@ -1170,7 +1307,7 @@ void launch_tile_as(const LinearArgs &a, hipStream_t stream) {
   static_assert(kTileForms[F].rows == S::kRows && kTileForms[F].cols == S::kCols, "the model's form is the kernel's");
   const int m_tiles = (a.m + S::kRows - 1) / S::kRows, groups = (a.n_out + S::kCols - 1) / S::kCols;
   hipLaunchKernelGGL((linear_tile_kernel<FM, FN, WM, WN, WD>), dim3(m_tiles * groups * a.splits), dim3(S::kThreads), 0, stream, a.w, a.x,
-                     a.n_kb, a.splits, a.n_in, a.m, a.n_tiles, m_tiles, groups, a);
+                     a.bias, a.n_kb, a.splits, a.n_in, a.m, a.n_tiles, m_tiles, groups, a);
 }
 
 template <int F, int FM, int FN, int WM, int WN, int NX>
@@ -1179,7 +1316,7 @@ void launch_wide_as(const LinearArgs &a, hipStream_t stream) {
   static_assert(kTileForms[F].rows == S::kRows && kTileForms[F].cols == S::kCols, "the model's form is the kernel's");
   const int m_tiles = (a.m + S::kRows - 1) / S::kRows, groups = (a.n_out + S::kCols - 1) / S::kCols;
   hipLaunchKernelGGL((linear_wide_kernel<FM, FN, WM, WN, NX>), dim3(m_tiles * groups * a.splits), dim3(S::kThreads), 0, stream, a.w, a.x,
-                     a.n_kb, a.splits, a.n_in, a.m, a.n_tiles, m_tiles, groups, a);
+                     a.bias, a.n_kb, a.splits, a.n_in, a.m, a.n_tiles, m_tiles, groups, a);
 }
 
 hipError_t launch_linear_tile(const LinearArgs &a, int form, hipStream_t stream) {
@@ -1337,7 +1474,6 @@ hipError_t launch_linear(const LinearLaunch &l, hipStream_t stream) {
   const int n_tiles = l.n_out / 16;
   a.n_tiles = n_tiles;
   a.n_out = l.n_out;
-  a.to_shares = 0;
   a.ln_gamma = static_cast<const _Float16 *>(l.ln_gamma);
   a.ln_beta = static_cast<const _Float16 *>(l.ln_beta);
   a.ln_out = nullptr;
@@ -1347,6 +1483,7 @@ hipError_t launch_linear(const LinearLaunch &l, hipStream_t stream) {
   const bool fast = plan.kind == LinearPlan::kStaged;
   a.splits = plan.kind == LinearPlan::kSimple ? 1 : plan.cuts;
   a.shares = static_cast<float *>(l.workspace);
+  a.to_shares = a.splits > 1;
   // a layer norm of the result rides on the share reduction when there is one to ride on (the staged kernel then writes
   // its share also when there is a single cut; with the tile kernel's hundreds of rows a pass of its own over the fp16
   // result moves less than fp32 shares would)
