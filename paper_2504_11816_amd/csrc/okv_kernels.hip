@@ -215,6 +215,75 @@ __device__ __forceinline__ void tile_stage(const Tile<D / 32> &t, char *ks, char
   }
 }
 
+// Values of other lanes of a wavefront without the round trip through LDS that a shuffle is (some 50 ns, one after the other in
+// every chain below).  The swaps exchange the odd rows of 16 lanes (the upper half of the wavefront) of one register with the even rows
+// (the lower half) of another: of two copies of a value one then holds lane & ~16 (& ~32) of it in every lane, the other lane | 16 (| 32).
+// Written as assembly: the compiler's builtin returned the first register twice.
+// us, shuffles -> these: a layer of 32 sequences x 768 keys x 32 heads (d = 128) 61.2 -> 59.9, 16 ragged sequences of 32 heads with
+// their joining launch 35.5 -> 33.5, a step of 4 layers of two long sequences of 32 / 8 heads 57 -> 55.5.
+template <int X>
+__device__ __forceinline__ void split_lanes(const float v, float &a, float &b) {
+  static_assert(X == 16 || X == 32, "");
+  a = v, b = v;
+  if constexpr (X == 16) asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+  else asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+template <int X>
+__device__ __forceinline__ float max_with_lane_xor(const float v) {
+  float a, b;
+  split_lanes<X>(v, a, b);
+  return fmaxf(a, b);
+}
+template <int X>
+__device__ __forceinline__ float sum_with_lane_xor(const float v) {
+  float a, b;
+  split_lanes<X>(v, a, b);
+  return a + b;
+}
+// the value CTRL lanes further in the row of 16 (row_ror: CTRL - 0x120)
+template <int CTRL>
+__device__ __forceinline__ float row_turned(const float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+// Over all 64 lanes, which all take part, in the order of a butterfly from lane ^ 32 to lane ^ 1 (a value that repeats every 2 n lanes is
+// the same n lanes further as in lane ^ n)
+__device__ __forceinline__ float wave_max(float v) {
+  v = max_with_lane_xor<16>(max_with_lane_xor<32>(v));
+  v = fmaxf(v, row_turned<0x128>(v));
+  v = fmaxf(v, row_turned<0x124>(v));
+  v = fmaxf(v, row_turned<0x122>(v));
+  return fmaxf(v, row_turned<0x121>(v));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  v = sum_with_lane_xor<16>(sum_with_lane_xor<32>(v));
+  v += row_turned<0x128>(v);
+  v += row_turned<0x124>(v);
+  v += row_turned<0x122>(v);
+  return v + row_turned<0x121>(v);
+}
+// Inclusive scan over all 64 lanes, which all take part: inside the rows of 16, then from the end of each odd row's predecessor, then
+// from the lower half.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr: 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // row_bcast: 15 into rows 1 and 3
+  return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast: 31 into rows 2 and 3
+}
+__device__ __forceinline__ int64_t wave_scan(int64_t v) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int64_t up = __shfl_up(v, off);
+    if (lane >= off) v += up;
+  }
+  return v;
+}
+__device__ __forceinline__ float of_lane(const float v, const int lane) {               // lane: the same in the whole wavefront
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+
 // Online-softmax update of one wavefront with the 16-token tile that tile_stage put into LDS
 // (tok_tile = its first token).  masked: tokens outside [lo, hi) get score -inf (weight exactly 0; the
 // running maximum stays finite because it starts at kNegBig).
@@ -239,8 +308,8 @@ __device__ __forceinline__ void tile_update_mfma(const half8_t (&qb)[D / 32], fl
     s[r] = (!masked || (tok >= lo && tok < hi)) ? acc[r] * scale : -__builtin_inff();
   }
   float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  mx = max_with_lane_xor<16>(mx);
+  mx = max_with_lane_xor<32>(mx);
   const float m_new = fmaxf(m, mx);
   if (__any(m_new != m)) {                          // some head's maximum moved: rescale what is summed so far
     const float alpha = __builtin_amdgcn_exp2f(m - m_new);
@@ -304,8 +373,8 @@ __device__ __forceinline__ void tile_update_pair(const half8_t (&qb)[2], float &
     }
   }
   float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  mx = max_with_lane_xor<16>(mx);
+  mx = max_with_lane_xor<32>(mx);
   const float m_new = fmaxf(m, mx);
   if (__any(m_new != m)) {
     const float alpha = __builtin_amdgcn_exp2f(m - m_new);
@@ -342,7 +411,7 @@ __device__ __forceinline__ void tile_update_pair(const half8_t (&qb)[2], float &
 // ---- the work list from the lengths alone ----------------------------------------------------------------------
 //
 // For a batch of at most 64 sequences a wavefront cuts the keys into stretches by itself, a sequence per lane: the
-// lengths in one load, their tiles summed up by shuffles, and the same plan that the bookkeeping kernel makes.  The launch
+// lengths in one load, their tiles summed up across the lanes, and the same plan that the bookkeeping kernel makes.  The launch
 // of that kernel (4.8 us, as long as the attention over a small batch) is then not needed where a call has no context to
 // keep a work list in.  Partial results of sequence b in stretch j go to slot b + j.
 constexpr int kLensBatch = 64;
@@ -356,12 +425,7 @@ __device__ __forceinline__ LensPlan plan_from_lens(const int32_t *lens, const in
   LensPlan p;
   p.n = lane < B ? min(max(lens[lane], 0), 1 << 28) : 0;                  // (a length no sequence can have stays within 32 bits)
   const int tiles = tiles_in(p.n);
-  int sum = tiles;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int up = __shfl_up(sum, off);
-    if (lane >= off) sum += up;
-  }
+  const int sum = wave_scan(tiles);
   p.before = sum - tiles;
   p.total = __builtin_amdgcn_readlane(sum, 63);
   const SpanPlanOf<int32_t> plan = span_plan<int32_t>(p.total, max_groups, min_span);
@@ -596,8 +660,8 @@ __device__ __forceinline__ void attn_split_body(char (*lds_all)[lds_region<D>()]
     if (live) {
       const bool seq_whole = (C.flags & kItemWhole) != 0;
       float lt = l;
-      lt += __shfl_xor(lt, 16);
-      lt += __shfl_xor(lt, 32);
+      lt = sum_with_lane_xor<16>(lt);
+      lt = sum_with_lane_xor<32>(lt);
       // NS > 1: every wavefront puts its sums (relative to its own maxima), maxima and weights where its tiles were; then
       // each takes the dims of its share of the u below from all of them.
       constexpr int kU = D / 32, kShare = NS > 1 ? (kU + NS - 1) / NS : kU;      // u's per wavefront
@@ -902,8 +966,8 @@ __global__ __launch_bounds__(most_waves_per_pair(D) * 64) void attn_split_planne
 // block class.  Lane c first fetches (m_c, l_c) of item c, so the maxima and weights of up to
 // 64 items are formed by wavefront reductions instead of a chain of dependent loads; the
 // weighted sums then stream the partial rows four items at a time.  The launch is all latency (5 us for the 2000
-// items of a ragged batch): the rows of the first four items are asked for together with the maxima and weights, so
-// a sequence in at most four pieces waits for two round trips (the item range, then everything) and not for three, and
+// items of a ragged batch): the rows of the first four items are asked for together with the maxima and weights of the first 64, once, so
+// a sequence in at most four pieces waits for two round trips (the item range, then everything), and
 // four (b, h) pairs share a workgroup.
 // LENS: `chunk_prefix` is the device array of lengths instead, and a sequence's pieces are where plan_from_lens puts them.
 // MergeOuts: the results of several layers (blockIdx.z), whose partial results follow one another.
@@ -938,11 +1002,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
     first0 = chunk_prefix[b], cnt0 = chunk_prefix[b + 1] - first0;
   }
   if (n_cls == 1 && cnt0 <= 1) return;                 // written by the split kernel
-  float ahead[4][EPT];                                 // rows of the first class's first four items (past its last: that one again)
+  // of the first class: rows of the first four items (past its last: that one again) and (m, l) of the first 64
+  typedef float row_t __attribute__((ext_vector_type(EPT)));
+  row_t ahead[4] = {};
+  float2 ml0 = make_float2(kNegBig, 0.f);
+  if (cnt0 > 0) {
+    ml0 = *reinterpret_cast<const float2 *>(part_ml + ((size_t)(first0 + min(lane, cnt0 - 1)) * H + h) * 2);
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) ahead[k][e] = cnt0 > 0 ? row_of(first0 + min(k, cnt0 - 1))[e] : 0.f;
+    for (int k = 0; k < 4; ++k) ahead[k] = *reinterpret_cast<const row_t *>(row_of(first0 + min(k, cnt0 - 1)));
+  }
   float M = kNegBig;
   int total = 0;
   for (int cls = 0; cls < n_cls; ++cls) {
@@ -951,10 +1019,10 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
     total += n_chunks;
     for (int c0 = 0; c0 < n_chunks; c0 += 64) {
       const int c = c0 + lane;
-      float mc = c < n_chunks ? part_ml[((size_t)(first + c) * H + h) * 2] : kNegBig;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) mc = fmaxf(mc, __shfl_xor(mc, off));
-      M = fmaxf(M, mc);
+      float mc = kNegBig;
+      if (cls == 0 && c0 == 0) mc = c < n_chunks ? ml0.x : kNegBig;
+      else if (c < n_chunks) mc = part_ml[((size_t)(first + c) * H + h) * 2];
+      M = fmaxf(M, wave_max(mc));
     }
   }
   if (total <= 1) return;                              // written by the split kernel
@@ -968,20 +1036,19 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
       const int c = c0 + lane;
       float w = 0.f, lw = 0.f;
       if (c < n_chunks) {
-        const float2 ml = *reinterpret_cast<const float2 *>(part_ml + ((size_t)(first + c) * H + h) * 2);
+        float2 ml = ml0;
+        if (cls > 0 || c0 > 0) ml = *reinterpret_cast<const float2 *>(part_ml + ((size_t)(first + c) * H + h) * 2);
         w = __builtin_amdgcn_exp2f(ml.x - M);
         lw = ml.y * w;
       }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) lw += __shfl_xor(lw, off);
-      L += lw;
+      L += wave_sum(lw);
       const int cnt = min(64, n_chunks - c0);
       int i = 0;
       if (cls == 0 && c0 == 0) {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
           if (k < cnt) {
-            const float wk = __shfl(w, k);
+            const float wk = of_lane(w, k);
 #pragma unroll
             for (int e = 0; e < EPT; ++e) acc[e] += ahead[k][e] * wk;
           }
@@ -995,13 +1062,13 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
           for (int e = 0; e < EPT; ++e) x[k][e] = row_of(first + c0 + i + k)[e];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const float wk = __shfl(w, i + k);
+          const float wk = of_lane(w, i + k);
 #pragma unroll
           for (int e = 0; e < EPT; ++e) acc[e] += x[k][e] * wk;
         }
       }
       for (; i < cnt; ++i) {
-        const float wk = __shfl(w, i);
+        const float wk = of_lane(w, i);
 #pragma unroll
         for (int e = 0; e < EPT; ++e) acc[e] += row_of(first + c0 + i)[e] * wk;
       }
@@ -1224,17 +1291,13 @@ namespace {
 constexpr int kStepThreads = 256;
 
 // Inclusive scan of one value per thread over the workgroup's kStepThreads threads, and the sum of all of them:
-// a shuffle scan inside every wavefront and one hand-over of the wavefronts' sums through LDS (two barriers,
+// a scan inside every wavefront and one hand-over of the wavefronts' sums through LDS (two barriers,
 // where a scan through shared memory needs two per doubling: the kernel runs once per step, in front of every
 // layer's attention, and a single-sequence step is short enough to see the difference).
 template <typename I>
 __device__ __forceinline__ I block_scan(I v, I *wave_sums, I *total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const I up = __shfl_up(v, off);
-    if (lane >= off) v += up;
-  }
+  v = wave_scan(v);
   if (lane == 63) wave_sums[wave] = v;
   __syncthreads();
   I before = 0, all = 0;
