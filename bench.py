@@ -34,17 +34,17 @@ PCIE5_X16_GBPS = 64.0       # nominal, one direction
 # the algorithmic KV bytes of the same launches: the kernel re-reads nothing, and what exceeds 1 is the
 # rounding of every sequence to whole 16-key tiles plus q, so the ratio carries over to any number of steps
 # of the workload.  Writes (outputs, partial results, the appended rows) are a fixed number of bytes per
-# launch of that batch.  Both are valid only for the kernel source they were taken on: if okv_kernels.hip
+# layer of that batch (a launch covers several layers, 4 in the run the counters are from).  Both are valid only for the kernel source they were taken on: if okv_kernels.hip
 # has changed since, `traffic` is reported as null.
 TRAFFIC_RECORD = {
     "workload": "cfg2",
-    "kernel_sha256": "dfd828e2c63f39d334fc380959b3cb19f3bf0329290bfbb2e4a4b963b8f34c3b",
-    "fetch_kib": 199120.5, "fetch_scale": 2.0000, "algorithmic_bytes": 402915328,   # context 737..800
-    "write_kib": 768.0, "write_scale": 1.0000,
+    "kernel_sha256": "ddab7bbc683403e1513f85a3e6135f44c0d48237bb0ad21a8dd6d6c26d86063d",
+    "fetch_kib": 796252.0, "fetch_scale": 2.0000, "algorithmic_bytes": 4 * 402915328,   # context 737..800
+    "write_kib": 3072.0, "write_scale": 1.0000, "layers": 4,
 }
 
 
-def recorded_traffic(workload, bytes_per_launch):
+def recorded_traffic(workload, bytes_per_launch, layers_per_launch):
     """HBM bytes per launch from the recorded counters, or None if they do not apply."""
     import hashlib
     rec = TRAFFIC_RECORD
@@ -56,7 +56,7 @@ def recorded_traffic(workload, bytes_per_launch):
     if not rec["kernel_sha256"] or sha != rec["kernel_sha256"] or workload != rec["workload"]:
         return None
     fetch_ratio = rec["fetch_kib"] * 1024 * rec["fetch_scale"] / rec["algorithmic_bytes"]
-    return fetch_ratio * bytes_per_launch + rec["write_kib"] * 1024 * rec["write_scale"]
+    return fetch_ratio * bytes_per_launch + rec["write_kib"] * 1024 * rec["write_scale"] * layers_per_launch / rec["layers"]
 
 
 def log(msg):
@@ -211,7 +211,8 @@ def cpu_baseline(st, ctx_now, q_layers, budget_s=15.0):
 
 def run_resident(args, workload=None, steps=None, warmup=None, with_cpu=None, layers=None):
     """An all-resident workload of synth.WORKLOADS: `steps` decode steps of the whole stack, timed end to
-    end, then once more with the split-K launches of every step bracketed by HIP events."""
+    end, then once more with the split-K launches of every step (one for all its layers, where they can run together)
+    bracketed by HIP events."""
     import torch
     from paper_2504_11816_amd import synth
     from paper_2504_11816_amd.harness import Stack
@@ -920,8 +921,8 @@ def main():
         "kv_gbps": res["kv_gbps"], "hbm_frac": res["kv_gbps"] / HBM_PEAK_GBPS,
         "roofline": {"bound": "hbm", "achieved": res["kernel_gbps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": res["kernel_gbps"] / HBM_PEAK_GBPS,
-                     "traffic": recorded_traffic(args.workload, res["kv_bytes_per_launch"]),
-                     "kernel": "attn_split_mfma_kernel",
+                     "traffic": recorded_traffic(args.workload, res["kv_bytes_per_launch"], res["L"] * res["steps"] / max(res["kernel_launches"], 1)),
+                     "kernel": "attn_split_layers_kernel" if res["kernel_launches"] < res["L"] * res["steps"] else "attn_split_mfma_kernel",
                      "avg_us": res["kernel_avg_us"],
                      "launches": res["kernel_launches"], "bytes_per_launch": res["kv_bytes_per_launch"]},
         "cpu_baseline": cpu,
