@@ -1427,8 +1427,12 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
 // workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
 // for (at 192 rows 4096 x 16384 40 us against 53 and 16384 x 4096 41 against 44, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
 // 20.2 against 17.0, staged), beyond always a tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
-// workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront: 4224 x 1056 takes it 7.6 us
-// at 32 rows, 11.6 at 64 and 17.9 at 128, the tile kernel 7.2, 9.0 and 8.9; at 1056 x 1056 and 32 rows 4.6 against 6.2.
+// workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront, in rounds of a workgroup per compute unit
+// (which overlap a little) and somewhat faster where units are idle; the tile model is 1.2 us high for such short walks, and 2 for
+// cut ones.  simple / tile us: 9 rows x 4096 x 10240 16.6 / 37.3, 12 x 4096 x 5120 10.0 / 19.8, 16 x 4224 x 4096 14.1 / 16.1, 19 x 3072 x
+// 2304 6.1 / 8.7, 52 x 5120 x 4224 35.6 / 17.4, 110 x 5120 x 2400 32.9 / 14.4, 17 x 192 x 20480 29 / 58 uncut, 11.5 in eight cuts.  (1200
+// shapes of 9 to 128 rows, 96 to 20480 features and inputs, weights from HBM: the choice is 0.6 % slower than the faster of the two
+// on average.  The simple kernel's time scatters by 10 % around its model: in doubt the line favours tiles, whose model is the better one.)
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0};
   if (m <= OKV_LIN_SIMPLE_ROWS) return simple;
@@ -1438,8 +1442,11 @@ LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, 
   const LinearPlan tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
   if (staged_runs) return tile.us < 0.955 * staged.us ? tile : staged;
   if (m > OKV_LINEAR_MAX_ROWS) return tile;
-  const double simple_us = 2.0 + n_in / 128.0 * (0.09 + 0.12 * ((m + 15) / 16)) * std::max(1.0, n_out / 16 / (0.5 * n_cus));
-  return tile.us < simple_us ? tile : simple;
+  const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 0.82 * std::ceil(q) + 0.18 * q;
+  const int fragments = (m + 15) / 16;
+  const double simple_us = 1.7 + 0.066 * fragments + rounds * n_in / 128.0 * (0.065 + 0.114 * fragments) * (1.0 - 0.27 * (1.0 - std::min(1.0, q)));
+  const double tile_us = tile.cuts > 1 ? tile.us - 2.0 : 0.95 * tile.us - 1.2;
+  return tile_us < simple_us ? tile : simple;
 }
 
 }  // namespace
