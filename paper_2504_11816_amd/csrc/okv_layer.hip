@@ -1286,8 +1286,10 @@ hipError_t launch_linear_mf(const LinearArgs &args, int n_tiles, bool fast, int 
 
 // The forms linear_tile_kernel and linear_wide_kernel (256 x 256, 192 x 128) are built in, with what a stage of 64 inputs takes a
 // workgroup when every compute unit has one (us, MI355X, weights from HBM) and whether a compute unit has room for more.
-// Fitted, with the constants of tile_plan, to 260 shapes of 129 to 1024 rows, 512 to 20480 features and inputs, every form and
-// cut within 30 % of the best timed on each: what they choose is 1.5 % slower than the fastest on average, 25 % at worst.
+// Fitted, with the constants of tile_plan, to 260 shapes of 129 to 1024 rows, 512 to 20480 features and inputs.  On others drawn since
+// (256 to 20480, every form and cut timed) what they choose is slower than the fastest by 1.9 % on average at 193 to 1024 rows (400
+// shapes; 25 % at worst) and by 1.4 % at 1025 to 4096 (310; 33 % at worst, the narrowest outputs).  Without 192 x 128 the latter were 2.2 %:
+// 1100 x 16384 x 4096 170 us instead of 160, 1281 x 4096 x 5120 67.5 instead of 61, 2066 x 2304 x 2304 31.8 instead of 29.5.
 // Wavefronts side by side in the rows (2 x 4) load every weight twice in linear_tile_kernel, which 256 x 192 needs to keep its
 // accumulators in registers; at 128 rows and below one row of wavefronts measured faster (128 x 128 at 1024 x 4096 x 4096: 41 us as 1 x 4,
 // 47 as 2 x 2).
@@ -1298,7 +1300,6 @@ struct TileForm {
 };
 constexpr TileForm kTileForms[] = {{256, 256, 1.442, false}, {256, 192, 1.23, false}, {128, 256, 0.825, false}, {192, 128, 0.7245, false}, {128, 128, 0.5305, true},
                                    {96, 128, 0.416, true},   {64, 128, 0.374, true},  {64, 64, 0.2256, true},   {32, 64, 0.164, true}};
-constexpr int kWideRows = 1024;          // rows up to which 192 x 128 was timed and is taken
 constexpr int kTileFormCount = sizeof(kTileForms) / sizeof(kTileForms[0]);
 
 template <int F, int FM, int FN, int WM, int WN, int WD>
@@ -1396,7 +1397,10 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
 // The tile kernels' form and cuts: 4 us for the launch, the weights at 19.4 MB/us (the part of their way from HBM that
 // the walk does not hide), the walk, and for a cut 2.8 us and the shares at 4.7 MB/us (written and read back); a launch that
 // leaves compute units idle walks up to 8 % faster, and a cut has to be worth 1 %.  Forms of which a compute unit holds several
-// workgroups are taken half way between whole and broken rounds.  (`us` of a cut counts the shares at 3.4 MB/us, which is
+// workgroups are taken half way between whole and broken rounds.  With an odd number of blocks of 32 inputs every other row of x begins
+// in the middle of a line and a 192 x 128 stage takes 12 to 15 % longer (4096 features x 4128 inputs: 1152 rows 47.2 -> 52.8 us,
+// 2304 rows 95 -> 107), a 256 x 192 one 3 %.  In a single round that changes no choice (what is left then, 96 x 128, loses as much); beyond one it is
+// counted: 4051 rows x 4112 x 4128 187 us so, 256 x 192 in two cuts 183.  (`us` of a cut counts the shares at 3.4 MB/us, which is
 // what they take at 129 to 192 rows, where it is compared with the staged kernel's.)
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
@@ -1405,13 +1409,13 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
   double best = 0;
   for (int f = 0; f < kTileFormCount; ++f) {
     const TileForm &form = kTileForms[f];
-    if (form.rows == 192 && m > kWideRows) continue;
     const int64_t tiles = (int64_t)((m + form.rows - 1) / form.rows) * ((n_out + form.cols - 1) / form.cols);
     for (int s = 1; s <= 8; ++s) {
       if (s > 1 && (stages / s < 4 || (int64_t)s * m * n_out * 4 > workspace_bytes)) break;
       const double q = (double)(tiles * s) / n_cus, whole = std::ceil(q);
+      const double stage_us = form.rows == 192 && n_in % 64 && q > 1.0 ? 1.12 * form.stage_us : form.stage_us;
       const double rounds = form.shares_cu ? 0.5 * (whole + std::max(1.0, q)) : whole;
-      double t = 4.0 + weight_mb / 19.4 + rounds * ((stages + s - 1) / s) * form.stage_us * (1.0 - 0.08 * (1.0 - std::min(1.0, q)));
+      double t = 4.0 + weight_mb / 19.4 + rounds * ((stages + s - 1) / s) * stage_us * (1.0 - 0.08 * (1.0 - std::min(1.0, q)));
       const double shares_mb = s > 1 ? (double)s * m * n_out * 4 / 1e6 : 0.0;
       if (s > 1) t += 2.8 + shares_mb / 4.7;
       const double us = t + 0.084 * shares_mb, counts = m <= OKV_LINEAR_MAX_ROWS_STAGED ? us : t, worth = s > 1 ? counts + 0.01 * t : counts;

@@ -21,3 +21,10 @@ def test_wide_tiles(form, cuts, m, n_out, n_in):
     product(m, n_out, n_in, 770 + m, relu=True, residual=True, workspace=not uncut)
     if uncut and n_in <= 160:
         product(m, n_out, n_in, 771 + m, bias=False, workspace=False)
+
+
+# more rows than 1024: in one round of workgroups and in several, rows one more than a tile's, inputs an odd number of blocks of 32 or not
+@pytest.mark.parametrize("m,n_out,n_in", [(1153, 4112, 96), (1153, 4112, 576), (4096, 1040, 544), (2111, 8208, 192)])
+def test_192_by_128_tiles_beyond_1024_rows(m, n_out, n_in):
+    assert binding.okv_linear_plan(m, n_out, n_in, 0) == (2, 192, 128, 1)
+    product(m, n_out, n_in, 780 + m, relu=True, residual=True, workspace=False)
