@@ -1400,8 +1400,11 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
 // workgroups are taken half way between whole and broken rounds.  With an odd number of blocks of 32 inputs every other row of x begins
 // in the middle of a line and a 192 x 128 stage takes 12 to 15 % longer (4096 features x 4128 inputs: 1152 rows 47.2 -> 52.8 us,
 // 2304 rows 95 -> 107), a 256 x 192 one 3 %.  In a single round that changes no choice (what is left then, 96 x 128, loses as much); beyond one it is
-// counted: 4051 rows x 4112 x 4128 187 us so, 256 x 192 in two cuts 183.  (`us` of a cut counts the shares at 3.4 MB/us, which is
-// what they take at 129 to 192 rows, where it is compared with the staged kernel's.)
+// counted: 4051 rows x 4112 x 4128 187 us so, 256 x 192 in two cuts 183.  At up to 192 rows, where there are
+// most cuts, shares beyond the 32 MB that the L2s hold together are counted at 0.2 us more a MB (168 rows x 13824 x 16384 123 us in two
+// cuts, 133 in seven of 65 MB).  (`us` of a cut counts all shares at 3.4 MB/us: for the comparison with the staged kernel at 129 to 192 rows,
+// which is the better for it.  Between tiles it favoured few cuts: 192 rows x 4096 x 16384 44.7 us in four cuts of 96 x 128 against
+// 38.8 in eight of 192 x 128.)
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
   const int stages = (n_in + 63) / 64;
@@ -1418,8 +1421,9 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
       double t = 4.0 + weight_mb / 19.4 + rounds * ((stages + s - 1) / s) * stage_us * (1.0 - 0.08 * (1.0 - std::min(1.0, q)));
       const double shares_mb = s > 1 ? (double)s * m * n_out * 4 / 1e6 : 0.0;
       if (s > 1) t += 2.8 + shares_mb / 4.7;
-      const double us = t + 0.084 * shares_mb, counts = m <= OKV_LINEAR_MAX_ROWS_STAGED ? us : t, worth = s > 1 ? counts + 0.01 * t : counts;
-      if (plan.cuts == 0 || worth < best) best = worth, plan.us = us, plan.form = f, plan.cuts = s;
+      const double past_l2 = m <= OKV_LINEAR_MAX_ROWS_STAGED ? 0.2 * std::max(0.0, shares_mb - 32.0) : 0.0;
+      const double worth = s > 1 ? 1.01 * t + past_l2 : t;
+      if (plan.cuts == 0 || worth < best) best = worth, plan.us = t + 0.084 * shares_mb, plan.form = f, plan.cuts = s;
     }
   }
   return plan;
@@ -1429,7 +1433,7 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
 // where it takes the shape (12288 x 4096 at 128 rows 28 us against the tile kernel's 31, 16384 x 4096 35 against 38; where the
 // inputs are many the tile kernel would win, 4096 x 16384 at 128 rows 35 against 43, with twice the cuts and so twice the
 // workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
-// for (at 192 rows 4096 x 16384 40 us against 53 and 16384 x 4096 41 against 44, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
+// for (at 192 rows 4096 x 16384 39 us against 52 and 16384 x 4096 39 against 43, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
 // 20.2 against 17.0, staged), beyond always a tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
 // workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront, in rounds of a workgroup per compute unit
 // (which overlap a little) and somewhat faster where units are idle; the tile model is 1.2 us high for such short walks, and 2 for
