@@ -23,9 +23,9 @@
  *     q / k / v / out) and keeps it alive until okv_destroy; the library never
  *     frees or reallocates them.  The library itself allocates only small
  *     bookkeeping arrays (O(max_batch * max_blocks_per_seq) integers, as much pinned host
- *     memory to upload them from, a few events) and, with two or more layers and none of
- *     them on the host, up to 64 MiB (or two layers' worth, where that is more) of partial
- *     results for okv_decode_step.
+ *     memory to upload them from, a few events) and, in the first okv_decode_step that
+ *     covers several layers a launch and has no room for their partial results in the
+ *     workspace, up to 64 MiB (or two layers' worth, where that is more) for them.
  *   - Work is enqueued on the two streams given at creation and the calls return
  *     without waiting for the GPU unless stated otherwise.  q / k_new / v_new / out
  *     may be reused once the work enqueued on the compute stream has finished.
@@ -370,9 +370,10 @@ int decode_attn(okv_ctx *ctx, int32_t layer, const void *q, void *out);
  * (attention over a cache with no linear layers in between, benchmarks).  The results are those
  * of the calls one by one, bit for bit.  Where every layer is in HBM and no layer's results or
  * pool overlap what another layer reads or writes, the layers are attended together: a launch
- * covers up to 32 of them (fewer where the batch is cut into pieces and their partial results
- * would take more than 64 MiB, which the library allocates with the context); otherwise the calls
- * are made one after the other, from inside the library.
+ * covers up to 32 of them (fewer where the batch is cut into pieces and there is no room for the
+ * partial results of so many: they are kept in the workspace where it holds those of all the layers
+ * of a launch, else in up to 64 MiB that the library allocates in the first step that needs them);
+ * otherwise the calls are made one after the other, from inside the library.
  *   q, k_new, v_new, out  HOST arrays [n_layers] of DEVICE pointers, each as in kv_append /
  *                         decode_attn
  * Stops at the first error and returns its code; the step is then left open as the failing

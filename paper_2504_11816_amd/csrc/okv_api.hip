@@ -130,9 +130,11 @@ struct okv_ctx {
   bool keep_cached = true;               // the batch's keys and values of all layers fit the memory-side cache
   int64_t max_items = 0;
   float *part_o = nullptr, *part_ml = nullptr;
-  // okv_decode_step over several layers a launch: their partial results side by side, if the batch is cut at all
-  float *layer_parts = nullptr;
+  // okv_decode_step over several layers a launch: their partial results side by side, if the batch is cut at all (room_for_layers)
+  float *layer_parts = nullptr;          // the caller's workspace, or own_parts where that is larger
   int64_t layer_parts_bytes = 0;
+  float *own_parts = nullptr;
+  bool own_parts_asked = false;
   int32_t layers_per_launch = 0;         // of the last okv_decode_step
   std::vector<okv::Buffer> step_buffers; // scratch of step_layers_together
 
@@ -253,8 +255,8 @@ int32_t max_classes_of(const okv_config *c) {
   return 1 + (int32_t)((c->blocks_per_layer - c->resident_blocks + c->chunk_blocks - 1) / c->chunk_blocks);
 }
 
-// Of the partial results that okv_decode_step keeps for the layers of a launch (cfg4-sized batches, 4.2 MB a layer, then go 15
-// layers at a time), or those of two layers where that is more.
+// Of the memory that okv_decode_step takes for the partial results of the layers of a launch where the workspace does not hold them
+// (4.2 MB a layer then go 15 layers at a time), or those of two layers where that is more.
 constexpr int64_t kLayerPartsBytes = 64 << 20;
 
 int64_t bytes_per_item(const okv_config *c) { return (int64_t)c->n_q_heads * (c->head_dim + 2) * 4; }
@@ -494,15 +496,37 @@ int exec_op(okv_ctx *ctx, const Op &op, const void *a0, const void *a1, void *ou
   return fail(ctx, OKV_ESTATE, "unknown pipeline op %d", op.kind);
 }
 
+// Of n layers whose batch is cut, how many have room for their partial results side by side.  The workspace is theirs where it holds
+// them all; otherwise the first step that would cover more asks for memory (once: a context that is refused goes on with
+// the workspace), so a context that never makes such a step holds none.
+int64_t room_for_layers(okv_ctx *ctx, int32_t n) {
+  const int64_t per_item = bytes_per_item(&ctx->cfg), per_layer = ctx->n_items * per_item;
+  if (!ctx->layer_parts) ctx->layer_parts = ctx->part_o, ctx->layer_parts_bytes = ctx->cfg.workspace_bytes;
+  if (n * per_layer > ctx->layer_parts_bytes && !ctx->own_parts_asked) {
+    ctx->own_parts_asked = true;
+    // items of a batch cut into equal stretches: one per sequence and one more per cut
+    const int64_t items = std::min<int64_t>(ctx->max_items, (int64_t)ctx->cfg.max_batch + ctx->max_groups - 1);
+    const int64_t want = std::min(n * items * per_item, std::max(kLayerPartsBytes, 2 * items * per_item));
+    void *p = nullptr;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;         // an allocation is no part of what is being captured, here or elsewhere
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (want > ctx->layer_parts_bytes && hipMalloc(&p, (size_t)want) == hipSuccess) {
+      ctx->own_parts = ctx->layer_parts = static_cast<float *>(p);
+      ctx->layer_parts_bytes = want;
+    } else {
+      (void)hipGetLastError();
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  return std::min<int64_t>(n, ctx->layer_parts_bytes / per_layer);
+}
+
 // Layers of a step that one launch may cover: 1 unless every layer is in HBM, the work list is one of equal stretches, the
 // layers can be attended in any order and no bracket per launch is wanted.  As many as the launch's arguments hold and, where
 // sequences are cut, as there is room for partial results of.  (A bad pointer is left to the calls one by one to refuse.)
 int32_t step_layers_together(okv_ctx *ctx, const void *const *q, const void *const *k, const void *const *v, void *const *out) {
   const int32_t L = ctx->cfg.n_layers;
   if (L < 2 || ctx->any_host || ctx->by_class || !ctx->spans || ctx->profile == 1 || ctx->n_items < 1) return 1;
-  int64_t most = okv::kLayersPerLaunch;
-  if (ctx->need_merge) most = std::min(most, ctx->layer_parts_bytes / (ctx->n_items * bytes_per_item(&ctx->cfg)));
-  if (most < 2) return 1;
   const okv::PoolShape &s = ctx->shape;
   const uintptr_t q_bytes = (uintptr_t)ctx->B * s.H * s.D * 2, kv_bytes = (uintptr_t)ctx->B * s.G * s.D * 2;
   const uintptr_t out_bytes = q_bytes * (ctx->cfg.out_dtype ? 2 : 1);
@@ -522,7 +546,8 @@ int32_t step_layers_together(okv_ctx *ctx, const void *const *q, const void *con
     add(ctx->dev_pool[l], (uintptr_t)ctx->pool_bytes, true);
   }
   if (!okv::layers_independent(ctx->step_buffers)) return 1;
-  return (int32_t)std::min<int64_t>(most, L);
+  const int32_t most = std::min(L, okv::kLayersPerLaunch);
+  return ctx->need_merge ? (int32_t)std::max<int64_t>(1, room_for_layers(ctx, most)) : most;
 }
 
 int exec_ops(okv_ctx *ctx, const std::vector<Op> &ops, const void *a0, const void *a1, void *out) {
@@ -990,18 +1015,6 @@ int okv_create(const okv_config *cfg, okv_ctx **out) {
   OKV_TRY_CREATE(hipMalloc(&ctx->d_pair_head, (size_t)max_pairs(ctx->max_waves) * okv::kPairHeadBytes));
   OKV_TRY_CREATE(hipMemset(ctx->d_pair_head, 0, (size_t)max_pairs(ctx->max_waves) * okv::kPairHeadBytes));
   OKV_TRY_CREATE(hipMalloc(&ctx->d_plan, 4 * sizeof(int32_t)));
-  if (L >= 2 && !any_host && !by_class) {
-    // items of a batch cut into equal stretches: one per sequence and one more per cut
-    const int64_t most = std::min<int64_t>(max_items, (int64_t)cfg->max_batch + ctx->max_groups - 1) * per_item;
-    const int64_t want = std::min(std::min(L, okv::kLayersPerLaunch) * most, std::max(kLayerPartsBytes, 2 * most));
-    void *p = nullptr;
-    if (hipMalloc(&p, (size_t)want) == hipSuccess) {
-      ctx->layer_parts = static_cast<float *>(p);
-      ctx->layer_parts_bytes = want;
-    } else {
-      (void)hipGetLastError();                           // steps whose batch is cut then go layer by layer
-    }
-  }
   // What a batch's tables and an ordinary prompt's tiles are uploaded from is had here: allocating it (and growing it) in
   // the first calls made a new context's first batch and prompt 0.4 ms slower.
   const int64_t tiles = (int64_t)cfg->max_batch * (((int64_t)ctx->cap_tokens + 15) / 16) * (int64_t)sizeof(int4);
@@ -1038,7 +1051,7 @@ int okv_destroy(okv_ctx *ctx) {
   (void)hipFree(ctx->d_item_desc);
   (void)hipFree(ctx->d_group_first);
   (void)hipFree(ctx->d_pair_head);
-  (void)hipFree(ctx->layer_parts);
+  (void)hipFree(ctx->own_parts);
   if (ctx->h_up) (void)hipHostFree(ctx->h_up);
   (void)hipFree(ctx->d_plan);
   (void)hipFree(ctx->d_items_dump);

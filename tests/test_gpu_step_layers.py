@@ -6,6 +6,9 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2504_11816_amd import synth
+from paper_2504_11816_amd.harness import Stack
+
 from gpu_util import build_stack, make_inputs
 
 pytestmark = pytest.mark.gpu
@@ -32,6 +35,48 @@ def same_steps(n_steps, together, **kw):
         np.testing.assert_array_equal(sts[0].read_pool(l).view(np.uint16), sts[1].read_pool(l).view(np.uint16))
     assert sts[0].ctx.okv_get_ctx_lens().tolist() == sts[1].ctx.okv_get_ctx_lens().tolist()
     for st in sts:
+        st.close()
+
+
+def free_mib():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0] / (1 << 20)
+
+
+def test_memory_for_partial_results_is_had_by_the_first_step_that_needs_it():
+    # 12 layers of 128 sequences, 64 heads of 128: 57 MB of partial results.  Contexts that never cover several layers of a cut
+    # batch by a launch, or whose workspace holds those of all layers, take none of it.
+    kw = dict(L=12, H=64, G=64, d=128, T=16, ctx_before=[20 + b % 30 for b in range(128)], cap_tokens=64, seed=5)
+    one_layer = 128 + 1024 // 64 - 1                       # most items
+    before = free_mib()
+    small = [build_stack(**kw), build_stack(split_tokens=64, **kw)]
+    wide = Stack(L=12, H=64, G=64, d=128, B=128, T=16, cap_tokens=64, blocks_per_layer=128 * 4 + 3, workspace_items=12 * one_layer)
+    for l in range(12):
+        wide.fill_pool(l, synth.stream_seed(5, synth.TENSOR_POOL, l))
+    wide.set_batch(np.asarray(kw["ctx_before"], np.int32), small[0].block_table)
+    q, k, v, out = make_inputs(small[0], 6, 0, small[0].device)
+    got = [[torch.full_like(o, float("nan")) for o in out] for _ in range(3)]
+    torch.cuda.synchronize()
+    print(f"{before - free_mib():.0f} MiB with three contexts", flush=True)
+    have = free_mib()
+    small[0].step(q, k, v, out)
+    wide.step_bound(wide.bind_step(q, k, v, got[0]))
+    small[1].step_bound(small[1].bind_step(q, k, v, got[1]))
+    for st in (small[0], wide, small[1]):
+        st.synchronize()
+    assert wide.ctx.okv_layers_per_launch() == 12 and small[1].ctx.okv_layers_per_launch() == 1
+    assert abs(have - free_mib()) < 8
+    for l in range(12):
+        np.testing.assert_array_equal(bits(out[l]), bits(got[0][l]))
+    for st in (small[0], wide):                            # the same step again, now several layers a launch in both
+        o = got[2] if st is wide else out
+        st.step_bound(st.bind_step(q, k, v, o))
+        st.synchronize()
+    assert small[0].ctx.okv_layers_per_launch() == 12
+    assert 40 < have - free_mib() < 70
+    for l in range(12):
+        np.testing.assert_array_equal(bits(out[l]), bits(got[2][l]))
+    for st in small + [wide]:
         st.close()
 
 
