@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2504_11816_amd import synth
+from paper_2504_11816_amd import binding, synth
 from paper_2504_11816_amd.harness import Stack
 
 from gpu_util import build_stack, make_inputs
@@ -18,7 +18,7 @@ def bits(t):
     return t.cpu().numpy().view(np.uint8)
 
 
-def same_steps(n_steps, together, **kw):
+def same_steps(n_steps, together, cut=None, **kw):
     sts = [build_stack(**kw) for _ in range(2)]
     L = kw["L"]
     for step in range(n_steps):
@@ -29,6 +29,8 @@ def same_steps(n_steps, together, **kw):
         for st in sts:
             st.synchronize()
         assert sts[1].ctx.okv_layers_per_launch() in (together if isinstance(together, tuple) else (together,))
+        if cut is not None:
+            assert (len(sts[1].ctx.okv_worklist(from_device=False)) > len(kw["ctx_before"])) == cut
         for l in range(L):
             np.testing.assert_array_equal(bits(one[l]), bits(two[l]), err_msg=f"step {step} layer {l}")
     for l in range(L):
@@ -85,7 +87,7 @@ RAGGED = [1, 15, 16, 17, 31, 33, 200, 47, 0, 64, 129, 500]
 
 @pytest.mark.parametrize("L,H,G,d,T,ctx,out_dtype,together", [
     (2, 8, 8, 128, 16, RAGGED, 0, 2), (3, 8, 2, 64, 16, RAGGED, 1, 3), (5, 12, 12, 64, 0, RAGGED, 0, 5),
-    (4, 16, 1, 128, 0, [700], 1, 4), (3, 64, 64, 128, 16, [33 + 3 * b for b in range(20)], 0, 3),       # one wavefront per pair
+    (4, 16, 1, 128, 0, [700], 1, 4), (3, 64, 64, 128, 16, [33 + 3 * b for b in range(20)], 0, 3),
     (3, 32, 32, 128, 64, [180 + b for b in range(24)], 0, 3), (3, 32, 32, 64, 0, [1500, 1800], 1, 3),
     (2, 32, 32, 128, 0, [400] * 32, 0, 2),                       # a stretch a sequence: nothing to merge
     (35, 4, 2, 64, 16, [100, 40], 0, 32),                        # more layers than a launch takes
@@ -94,6 +96,24 @@ RAGGED = [1, 15, 16, 17, 31, 33, 200, 47, 0, 64, 129, 500]
 def test_same_bits_as_layer_by_layer(L, H, G, d, T, ctx, out_dtype, together):
     print(f"L={L} H={H} G={G} d={d} T={T} B={len(ctx)} out={out_dtype}", flush=True)
     same_steps(3, together, L=L, H=H, G=G, d=d, T=T, ctx_before=ctx, cap_tokens=max(ctx) // 64 * 64 + 128, out_dtype=out_dtype, seed=811)
+
+
+# Launches of one wavefront per pair at d = 128, which go from layer to layer and by 0.382 of the stretches to another pair each
+# time: cut and not, paged and not, with keys that stay cached and keys that do not, over enough layers for the pairs to wrap round.
+@pytest.mark.parametrize("L,H,G,T,ctx,out_dtype,cut,cached", [
+    (3, 32, 32, 16, [1700, 1300, 1450], 0, True, True), (5, 32, 32, 16, [1700, 1300, 1450], 1, True, False),
+    (3, 32, 8, 16, [8200, 300, 9000], 0, True, True), (4, 64, 8, 0, [9000, 7900], 0, True, False),
+    (4, 32, 8, 64, [130 + 37 * b % 471 for b in range(128)], 1, True, False),        # ragged, most sequences cut once
+    (3, 40, 40, 0, [900 + 111 * b % 1000 for b in range(4)], 0, True, False),          # wavefronts that do not fill the last workgroup
+    (3, 32, 32, 16, [124] * 32, 0, False, True), (6, 32, 32, 16, [180] * 32, 1, False, False)])
+def test_one_wavefront_a_pair_walks_the_layers(L, H, G, T, ctx, out_dtype, cut, cached):
+    print(f"L={L} H={H} G={G} T={T} B={len(ctx)} out={out_dtype}", flush=True)
+    groups = 4 * torch.cuda.get_device_properties(0).multi_processor_count // G
+    for n in (1, 2, 3):
+        lens = np.asarray(ctx) + n
+        assert binding.okv_waves_per_pair(128, G, lens, groups) == 1
+        assert (int(lens.sum()) * G * 128 * 4 * L <= 256000000) == cached
+    same_steps(3, L, cut=cut, L=L, H=H, G=G, d=128, T=T, ctx_before=ctx, cap_tokens=max(ctx) // 64 * 64 + 128, out_dtype=out_dtype, seed=811)
 
 
 def test_a_split_size_or_host_layers_go_layer_by_layer():
