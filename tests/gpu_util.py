@@ -77,14 +77,17 @@ def build_stack(*, L, H, G, d, T, ctx_before, cap_tokens=None, on_host=None, out
     return st
 
 
-def run_and_check(st, n_steps=1, seed=0, pairs=None, check_layers=None):
-    """Run n_steps decode steps; after each, compare every (or the sampled)
-    output with the oracle.  Returns the list of GPU outputs per step."""
+def run_and_check(st, n_steps=1, seed=0, pairs=None, check_layers=None, at_once=False):
+    """Run n_steps decode steps, layer by layer or each in one call; after each, compare every (or
+    the sampled) output with the oracle.  Returns the list of GPU outputs per step."""
     dev = st.device
     results = []
     for step in range(n_steps):
         q, k, v, out = make_inputs(st, seed, step, dev)
-        st.step(q, k, v, out)
+        if at_once:
+            st.step_bound(st.bind_step(q, k, v, out))
+        else:
+            st.step(q, k, v, out)
         st.synchronize()
         outs = [o.float().cpu().numpy() for o in out]
         results.append(outs)

@@ -1,6 +1,6 @@
 """Sequences in very different numbers of pieces: the launch that joins them takes the first four rows and the first 64 maxima
-and weights of a sequence ahead of the rest.  Every output against the fp64 oracle at the usual tolerance, resident and stepped
-through several layers at once."""
+and weights of a sequence ahead of the rest.  Every output against the fp64 oracle at the usual tolerance, of a single layer and
+of three that one launch attends and one launch joins."""
 import pytest
 
 from gpu_util import build_stack, run_and_check
@@ -17,5 +17,6 @@ def test_pieces(d, H, G, T, ctx):
     print(f"d={d} H={H} G={G} T={T} ctx={ctx}", flush=True)
     for L in (1, 3):
         st = build_stack(L=L, H=H, G=G, d=d, T=T, ctx_before=list(ctx), cap_tokens=cap, out_dtype=L & 1, seed=81)
-        run_and_check(st, n_steps=2, seed=83, pairs=[(b, h) for b in range(len(ctx)) for h in range(H)])
+        run_and_check(st, n_steps=2, seed=83, pairs=[(b, h) for b in range(len(ctx)) for h in range(H)], at_once=L > 1)
+        assert st.ctx.okv_layers_per_launch() == (L if L > 1 else 0) and len(st.ctx.okv_worklist(from_device=False)) > len(ctx)
         st.close()
