@@ -787,20 +787,19 @@ struct WideShape {
   static constexpr int kXBuffers = NX, kWBuffers = 2 * NX - 2;        // stages of x, half stages of weights
   static constexpr int kXBytes = kRows * 128, kWBytes = kCols * 64;
   static constexpr int kAhead = FM / 2;                  // fragments of x a wavefront reads ahead; the barrier is as far into a half stage
-  // loads of a wavefront: LX per stage of x; of the half stage's FN WN pieces of weights LW, and one less where the
-  // pieces do not come out even and the wavefront is past the first kMore
-  static constexpr int LX = kRows / 8 / kWaves, LW = (FN * WN + kWaves - 1) / kWaves, kMore = FN * WN - (LW - 1) * kWaves;
-  // How many loads a wavefront with lw pieces may have outstanding for the next half stage to have landed: those issued after its last one,
-  // which are kWBuffers - 3 half stages of weights and the stages of x among them (one more in front of an odd half)
-  static constexpr int outstanding(int lw, int odd) { return (kWBuffers - 3) * lw + (kWBuffers - (odd ? 2 : 4)) / 2 * LX; }
-  static constexpr int first(int lw) { return (kWBuffers - 2) * lw + (kXBuffers - 2) * LX; }        // and in front of the first half stage
+  // loads of a wavefront: LX per stage of x, LW of the half stage's FN WN pieces of weights
+  static constexpr int LX = kRows / 8 / kWaves, LW = FN * WN / kWaves;
+  // How many loads may be outstanding for the next half stage to have landed: those issued after its last one, which are
+  // kWBuffers - 3 half stages of weights and the stages of x among them (one more in front of an odd half)
+  static constexpr int outstanding(int odd) { return (kWBuffers - 3) * LW + (kWBuffers - (odd ? 2 : 4)) / 2 * LX; }
+  static constexpr int first() { return (kWBuffers - 2) * LW + (kXBuffers - 2) * LX; }        // and in front of the first half stage
   static constexpr int kOutStride = 16 * FN + 4;         // floats between two rows of a wavefront's results in LDS
   static constexpr int kOutBytes = kWaves * 32 * kOutStride * 4;
   static constexpr int kStageBytes = kXBuffers * kXBytes + kWBuffers * kWBytes;
   static constexpr int kLds = kStageBytes > kOutBytes ? kStageBytes : kOutBytes;
-  static_assert(FM % 2 == 0 && NX >= 3 && kRows % (8 * kWaves) == 0, "fragments and staging instructions come out even");
+  static_assert(FM % 2 == 0 && NX >= 3 && kRows % (8 * kWaves) == 0 && FN * WN % kWaves == 0, "fragments and staging instructions come out even");
   static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
-  static_assert(outstanding(LW, 1) <= 63 && first(LW) <= 63, "the wait for a half stage must fit the load counter");
+  static_assert(outstanding(1) <= 63 && first() <= 63, "the wait for a half stage must fit the load counter");
 };
 
 // A barrier that does not wait for this wavefront's reads from LDS (__syncthreads does): what they read is not overwritten behind it.
@@ -865,18 +864,14 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
   for (int j = 0; j < S::LW; ++j)
     woff[j] = (uint32_t)min(wave + j * S::kWaves, n_tiles - 1 - tile0) * (uint32_t)n_kb * 1024 + lane * 16;
   const char *wbase = reinterpret_cast<const char *>(w) + (size_t)tile0 * n_kb * 1024;
-  const bool more = S::kMore == S::kWaves || wave < S::kMore;          // has LW pieces of a half stage
   auto stage_w = [&](int h, int buf) {
     const char *src = wbase + (size_t)min(2 * stage_at(h >> 1) + (h & 1), n_kb - 1) * 1024;
     const uint32_t dst = lds0 + kW0 + (uint32_t)buf * S::kWBytes + (uint32_t)wave * 1024;
 #pragma unroll
-    for (int j = 0; j < S::LW; ++j)
-      if (j < S::LW - 1 || more) load_to_lds(src, woff[j], dst + j * S::kWaves * 1024);
+    for (int j = 0; j < S::LW; ++j) load_to_lds(src, woff[j], dst + j * S::kWaves * 1024);
   };
   auto landed = [&](auto odd) {                          // the next half stage: this wavefront's share of it
-    constexpr int O = decltype(odd)::value;
-    if (more) __builtin_amdgcn_s_waitcnt(vmcnt_only(S::outstanding(S::LW, O)));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_only(S::outstanding(S::LW - 1, O)));
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(S::outstanding(decltype(odd)::value)));
   };
 
   const int rr = lane & 15, q = lane >> 4;
@@ -906,8 +901,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
   const Sink sink(a);
   sink.arrive();
   sink.shares_arrive();
-  if (more) __builtin_amdgcn_s_waitcnt(vmcnt_only(S::first(S::LW)));
-  else __builtin_amdgcn_s_waitcnt(vmcnt_only(S::first(S::LW - 1)));
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(S::first()));
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kAhead; ++j) xf[j] = read_x(0, j);
