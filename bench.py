@@ -255,6 +255,12 @@ def run_resident(args, workload=None, steps=None, warmup=None, with_cpu=None, la
     log(f"[bench] {steps} steps in {dt * 1e3:.1f} ms, split {split}")
     k_s, k_n = kernel_time(st, ctx0, table, inputs, steps, per_step=True)
     log(f"[bench] split-K kernel: {k_n} launches, {k_s / max(k_n, 1) * 1e6:.1f} us average")
+    # What a decoder gets, whose layers wait for one another: the same step with one output buffer for every layer, which the
+    # library attends one after the other (at most 20 steps, in the middle of the timed ones)
+    n_apart = min(steps, 20)
+    q, k_new, v_new, out = inputs
+    dt_apart = timed_steps(st, ctx0 + (steps - n_apart) // 2, table, (q, k_new, v_new, [out[0]] * L), n_apart, min(warmup, n_apart))
+    log(f"[bench] layer by layer: {dt_apart / n_apart * 1e3:.3f} ms a step")
     res = {
         "workload": workload,
         "tokens_per_s": B * steps / dt, "ms_per_step": dt / steps * 1e3, "kv_gbps": kv_bytes / dt / 1e9,
@@ -262,6 +268,8 @@ def run_resident(args, workload=None, steps=None, warmup=None, with_cpu=None, la
         "kernel_gbps": kv_bytes / k_s / 1e9, "kernel_frac": kv_bytes / k_s / 1e9 / HBM_PEAK_GBPS,
         "kernel_avg_us": k_s / max(k_n, 1) * 1e6, "kernel_launches": k_n,
         "kernel_time_includes_merge_pass": n_items > B, "settle_s": settled,
+        "layers_per_launch": L * steps / max(k_n, 1), "layer_by_layer": {"ms_per_step": dt_apart / n_apart * 1e3, "tokens_per_s": B * n_apart / dt_apart,
+                                                                       "steps": n_apart},
         "kv_bytes_per_launch": kv_bytes / max(k_n, 1), "split_tokens": split, "work_items": n_items, "steps": steps,
         "B": B, "L": L, "H": H, "G": G, "d": d, "T": T, "first_step": first_step + 1, "workload_steps": w["steps"],
         "ctx_desc": (f"{int(ctx_first.max())}..{int(ctx_first.max()) + steps - 1}" if not w["ragged"] else
@@ -925,6 +933,7 @@ def main():
                      "kernel": "attn_split_layers_kernel" if res["kernel_launches"] < res["L"] * res["steps"] else "attn_split_mfma_kernel",
                      "avg_us": res["kernel_avg_us"],
                      "launches": res["kernel_launches"], "bytes_per_launch": res["kv_bytes_per_launch"]},
+        "layers_per_launch": res["layers_per_launch"], "layer_by_layer": res["layer_by_layer"],
         "cpu_baseline": cpu,
         "offload": off,
         "offload_blocks": off_blocks,
