@@ -775,12 +775,13 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(1,
 // and the next half stage's weights under them; one barrier per half stage, in its middle: behind it the next half stage is in
 // LDS and the buffers of the one before are free, so the reads ahead go on across half stages.
 //
-// What bounds it: 256 x 256 the matrix cores and LDS beside them (1024 rows x 16384 x 4096 1.2 PFLOP/s; with nothing loaded
-// 1.45), 192 x 128 what a compute unit takes in.  us, the kernel above with the same tiles -> this one: 256 x 256, 1024 x 16384 x 4096
-// 119 -> 114.5 and 4096 x 16384 in four cuts 136 -> 129; 192 x 128, 384 x 12288 x 4096 54 -> 49 (96 x 128 above: 59), 192 x 4096 x 16384
-// in eight cuts 45 -> 40.  Not for the other forms: 128 x 256 is 4 % slower so, 128 x 128 9 %, the smallest 10 %, whose walk is
-// the latency of a half stage (two barriers a stage); 256 x 192, whose pieces do not come out even, 2 %.  Four wavefronts of 128 x 128,
-// whole stages of weights, nontemporal weights and more stages in flight change nothing.
+// What bounds it: 256 x 256 the matrix cores, busy in 66 % of a compute unit's cycles (1024 rows x 16384 x 4096 1.2 PFLOP/s; with nothing
+// loaded 1.45), LDS in 27 %, of which conflicts are 2 %; 192 x 128 what a compute unit takes in (matrix cores 41 to 48 %, LDS 30 to
+// 34 %).  us, the kernel above with the same tiles -> this one: 256 x 256, 1024 x 16384 x 4096 119 -> 114.5 and 4096 x 16384 in four cuts
+// 136 -> 129; 192 x 128, 384 x 12288 x 4096 54 -> 50 (96 x 128 above: 59), 192 x 4096 x 16384 in eight cuts, with the launch that
+// adds the shares, 42 (96 x 128 above, four cuts: 45).  Not for the other forms: 128 x 256 is 4 % slower so, 128 x 128 9 %, the smallest 10 %,
+// whose walk is the latency of a half stage (two barriers a stage); 256 x 192, whose pieces do not come out even, 2 %.  Four wavefronts of
+// 128 x 128, whole stages of weights, nontemporal weights and more stages in flight change nothing.
 template <int FM, int FN, int WM, int WN, int NX>
 struct WideShape {
   static constexpr int kWaves = WM * WN, kThreads = kWaves * 64, kRows = 16 * FM * WM, kCols = 16 * FN * WN;
@@ -1394,11 +1395,10 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
 // workgroups are taken half way between whole and broken rounds.  With an odd number of blocks of 32 inputs every other row of x begins
 // in the middle of a line and a 192 x 128 stage takes 12 to 15 % longer (4096 features x 4128 inputs: 1152 rows 47.2 -> 52.8 us,
 // 2304 rows 95 -> 107), a 256 x 192 one 3 %.  In a single round that changes no choice (what is left then, 96 x 128, loses as much); beyond one it is
-// counted: 4051 rows x 4112 x 4128 187 us so, 256 x 192 in two cuts 183.  At up to 192 rows, where there are
-// most cuts, shares beyond the 32 MB that the L2s hold together are counted at 0.2 us more a MB (168 rows x 13824 x 16384 123 us in two
-// cuts, 133 in seven of 65 MB).  (`us` of a cut counts all shares at 3.4 MB/us: for the comparison with the staged kernel at 129 to 192 rows,
-// which is the better for it.  Between tiles it favoured few cuts: 192 rows x 4096 x 16384 44.7 us in four cuts of 96 x 128 against
-// 38.8 in eight of 192 x 128.)
+// counted: 4051 rows x 4112 x 4128 187 us so, 256 x 192 in two cuts 183.  At up to 192 rows shares take
+// longer, 3.9 MB/us between tiles (`worth`) and, in the comparison with the staged kernel, 3.4 (`us`).  The 3.4 between tiles favoured few cuts: 192
+// rows x 4096 x 16384 45.0 us in four cuts of 96 x 128 against 42.5 in eight of 192 x 128, 180 x 5120 x 11008 40.8 in three against 37.8 in
+// six, 168 x 4224 x 4096 22.1 uncut against 18.4 in three.  With none dearer, 13824-wide products go from two cuts to seven and 8 % slower.
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
   const int stages = (n_in + 63) / 64;
@@ -1415,8 +1415,7 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
       double t = 4.0 + weight_mb / 19.4 + rounds * ((stages + s - 1) / s) * stage_us * (1.0 - 0.08 * (1.0 - std::min(1.0, q)));
       const double shares_mb = s > 1 ? (double)s * m * n_out * 4 / 1e6 : 0.0;
       if (s > 1) t += 2.8 + shares_mb / 4.7;
-      const double past_l2 = m <= OKV_LINEAR_MAX_ROWS_STAGED ? 0.2 * std::max(0.0, shares_mb - 32.0) : 0.0;
-      const double worth = s > 1 ? 1.01 * t + past_l2 : t;
+      const double worth = s > 1 ? 1.01 * t + (m <= OKV_LINEAR_MAX_ROWS_STAGED ? 0.045 * shares_mb : 0.0) : t;
       if (plan.cuts == 0 || worth < best) best = worth, plan.us = t + 0.084 * shares_mb, plan.form = f, plan.cuts = s;
     }
   }
@@ -1427,7 +1426,7 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
 // where it takes the shape (12288 x 4096 at 128 rows 28 us against the tile kernel's 31, 16384 x 4096 35 against 38; where the
 // inputs are many the tile kernel would win, 4096 x 16384 at 128 rows 35 against 43, with twice the cuts and so twice the
 // workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
-// for (at 192 rows 4096 x 16384 39 us against 52 and 16384 x 4096 39 against 43, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
+// for (at 192 rows 4096 x 16384 42 us against 53 and 16384 x 4096 40 against 43, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
 // 20.2 against 17.0, staged), beyond always a tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
 // workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront, in rounds of a workgroup per compute unit
 // (which overlap a little) and somewhat faster where units are idle; the tile model is 1.2 us high for such short walks, and 2 for
