@@ -1399,6 +1399,8 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
 // longer, 3.9 MB/us between tiles (`worth`) and, in the comparison with the staged kernel, 3.4 (`us`).  The 3.4 between tiles favoured few cuts: 192
 // rows x 4096 x 16384 45.0 us in four cuts of 96 x 128 against 42.5 in eight of 192 x 128, 180 x 5120 x 11008 40.8 in three against 37.8 in
 // six, 168 x 4224 x 4096 22.1 uncut against 18.4 in three.  With none dearer, 13824-wide products go from two cuts to seven and 8 % slower.
+// Shares beyond 134 MB, which with the weights no longer stay in the memory-side cache until they are added, take 0.3 us a MB more: 3507 rows x 6144
+// x 8192 370 us in three cuts (258 MB), 324 uncut, 1405 x 16384 x 12288 544 in two, 504 uncut.
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
   const int stages = (n_in + 63) / 64;
@@ -1415,7 +1417,8 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
       double t = 4.0 + weight_mb / 19.4 + rounds * ((stages + s - 1) / s) * stage_us * (1.0 - 0.08 * (1.0 - std::min(1.0, q)));
       const double shares_mb = s > 1 ? (double)s * m * n_out * 4 / 1e6 : 0.0;
       if (s > 1) t += 2.8 + shares_mb / 4.7;
-      const double worth = s > 1 ? 1.01 * t + (m <= OKV_LINEAR_MAX_ROWS_STAGED ? 0.045 * shares_mb : 0.0) : t;
+      const double dearer = 0.3 * std::max(0.0, shares_mb - 134.0) + (m <= OKV_LINEAR_MAX_ROWS_STAGED ? 0.045 * shares_mb : 0.0);
+      const double worth = s > 1 ? 1.01 * t + dearer : t;
       if (plan.cuts == 0 || worth < best) best = worth, plan.us = t + 0.084 * shares_mb, plan.form = f, plan.cuts = s;
     }
   }

@@ -23,6 +23,8 @@ def test_the_faster_kernel(m, n_out, n_in, workspace, simple_us, tile_us):
 
 # rows, features, inputs, the form and cuts that measured faster than the next choice by 5 % and more, with the launch that adds the shares
 @pytest.mark.parametrize("m,n_out,n_in,form,cuts", [(192, 4096, 16384, (192, 128), 8), (180, 5120, 11008, (192, 128), 6),
-                                                    (1100, 16384, 4096, (192, 128), 1), (1281, 4096, 5120, (192, 128), 1)])
+                                                    (1100, 16384, 4096, (192, 128), 1), (1281, 4096, 5120, (192, 128), 1),
+                                                    # three, two and four cuts of 256 x 256 would leave 258, 181 and 187 MB of shares
+                                                    (3507, 6144, 8192, (256, 192), 1), (1842, 12288, 10240, (256, 192), 1), (952, 12288, 20480, (256, 192), 1)])
 def test_the_faster_tiles(m, n_out, n_in, form, cuts):
     assert binding.okv_linear_plan(m, n_out, n_in) == (2, *form, cuts)
