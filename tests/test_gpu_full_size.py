@@ -1,7 +1,8 @@
 """The benchmark workloads at their full size and full depth, sampled: every one of the 32 layers, a few
 (sequence, head) pairs per layer, at the steps the measurement plan names, element by element against the fp64
 oracle (max abs error 2e-3 and relative L2 error 1e-2 per output vector: gpu_util.assert_close).  The launch
-configuration is the one bench.py times: split size left to the library, outputs in fp16."""
+configuration is the one bench.py times: split size left to the library, outputs in fp16, and the all-resident workloads
+stepped in one call as well as layer by layer."""
 import numpy as np
 import pytest
 import torch
@@ -38,6 +39,9 @@ def test_cfg2_all_layers_first_middle_and_last_step():
         st.set_batch([ctx_before] * 32, None)
         say(f"  step to context {ctx_before + 1}, split {st.ctx.okv_get_split_tokens()}")
         run_and_check(st, n_steps=1, seed=510 + ctx_before, pairs=pairs)
+        st.set_batch([ctx_before] * 32, None)
+        run_and_check(st, n_steps=1, seed=511 + ctx_before, pairs=pairs, at_once=True)
+        assert st.ctx.okv_layers_per_launch() == 32
     st.close()
     torch.cuda.empty_cache()
 
@@ -63,6 +67,8 @@ def test_cfg4_all_layers_ragged_grouped_heads():
     say(f"  contexts {int(ctx.min()) + 1}..{int(ctx.max()) + 1}, stretches of {st.ctx.okv_get_split_tokens()} keys, "
         f"{len(st.ctx.okv_worklist(from_device=False))} items")
     run_and_check(st, n_steps=2, seed=532, pairs=[(shortest, 0), (longest, 31), (64, 13), (1, 20)])
+    run_and_check(st, n_steps=1, seed=534, pairs=[(shortest, 0), (longest, 31), (64, 13), (1, 20)], at_once=True)
+    assert st.ctx.okv_layers_per_launch() > 1
     st.close()
     torch.cuda.empty_cache()
 
