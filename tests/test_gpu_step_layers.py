@@ -82,6 +82,32 @@ def test_memory_for_partial_results_is_had_by_the_first_step_that_needs_it():
         st.close()
 
 
+def test_the_first_step_that_needs_the_memory_may_be_a_captured_one():
+    kw = dict(L=12, H=32, G=32, d=64, T=16, ctx_before=[300, 1000, 77, 512, 640], cap_tokens=1088, seed=3)
+    sts = [build_stack(**kw) for _ in range(2)]
+    q, k, v, out = make_inputs(sts[0], 5, 0, sts[0].device)
+    two = [torch.full_like(o, float("nan")) for o in out]
+    bound = sts[1].bind_step(q, k, v, two)
+    sts[0].step(q, k, v, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=sts[1].compute_stream):
+        sts[1].step_bound(bound)
+    assert sts[1].ctx.okv_layers_per_launch() == 12 and len(sts[1].ctx.okv_worklist(from_device=False)) > 5
+    graph.replay()                                         # once: a replay is the step for the lengths it was captured with
+    torch.cuda.synchronize()
+    for again in (False, True):                            # then a step of its own
+        if again:
+            sts[0].step(q, k, v, out)
+            sts[1].step_bound(bound)
+            torch.cuda.synchronize()
+        for l in range(12):
+            np.testing.assert_array_equal(bits(out[l]), bits(two[l]))
+            np.testing.assert_array_equal(sts[0].read_pool(l).view(np.uint16), sts[1].read_pool(l).view(np.uint16))
+    for st in sts:
+        st.close()
+
+
 RAGGED = [1, 15, 16, 17, 31, 33, 200, 47, 0, 64, 129, 500]
 
 
