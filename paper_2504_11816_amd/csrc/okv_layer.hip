@@ -190,16 +190,15 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
   const int ntile = blockIdx.x;
   const int kb0 = (int)((int64_t)wave * n_kb / kLinWaves), kb1 = (int)((int64_t)(wave + 1) * n_kb / kLinWaves);
   const int nk = kb1 - kb0;
-  const uint4 *wp = w + ((size_t)ntile * n_kb + kb0) * 64 + lane;
+  const char *const wp = reinterpret_cast<const char *>(w + ((size_t)ntile * n_kb + kb0) * 64);
   // this lane's piece of x for k-block kb and row fragment f: row 16 f + lane % 16, inputs 32 kb + 8 (lane / 16) .. + 7
   const int row = lane & 15, kq = lane >> 4;
-  const int row_pieces = n_in >> 3;
+  const char *const xp = reinterpret_cast<const char *>(x + (size_t)kb0 * 4);
   // Rows past the batch read row 0 instead: a row of x only ever reaches the same row of the
   // result, and those rows are not stored.
-  const uint4 *xp[MF];
+  uint32_t xoff[MF];
 #pragma unroll
-  for (int f = 0; f < MF; ++f)
-    xp[f] = x + (size_t)(f * 16 + row < m ? f * 16 + row : 0) * row_pieces + (size_t)kb0 * 4 + kq;
+  for (int f = 0; f < MF; ++f) xoff[f] = (uint32_t)(f * 16 + row < m ? f * 16 + row : 0) * (uint32_t)n_in * 2 + (uint32_t)kq * 16;
   floatx4 acc[MF];
 #pragma unroll
   for (int f = 0; f < MF; ++f) acc[f] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -211,12 +210,19 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
   // range length at any moment, i.e. from a few of the memory channels at a time (the same shift
   // in the staged kernel below is worth up to 10 % on weights that come from HBM).
   const int rot = nk > 0 ? (int)(((unsigned)ntile * 5u + (unsigned)wave * 11u) % (unsigned)nk) : 0;
+  // Past the last block the last one is asked for again and not used (of x a single line, by every lane): every load is
+  // unconditional, so the waits in front of the blocks are exact.  With the loads of the last round behind conditions each wait had
+  // to cover the case that none of them was made, and waited for those that were: a round trip to HBM at the end of every walk that
+  // is no multiple of D blocks.  us before -> now, weights from HBM: 1 row x 2560 x 2560 6.1 -> 4.2 (3.1 TB/s), 8 rows x 2560 x 2560 6.7 ->
+  // 5.0, 8 x 4224 x 1056 4.9 -> 4.3, 28 x 1056 x 4224 12.2 -> 11.9 (12.8 where lanes ask for their own lines of x again), 4 x 5120 x 13824
+  // 30.7 -> 29.5; whole rounds gain by the loads in fetch_rest, 8 x 4096 x 4096 7.4 -> 7.0.
   auto load = [&](int slot, int k) {                           // k: position in this wavefront's walk
-    int kk = k + rot;
+    int kk = min(k, nk - 1) + rot;
     kk = kk >= nk ? kk - nk : kk;                              // block index relative to kb0
-    wbuf[slot] = load_weight<NT>(wp + (size_t)kk * 64);
+    wbuf[slot] = load_weight<NT>(reinterpret_cast<const uint4 *>(wp + (size_t)(uint32_t)kk * 1024 + lane * 16));
+    const uint32_t own = k < nk ? ~0u : 0u;
 #pragma unroll
-    for (int f = 0; f < MF; ++f) xbuf[slot][f] = xp[f][(size_t)kk * 4];
+    for (int f = 0; f < MF; ++f) xbuf[slot][f] = *reinterpret_cast<const uint4 *>(xp + (size_t)(uint32_t)kk * 64 + (xoff[f] & own));
   };
   auto use = [&](int slot) {
     const uint4 w = wbuf[slot];
@@ -230,52 +236,41 @@ __global__ __launch_bounds__(kLinWaves * 64) void linear_kernel(const uint4 *w, 
   // This thread's results are feature threadIdx.x % 16 of rows threadIdx.x / 16 + 16 f: what is added to them, asked for
   // behind the first weights.
   const Sink sink(a);
-  _Float16 add_bias = 0, add_residual[MF];
+  _Float16 add_bias, add_residual[MF];
   const int out_row = (int)threadIdx.x >> 4, out_feature = ntile * 16 + ((int)threadIdx.x & 15);
   uint64_t out, at;
   auto fetch_rest = [&]() {
+    // (without them, weights: a branch around a load waits for it, and for all loads before it, where the paths meet)
     sink.arrive();
-    if (bias) add_bias = bias[out_feature];
+    add_bias = load_at<_Float16>((uint64_t)(bias ? bias + out_feature : reinterpret_cast<const _Float16 *>(w)));
 #pragma unroll
     for (int f = 0; f < MF; ++f) {
       sink.place(min(16 * f + out_row, m - 1), out_feature, out, at);
-      add_residual[f] = sink.residual ? load_at<_Float16>(sink.residual + at) : (_Float16)0;
+      add_residual[f] = load_at<_Float16>(sink.residual ? sink.residual + at : (uint64_t)w);
     }
   };
-  int k = 0;
-  if (nk >= 2 * D) {
+  if (nk > 0) {
 #pragma unroll
     for (int i = 0; i < D; ++i) {
       load(i, i);
       __builtin_amdgcn_sched_barrier(0);    // oldest first: the loop waits for the loads in this order
     }
-    fetch_rest();
-    __builtin_amdgcn_sched_barrier(0);
-    for (; k + 2 * D <= nk; k += D) {                          // steady state: no conditional loads
-#pragma unroll
-      for (int i = 0; i < D; ++i) {
-        use(i);
-        __builtin_amdgcn_sched_barrier(0);
-        load(i, k + D + i);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < D; ++i)
-      if (i < nk) load(i, i);
-    fetch_rest();
   }
-  // drain: at most 2 D - 1 blocks are left, the first D of them in flight
+  fetch_rest();
+  __builtin_amdgcn_sched_barrier(0);
+  int k = 0;
+  for (; k + D < nk; k += D) {
 #pragma unroll
-  for (int i = 0; i < D; ++i)
-    if (k + i < nk) {
+    for (int i = 0; i < D; ++i) {
       use(i);
-      if (k + D + i < nk) load(i, k + D + i);
+      __builtin_amdgcn_sched_barrier(0);
+      load(i, k + D + i);
+      __builtin_amdgcn_sched_barrier(0);
     }
+  }
 #pragma unroll
   for (int i = 0; i < D; ++i)
-    if (k + D + i < nk) use(i);
+    if (k + i < nk) use(i);
 
   // add the wavefronts' shares and finish: result element (row 16 f + 4 (lane / 16) + r, feature lane % 16)
   // sits in acc[f][r] of that lane

@@ -1,0 +1,19 @@
+"""The product kernel for few rows where its walk over the inputs can go wrong: wavefronts without a block of 32 inputs, with one, with
+one less and one more than the blocks it keeps in flight (8, or 4 and 2 with more fragments of rows) and than twice as many, wavefronts
+that get different numbers of blocks; one row, a full and a begun fragment.  Tolerance as for the tiles."""
+import pytest
+
+from paper_2504_11816_amd import binding
+
+from test_gpu_linear_tiles import product
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,blocks", [(m, n) for m in (1, 8, 17) for n in (1, 2, 5, 7, 9, 17, 31, 33, 35, 37, 63, 65, 67, 71)] +
+                         [(50, 5), (50, 9), (50, 17), (100, 1), (100, 5)])
+def test_blocks_of_a_wavefront(m, blocks):
+    n_in = 32 * blocks
+    assert binding.okv_linear_plan(m, 80, n_in, 0)[0] == 0
+    product(m, 80, n_in, 700 + m, relu=True, residual=True, workspace=False)
+    product(m, 80, n_in, 701 + m, bias=False, workspace=False)
