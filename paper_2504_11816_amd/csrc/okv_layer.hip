@@ -32,9 +32,9 @@
 //     fences, which on this GPU write back and invalidate the L2 caches: 75 us instead of 11.
 //     Where three tiles per workgroup fill the compute units without a cut (12288 features on
 //     256 units) the workgroups have three streaming wavefronts and there is no second kernel;
-//   * up to 8 rows, and some shapes the fast kernel does not take (input dimension not a multiple
-//     of 256), run the simple kernel: a workgroup per 16 features, its wavefronts split the
-//     inputs and add up through LDS, x by gather;
+//   * up to 8 rows, up to 16 where a model of both is in its favour, and some shapes the fast kernel does
+//     not take (input dimension not a multiple of 256), run the simple kernel: a workgroup per 16
+//     features, its wavefronts split the inputs and add up through LDS, x by gather;
 //   * with hundreds of rows the matrix cores and what feeds them bound the product: linear_tile_kernel, and
 //     linear_wide_kernel for the largest tiles.
 #include "okv_kernels.h"
@@ -55,9 +55,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 #ifndef OKV_LIN_DEPTH
 #define OKV_LIN_DEPTH 8
 #endif
-// Up to this many rows the simple kernel is the faster one (its gather of x costs in proportion to the rows, and it
-// has more, shorter-lived workgroups and needs no second kernel); measured with the weights coming from HBM, 16384 x
-// 4096: 26.6 us against 27.0 at 8 rows, 27.8 against 26.9 at 10, 34.3 against 27.4 at 16.
+// Up to this many rows the simple kernel runs unless the staged one is clearly faster, and up to a fragment of rows where its model
+// says so (see few_rows_simple).
 #ifndef OKV_LIN_SIMPLE_ROWS
 #define OKV_LIN_SIMPLE_ROWS 8
 #endif
@@ -1263,7 +1262,7 @@ hipError_t launch_linear_mf(const LinearArgs &args, int n_tiles, bool fast, int 
       launch_reduce(args, stream);
     }
   } else if constexpr (MF <= OKV_LINEAR_MAX_ROWS / 16) {
-    const bool stream_w = MF == 1 && args.m <= OKV_LIN_SIMPLE_ROWS && (int64_t)args.n_out * args.n_in * 2 >= kStreamSimpleBytes;
+    const bool stream_w = MF == 1 && (int64_t)args.n_out * args.n_in * 2 >= kStreamSimpleBytes;
     if (stream_w) hipLaunchKernelGGL((linear_kernel<1, true>), dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.bias, args.n_kb,
                                      args.n_in, args.m, args);
     else hipLaunchKernelGGL((linear_kernel<MF, false>), dim3(n_tiles), dim3(kLinWaves * 64), 0, stream, args.w, args.x, args.bias, args.n_kb, args.n_in,
@@ -1420,7 +1419,30 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
   return plan;
 }
 
-// The kernel for a product.  Up to OKV_LIN_SIMPLE_ROWS rows the simple one.  Up to OKV_LINEAR_MAX_ROWS rows the staged one
+// Up to 16 rows (one fragment): the simple kernel rather than the staged one?  It needs no second launch and has more workgroups, the
+// staged one reads x in whole lines and evens out products whose 16-feature tiles leave compute units idle or one round short.
+// Models of both in us: 2.57 (2.91) for the launch, 0.56 where a wavefront's quarter of the inputs is no whole number of rounds of
+// the walk, 3.39 for cuts, and the root of the sum of squares of the weights at 9.3 (8.1) MB/us and of what a compute unit takes in at
+// 72 (58) KB/us, of which a row of x counts 2 of a feature's bytes (0.42), workgroups beyond whole rounds for 1 / 1.29 of one.  (414
+// shapes of 1 to 24 rows, 256 to 24576 features, 256 to 20480 inputs, weights from HBM: 8 and 9 % rms.)  Up to 8 rows the staged
+// one has to be 14 % better, which the models are not always good for (8 rows x 16384 x 4096 22 us simple, 25 staged).  Beyond, the simple
+// one has to be 2 us better, since a layer norm of the result is a launch more behind it and not behind the staged kernel's shares (16
+// x 768 x 3072 6.2 / 7.5 us simple / staged, with a norm 8.8 / 8.1), and the inputs have to be whole rounds (shapes that host tests hold to
+// the staged kernel are not).  us, the rule by rows alone -> this one: 8 rows x 5120 x 20480 48.4 -> 36.7, 3 x 512 x 20480 with a norm 18.1 ->
+// 10.5, 8 x 1632 x 17920 19.9 -> 14.0; 12 x 4096 x 4096 10.6 -> 7.3, with a norm 12.2 -> 10.1, 12 x 2048 x 2048 7.8 -> 4.7, 11 x 4096 x 2048
+// 8.2 -> 4.9.
+bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, const LinearPlan &staged) {
+  const double weight_mb = (double)n_out * n_in * 2 / 1e6, row_kb = (double)n_in * 2 / 1e3;
+  const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 1.29 * std::ceil(q) - 0.29 * q;
+  const double simple_us = 2.57 + (n_in % 1024 ? 0.56 : 0.0) + std::hypot(rounds * row_kb * (16.0 + 2.0 * m) / 72.0, weight_mb / 9.3);
+  const int64_t wgs = (int64_t)((n_out / 16 + staged.waves - 1) / staged.waves) * staged.cuts;
+  const double intake_kb = (double)((wgs + n_cus - 1) / n_cus) * (16.0 * staged.waves + 0.42 * m) * row_kb / staged.cuts;
+  const double staged_us = 2.91 + (staged.cuts > 1 ? 3.39 : 0.0) + std::hypot(intake_kb / 58.0, weight_mb / 8.1);
+  if (m <= OKV_LIN_SIMPLE_ROWS) return simple_us < 1.14 * staged_us;
+  return n_in % 1024 == 0 && simple_us + 2.0 < staged_us;
+}
+
+// The kernel for a product.  Up to 16 rows the simple or the staged one (few_rows_simple).  Up to OKV_LINEAR_MAX_ROWS rows the staged one
 // where it takes the shape (12288 x 4096 at 128 rows 28 us against the tile kernel's 31, 16384 x 4096 35 against 38; where the
 // inputs are many the tile kernel would win, 4096 x 16384 at 128 rows 35 against 43, with twice the cuts and so twice the
 // workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
@@ -1434,9 +1456,10 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
 // on average.  The simple kernel's time scatters by 10 % around its model: in doubt the line favours tiles, whose model is the better one.)
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0};
-  if (m <= OKV_LIN_SIMPLE_ROWS) return simple;
   const LinearPlan staged = staged_plan(m, n_out, n_in, n_cus);
   const bool staged_runs = staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes);
+  if (m <= OKV_LIN_SIMPLE_ROWS && !staged_runs) return simple;
+  if (m <= 16 && staged.cuts > 0 && few_rows_simple(m, n_out, n_in, n_cus, staged)) return simple;
   if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return staged;
   const LinearPlan tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
   if (staged_runs) return tile.us < 0.955 * staged.us ? tile : staged;

@@ -1,0 +1,26 @@
+"""Which kernel a product of up to 16 rows takes, against what the simple and the staged kernel took on MI355X (us, weights from HBM):
+the faster one wherever they are more than 12 % apart (from 9 rows on also 2 us, which a layer norm behind the simple one takes more).  No GPU: the choice is made on the host."""
+import pytest
+
+from paper_2504_11816_amd import binding
+
+# rows, features, inputs, simple kernel, staged kernel with the launch that adds its shares
+MEASURED = [
+    (4, 4096, 4096, 6.8, 10.4), (8, 4096, 4096, 7.1, 10.4), (8, 16384, 4096, 21.9, 25.1), (8, 4096, 16384, 21.6, 25.3), (1, 2560, 10240, 10.5, 13.0),
+    (8, 768, 3072, 4.9, 7.5), (8, 2048, 2048, 4.7, 7.5), (8, 2560, 2560, 5.0, 7.6), (1, 768, 3072, 4.5, 7.4), (1, 304, 3072, 4.6, 7.4),
+    (8, 5120, 20480, 48.5, 34.9), (8, 1024, 18432, 19.4, 11.4), (2, 512, 20480, 17.3, 10.4), (7, 416, 12800, 13.6, 8.9), (8, 1632, 17920, 19.9, 14.0),
+    (12, 4096, 4096, 7.3, 10.5), (16, 4096, 4096, 8.3, 10.6), (12, 2048, 2048, 4.6, 7.5), (16, 2048, 2048, 5.0, 7.4), (11, 4096, 2048, 4.9, 8.2),
+    (12, 5120, 5120, 15.4, 12.9), (16, 12288, 4096, 21.3, 17.9), (12, 5120, 20480, 54.8, 36.8), (16, 20480, 5120, 45.0, 34.9), (16, 15360, 5120, 36.1, 25.7)]
+
+
+@pytest.mark.parametrize("m,n_out,n_in,simple_us,staged_us", MEASURED)
+def test_the_faster_kernel(m, n_out, n_in, simple_us, staged_us):
+    assert max(simple_us, staged_us) > 1.12 * min(simple_us, staged_us) and (m <= 8 or abs(simple_us - staged_us) > 2.0)
+    assert binding.okv_linear_plan(m, n_out, n_in)[0] == (0 if simple_us < staged_us else 1)
+
+
+def test_without_a_workspace_few_rows_run_uncut():
+    for m in (1, 8):
+        assert binding.okv_linear_plan(m, 1024, 18432, 0) == (0, 16, 16, 1)
+    assert binding.okv_linear_plan(8, 1024, 18432)[3] > 1
+    assert binding.okv_linear_plan(16, 4096, 4096, 0) == binding.okv_linear_plan(16, 4096, 4096, 1 << 30) == (0, 16, 16, 1)
