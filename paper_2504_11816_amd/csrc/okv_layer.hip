@@ -38,6 +38,7 @@
 //   * with hundreds of rows the matrix cores and what feeds them bound the product: linear_tile_kernel, and
 //     linear_wide_kernel for the largest tiles.
 #include "okv_kernels.h"
+#include "okv_lanes.h"
 #include "okv_layer.h"
 
 #include <algorithm>
@@ -1079,25 +1080,56 @@ constexpr int kLnMaxThreads = 1024, kLnMaxPieces = 2;
 constexpr int kLnMaxWidth = kLnMaxThreads * kLnMaxPieces * 8;
 inline int ln_threads(int h) { return std::min(kLnMaxThreads, ((h >> 3) + 63) / 64 * 64); }
 
-__device__ __forceinline__ float block_sum(float v, float *scratch) {
+// Mean and 1 / sqrt(variance + eps) of a row of h numbers of which a thread holds PPT pieces of eight (piece threadIdx.x + i blockDim.x).
+// Every wavefront takes the mean of its own numbers and the squares around that; the wavefronts' (sum, squares) meet in LDS once
+// and are joined as sum of squares + count x (distance of the means)^2.  The kernels are a chain of waits: a mean over the whole row
+// first and the squares around it afterwards was two trips through LDS for six lane exchanges each and four barriers.
+// us before -> now, with the product in front: 32 rows x 4096 x 4096 12.6 -> 12.0, 32 x 5120 x 5120 16.4 -> 15.7, 100 x 10240 x 2560 23.5 -> 23.0; the
+// norm alone, 1024 rows of 16384 14.6 -> 12.7 (5.3 TB/s), 4096 of 4096 13.3 -> 12.2.  (An approximate 1 / count does not matter: squares around any
+// number near the mean will do.  With true divisions the norm of 1024 rows of 4096 took 4.9 instead of 4.6.)
+template <int PPT>
+__device__ __forceinline__ void row_stats(const float (&v)[PPT][8], const int h, const float eps, float2 *scratch, float &mean, float &rstd) {
+  const int pieces = h >> 3, waves = (int)(blockDim.x >> 6), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto count_of = [&](int w) {                           // numbers that wavefront w holds (at least one piece)
+    int n = min(pieces - 64 * w, 64);
+    if (PPT > 1) n += min(max(pieces - 64 * w - (int)blockDim.x, 0), 64);
+    return (float)(8 * n);
+  };
+  float s = 0.f, q = 0.f;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  __syncthreads();                                             // scratch may still be read from the previous call
-  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+  for (int i = 0; i < PPT; ++i)
+    if ((int)(threadIdx.x + i * blockDim.x) < pieces) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += v[i][e];
+    }
+  s = wave_sum(s);
+  const float mine = s * __builtin_amdgcn_rcpf(count_of(wave));
+#pragma unroll
+  for (int i = 0; i < PPT; ++i)
+    if ((int)(threadIdx.x + i * blockDim.x) < pieces) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) q += (v[i][e] - mine) * (v[i][e] - mine);
+    }
+  q = wave_sum(q);
+  if ((threadIdx.x & 63) == 0) scratch[wave] = make_float2(s, q);
   __syncthreads();
-  float t = 0.f;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += scratch[w];
-  return t;
+  // a wavefront's pair in every row of 16 lanes (there are at most 16 of them)
+  static_assert(kLnMaxThreads / 64 <= 16, "");
+  const int w = (int)(threadIdx.x & 15);
+  const bool in = w < waves;
+  const float2 pair = scratch[in ? w : 0];
+  mean = row_sum(in ? pair.x : 0.f) / (float)h;
+  const float n = count_of(in ? w : 0), off = pair.x * __builtin_amdgcn_rcpf(n) - mean;
+  rstd = 1.0f / sqrtf(row_sum(in ? pair.y + n * off * off : 0.f) / (float)h + eps);
 }
 
 template <int PPT>
 __global__ __launch_bounds__(kLnMaxThreads) void layernorm_kernel(const uint4 *x, const uint4 *gamma, const uint4 *beta, uint4 *out,
                                                                 int32_t h, float eps) {
-  __shared__ float scratch[kLnMaxThreads / 64];
+  __shared__ float2 scratch[kLnMaxThreads / 64];
   const int pieces = h >> 3;
   const uint4 *xr = x + (size_t)blockIdx.x * pieces;
   float v[PPT][8];
-  float s = 0.f;
 #pragma unroll
   for (int i = 0; i < PPT; ++i) {
     const int p = threadIdx.x + i * blockDim.x;
@@ -1105,21 +1137,11 @@ __global__ __launch_bounds__(kLnMaxThreads) void layernorm_kernel(const uint4 *x
       const uint4 u = xr[p];
       const _Float16 *hp = reinterpret_cast<const _Float16 *>(&u);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        v[i][e] = (float)hp[e];
-        s += v[i][e];
-      }
+      for (int e = 0; e < 8; ++e) v[i][e] = (float)hp[e];
     }
   }
-  const float mean = block_sum(s, scratch) / (float)h;
-  float q = 0.f;
-#pragma unroll
-  for (int i = 0; i < PPT; ++i)
-    if ((int)(threadIdx.x + i * blockDim.x) < pieces) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) q += (v[i][e] - mean) * (v[i][e] - mean);
-    }
-  const float rstd = 1.0f / sqrtf(block_sum(q, scratch) / (float)h + eps);
+  float mean, rstd;
+  row_stats<PPT>(v, h, eps, scratch, mean, rstd);
   uint4 *orow = out + (size_t)blockIdx.x * pieces;
 #pragma unroll
   for (int i = 0; i < PPT; ++i) {
@@ -1145,11 +1167,10 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
                                                                            const _Float16 *gamma, const _Float16 *beta, const int32_t n_out,
                                                                            const int32_t splits, const int32_t m, const LinearArgs a) {
   // (leading parameters: in scalar registers when the wavefront starts, so everything is asked for at once)
-  __shared__ float scratch[kLnMaxThreads / 64];
+  __shared__ float2 scratch[kLnMaxThreads / 64];
   const int h = n_out, pieces = h >> 3, mrow = blockIdx.x;
   const Sink sink(a);
   float v[PPT][8];
-  float s = 0.f;
   // the bias, the residual, gamma and beta are fetched behind the first shares: not behind the sums nor behind the reductions,
   // whose barriers would otherwise stand between these loads and what they do not depend on
   uint4 gam[PPT], bet[PPT];
@@ -1197,20 +1218,12 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
         y += (float)rp[e];
         yp[e] = (_Float16)y;                               // the norm sees the row as it is stored
         v[i][e] = (float)yp[e];
-        s += v[i][e];
       }
       store_at(sink.out0 + at, __builtin_bit_cast(u32x4_t, yo));
     }
   }
-  const float mean = block_sum(s, scratch) / (float)h;
-  float q = 0.f;
-#pragma unroll
-  for (int i = 0; i < PPT; ++i)
-    if ((int)(threadIdx.x + i * blockDim.x) < pieces) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) q += (v[i][e] - mean) * (v[i][e] - mean);
-    }
-  const float rstd = 1.0f / sqrtf(block_sum(q, scratch) / (float)h + a.ln_eps);
+  float mean, rstd;
+  row_stats<PPT>(v, h, a.ln_eps, scratch, mean, rstd);
 #pragma unroll
   for (int i = 0; i < PPT; ++i) {
     const int p = threadIdx.x + i * blockDim.x;
