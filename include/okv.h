@@ -518,8 +518,8 @@ int okv_worklist(okv_ctx *ctx, int32_t from_device, int32_t *items, int64_t max_
                  int64_t *n_items);
 
 /* With equal stretches (no split size fixed), what the wavefronts of a launch start from: one record of
- * eight int32 per (stretch, KV head) pair, pair = stretch * G + head, as the bookkeeping kernel of the last
- * okv_step_begin / okv_set_batch wrote them on the device (synchronous copy):
+ * eight int32 per (stretch, KV head) pair, pair = stretch * G + head, as the bookkeeping kernel writes them on the
+ * device for the batch as it is (in okv_step_begin; in this call where no step has begun since; synchronous copy):
  *   [0] the stretch's first item (index into okv_worklist's list)   [1] items of the stretch
  *   [2] that item's sequence   [3] its first key   [4] one past its last key
  *   [5] bit 0: the item ends its sequence, bit 1: it is the whole sequence; the KV head in the bits from 8 up

@@ -127,6 +127,7 @@ struct okv_ctx {
   int32_t max_waves = 0;                 // wavefronts of the persistent attention launch
   char *h_up = nullptr;                  // mapped host memory the small tables are uploaded from (NULL: synchronous copies)
   int64_t up_cap = 0;
+  bool list_stale = false;               // the device work list is not that of the host's lengths: see rebuild_worklist
   bool keep_cached = true;               // the batch's keys and values of all layers fit the memory-side cache
   int64_t max_items = 0;
   float *part_o = nullptr, *part_ml = nullptr;
@@ -600,7 +601,11 @@ int upload_tables(okv_ctx *ctx, void *dst0, const void *src0, int64_t bytes0, vo
 
 // Recomputes split size, item count and merge flag from the host lengths and
 // rebuilds the device work list (adding `inc` to every device length first).
-int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false) {
+// Unless `now`, the device list is left for later: a step builds its own when it begins, so the list of a batch that was just
+// described or whose prompt was stored is only read by the calls that hand it out (current_worklist).  Building it anyway was a launch
+// of 5 us in front of every first step and 4 us of the host's time; a batch of one sequence described and stepped three times 146 ->
+// 131 us, one layer's prompts of 21 x 87..175 tokens described and stored 104 -> 92, four layers of 24 x 100..2000 587 -> 580.
+int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false, bool now = true) {
   int64_t keys = 0;
   for (int32_t b = 0; b < ctx->B; ++b) keys += ctx->h_ctx_lens[b];
   ctx->keep_cached = keys * ctx->cfg.n_kv_heads * ctx->cfg.head_dim * 4 * ctx->cfg.n_layers <= okv::kKeepCachedBytes;
@@ -630,9 +635,10 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false) {
     ctx->need_merge = false;
     ctx->spans = false;
     for (int32_t b = 0; b < ctx->B; ++b) ctx->need_merge |= per_seq[b] > 1;
-    OKV_HIP(ctx, okv::launch_step_advance_classes(ctx->d_ctx_lens, ctx->d_runs, ctx->d_pair_first, ctx->d_chunk_prefix,
+    if (now) OKV_HIP(ctx, okv::launch_step_advance_classes(ctx->d_ctx_lens, ctx->d_runs, ctx->d_pair_first, ctx->d_chunk_prefix,
                                                   ctx->d_item_desc, ctx->d_seq_total, ctx->B, ctx->n_cls, ctx->split, inc,
                                                   ctx->compute));
+    ctx->list_stale = !now;
     return OKV_OK;
   }
   if (const int32_t S = fixed_split(ctx)) {
@@ -650,8 +656,9 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false) {
       okv::seq_chunks(ctx->h_ctx_lens[b], S, &cnt, &sz);
       if (cnt > 1) ctx->need_merge = true;
     }
-    OKV_HIP(ctx, okv::launch_step_advance(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->B, S, inc,
-                                          ctx->compute));
+    if (now) OKV_HIP(ctx, okv::launch_step_advance(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->B, S, inc,
+                                                   ctx->compute));
+    ctx->list_stale = !now;
     return OKV_OK;
   }
   // equal stretches: the host walks the same arithmetic as the kernel for the counts it needs
@@ -676,12 +683,16 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false) {
   ctx->split = (int32_t)std::min<int64_t>(plan.span * 16, 0x7fffffff);
   ctx->n_items = (int32_t)n;
   ctx->need_merge = merge;
-  OKV_HIP(ctx, okv::launch_step_advance_spans(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->d_group_first,
-                                              ctx->d_plan, ctx->B, ctx->max_groups, kMinSpanTiles, inc, ctx->d_pair_head,
-                                              okv::head_geom(ctx->shape, ctx->d_block_table, max_pairs(ctx->max_waves)),
-                                              ((int64_t)ctx->cap_tokens + 15) / 16, ctx->compute));
+  if (now) OKV_HIP(ctx, okv::launch_step_advance_spans(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->d_group_first,
+                                                       ctx->d_plan, ctx->B, ctx->max_groups, kMinSpanTiles, inc, ctx->d_pair_head,
+                                                       okv::head_geom(ctx->shape, ctx->d_block_table, max_pairs(ctx->max_waves)),
+                                                       ((int64_t)ctx->cap_tokens + 15) / 16, ctx->compute));
+  ctx->list_stale = !now;
   return OKV_OK;
 }
+
+// The device work list, built now if it was left for later.
+int current_worklist(okv_ctx *ctx) { return ctx->list_stale ? rebuild_worklist(ctx, 0) : OKV_OK; }
 
 // Restarts the copy pipeline for the batch just described.
 void reset_schedule(okv_ctx *ctx) {
@@ -1186,7 +1197,7 @@ int okv_set_batch(okv_ctx *ctx, int32_t B, const int32_t *block_table, const int
   rc = tail_restart(ctx);
   if (rc) return rc;
   ctx->batch_set = true;
-  rc = rebuild_worklist(ctx, 0);
+  rc = rebuild_worklist(ctx, 0, false, /*now=*/false);
   if (rc) { ctx->batch_set = false; return rc; }
   return OKV_OK;
 }
@@ -1585,7 +1596,7 @@ int okv_prefill_end(okv_ctx *ctx) {
   ctx->in_prefill = false;
   reset_schedule(ctx);
   if (int rc = tail_restart(ctx)) return rc;
-  return rebuild_worklist(ctx, 0, /*upload_lens=*/true);
+  return rebuild_worklist(ctx, 0, /*upload_lens=*/true, /*now=*/false);
 }
 
 int okv_set_split_tokens(okv_ctx *ctx, int32_t split_tokens) {
@@ -1600,7 +1611,7 @@ int okv_set_split_tokens(okv_ctx *ctx, int32_t split_tokens) {
                   (long long)worst, (long long)ctx->max_items);
   }
   ctx->split_override = split_tokens;
-  if (ctx->batch_set) return rebuild_worklist(ctx, 0);
+  if (ctx->batch_set) return rebuild_worklist(ctx, 0, false, /*now=*/false);
   return OKV_OK;
 }
 
@@ -1621,6 +1632,7 @@ int okv_worklist(okv_ctx *ctx, int32_t from_device, int32_t *items, int64_t max_
   if (ctx->n_items > max_items) return fail(ctx, OKV_ENOSPC, "work list has %d items", ctx->n_items);
   if (ctx->n_items == 0) return OKV_OK;
   if (from_device) {
+    if (int rc = current_worklist(ctx)) return rc;
     if (!ctx->d_items_dump) OKV_HIP(ctx, hipMalloc(&ctx->d_items_dump, (size_t)ctx->max_items * 3 * sizeof(int32_t)));
     okv::BatchState bs{ctx->d_block_table, ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->B, ctx->split,
                        ctx->n_items, ctx->n_cls};
@@ -1676,6 +1688,7 @@ int okv_pair_heads(okv_ctx *ctx, int32_t *records, int64_t max_records, int64_t 
   const int64_t n = std::min<int64_t>((int64_t)ctx->n_groups * ctx->shape.G, max_pairs(ctx->max_waves));
   *n_records = n;
   if (n > max_records) return fail(ctx, OKV_ENOSPC, "okv_pair_heads: %lld records", (long long)n);
+  if (int rc = current_worklist(ctx)) return rc;
   OKV_HIP(ctx, hipStreamSynchronize(ctx->compute));
   OKV_HIP(ctx, hipMemcpy(records, ctx->d_pair_head, (size_t)n * okv::kPairHeadBytes, hipMemcpyDeviceToHost));
   return OKV_OK;
@@ -1687,6 +1700,7 @@ int okv_worklist_classes(okv_ctx *ctx, int32_t from_device, int32_t *class_first
   *n_classes = ctx->n_cls;
   if (ctx->n_cls + 1 > max_classes) return fail(ctx, OKV_ENOSPC, "%d classes", ctx->n_cls);
   if (from_device) {
+    if (int rc = current_worklist(ctx)) return rc;
     OKV_HIP(ctx, hipStreamSynchronize(ctx->compute));
     for (int32_t c = 0; c <= ctx->n_cls; ++c)             // chunk_prefix[cls * B] = items before class cls
       OKV_HIP(ctx, hipMemcpy(class_first + c, ctx->d_chunk_prefix + (size_t)c * ctx->B, sizeof(int32_t), hipMemcpyDeviceToHost));
