@@ -76,6 +76,37 @@ struct AttnLaunch {
   int32_t mirror_is_tail = 0;
 };
 
+constexpr int kPairHeadBytes = 32, kHeadGroupsMax = 1024;
+struct HeadGeom {
+  const int32_t *block_table = nullptr;   // device; NULL: contiguous pools (a sequence's slice is its block)
+  int32_t max_blocks = 1, log2_T = 0;
+  int32_t tiles = 1;                      // 16-token tiles of a pool slice (tcap / 16)
+  int32_t st_log2 = 0, G = 1, gg = 1;     // slab geometry, as in PoolShape
+  int32_t max_pairs = 0;                  // records to write
+};
+inline HeadGeom head_geom(const PoolShape &s, const int32_t *block_table, int32_t max_pairs) {
+  HeadGeom g;
+  g.block_table = s.paged ? block_table : nullptr;
+  g.max_blocks = s.max_blocks, g.log2_T = s.log2_T, g.tiles = s.tcap >> 4;
+  g.st_log2 = s.st_log2, g.G = s.G, g.gg = s.gg, g.max_pairs = max_pairs;
+  return g;
+}
+
+// The work list of the step after this one, made by a merge launch on the side (next_list_rides says where): the lengths in
+// ctx_lens advance by `lag` (what the step itself left undone because its own list was made this way) and the list
+// is for one token more.  Everything but ctx_lens is another set of arrays than the launch itself reads.
+struct NextList {
+  int32_t *ctx_lens, *chunk_prefix;
+  int4 *item_desc;
+  int32_t *group_first, *plan;
+  void *pair_head;
+  int32_t B, max_groups, min_span, lag, most_tiles;
+  HeadGeom geom;
+};
+// At most this many sequences (a thread each) and stretches (kept in LDS), and sums of tiles that fit 32 bits.
+bool next_list_rides(int32_t B, int32_t max_groups, int64_t cap_tiles);
+constexpr int kRiderGroupsMax = 256;
+
 // Up to this many bytes of keys and values (over all layers that a step reads) launches keep them cached: the
 // memory-side cache of MI355X (see load_kv for both sides measured).
 constexpr int64_t kKeepCachedBytes = 256000000;
@@ -87,11 +118,12 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream,
 // The same for n_layers (at most kLayersPerLaunch) layers in HBM at once, merge included: two launches whatever their number.
 // Of `a` everything but pool, q, k_new, v_new and out is the layers' own in common; the work list is one of equal stretches
 // (pair_head), and part_o / part_ml hold batch.n_items slots per layer, one layer after the other.
-hipError_t launch_decode_layers(const AttnLaunch &a, const DecodeLayer *layers, int32_t n_layers, hipStream_t stream);
+// next: made by the merge launch, where there is one (need_merge).
+hipError_t launch_decode_layers(const AttnLaunch &a, const DecodeLayer *layers, int32_t n_layers, const NextList *next, hipStream_t stream);
 
 // Merge of the partial results of every sequence that has more than one item (reads
 // shape, batch, out, part_o, part_ml, out_fp32 of `a`).
-hipError_t launch_merge(const AttnLaunch &a, hipStream_t stream);
+hipError_t launch_merge(const AttnLaunch &a, const NextList *next, hipStream_t stream);
 
 // ctx_lens[b] += inc; rebuilds chunk_prefix and the item list for split size S (every sequence cut
 // into equal pieces of at most S keys).
@@ -109,21 +141,6 @@ hipError_t launch_step_advance(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *i
 // cap_tiles: no sequence holds more 16-key tiles than this.
 // The bookkeeping kernel keeps what opens each stretch in LDS, for at most kHeadGroupsMax stretches: callers
 // keep max_groups at or below that.
-constexpr int kPairHeadBytes = 32, kHeadGroupsMax = 1024;
-struct HeadGeom {
-  const int32_t *block_table = nullptr;   // device; NULL: contiguous pools (a sequence's slice is its block)
-  int32_t max_blocks = 1, log2_T = 0;
-  int32_t tiles = 1;                      // 16-token tiles of a pool slice (tcap / 16)
-  int32_t st_log2 = 0, G = 1, gg = 1;     // slab geometry, as in PoolShape
-  int32_t max_pairs = 0;                  // records to write
-};
-inline HeadGeom head_geom(const PoolShape &s, const int32_t *block_table, int32_t max_pairs) {
-  HeadGeom g;
-  g.block_table = s.paged ? block_table : nullptr;
-  g.max_blocks = s.max_blocks, g.log2_T = s.log2_T, g.tiles = s.tcap >> 4;
-  g.st_log2 = s.st_log2, g.G = s.G, g.gg = s.gg, g.max_pairs = max_pairs;
-  return g;
-}
 hipError_t launch_step_advance_spans(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *item_desc, int32_t *group_first,
                                      int32_t *plan_out, int32_t B, int32_t max_groups, int32_t min_span, int32_t inc,
                                      void *pair_head, const HeadGeom &geom, int64_t cap_tiles, hipStream_t stream);

@@ -916,6 +916,155 @@ __global__ __launch_bounds__(most_waves_per_pair(D) * 64) void attn_split_planne
   run(std::integral_constant<int, 1>{}, PAGED || D == 128 ? a1 : a);
 }
 
+constexpr int kStepThreads = 256;          // of the bookkeeping kernels
+
+// One record per (stretch, KV head) pair, by the whole workgroup: the stretch's first item and where that head's rows of the
+// item's first two tiles lie.  Nothing is written for pairs past the last stretch: the attention kernel
+// knows how many stretches there are.
+__device__ __forceinline__ void write_pair_heads(const int32_t n_groups, const int32_t *open_item, const int4 *open_desc, const int2 *open_blk,
+                                                 PairHead *pair_head, const HeadGeom &hg) {
+  const int32_t St_mask = (1 << hg.st_log2) - 1;
+  const int32_t n_pairs = (int32_t)min((int64_t)n_groups * hg.G, (int64_t)hg.max_pairs);
+  for (int p = threadIdx.x; p < n_pairs; p += kStepThreads) {
+    const int32_t group = p / hg.G, g = p - group * hg.G;
+    PairHead h = {};
+    const int32_t it = group < n_groups && group < kHeadGroupsMax ? open_item[group] : -1;
+    const int32_t n = it >= 0 ? open_item[group + 1] - it : 0;
+    if (n > 0) {                                         // (a batch with no keys at all has one stretch and no item)
+      h.item = it, h.count = n;
+      const int4 d = open_desc[group];
+      h.b = d.x, h.lo = d.y, h.hi = d.z, h.flags_g = d.w | (g << 8);
+      const int32_t grp = g / hg.gg;
+      const int32_t head_k = ((grp * 2 * hg.gg) << hg.st_log2) + (g - grp * hg.gg);
+      const int32_t t0 = d.y >> 4, t_last = (d.z - 1) >> 4;
+      for (int i = 0; i < 2; ++i) {
+        const int32_t t = min(t0 + i, t_last);
+        const int32_t blk = i ? open_blk[group].y : open_blk[group].x;
+        const int64_t lin = (int64_t)blk * hg.tiles + (hg.block_table ? t & (hg.tiles - 1) : t);
+        const int64_t base = (lin >> hg.st_log2) * ((int64_t)(2 * hg.G) << hg.st_log2) + (lin & St_mask) * hg.gg + head_k;
+        (i ? h.base1 : h.base0) = (int32_t)base;
+      }
+    }
+    pair_head[p] = h;
+  }
+}
+
+// The bookkeeping of a step for equal stretches (see step_advance_spans_kernel) for at most a sequence per thread, with an item per thread too: a thread counts and scans its sequence, and then finds
+// for one stretch the sequence that its first tile lies in.  Every item either opens a stretch or begins its sequence in mid-stretch, so
+// an item's place in the list is the number of stretches that begin before it and of sequences that begin in mid-stretch before it.
+// (There, the thread of a long sequence writes all of its items one after the other, each behind a look-up in the block table.)
+// us before -> now: one sequence of 4096 keys, 4 and 32 KV heads 9.5 -> 3.6 and 10.5 -> 4.7, two of 4000 with 8 heads 10.0 -> 4.1, 16 of up to
+// 4096 6.7 -> 4.8, 128 of up to 4096 5.8 -> 5.1, 24 of up to 1150 4.8 (about what a dependent launch takes behind a long one) either way.
+// With 512 or 1024 threads the small ones take 0.3 or 1 us more.
+// `inc` is added to the lengths; the list is for `ahead` more tokens than that.  GROUPS: the most stretches there may be.
+template <int GROUPS>
+__device__ __forceinline__ void step_advance_items(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *item_desc, int32_t *group_first,
+                                                   int32_t *plan_out, const int32_t B, const int32_t max_groups, const int32_t min_span,
+                                                   const int32_t inc, const int32_t ahead, PairHead *pair_head, const int32_t most_tiles,
+                                                   const HeadGeom &hg) {
+  __shared__ int32_t wave_tiles[kStepThreads / 64], wave_mids[kStepThreads / 64];
+  // per sequence: tiles before it (past the batch: more than there are), place of its first item, keys
+  __shared__ int32_t seq_first[kStepThreads], seq_at[kStepThreads], seq_n[kStepThreads];
+  // what opens each stretch: its first item, that item's descriptor and the block ids of the item's first two tiles
+  // (the second clamped to the item's last tile)
+  __shared__ int32_t open_item[GROUPS + 1];
+  __shared__ int4 open_desc[GROUPS];
+  __shared__ int2 open_blk[GROUPS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // (a length no sequence can have, which only a caller's own device array could hold, does not leave the arithmetic)
+  auto tiles_of = [&](int32_t n) -> int32_t { return min(max((n >> 4) + ((n & 15) != 0), 0), most_tiles); };
+  auto keys_to = [&](int32_t n, int32_t tile) -> int32_t { return (int32_t)min((int64_t)n, (int64_t)tile << 4); };
+  int32_t n = 0;
+  if (tid < B) {
+    n = ctx_lens[tid] + inc;
+    if (inc) ctx_lens[tid] = n;                                // inc == 0: the lengths are only read
+    n += ahead;
+  }
+  const int32_t tiles = tiles_of(n);
+  const int32_t upto = wave_scan(tiles);
+  if (lane == 63) wave_tiles[wave] = upto;
+  __syncthreads();
+  int32_t before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kStepThreads / 64; ++w) {
+    const int32_t t = wave_tiles[w];
+    before += w < wave ? t : 0;
+    total += t;
+  }
+  const int32_t first = before + upto - tiles;
+  const SpanPlanOf<int32_t> plan = span_plan<int32_t>(total, max_groups, min_span);
+  const int32_t span = __builtin_amdgcn_readfirstlane(plan.span), n_groups = __builtin_amdgcn_readfirstlane(plan.n_groups);
+  const int32_t in_stretch = first / span, into = first - in_stretch * span;       // the stretch its first tile lies in, how far
+  const bool mid = tiles > 0 && into != 0;
+  const uint64_t mids = __ballot(mid);
+  if (lane == 0) wave_mids[wave] = (int32_t)__builtin_popcountll(mids);
+  seq_first[tid] = tid < B ? first : INT32_MAX;
+  seq_n[tid] = n;
+  __syncthreads();
+  int32_t mids_before = (int32_t)__builtin_popcountll(mids & ((1ull << lane) - 1)), all_mids = 0;
+#pragma unroll
+  for (int w = 0; w < kStepThreads / 64; ++w) {
+    const int32_t k = wave_mids[w];
+    mids_before += w < wave ? k : 0;
+    all_mids += k;
+  }
+  const int32_t n_items = n_groups + all_mids;
+  const int32_t at = in_stretch + (into != 0) + mids_before;
+  seq_at[tid] = at;
+  if (tid < B) chunk_prefix[tid] = at;
+  if (mid) {
+    const bool ends = span - into >= tiles;
+    item_desc[at] = make_int4(tid, 0, keys_to(n, min(span - into, tiles)), ends ? kItemLast | kItemWhole : 0);
+  }
+  __syncthreads();
+  for (int32_t j = tid; j < n_groups; j += kStepThreads) {
+    const int32_t tile = j * span;
+    int b = 0;                                           // the last sequence that begins at or before the tile (an empty one never is)
+#pragma unroll
+    for (int step = kStepThreads / 2; step > 0; step >>= 1)
+      if (seq_first[b + step] <= tile) b += step;
+    const int32_t nb = seq_n[b], from = tile - seq_first[b], end = tiles_of(nb);
+    const int32_t it = seq_at[b] + j - (tile - from) / span;
+    const bool ends = from + span >= end;
+    const int32_t lo = from << 4, hi = keys_to(nb, min(from + span, end));
+    const int4 desc = make_int4(b, lo, hi, ends ? (from == 0 ? kItemLast | kItemWhole : kItemLast) : 0);
+    item_desc[it] = desc;
+    group_first[j] = it;
+    if (pair_head) {
+      int2 blk = make_int2(b, b);
+      if (hg.block_table) {
+        const int32_t t0 = lo >> 4, t1 = min(t0 + 1, (hi - 1) >> 4);
+        const int32_t *row = hg.block_table + (size_t)b * hg.max_blocks;
+        blk.x = row[min((t0 << 4) >> hg.log2_T, hg.max_blocks - 1)];
+        blk.y = row[min((t1 << 4) >> hg.log2_T, hg.max_blocks - 1)];
+      }
+      open_item[j] = it;
+      open_desc[j] = desc;
+      open_blk[j] = blk;
+    }
+  }
+  if (tid == kStepThreads - 1) {
+    if (pair_head) open_item[n_groups] = n_items;
+    group_first[n_groups] = n_items;
+    chunk_prefix[B] = n_items;
+    plan_out[0] = n_groups;
+    plan_out[1] = n_items;
+    plan_out[2] = span;
+    plan_out[3] = 0;
+  }
+  if (!pair_head) return;
+  __syncthreads();
+  write_pair_heads(n_groups, open_item, open_desc, open_blk, pair_head, hg);
+}
+
+__global__ __launch_bounds__(kStepThreads) void step_advance_items_kernel(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *item_desc,
+                                                                         int32_t *group_first, int32_t *plan_out, const int32_t B,
+                                                                         const int32_t max_groups, const int32_t min_span, const int32_t inc,
+                                                                         PairHead *pair_head, const int32_t most_tiles, const HeadGeom hg) {
+  step_advance_items<kHeadGroupsMax>(ctx_lens, chunk_prefix, item_desc, group_first, plan_out, B, max_groups, min_span, inc, 0, pair_head,
+                                     most_tiles, hg);
+}
+
 // out[b][h] = sum_c o_c 2^(m_c - M) / sum_c l_c 2^(m_c - M) over the items c of sequence b.
 // One wavefront per (b, h).  The items of a sequence are one contiguous range of the list per
 // block class.  Lane c first fetches (m_c, l_c) of item c, so the maxima and weights of up to
@@ -926,19 +1075,34 @@ __global__ __launch_bounds__(most_waves_per_pair(D) * 64) void attn_split_planne
 // four (b, h) pairs share a workgroup.
 // LENS: `chunk_prefix` is the device array of lengths instead, and a sequence's pieces are where plan_from_lens puts them.
 // MergeOuts: the results of several layers (blockIdx.z), whose partial results follow one another.
+// Next = NextList: the first row of workgroups makes the next step's work list (one of them; the sequences follow), which saves that
+// step a launch in front of its attention, us a step: 2 layers of one sequence of 256 keys, 8 heads 14.7 -> 11.3; 4 layers, 4 x 600, 32 / 8
+// heads 19.1 -> 15.1; 4 layers, 8 x 1500, 8 heads 41.3 -> 37.7; 6 layers, 24 x 700, 32 heads x 64 149.1 -> 147.3.
 struct MergeOuts {
   int32_t slots;                   // as in LayerList
   void *at[kLayersPerLaunch];
 };
-template <int D, bool LENS, typename Outs>
+struct NoNextList {};
+template <int D, bool LENS, typename Outs, typename Next>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_prefix, const float *part_ml, const float *part_o,
                                                           const int32_t B, const int32_t n_cls, const int32_t H, const AttnArgs a,
-                                                          const Outs outs) {
+                                                          const Outs outs, const Next next) {
   // (leading parameters: in scalar registers when the wavefront starts, so the first look-ups need no round trip
   // to the argument segment; most wavefronts of a launch find a sequence in one piece and leave at once)
   constexpr int EPT = D / 64;
   const int lane = threadIdx.x & 63;
-  const int b = blockIdx.y, h = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr bool kNext = std::is_same<Next, NextList>::value;
+  static_assert(kStepThreads == 256, "the workgroup that makes the next list is one of the merge's");
+  if constexpr (kNext) {
+    if (blockIdx.y == 0) {
+      if (blockIdx.x == 0 && blockIdx.z == 0)
+        step_advance_items<kRiderGroupsMax>(next.ctx_lens, next.chunk_prefix, next.item_desc, next.group_first, next.plan, next.B,
+                                            next.max_groups, next.min_span, next.lag, 1, static_cast<PairHead *>(next.pair_head),
+                                            next.most_tiles, next.geom);
+      return;
+    }
+  }
+  const int b = (int)blockIdx.y - (kNext ? 1 : 0), h = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (h >= H) return;
   void *out = a.out;
   if constexpr (std::is_same<Outs, MergeOuts>::value) {
@@ -1181,7 +1345,35 @@ hipError_t launch_decode_attn(const AttnLaunch &a, hipStream_t stream, hipEvent_
   return hipSuccess;
 }
 
-hipError_t launch_decode_layers(const AttnLaunch &a, const DecodeLayer *layers, int32_t n_layers, hipStream_t stream) {
+namespace {
+
+template <int D, typename Outs>
+void launch_merge_of(const AttnArgs &args, const Outs &outs, int32_t n_layers, const NextList *next, hipStream_t stream) {
+  const dim3 grid((args.H + 3) / 4, args.B + (next ? 1 : 0), n_layers);
+  if (next)
+    hipLaunchKernelGGL((attn_merge_kernel<D, false, Outs, NextList>), grid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o,
+                       args.B, args.n_cls, args.H, args, outs, *next);
+  else
+    hipLaunchKernelGGL((attn_merge_kernel<D, false, Outs, NoNextList>), grid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o,
+                       args.B, args.n_cls, args.H, args, outs, NoNextList{});
+}
+
+template <typename Outs>
+hipError_t launch_merge_as(const AttnArgs &args, const Outs &outs, const PoolShape &s, int32_t n_layers, const NextList *next, hipStream_t stream) {
+  if (next && (next->B < 1 || next->B > kStepThreads || next->max_groups > kRiderGroupsMax)) return hipErrorInvalidValue;
+  if (s.D == 128) launch_merge_of<128>(args, outs, n_layers, next, stream);
+  else if (s.D == 64) launch_merge_of<64>(args, outs, n_layers, next, stream);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool next_list_rides(int32_t B, int32_t max_groups, int64_t cap_tiles) {
+  return B >= 1 && B <= kStepThreads && max_groups <= kRiderGroupsMax && cap_tiles <= (1 << 30) / B;
+}
+
+hipError_t launch_decode_layers(const AttnLaunch &a, const DecodeLayer *layers, int32_t n_layers, const NextList *next, hipStream_t stream) {
   const PoolShape &s = a.shape;
   const int R = s.G > 0 ? s.H / s.G : 0, waves = a.waves_per_pair;
   if (n_layers < 1 || n_layers > kLayersPerLaunch || !a.pair_head || a.plan_dev || a.from_lens || a.pool_mirror || a.id_base != 0 ||
@@ -1207,43 +1399,29 @@ hipError_t launch_decode_layers(const AttnLaunch &a, const DecodeLayer *layers, 
   MergeOuts outs = {};
   outs.slots = list.slots;
   for (int32_t l = 0; l < n_layers; ++l) outs.at[l] = layers[l].out;
-  const dim3 mgrid((s.H + 3) / 4, a.batch.B, n_layers);
-  if (s.D == 128)
-    hipLaunchKernelGGL((attn_merge_kernel<128, false, MergeOuts>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o,
-                       args.B, 1, args.H, args, outs);
-  else
-    hipLaunchKernelGGL((attn_merge_kernel<64, false, MergeOuts>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o,
-                       args.B, 1, args.H, args, outs);
-  return hipGetLastError();
+  return launch_merge_as(args, outs, s, n_layers, next, stream);
 }
 
-hipError_t launch_merge(const AttnLaunch &a, hipStream_t stream) {
+hipError_t launch_merge(const AttnLaunch &a, const NextList *next, hipStream_t stream) {
   const PoolShape &s = a.shape;
   const AttnArgs args = make_args(a);
-  dim3 mgrid((s.H + 3) / 4, a.batch.B);
   if (args.lens) {
+    const dim3 mgrid((s.H + 3) / 4, a.batch.B);
+    if (next) return hipErrorInvalidValue;
     if (s.D == 128)
-      hipLaunchKernelGGL((attn_merge_kernel<128, true, NoLayers>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args, NoLayers{});
+      hipLaunchKernelGGL((attn_merge_kernel<128, true, NoLayers, NoNextList>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args, NoLayers{}, NoNextList{});
     else if (s.D == 64)
-      hipLaunchKernelGGL((attn_merge_kernel<64, true, NoLayers>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args, NoLayers{});
+      hipLaunchKernelGGL((attn_merge_kernel<64, true, NoLayers, NoNextList>), mgrid, dim3(256), 0, stream, args.lens, args.part_ml, args.part_o, args.B, 1, args.H, args, NoLayers{}, NoNextList{});
     else
       return hipErrorInvalidValue;
     return hipGetLastError();
   }
-  if (s.D == 128)
-    hipLaunchKernelGGL((attn_merge_kernel<128, false, NoLayers>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args, NoLayers{});
-  else if (s.D == 64)
-    hipLaunchKernelGGL((attn_merge_kernel<64, false, NoLayers>), mgrid, dim3(256), 0, stream, args.chunk_prefix, args.part_ml, args.part_o, args.B, args.n_cls, args.H, args, NoLayers{});
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  return launch_merge_as(args, NoLayers{}, s, 1, next, stream);
 }
 
 // ---- step bookkeeping ------------------------------------------------------------
 
 namespace {
-
-constexpr int kStepThreads = 256;
 
 // Inclusive scan of one value per thread over the workgroup's kStepThreads threads, and the sum of all of them:
 // a scan inside every wavefront and one hand-over of the wavefronts' sums through LDS (two barriers,
@@ -1298,37 +1476,6 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_kernel(int32_t *ctx
     at += cnt;
   }
   if (tid == kStepThreads - 1) chunk_prefix[B] = (int32_t)total_items;
-}
-
-// One record per (stretch, KV head) pair, by the whole workgroup: the stretch's first item and where that head's rows of the
-// item's first two tiles lie.  Nothing is written for pairs past the last stretch: the attention kernel
-// knows how many stretches there are.
-__device__ __forceinline__ void write_pair_heads(const int32_t n_groups, const int32_t *open_item, const int4 *open_desc, const int2 *open_blk,
-                                                 PairHead *pair_head, const HeadGeom &hg) {
-  const int32_t St_mask = (1 << hg.st_log2) - 1;
-  const int32_t n_pairs = (int32_t)min((int64_t)n_groups * hg.G, (int64_t)hg.max_pairs);
-  for (int p = threadIdx.x; p < n_pairs; p += kStepThreads) {
-    const int32_t group = p / hg.G, g = p - group * hg.G;
-    PairHead h = {};
-    const int32_t it = group < n_groups && group < kHeadGroupsMax ? open_item[group] : -1;
-    const int32_t n = it >= 0 ? open_item[group + 1] - it : 0;
-    if (n > 0) {                                         // (a batch with no keys at all has one stretch and no item)
-      h.item = it, h.count = n;
-      const int4 d = open_desc[group];
-      h.b = d.x, h.lo = d.y, h.hi = d.z, h.flags_g = d.w | (g << 8);
-      const int32_t grp = g / hg.gg;
-      const int32_t head_k = ((grp * 2 * hg.gg) << hg.st_log2) + (g - grp * hg.gg);
-      const int32_t t0 = d.y >> 4, t_last = (d.z - 1) >> 4;
-      for (int i = 0; i < 2; ++i) {
-        const int32_t t = min(t0 + i, t_last);
-        const int32_t blk = i ? open_blk[group].y : open_blk[group].x;
-        const int64_t lin = (int64_t)blk * hg.tiles + (hg.block_table ? t & (hg.tiles - 1) : t);
-        const int64_t base = (lin >> hg.st_log2) * ((int64_t)(2 * hg.G) << hg.st_log2) + (lin & St_mask) * hg.gg + head_k;
-        (i ? h.base1 : h.base0) = (int32_t)base;
-      }
-    }
-    pair_head[p] = h;
-  }
 }
 
 // The bookkeeping for equal stretches: lengths advance, the tiles of all sequences are counted and
@@ -1429,111 +1576,6 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_spans_kernel(int32_
     plan_out[2] = (int32_t)((int64_t)plan.span & 0x7fffffff);
     plan_out[3] = (int32_t)((int64_t)plan.span >> 31);
   }
-}
-
-// The same for at most a sequence per thread, with an item per thread too: a thread counts and scans its sequence, and then finds
-// for one stretch the sequence that its first tile lies in.  Every item either opens a stretch or begins its sequence in mid-stretch, so
-// an item's place in the list is the number of stretches that begin before it and of sequences that begin in mid-stretch before it.
-// (Above, the thread of a long sequence writes all of its items one after the other, each behind a look-up in the block table.)
-// us before -> now: one sequence of 4096 keys, 4 and 32 KV heads 9.5 -> 3.6 and 10.5 -> 4.7, two of 4000 with 8 heads 10.0 -> 4.1, 16 of up to
-// 4096 6.7 -> 4.8, 128 of up to 4096 5.8 -> 5.1, 24 of up to 1150 4.8 (about what a dependent launch takes behind a long one) either way.
-// With 512 or 1024 threads the small ones take 0.3 or 1 us more.
-__global__ __launch_bounds__(kStepThreads) void step_advance_items_kernel(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *item_desc,
-                                                                         int32_t *group_first, int32_t *plan_out, const int32_t B,
-                                                                         const int32_t max_groups, const int32_t min_span, const int32_t inc,
-                                                                         PairHead *pair_head, const int32_t most_tiles, const HeadGeom hg) {
-  __shared__ int32_t wave_tiles[kStepThreads / 64], wave_mids[kStepThreads / 64];
-  // per sequence: tiles before it (past the batch: more than there are), place of its first item, keys
-  __shared__ int32_t seq_first[kStepThreads], seq_at[kStepThreads], seq_n[kStepThreads];
-  // what opens each stretch: its first item, that item's descriptor and the block ids of the item's first two tiles
-  // (the second clamped to the item's last tile)
-  __shared__ int32_t open_item[kHeadGroupsMax + 1];
-  __shared__ int4 open_desc[kHeadGroupsMax];
-  __shared__ int2 open_blk[kHeadGroupsMax];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // (a length no sequence can have, which only a caller's own device array could hold, does not leave the arithmetic)
-  auto tiles_of = [&](int32_t n) -> int32_t { return min(max((n >> 4) + ((n & 15) != 0), 0), most_tiles); };
-  auto keys_to = [&](int32_t n, int32_t tile) -> int32_t { return (int32_t)min((int64_t)n, (int64_t)tile << 4); };
-  int32_t n = 0;
-  if (tid < B) {
-    n = ctx_lens[tid] + inc;
-    if (inc) ctx_lens[tid] = n;                                // inc == 0: the lengths are only read
-  }
-  const int32_t tiles = tiles_of(n);
-  const int32_t upto = wave_scan(tiles);
-  if (lane == 63) wave_tiles[wave] = upto;
-  __syncthreads();
-  int32_t before = 0, total = 0;
-#pragma unroll
-  for (int w = 0; w < kStepThreads / 64; ++w) {
-    const int32_t t = wave_tiles[w];
-    before += w < wave ? t : 0;
-    total += t;
-  }
-  const int32_t first = before + upto - tiles;
-  const SpanPlanOf<int32_t> plan = span_plan<int32_t>(total, max_groups, min_span);
-  const int32_t span = __builtin_amdgcn_readfirstlane(plan.span), n_groups = __builtin_amdgcn_readfirstlane(plan.n_groups);
-  const int32_t in_stretch = first / span, into = first - in_stretch * span;       // the stretch its first tile lies in, how far
-  const bool mid = tiles > 0 && into != 0;
-  const uint64_t mids = __ballot(mid);
-  if (lane == 0) wave_mids[wave] = (int32_t)__builtin_popcountll(mids);
-  seq_first[tid] = tid < B ? first : INT32_MAX;
-  seq_n[tid] = n;
-  __syncthreads();
-  int32_t mids_before = (int32_t)__builtin_popcountll(mids & ((1ull << lane) - 1)), all_mids = 0;
-#pragma unroll
-  for (int w = 0; w < kStepThreads / 64; ++w) {
-    const int32_t k = wave_mids[w];
-    mids_before += w < wave ? k : 0;
-    all_mids += k;
-  }
-  const int32_t n_items = n_groups + all_mids;
-  const int32_t at = in_stretch + (into != 0) + mids_before;
-  seq_at[tid] = at;
-  if (tid < B) chunk_prefix[tid] = at;
-  if (mid) {
-    const bool ends = span - into >= tiles;
-    item_desc[at] = make_int4(tid, 0, keys_to(n, min(span - into, tiles)), ends ? kItemLast | kItemWhole : 0);
-  }
-  __syncthreads();
-  for (int32_t j = tid; j < n_groups; j += kStepThreads) {
-    const int32_t tile = j * span;
-    int b = 0;                                           // the last sequence that begins at or before the tile (an empty one never is)
-#pragma unroll
-    for (int step = kStepThreads / 2; step > 0; step >>= 1)
-      if (seq_first[b + step] <= tile) b += step;
-    const int32_t nb = seq_n[b], from = tile - seq_first[b], end = tiles_of(nb);
-    const int32_t it = seq_at[b] + j - (tile - from) / span;
-    const bool ends = from + span >= end;
-    const int32_t lo = from << 4, hi = keys_to(nb, min(from + span, end));
-    const int4 desc = make_int4(b, lo, hi, ends ? (from == 0 ? kItemLast | kItemWhole : kItemLast) : 0);
-    item_desc[it] = desc;
-    group_first[j] = it;
-    if (pair_head) {
-      int2 blk = make_int2(b, b);
-      if (hg.block_table) {
-        const int32_t t0 = lo >> 4, t1 = min(t0 + 1, (hi - 1) >> 4);
-        const int32_t *row = hg.block_table + (size_t)b * hg.max_blocks;
-        blk.x = row[min((t0 << 4) >> hg.log2_T, hg.max_blocks - 1)];
-        blk.y = row[min((t1 << 4) >> hg.log2_T, hg.max_blocks - 1)];
-      }
-      open_item[j] = it;
-      open_desc[j] = desc;
-      open_blk[j] = blk;
-    }
-  }
-  if (tid == kStepThreads - 1) {
-    if (pair_head) open_item[n_groups] = n_items;
-    group_first[n_groups] = n_items;
-    chunk_prefix[B] = n_items;
-    plan_out[0] = n_groups;
-    plan_out[1] = n_items;
-    plan_out[2] = span;
-    plan_out[3] = 0;
-  }
-  if (!pair_head) return;
-  __syncthreads();
-  write_pair_heads(n_groups, open_item, open_desc, open_blk, pair_head, hg);
 }
 
 // The same bookkeeping when a sequence is cut into runs of one block class each.  Pairs

@@ -1,0 +1,165 @@
+"""Steps whose work list the merge of the step before made: every step's list, lengths and outputs are those of a batch that was
+described anew before it, bit for bit, over batches that are cut in every step, that go from cut to whole and back, that reach
+their capacity, and with calls in between that change what a step needs."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import worklist
+from paper_2504_11816_amd import binding, synth
+from paper_2504_11816_amd.harness import Stack
+
+from gpu_util import make_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def waves(G):
+    return max(1, 4 * torch.cuda.get_device_properties(0).multi_processor_count // G)
+
+
+def cut(lens, G):
+    items, _, _ = worklist.expected_items_equal_stretches(np.asarray(lens, dtype=np.int32), waves(G))
+    return len(items) > len(lens)
+
+
+def toggling(G, B, steps):
+    """Lengths whose batch is cut at some of the next steps and whole at others, in both directions."""
+    rng = np.random.Generator(np.random.PCG64(B))
+    for _ in range(20000):
+        lens = rng.integers(40, 300, size=B)
+        seen = "".join("c" if cut(lens + 1 + i, G) else "w" for i in range(steps))
+        if "cw" in seen and "wc" in seen:
+            return lens.astype(np.int32)
+    raise AssertionError("no such lengths")
+
+
+def pair(L, G, d, T, B, cap):
+    table = None if not T else synth.shuffled_block_table([cap] * B, T, B * synth.blocks_needed(cap, T), seed=B)
+    stacks = [Stack(L=L, H=2 * G, G=G, d=d, B=B, T=T, cap_tokens=cap) for _ in range(2)]
+    for l in range(L):
+        stacks[0].fill_pool(l, 7 + l)
+        stacks[1].pools[l].copy_(stacks[0].pools[l])
+    torch.cuda.synchronize()
+    return stacks, table
+
+
+def check_step(a, b, lens, table, i, together):
+    """Step a goes on, b is described anew; both are at `lens` before."""
+    b.set_batch(lens, table)
+    outs = []
+    for st in (a, b):
+        q, k, v, out = make_inputs(st, 50 + i, 0, st.device)
+        for o in out:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        if together:
+            st.step_bound(st.bind_step(q, k, v, out))
+        else:
+            st.step(q, k, v, out)
+        st.synchronize()
+        outs.append(torch.stack(out).cpu().numpy().view(np.uint16))
+    assert np.array_equal(*outs), i
+    assert np.array_equal(a.ctx.okv_get_ctx_lens(), lens + 1)
+    items = a.ctx.okv_worklist(from_device=True)
+    np.testing.assert_array_equal(items, a.ctx.okv_worklist(from_device=False))
+    np.testing.assert_array_equal(items, b.ctx.okv_worklist(from_device=True))
+
+
+@pytest.mark.parametrize("together", [False, True])
+@pytest.mark.parametrize("L,G,d,T,B,lens", [
+    (3, 8, 128, 16, 5, (300, 17, 900, 1, 333)), (2, 4, 64, 0, 3, (700, 127, 640)), (2, 32, 64, 32, 24, None), (1, 4, 128, 16, 1, (2000,)),
+    (2, 4, 64, 16, 3, "toggling"), (2, 16, 128, 0, 2, "toggling"), (2, 4, 64, 16, 256, None)])
+def test_going_on_equals_being_described_anew(L, G, d, T, B, lens, together):
+    print(f"L={L} G={G} d={d} T={T} B={B} together={together}", flush=True)
+    steps = 14 if isinstance(lens, str) else 6
+    lens = toggling(G, B, steps) if isinstance(lens, str) else synth.ragged_ctx_lens(B, 20, 400, 3) if lens is None else np.array(lens)
+    lens = np.asarray(lens, dtype=np.int32)
+    (a, b), table = pair(L, G, d, T, B, int(lens.max()) + steps + 2)
+    a.set_batch(lens, table)
+    for i in range(steps):
+        check_step(a, b, lens + i, table, i, together)
+    a.close()
+    b.close()
+
+
+def test_calls_between_steps():
+    lens = np.array([300, 40, 512, 90], dtype=np.int32)
+    (a, b), table = pair(2, 8, 128, 16, 4, 640)
+    a.set_batch(lens, table)
+    n = lens.copy()
+    for i in range(8):
+        if i == 2:                                       # another cutting of the batch, and back
+            a.ctx.okv_set_split_tokens(128)
+            assert max(e - s for _, s, e in a.ctx.okv_worklist(from_device=True)) <= 128
+        if i == 3:
+            a.ctx.okv_set_split_tokens(0)
+        if i == 2:
+            b.ctx.okv_set_split_tokens(128)
+        if i == 3:
+            b.ctx.okv_set_split_tokens(0)
+        if i == 5:                                       # tokens are stored in between
+            rows = torch.randn((6, 8, 128), device=a.device).half()
+            for st in (a, b):
+                if st is b:
+                    st.set_batch(n, table)
+                st.prefill([3, 0, 1, 2], rows, rows)
+            n = n + np.array([3, 0, 1, 2], dtype=np.int32)
+            np.testing.assert_array_equal(a.ctx.okv_get_ctx_lens(), n)
+        check_step(a, b, n, table, i, i % 2 == 0)
+        n = n + 1
+    a.set_batch(lens, table)                             # described anew right behind a step
+    np.testing.assert_array_equal(a.ctx.okv_get_ctx_lens(), lens)
+    check_step(a, b, lens, table, 20, True)
+    a.close()
+    b.close()
+
+
+def test_a_step_past_the_capacity_is_refused_and_changes_nothing():
+    lens = np.array([200, 318, 77], dtype=np.int32)
+    (a, b), table = pair(1, 4, 64, 16, 3, 320)
+    a.set_batch(lens, table)
+    for i in range(2):
+        check_step(a, b, lens + i, table, i, False)
+    items = a.ctx.okv_worklist(from_device=True)
+    for _ in range(2):
+        with pytest.raises(binding.OkvError) as e:
+            a.ctx.okv_step_begin()
+        assert e.value.code == binding.OKV_ENOSPC
+        np.testing.assert_array_equal(a.ctx.okv_get_ctx_lens(), lens + 2)
+        np.testing.assert_array_equal(a.ctx.okv_worklist(from_device=True), items)
+    a.close()
+    b.close()
+
+
+def test_a_captured_step_makes_its_own_list():
+    lens = np.array([300, 40, 512, 90], dtype=np.int32)
+    (a, b), table = pair(2, 8, 128, 16, 4, 640)
+    a.set_batch(lens, table)
+    for i in range(3):                                   # the last of them leaves a list for the step that is captured
+        check_step(a, b, lens + i, table, i, True)
+    q, k, v, out = make_inputs(a, 90, 0, a.device)
+    bound = a.bind_step(q, k, v, out)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=a.compute_stream):
+        a.step_bound(bound)
+    for r in range(5):
+        for o in out:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.isfinite(torch.randn(1 << 12, device=a.device).sum().item())
+        b.set_batch(lens + 3 + r, table)
+        ref = [torch.full_like(o, float("nan")) for o in out]
+        b.step_bound(b.bind_step(q, k, v, ref))
+        b.synchronize()
+        np.testing.assert_array_equal(a.ctx.okv_get_ctx_lens(), lens + 4 + r)
+        for x, y in zip(out, ref):
+            assert torch.equal(x, y), r
+    a.set_batch(lens, table)
+    for i in range(2):
+        check_step(a, b, lens + i, table, 30 + i, True)
+    a.close()
+    b.close()
