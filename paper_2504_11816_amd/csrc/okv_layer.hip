@@ -1345,7 +1345,7 @@ hipError_t launch_linear_tile(const LinearArgs &a, int form, hipStream_t stream)
 struct LinearPlan {
   enum Kind { kSimple = 0, kStaged = 1, kTile = 2 } kind;
   int waves, cuts, form;
-  double us;
+  double us, us_by_intake;               // (the second: the staged kernel from 129 rows on)
 };
 
 // Streaming wavefronts per workgroup (4 or 3) and cuts of the input dimension for the staged kernel, by a small
@@ -1364,8 +1364,11 @@ struct LinearPlan {
 // alternative: 3.9 us, the weights at 7.7 MB/us, the rows of x that a compute unit takes in at 71.5 KB/us (60 where they
 // are 16384 inputs apart: rows at multiples of 32 KiB share the memory channels) and for a cut 2.5 us and the shares at
 // 4.4 MB/us.  (60 shapes of 129 to 192 rows, 512 to 20480 features and inputs, weights from HBM, warm clocks: within 4.6 % rms.)
+// `us_by_intake` is a second estimate, better for many cuts and for several rounds (309 shapes, 256 to 20480: 7.4 % rms, `us` 10 %): 3.4 us,
+// the root of the sum of squares of the weights at 4.85 MB/us and of what a compute unit takes in at 58 KB/us (of its weights a quarter), and
+// for a cut 1.9 us, 0.14 for each and the shares at 4.15 MB/us.
 LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
-  LinearPlan plan = {LinearPlan::kStaged, 4, 0, 0, 0.0};
+  LinearPlan plan = {LinearPlan::kStaged, 4, 0, 0, 0.0, 0.0};
   if (m > OKV_LINEAR_MAX_ROWS_STAGED) return plan;
   const int chunk = lin_chunk((m + 15) / 16), pace = lin_weight_lead((m + 15) / 16);
   if (n_in % (32 * chunk * pace)) return plan;
@@ -1390,6 +1393,9 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
         plan.cuts = s;
         const double intake_kb = (double)rounds * m * (n_in / s) * 2 / 1e3;
         plan.us = 3.9 + weight_mb / 7.7 + intake_kb / (n_in % 16384 ? 71.5 : 60.0) + (s > 1 ? 2.5 + (double)s * m * n_out * 4 / 4.4e6 : 0.0);
+        const double weights_kb = (double)rounds * 16 * w * (n_in / s) * 2 / 1e3;
+        plan.us_by_intake = 3.41 + std::hypot(weight_mb / 4.85, (intake_kb + 0.24 * weights_kb) / 58.1) +
+                            (s > 1 ? 1.87 + 0.14 * s + (double)s * m * n_out * 4 / 4.15e6 : 0.0);
       }
     }
   }
@@ -1409,7 +1415,7 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
 // Shares beyond 134 MB, which with the weights no longer stay in the memory-side cache until they are added, take 0.3 us a MB more: 3507 rows x 6144
 // x 8192 370 us in three cuts (258 MB), 324 uncut, 1405 x 16384 x 12288 544 in two, 504 uncut.
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
-  LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
+  LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0, 0.0};
   const int stages = (n_in + 63) / 64;
   const double weight_mb = (double)n_out * n_in * 2 / 1e6;
   double best = 0;
@@ -1460,7 +1466,9 @@ bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, cons
 // inputs are many the tile kernel would win, 4096 x 16384 at 128 rows 35 against 43, with twice the cuts and so twice the
 // workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
 // for (at 192 rows 4096 x 16384 42 us against 53 and 16384 x 4096 40 against 43, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
-// 20.2 against 17.0, staged), beyond always a tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
+// 20.2 against 17.0, staged), or whichever the second estimate of the staged one favours by 4 % (129 rows x 496 x 6400, 25 cuts, 13.1 against
+// 8.9, 136 x 608 x 12032, 47 cuts, 20.2 against 12.8, 192 x 20480 x 5120 uncut in two rounds 85 against 72,
+// tiles; none of the 309 shapes slower; the narrowest outputs are ties that host tests hold to the staged kernel), beyond always a tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
 // workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront, in rounds of a workgroup per compute unit
 // (which overlap a little) and somewhat faster where units are idle; the tile model is 1.2 us high for such short walks, and 2 for
 // cut ones.  simple / tile us: 9 rows x 4096 x 10240 16.6 / 37.3, 12 x 4096 x 5120 10.0 / 19.8, 16 x 4224 x 4096 14.1 / 16.1, 19 x 3072 x
@@ -1468,14 +1476,14 @@ bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, cons
 // shapes of 9 to 128 rows, 96 to 20480 features and inputs, weights from HBM: the choice is 0.6 % slower than the faster of the two
 // on average.  The simple kernel's time scatters by 10 % around its model: in doubt the line favours tiles, whose model is the better one.)
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
-  const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0};
+  const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0, 0.0};
   const LinearPlan staged = staged_plan(m, n_out, n_in, n_cus);
   const bool staged_runs = staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes);
   if (m <= OKV_LIN_SIMPLE_ROWS && !staged_runs) return simple;
   if (m <= 16 && staged.cuts > 0 && few_rows_simple(m, n_out, n_in, n_cus, staged)) return simple;
   if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return staged;
   const LinearPlan tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
-  if (staged_runs) return tile.us < 0.955 * staged.us ? tile : staged;
+  if (staged_runs) return tile.us < 0.955 * staged.us || (n_out >= 288 && tile.us < 0.96 * staged.us_by_intake) ? tile : staged;
   if (m > OKV_LINEAR_MAX_ROWS) return tile;
   const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 0.82 * std::ceil(q) + 0.18 * q;
   const int fragments = (m + 15) / 16;
