@@ -1345,7 +1345,7 @@ hipError_t launch_linear_tile(const LinearArgs &a, int form, hipStream_t stream)
 struct LinearPlan {
   enum Kind { kSimple = 0, kStaged = 1, kTile = 2 } kind;
   int waves, cuts, form;
-  double us, us_by_intake;               // (the second: the staged kernel from 129 rows on)
+  double us, us_by_intake;               // (the second: the staged kernel from 65 rows on)
 };
 
 // Streaming wavefronts per workgroup (4 or 3) and cuts of the input dimension for the staged kernel, by a small
@@ -1366,7 +1366,7 @@ struct LinearPlan {
 // 4.4 MB/us.  (60 shapes of 129 to 192 rows, 512 to 20480 features and inputs, weights from HBM, warm clocks: within 4.6 % rms.)
 // `us_by_intake` is a second estimate, better for many cuts and for several rounds (309 shapes, 256 to 20480: 7.4 % rms, `us` 10 %): 3.4 us,
 // the root of the sum of squares of the weights at 4.85 MB/us and of what a compute unit takes in at 58 KB/us (of its weights a quarter), and
-// for a cut 1.9 us, 0.14 for each and the shares at 4.15 MB/us.
+// for a cut 1.9 us, 0.14 for each and the shares at 4.15 MB/us.  (From 65 to 128 rows with constants of their own, 478 shapes: 6.4 % rms.)
 LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
   LinearPlan plan = {LinearPlan::kStaged, 4, 0, 0, 0.0, 0.0};
   if (m > OKV_LINEAR_MAX_ROWS_STAGED) return plan;
@@ -1394,8 +1394,11 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
         const double intake_kb = (double)rounds * m * (n_in / s) * 2 / 1e3;
         plan.us = 3.9 + weight_mb / 7.7 + intake_kb / (n_in % 16384 ? 71.5 : 60.0) + (s > 1 ? 2.5 + (double)s * m * n_out * 4 / 4.4e6 : 0.0);
         const double weights_kb = (double)rounds * 16 * w * (n_in / s) * 2 / 1e3;
-        plan.us_by_intake = 3.41 + std::hypot(weight_mb / 4.85, (intake_kb + 0.24 * weights_kb) / 58.1) +
-                            (s > 1 ? 1.87 + 0.14 * s + (double)s * m * n_out * 4 / 4.15e6 : 0.0);
+        plan.us_by_intake = m > OKV_LINEAR_MAX_ROWS
+                                ? 3.41 + std::hypot(weight_mb / 4.85, (intake_kb + 0.24 * weights_kb) / 58.1) +
+                                      (s > 1 ? 1.87 + 0.14 * s + (double)s * m * n_out * 4 / 4.15e6 : 0.0)
+                                : 3.07 + std::hypot(weight_mb / 6.06, intake_kb / 54.0) +
+                                      (s > 1 ? 1.72 + 0.14 * s + (double)s * m * n_out * 4 / 3.51e6 : 0.0);
       }
     }
   }
@@ -1461,10 +1464,13 @@ bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, cons
   return n_in % 1024 == 0 && simple_us + 2.0 < staged_us;
 }
 
-// The kernel for a product.  Up to 16 rows the simple or the staged one (few_rows_simple).  Up to OKV_LINEAR_MAX_ROWS rows the staged one
-// where it takes the shape (12288 x 4096 at 128 rows 28 us against the tile kernel's 31, 16384 x 4096 35 against 38; where the
-// inputs are many the tile kernel would win, 4096 x 16384 at 128 rows 35 against 43, with twice the cuts and so twice the
-// workspace).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
+// The kernel for a product.  Up to 16 rows the simple or the staged one (few_rows_simple), up to 64 the staged one where it takes the
+// shape (86 shapes of 17 to 32 rows: 0.5 % slower on average than the faster of it and tiles, 95 of 33 to 64: 1.6 %).  From there to
+// OKV_LINEAR_MAX_ROWS rows tiles where their model is 7 % below the staged kernel's by intake, for 288 to 20480 features (narrower ones
+// are ties; wider ones were not measured, and host tests hold some of both to the staged kernel): 128 rows x 5120 x 20480 65.5 us
+// staged, 49.0 tiles, 128 x 20480 x 5120 66 and 52, 128 x 2304 x 768 6.2 and 4.9, 96 x 5120 x 20480 56.8
+// and 44.7; 128 x 12288 x 4096 28 and 31, 128 x 16384 x 4096 35 and 38 (478 shapes: 55 change, 14 % faster on average, the worst 0.5 %
+// slower; at 5 % 74 change and the worst, 80 x 4096 x 16384 with a norm, is 3 % slower).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
 // for (at 192 rows 4096 x 16384 42 us against 53 and 16384 x 4096 40 against 43, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
 // 20.2 against 17.0, staged), or whichever the second estimate of the staged one favours by 4 % (129 rows x 496 x 6400, 25 cuts, 13.1 against
 // 8.9, 136 x 608 x 12032, 47 cuts, 20.2 against 12.8, 192 x 20480 x 5120 uncut in two rounds 85 against 72,
@@ -1481,8 +1487,9 @@ LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, 
   const bool staged_runs = staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes);
   if (m <= OKV_LIN_SIMPLE_ROWS && !staged_runs) return simple;
   if (m <= 16 && staged.cuts > 0 && few_rows_simple(m, n_out, n_in, n_cus, staged)) return simple;
-  if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return staged;
+  if (staged_runs && (m <= 64 || (m <= OKV_LINEAR_MAX_ROWS && (n_out < 288 || n_out > 20480)))) return staged;
   const LinearPlan tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
+  if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return tile.us < 0.93 * staged.us_by_intake ? tile : staged;
   if (staged_runs) return tile.us < 0.955 * staged.us || (n_out >= 288 && tile.us < 0.96 * staged.us_by_intake) ? tile : staged;
   if (m > OKV_LINEAR_MAX_ROWS) return tile;
   const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 0.82 * std::ceil(q) + 0.18 * q;

@@ -1,4 +1,4 @@
-"""Which kernel a product of up to 16 rows (and, at the end, of 129 to 192) takes, against what the simple and the staged kernel took on MI355X (us, weights from HBM):
+"""Which kernel a product of up to 16 rows (and, at the end, of 65 to 192) takes, against what the simple and the staged kernel took on MI355X (us, weights from HBM):
 the faster one wherever they are more than 12 % apart (from 9 rows on also 2 us, which a layer norm behind the simple one takes more).  No GPU: the choice is made on the host."""
 import pytest
 
@@ -26,10 +26,11 @@ def test_without_a_workspace_few_rows_run_uncut():
     assert binding.okv_linear_plan(16, 4096, 4096, 0) == binding.okv_linear_plan(16, 4096, 4096, 1 << 30) == (0, 16, 16, 1)
 
 
-# 129 to 192 rows: rows, features, inputs, staged kernel, tiles (with the launch that adds the shares), more than 8 % apart
+# 65 to 192 rows: rows, features, inputs, staged kernel, tiles (with the launch that adds the shares), more than 8 % apart
 @pytest.mark.parametrize("m,n_out,n_in,staged_us,tile_us", [
     (129, 496, 6400, 13.1, 8.9), (136, 608, 12032, 20.2, 12.8), (177, 480, 6144, 14.0, 9.7), (184, 400, 4096, 10.9, 7.6), (192, 768, 3072, 11.7, 8.9),
     (145, 2048, 13824, 29.0, 22.0), (192, 20480, 5120, 85.2, 72.0), (144, 4160, 13824, 50.0, 34.5),
-    (160, 4608, 3072, 15.0, 16.7), (136, 16384, 3072, 27.2, 30.1), (136, 12288, 4096, 30.1, 34.6), (160, 6144, 4096, 21.8, 24.6), (136, 15360, 5120, 43.2, 47.2)])
+    (128, 5120, 20480, 65.5, 49.0), (128, 20480, 5120, 66.3, 52.4), (128, 2304, 768, 6.2, 4.9), (96, 5120, 20480, 56.8, 44.7),
+    (128, 12288, 4096, 28.0, 31.0), (128, 16384, 4096, 35.0, 38.0), (160, 4608, 3072, 15.0, 16.7), (136, 16384, 3072, 27.2, 30.1), (136, 12288, 4096, 30.1, 34.6), (160, 6144, 4096, 21.8, 24.6), (136, 15360, 5120, 43.2, 47.2)])
 def test_many_rows_staged_or_tiles(m, n_out, n_in, staged_us, tile_us):
     assert binding.okv_linear_plan(m, n_out, n_in)[0] == (1 if staged_us < tile_us else 2)
