@@ -1453,13 +1453,17 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
 // the staged kernel are not).  us, the rule by rows alone -> this one: 8 rows x 5120 x 20480 48.4 -> 36.7, 3 x 512 x 20480 with a norm 18.1 ->
 // 10.5, 8 x 1632 x 17920 19.9 -> 14.0; 12 x 4096 x 4096 10.6 -> 7.3, with a norm 12.2 -> 10.1, 12 x 2048 x 2048 7.8 -> 4.7, 11 x 4096 x 2048
 // 8.2 -> 4.9.
+double few_rows_simple_us(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
+  const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 1.29 * std::ceil(q) - 0.29 * q;
+  const double intake_us = rounds * n_in * 2 / 1e3 * (16.0 + 2.0 * m) / 72.0, weights_us = (double)n_out * n_in * 2 / 1e6 / 9.3;
+  return 2.57 + (n_in % 1024 ? 0.56 : 0.0) + std::sqrt(intake_us * intake_us + weights_us * weights_us);
+}
 bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, const LinearPlan &staged) {
   const double weight_mb = (double)n_out * n_in * 2 / 1e6, row_kb = (double)n_in * 2 / 1e3;
-  const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 1.29 * std::ceil(q) - 0.29 * q;
-  const double simple_us = 2.57 + (n_in % 1024 ? 0.56 : 0.0) + std::hypot(rounds * row_kb * (16.0 + 2.0 * m) / 72.0, weight_mb / 9.3);
+  const double simple_us = few_rows_simple_us(m, n_out, n_in, n_cus);
   const int64_t wgs = (int64_t)((n_out / 16 + staged.waves - 1) / staged.waves) * staged.cuts;
   const double intake_kb = (double)((wgs + n_cus - 1) / n_cus) * (16.0 * staged.waves + 0.42 * m) * row_kb / staged.cuts;
-  const double staged_us = 2.91 + (staged.cuts > 1 ? 3.39 : 0.0) + std::hypot(intake_kb / 58.0, weight_mb / 8.1);
+  const double staged_us = 2.91 + (staged.cuts > 1 ? 3.39 : 0.0) + std::sqrt(intake_kb / 58.0 * (intake_kb / 58.0) + weight_mb / 8.1 * (weight_mb / 8.1));
   if (m <= OKV_LIN_SIMPLE_ROWS) return simple_us < 1.14 * staged_us;
   return n_in % 1024 == 0 && simple_us + 2.0 < staged_us;
 }
@@ -1483,6 +1487,9 @@ bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, cons
 // on average.  The simple kernel's time scatters by 10 % around its model: in doubt the line favours tiles, whose model is the better one.)
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0, 0.0};
+  // (most products of up to 8 rows are faster than the staged kernel could stream the weights alone: the same choice without its plan, 12 ns of
+  // the call's host time for 4 x 4096 x 4096 instead of 147)
+  if (m <= OKV_LIN_SIMPLE_ROWS && few_rows_simple_us(m, n_out, n_in, n_cus) < 1.14 * (2.91 + (double)n_out * n_in * 2 / 8.1e6)) return simple;
   const LinearPlan staged = staged_plan(m, n_out, n_in, n_cus);
   const bool staged_runs = staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes);
   if (m <= OKV_LIN_SIMPLE_ROWS && !staged_runs) return simple;
