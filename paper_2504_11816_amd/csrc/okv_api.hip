@@ -133,7 +133,9 @@ struct okv_ctx {
   int32_t *d_chunk_prefix2 = nullptr, *d_group_first2 = nullptr, *d_plan2 = nullptr;
   int4 *d_item_desc2 = nullptr;
   void *d_pair_head2 = nullptr;
+  // A context of which a step was captured makes none any more: a replay advances the device's lengths without the host.
   bool list_ahead = false;
+  bool was_captured = false;
   int32_t lens_lag = 0;
   bool keep_cached = true;               // the batch's keys and values of all layers fit the memory-side cache
   int64_t max_items = 0;
@@ -435,16 +437,19 @@ bool is_capturing(hipStream_t stream) {
 
 // What the merge of a step's last layer makes on the side: the work list of the step after this one, in the arrays that the step itself
 // does not read.  That step then begins without a launch (it exchanges the two sets of arrays); its own last merge, or
-// okv_step_end where there is none, brings the device's lengths up to date.  Not while the stream is being captured: a graph's steps each
-// make their own list.  Lengths that the next step refuses (a sequence at its capacity) give a list that nobody reads, in
-// arrays that hold as many items as they can give: one per stretch and one per sequence that begins in mid-stretch.
+// okv_step_end where there is none, brings the device's lengths up to date.  Not while the stream is being captured, nor ever after: a
+// graph's steps each make their own list, and so has a step behind a replay to, whose lengths only the device knows.  Lengths that
+// the next step refuses (a sequence at its capacity) give a list that nobody reads, in arrays that hold as many items as they can
+// give: one per stretch and one per sequence that begins in mid-stretch.
 const okv::NextList *next_list(okv_ctx *ctx, okv::NextList *n) {
   const int64_t cap_tiles = ((int64_t)ctx->cap_tokens + 15) / 16;
-  if (!ctx->d_item_desc2 || !ctx->spans || !ctx->need_merge || !okv::next_list_rides(ctx->B, ctx->max_groups, cap_tiles + 1)) return nullptr;
+  if (!ctx->d_item_desc2 || ctx->was_captured || !ctx->spans || !ctx->need_merge) return nullptr;
+  if (!okv::next_list_rides(ctx->B, ctx->max_groups, cap_tiles + 1)) return nullptr;
   int64_t total = 0;
   for (int32_t b = 0; b < ctx->B; ++b) total += (ctx->h_ctx_lens[b] + 16) >> 4;      // with the next token
   const okv::SpanPlan plan = okv::span_plan(total, ctx->max_groups, kMinSpanTiles);
-  if ((int64_t)ctx->B + plan.n_groups > ctx->max_items || is_capturing(ctx->compute)) return nullptr;
+  if ((int64_t)ctx->B + plan.n_groups > ctx->max_items) return nullptr;
+  if ((ctx->was_captured = is_capturing(ctx->compute))) return nullptr;      // (a capture that began inside the step)
   *n = okv::NextList{ctx->d_ctx_lens, ctx->d_chunk_prefix2, ctx->d_item_desc2, ctx->d_group_first2, ctx->d_plan2, ctx->d_pair_head2, ctx->B,
                      ctx->max_groups, kMinSpanTiles, ctx->lens_lag, (1 << 30) / std::max(ctx->B, 1),
                      okv::head_geom(ctx->shape, ctx->d_block_table, max_pairs(ctx->max_waves))};
@@ -1285,7 +1290,8 @@ int okv_step_begin(okv_ctx *ctx) {
     }
   }
   for (int32_t b = 0; b < ctx->B; ++b) ctx->h_ctx_lens[b] += 1;
-  const bool ahead = ctx->list_ahead && !is_capturing(ctx->compute);
+  if (ctx->d_item_desc2 && !ctx->was_captured) ctx->was_captured = is_capturing(ctx->compute);
+  const bool ahead = ctx->list_ahead && !ctx->was_captured;
   const int rc = rebuild_worklist(ctx, 1, false, /*now=*/!ahead);
   if (rc) {
     for (int32_t b = 0; b < ctx->B; ++b) ctx->h_ctx_lens[b] -= 1;

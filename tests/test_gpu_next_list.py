@@ -163,3 +163,33 @@ def test_a_captured_step_makes_its_own_list():
         check_step(a, b, lens + i, table, 30 + i, True)
     a.close()
     b.close()
+
+
+def test_eager_steps_between_replays_follow_the_lengths_of_the_device():
+    lens = np.array([290, 34, 514, 82], dtype=np.int32)  # no sequence comes to another tile in the steps below
+    (a, b), table = pair(2, 8, 128, 16, 4, 640)
+    a.set_batch(lens, table)
+    q, k, v, out = make_inputs(a, 91, 0, a.device)
+    bound = a.bind_step(q, k, v, out)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=a.compute_stream):
+        a.step_bound(bound)
+    for r, replayed in enumerate([True, False, True, False, False, True, True, False]):
+        for o in out:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        if replayed:
+            g.replay()
+        else:
+            a.step_bound(bound)
+        torch.cuda.synchronize()
+        b.set_batch(lens + r, table)
+        ref = [torch.full_like(o, float("nan")) for o in out]
+        b.step_bound(b.bind_step(q, k, v, ref))
+        b.synchronize()
+        np.testing.assert_array_equal(a.ctx.okv_get_ctx_lens(), lens + r + 1)
+        for x, y in zip(out, ref):
+            assert torch.equal(x, y), r
+    a.close()
+    b.close()
