@@ -716,8 +716,8 @@ def run_layers(args):
     w_bytes = sum(wt.bytes_read_per_step() for wt in weights) * steps
     # each product alone, back to back over the layers' own matrices in turn (two rounds): with L layers the
     # weights come from HBM as they do in a step, not from the memory-side cache a single matrix would sit in;
-    # at the leg's own batch and at 32, 64, 128 and 192 rows (more than 128 rows take two launches, each reading
-    # the weights again: the rate below counts the matrix once)
+    # at the leg's own batch and at 32, 64, 128 and 192 rows (each product one launch, with its shares two,
+    # which reads the matrix once)
     cs = st.compute_stream
 
     def products_alone(m, sc):

@@ -494,7 +494,7 @@ int okv_synchronize(okv_ctx *ctx);
 /* ---- introspection used by tests and the benchmark -------------------------------- */
 
 /* Overrides the split size (0 = back to cfg.split_tokens, or to the library's choice
- * if that is 0 too).  The work list is rebuilt at once.  OKV_ENOSPC if the workspace
+ * if that is 0 too).  The work list is another from here on (made when it is needed).  OKV_ENOSPC if the workspace
  * is too small for it. */
 int okv_set_split_tokens(okv_ctx *ctx, int32_t split_tokens);
 
