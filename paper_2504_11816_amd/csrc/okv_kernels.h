@@ -103,9 +103,11 @@ struct NextList {
   int32_t B, max_groups, min_span, lag, most_tiles;
   HeadGeom geom;
 };
-// At most this many sequences (a thread each) and stretches (kept in LDS), and sums of tiles that fit 32 bits.
+// At most this many sequences (a thread each) and stretches, and sums of tiles that fit 32 bits.  Stretches: what opens each lies in LDS, which
+// every workgroup of the merge is given; 512 (two KV heads; 17 KB) leave a compute unit its eight workgroups, 1024 (one KV head) would not.  A
+// step of 3 layers, 15 x 1668 keys, 2 KV heads x 64, 256 -> 512: 4.7 us of its own launch less, three steps 150.7 -> 138.5; 4 heads and more the same.
 bool next_list_rides(int32_t B, int32_t max_groups, int64_t cap_tiles);
-constexpr int kRiderGroupsMax = 256;
+constexpr int kRiderGroupsMax = 512;
 
 // Up to this many bytes of keys and values (over all layers that a step reads) launches keep them cached: the
 // memory-side cache of MI355X (see load_kv for both sides measured).

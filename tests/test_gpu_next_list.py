@@ -69,7 +69,8 @@ def check_step(a, b, lens, table, i, together):
 @pytest.mark.parametrize("together", [False, True])
 @pytest.mark.parametrize("L,G,d,T,B,lens", [
     (3, 8, 128, 16, 5, (300, 17, 900, 1, 333)), (2, 4, 64, 0, 3, (700, 127, 640)), (2, 32, 64, 32, 24, None), (1, 4, 128, 16, 1, (2000,)),
-    (2, 4, 64, 16, 3, "toggling"), (2, 16, 128, 0, 2, "toggling"), (2, 4, 64, 16, 256, None)])
+    (2, 4, 64, 16, 3, "toggling"), (2, 16, 128, 0, 2, "toggling"), (2, 4, 64, 16, 256, None),
+    (2, 2, 128, 16, 6, (1668, 40, 700, 1668, 900, 15)), (1, 2, 64, 16, 4, (20000, 300, 24000, 22000))])
 def test_going_on_equals_being_described_anew(L, G, d, T, B, lens, together):
     print(f"L={L} G={G} d={d} T={T} B={B} together={together}", flush=True)
     steps = 14 if isinstance(lens, str) else 6
