@@ -1080,21 +1080,36 @@ constexpr int kLnMaxThreads = 1024, kLnMaxPieces = 2;
 constexpr int kLnMaxWidth = kLnMaxThreads * kLnMaxPieces * 8;
 inline int ln_threads(int h) { return std::min(kLnMaxThreads, ((h >> 3) + 63) / 64 * 64); }
 
-// Mean and 1 / sqrt(variance + eps) of a row of h numbers of which a thread holds PPT pieces of eight (piece threadIdx.x + i blockDim.x).
-// Every wavefront takes the mean of its own numbers and the squares around that; the wavefronts' (sum, squares) meet in LDS once
-// and are joined as sum of squares + count x (distance of the means)^2.  The kernels are a chain of waits: a mean over the whole row
-// first and the squares around it afterwards was two trips through LDS for six lane exchanges each and four barriers.
-// us before -> now, with the product in front: 32 rows x 4096 x 4096 12.6 -> 12.0, 32 x 5120 x 5120 16.4 -> 15.7, 100 x 10240 x 2560 23.5 -> 23.0; the
-// norm alone, 1024 rows of 16384 14.6 -> 12.7 (5.3 TB/s), 4096 of 4096 13.3 -> 12.2.  (An approximate 1 / count does not matter: squares around any
-// number near the mean will do.  With true divisions the norm of 1024 rows of 4096 took 4.9 instead of 4.6.)
+// The sum of a value per thread, in every thread: over the lanes of a wavefront, then wavefront by wavefront through `scratch` (a place per
+// wavefront, read by nobody else since the last barrier).
+__device__ __forceinline__ float block_sum(float v, float4 (&scratch)[kLnMaxThreads / 256]) {
+  const int waves = (int)(blockDim.x >> 6);
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) reinterpret_cast<float *>(scratch)[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float t = 0.f;
+#pragma unroll
+  for (int w = 0; w < kLnMaxThreads / 64; w += 4) {
+    if (w >= waves) break;
+    const float4 s = scratch[w / 4];                       // (past the last wavefront: whatever is there, left out)
+    t += s.x;
+    t += w + 1 < waves ? s.y : 0.f;
+    t += w + 2 < waves ? s.z : 0.f;
+    t += w + 3 < waves ? s.w : 0.f;
+  }
+  return t;
+}
+
+// Mean and 1 / sqrt(variance + eps) of a row of h numbers of which a thread holds PPT pieces of eight (piece threadIdx.x + i blockDim.x): the
+// mean of the whole row, then the squares around it.  The kernels are a chain of waits, and the two sums are most of it.  us with lane
+// shuffles and two barriers a sum -> now, with the product in front: 32 rows x 4096 x 4096 12.5 -> 12.1, 32 x 5120 x 5120 16.3 -> 15.8, 100 x
+// 10240 x 2560 23.4 -> 23.2; the norm alone, 1024 rows of 16384 14.6 -> 13.8, 4096 of 4096 13.3 -> 12.4.  The sums' order is the same bit for bit:
+// squares around every wavefront's own mean, joined in one trip through LDS, took 0.2 us less (11.9, 15.5, 22.9; alone 12.7 and 12.2) and
+// changed the roundings of a few results in 10000, in whole decoder layers as much as half of a result's error.
 template <int PPT>
-__device__ __forceinline__ void row_stats(const float (&v)[PPT][8], const int h, const float eps, float2 *scratch, float &mean, float &rstd) {
-  const int pieces = h >> 3, waves = (int)(blockDim.x >> 6), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  auto count_of = [&](int w) {                           // numbers that wavefront w holds (at least one piece)
-    int n = min(pieces - 64 * w, 64);
-    if (PPT > 1) n += min(max(pieces - 64 * w - (int)blockDim.x, 0), 64);
-    return (float)(8 * n);
-  };
+__device__ __forceinline__ void row_stats(const float (&v)[PPT][8], const int h, const float eps, float4 (&scratch)[2][kLnMaxThreads / 256], float &mean,
+                                          float &rstd) {
+  const int pieces = h >> 3;
   float s = 0.f, q = 0.f;
 #pragma unroll
   for (int i = 0; i < PPT; ++i)
@@ -1102,31 +1117,20 @@ __device__ __forceinline__ void row_stats(const float (&v)[PPT][8], const int h,
 #pragma unroll
       for (int e = 0; e < 8; ++e) s += v[i][e];
     }
-  s = wave_sum(s);
-  const float mine = s * __builtin_amdgcn_rcpf(count_of(wave));
+  mean = block_sum(s, scratch[0]) / (float)h;
 #pragma unroll
   for (int i = 0; i < PPT; ++i)
     if ((int)(threadIdx.x + i * blockDim.x) < pieces) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) q += (v[i][e] - mine) * (v[i][e] - mine);
+      for (int e = 0; e < 8; ++e) q += (v[i][e] - mean) * (v[i][e] - mean);
     }
-  q = wave_sum(q);
-  if ((threadIdx.x & 63) == 0) scratch[wave] = make_float2(s, q);
-  __syncthreads();
-  // a wavefront's pair in every row of 16 lanes (there are at most 16 of them)
-  static_assert(kLnMaxThreads / 64 <= 16, "");
-  const int w = (int)(threadIdx.x & 15);
-  const bool in = w < waves;
-  const float2 pair = scratch[in ? w : 0];
-  mean = row_sum(in ? pair.x : 0.f) / (float)h;
-  const float n = count_of(in ? w : 0), off = pair.x * __builtin_amdgcn_rcpf(n) - mean;
-  rstd = 1.0f / sqrtf(row_sum(in ? pair.y + n * off * off : 0.f) / (float)h + eps);
+  rstd = 1.0f / sqrtf(block_sum(q, scratch[1]) / (float)h + eps);
 }
 
 template <int PPT>
 __global__ __launch_bounds__(kLnMaxThreads) void layernorm_kernel(const uint4 *x, const uint4 *gamma, const uint4 *beta, uint4 *out,
                                                                 int32_t h, float eps) {
-  __shared__ float2 scratch[kLnMaxThreads / 64];
+  __shared__ float4 scratch[2][kLnMaxThreads / 256];
   const int pieces = h >> 3;
   const uint4 *xr = x + (size_t)blockIdx.x * pieces;
   float v[PPT][8];
@@ -1167,7 +1171,7 @@ __global__ __launch_bounds__(kLnMaxThreads) void reduce_layernorm_kernel(const f
                                                                            const _Float16 *gamma, const _Float16 *beta, const int32_t n_out,
                                                                            const int32_t splits, const int32_t m, const LinearArgs a) {
   // (leading parameters: in scalar registers when the wavefront starts, so everything is asked for at once)
-  __shared__ float2 scratch[kLnMaxThreads / 64];
+  __shared__ float4 scratch[2][kLnMaxThreads / 256];
   const int h = n_out, pieces = h >> 3, mrow = blockIdx.x;
   const Sink sink(a);
   float v[PPT][8];
