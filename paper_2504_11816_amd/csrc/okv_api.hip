@@ -128,15 +128,14 @@ struct okv_ctx {
   char *h_up = nullptr;                  // mapped host memory the small tables are uploaded from (NULL: synchronous copies)
   int64_t up_cap = 0;
   bool list_stale = false;               // the device work list is not that of the host's lengths: see rebuild_worklist
-  // The next step's work list, made by the last merge of a step (see next_list): the arrays it goes to, whether it is there,
-  // and by how much the device's lengths are behind the host's while a step runs on a list made that way.
-  int32_t *d_chunk_prefix2 = nullptr, *d_group_first2 = nullptr, *d_plan2 = nullptr;
+  // The next step's lengths and work list, made by the last merge of a step (see next_list): the arrays they go to, and whether they
+  // are there.
+  int32_t *d_ctx_lens2 = nullptr, *d_chunk_prefix2 = nullptr, *d_group_first2 = nullptr, *d_plan2 = nullptr;
   int4 *d_item_desc2 = nullptr;
   void *d_pair_head2 = nullptr;
   // A context of which a step was captured makes none any more: a replay advances the device's lengths without the host.
   bool list_ahead = false;
   bool was_captured = false;
-  int32_t lens_lag = 0;
   bool keep_cached = true;               // the batch's keys and values of all layers fit the memory-side cache
   int64_t max_items = 0;
   float *part_o = nullptr, *part_ml = nullptr;
@@ -435,10 +434,10 @@ bool is_capturing(hipStream_t stream) {
   return true;
 }
 
-// What the merge of a step's last layer makes on the side: the work list of the step after this one, in the arrays that the step itself
-// does not read.  That step then begins without a launch (it exchanges the two sets of arrays); its own last merge, or
-// okv_step_end where there is none, brings the device's lengths up to date.  Not while the stream is being captured, nor ever after: a
-// graph's steps each make their own list, and so has a step behind a replay to, whose lengths only the device knows.  Lengths that
+// What the merge of a step's last layer makes on the side: the lengths and the work list of the step after this one, in arrays that the
+// step itself does not read.  That step then begins without a launch (it exchanges the two sets of arrays, so the lengths that a
+// launch is given are always those of the list beside them).  Not while the stream is being captured, nor ever after: a
+// graph's steps each make their own list, and so does a step behind a replay, whose lengths only the device knows.  Lengths that
 // the next step refuses (a sequence at its capacity) give a list that nobody reads, in arrays that hold as many items as they can
 // give: one per stretch and one per sequence that begins in mid-stretch.
 const okv::NextList *next_list(okv_ctx *ctx, okv::NextList *n) {
@@ -450,16 +449,10 @@ const okv::NextList *next_list(okv_ctx *ctx, okv::NextList *n) {
   const okv::SpanPlan plan = okv::span_plan(total, ctx->max_groups, kMinSpanTiles);
   if ((int64_t)ctx->B + plan.n_groups > ctx->max_items) return nullptr;
   if ((ctx->was_captured = is_capturing(ctx->compute))) return nullptr;      // (a capture that began inside the step)
-  *n = okv::NextList{ctx->d_ctx_lens, ctx->d_chunk_prefix2, ctx->d_item_desc2, ctx->d_group_first2, ctx->d_plan2, ctx->d_pair_head2, ctx->B,
-                     ctx->max_groups, kMinSpanTiles, ctx->lens_lag, (1 << 30) / std::max(ctx->B, 1),
+  *n = okv::NextList{ctx->d_ctx_lens, ctx->d_ctx_lens2, ctx->d_chunk_prefix2, ctx->d_item_desc2, ctx->d_group_first2, ctx->d_plan2,
+                     ctx->d_pair_head2, ctx->B, ctx->max_groups, kMinSpanTiles, (1 << 30) / std::max(ctx->B, 1),
                      okv::head_geom(ctx->shape, ctx->d_block_table, max_pairs(ctx->max_waves))};
   return n;
-}
-
-void next_list_made(okv_ctx *ctx, const okv::NextList *next) {
-  if (!next) return;
-  ctx->list_ahead = true;
-  ctx->lens_lag = 0;
 }
 
 int exec_op(okv_ctx *ctx, const Op &op, const void *a0, const void *a1, void *out) {
@@ -536,7 +529,7 @@ int exec_op(okv_ctx *ctx, const Op &op, const void *a0, const void *a1, void *ou
       okv::NextList n;
       const okv::NextList *next = op.layer + 1 == ctx->cfg.n_layers ? next_list(ctx, &n) : nullptr;
       OKV_HIP(ctx, okv::launch_merge(a, next, ctx->compute));
-      next_list_made(ctx, next);
+      ctx->list_ahead |= next != nullptr;
       return OKV_OK;
     }
   }
@@ -659,7 +652,6 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false, bool n
     // the device lengths are replaced by the host's (after a bulk store)
     OKV_HIP(ctx, hipStreamSynchronize(ctx->compute));
     if (int rc = upload_tables(ctx, ctx->d_ctx_lens, ctx->h_ctx_lens.data(), (int64_t)ctx->B * sizeof(int32_t))) return rc;
-    ctx->lens_lag = 0;
   }
   if (ctx->by_class) {
     ctx->split = ctx->split_override ? ctx->split_override : ctx->cfg.split_tokens ? ctx->cfg.split_tokens : kClassSplit;
@@ -703,9 +695,8 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false, bool n
       okv::seq_chunks(ctx->h_ctx_lens[b], S, &cnt, &sz);
       if (cnt > 1) ctx->need_merge = true;
     }
-    if (now) OKV_HIP(ctx, okv::launch_step_advance(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->B, S, inc + ctx->lens_lag,
+    if (now) OKV_HIP(ctx, okv::launch_step_advance(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->B, S, inc,
                                                    ctx->compute));
-    if (now) ctx->lens_lag = 0;
     ctx->list_stale = !now;
     return OKV_OK;
   }
@@ -732,10 +723,9 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false, bool n
   ctx->n_items = (int32_t)n;
   ctx->need_merge = merge;
   if (now) OKV_HIP(ctx, okv::launch_step_advance_spans(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->d_group_first,
-                                                       ctx->d_plan, ctx->B, ctx->max_groups, kMinSpanTiles, inc + ctx->lens_lag, ctx->d_pair_head,
+                                                       ctx->d_plan, ctx->B, ctx->max_groups, kMinSpanTiles, inc, ctx->d_pair_head,
                                                        okv::head_geom(ctx->shape, ctx->d_block_table, max_pairs(ctx->max_waves)),
                                                        ((int64_t)ctx->cap_tokens + 15) / 16, ctx->compute));
-  if (now) ctx->lens_lag = 0;
   ctx->list_stale = !now;
   return OKV_OK;
 }
@@ -1076,6 +1066,7 @@ int okv_create(const okv_config *cfg, okv_ctx **out) {
   OKV_TRY_CREATE(hipMemset(ctx->d_pair_head, 0, (size_t)max_pairs(ctx->max_waves) * okv::kPairHeadBytes));
   OKV_TRY_CREATE(hipMalloc(&ctx->d_plan, 4 * sizeof(int32_t)));
   if (!by_class && !any_host && ctx->max_groups <= okv::kRiderGroupsMax) {
+    OKV_TRY_CREATE(hipMalloc(&ctx->d_ctx_lens2, (size_t)cfg->max_batch * sizeof(int32_t)));
     OKV_TRY_CREATE(hipMalloc(&ctx->d_chunk_prefix2, ((size_t)cfg->max_batch + 1) * sizeof(int32_t)));
     OKV_TRY_CREATE(hipMalloc(&ctx->d_item_desc2, (size_t)std::max<int64_t>(1, max_items) * sizeof(int4)));
     OKV_TRY_CREATE(hipMalloc(&ctx->d_group_first2, ((size_t)ctx->max_groups + 1) * sizeof(int32_t)));
@@ -1116,6 +1107,7 @@ int okv_destroy(okv_ctx *ctx) {
   (void)hipFree(ctx->d_block_table);
   (void)hipFree(ctx->d_ctx_lens);
   (void)hipFree(ctx->d_chunk_prefix);
+  (void)hipFree(ctx->d_ctx_lens2);
   (void)hipFree(ctx->d_chunk_prefix2);
   (void)hipFree(ctx->d_group_first2);
   (void)hipFree(ctx->d_plan2);
@@ -1205,7 +1197,6 @@ int okv_set_batch(okv_ctx *ctx, int32_t B, const int32_t *block_table, const int
   if (rc) return rc;
   ctx->batch_set = false;
   ctx->list_ahead = false;
-  ctx->lens_lag = 0;
   ctx->B = B;
   ctx->h_ctx_lens.assign(ctx_lens, ctx_lens + B);
   if (s.paged) {
@@ -1301,13 +1292,13 @@ int okv_step_begin(okv_ctx *ctx) {
     return rc;
   }
   if (ahead) {                                           // the list is there: the last step's merge made it
+    std::swap(ctx->d_ctx_lens, ctx->d_ctx_lens2);
     std::swap(ctx->d_chunk_prefix, ctx->d_chunk_prefix2);
     std::swap(ctx->d_item_desc, ctx->d_item_desc2);
     std::swap(ctx->d_group_first, ctx->d_group_first2);
     std::swap(ctx->d_plan, ctx->d_plan2);
     std::swap(ctx->d_pair_head, ctx->d_pair_head2);
     ctx->list_stale = false;
-    ctx->lens_lag = 1;
   }
   ctx->list_ahead = false;
   if (ctx->tail_on) {
@@ -1357,9 +1348,6 @@ int okv_step_end(okv_ctx *ctx) {
       ctx->flush_recorded = true;
     }
   }
-  // a step on a list made ahead that was not followed by another one: the device's lengths are still to advance
-  if (ctx->lens_lag && !is_capturing(ctx->compute))
-    if (int rc = rebuild_worklist(ctx, 0)) return rc;
   if (int rc = mark_step_done(ctx)) return rc;
   ctx->in_step = false;
   ctx->step += 1;
@@ -1434,7 +1422,7 @@ int okv_decode_step(okv_ctx *ctx, const void *const *q, const void *const *k_new
       okv::NextList nl;
       const okv::NextList *next = l + n == L ? next_list(ctx, &nl) : nullptr;
       if (rc == OKV_OK) OKV_HIP(ctx, okv::launch_decode_layers(a, at, n, next, ctx->compute));
-      if (rc == OKV_OK) next_list_made(ctx, next);
+      ctx->list_ahead |= rc == OKV_OK && next;
       l += n - 1;
       ctx->next_layer = l + 1;
       continue;
@@ -1706,7 +1694,6 @@ int okv_get_ctx_lens(okv_ctx *ctx, int32_t *out) {
   if (!ctx->batch_set) return fail(ctx, OKV_ESTATE, "no batch set");
   OKV_HIP(ctx, hipStreamSynchronize(ctx->compute));
   OKV_HIP(ctx, hipMemcpy(out, ctx->d_ctx_lens, (size_t)ctx->B * sizeof(int32_t), hipMemcpyDeviceToHost));
-  for (int32_t b = 0; b < ctx->B; ++b) out[b] += ctx->lens_lag;
   return OKV_OK;
 }
 

@@ -92,15 +92,15 @@ inline HeadGeom head_geom(const PoolShape &s, const int32_t *block_table, int32_
   return g;
 }
 
-// The work list of the step after this one, made by a merge launch on the side (next_list_rides says where): the lengths in
-// ctx_lens advance by `lag` (what the step itself left undone because its own list was made this way) and the list
-// is for one token more.  Everything but ctx_lens is another set of arrays than the launch itself reads.
+// The lengths (one more than in lens_now) and the work list of the step after this one, made by a merge launch on the side
+// (next_list_rides says where), in another set of arrays than any launch of the step itself reads.
 struct NextList {
+  const int32_t *lens_now;
   int32_t *ctx_lens, *chunk_prefix;
   int4 *item_desc;
   int32_t *group_first, *plan;
   void *pair_head;
-  int32_t B, max_groups, min_span, lag, most_tiles;
+  int32_t B, max_groups, min_span, most_tiles;
   HeadGeom geom;
 };
 // At most this many sequences (a thread each) and stretches, and sums of tiles that fit 32 bits.  Stretches: what opens each lies in LDS, which

@@ -956,12 +956,12 @@ __device__ __forceinline__ void write_pair_heads(const int32_t n_groups, const i
 // us before -> now: one sequence of 4096 keys, 4 and 32 KV heads 9.5 -> 3.6 and 10.5 -> 4.7, two of 4000 with 8 heads 10.0 -> 4.1, 16 of up to
 // 4096 6.7 -> 4.8, 128 of up to 4096 5.8 -> 5.1, 24 of up to 1150 4.8 (about what a dependent launch takes behind a long one) either way.
 // With 512 or 1024 threads the small ones take 0.3 or 1 us more.
-// `inc` is added to the lengths; the list is for `ahead` more tokens than that.  GROUPS: the most stretches there may be.
+// The list is for the lengths in lens_now plus inc, which go to ctx_lens (NULL: nowhere).  GROUPS: the most stretches there may be.
 template <int GROUPS>
-__device__ __forceinline__ void step_advance_items(int32_t *ctx_lens, int32_t *chunk_prefix, int4 *item_desc, int32_t *group_first,
-                                                   int32_t *plan_out, const int32_t B, const int32_t max_groups, const int32_t min_span,
-                                                   const int32_t inc, const int32_t ahead, PairHead *pair_head, const int32_t most_tiles,
-                                                   const HeadGeom &hg) {
+__device__ __forceinline__ void step_advance_items(const int32_t *lens_now, const int32_t inc, int32_t *ctx_lens, int32_t *chunk_prefix,
+                                                   int4 *item_desc, int32_t *group_first, int32_t *plan_out, const int32_t B,
+                                                   const int32_t max_groups, const int32_t min_span, PairHead *pair_head,
+                                                   const int32_t most_tiles, const HeadGeom &hg) {
   __shared__ int32_t wave_tiles[kStepThreads / 64], wave_mids[kStepThreads / 64];
   // per sequence: tiles before it (past the batch: more than there are), place of its first item, keys
   __shared__ int32_t seq_first[kStepThreads], seq_at[kStepThreads], seq_n[kStepThreads];
@@ -976,9 +976,8 @@ __device__ __forceinline__ void step_advance_items(int32_t *ctx_lens, int32_t *c
   auto keys_to = [&](int32_t n, int32_t tile) -> int32_t { return (int32_t)min((int64_t)n, (int64_t)tile << 4); };
   int32_t n = 0;
   if (tid < B) {
-    n = ctx_lens[tid] + inc;
-    if (inc) ctx_lens[tid] = n;                                // inc == 0: the lengths are only read
-    n += ahead;
+    n = lens_now[tid] + inc;
+    if (ctx_lens) ctx_lens[tid] = n;
   }
   const int32_t tiles = tiles_of(n);
   const int32_t upto = wave_scan(tiles);
@@ -1061,8 +1060,9 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_items_kernel(int32_
                                                                          int32_t *group_first, int32_t *plan_out, const int32_t B,
                                                                          const int32_t max_groups, const int32_t min_span, const int32_t inc,
                                                                          PairHead *pair_head, const int32_t most_tiles, const HeadGeom hg) {
-  step_advance_items<kHeadGroupsMax>(ctx_lens, chunk_prefix, item_desc, group_first, plan_out, B, max_groups, min_span, inc, 0, pair_head,
-                                     most_tiles, hg);
+  // inc == 0: the lengths are only read
+  step_advance_items<kHeadGroupsMax>(ctx_lens, inc, inc ? ctx_lens : nullptr, chunk_prefix, item_desc, group_first, plan_out, B, max_groups,
+                                     min_span, pair_head, most_tiles, hg);
 }
 
 // out[b][h] = sum_c o_c 2^(m_c - M) / sum_c l_c 2^(m_c - M) over the items c of sequence b.
@@ -1096,8 +1096,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int32_t *chunk_pr
   if constexpr (kNext) {
     if (blockIdx.y == 0) {
       if (blockIdx.x == 0 && blockIdx.z == 0)
-        step_advance_items<kRiderGroupsMax>(next.ctx_lens, next.chunk_prefix, next.item_desc, next.group_first, next.plan, next.B,
-                                            next.max_groups, next.min_span, next.lag, 1, static_cast<PairHead *>(next.pair_head),
+        step_advance_items<kRiderGroupsMax>(next.lens_now, 1, next.ctx_lens, next.chunk_prefix, next.item_desc, next.group_first, next.plan,
+                                            next.B, next.max_groups, next.min_span, static_cast<PairHead *>(next.pair_head),
                                             next.most_tiles, next.geom);
       return;
     }

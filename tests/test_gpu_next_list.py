@@ -194,3 +194,46 @@ def test_eager_steps_between_replays_follow_the_lengths_of_the_device():
             assert torch.equal(x, y), r
     a.close()
     b.close()
+
+
+def replayed_equals_described(a, b, g, q, k, v, out, lens, table):
+    """A replay of g takes a from `lens` one step on, as a step of b does."""
+    for o in out:
+        o.fill_(float("nan"))
+    torch.cuda.synchronize()
+    g.replay()
+    torch.cuda.synchronize()
+    b.set_batch(lens, table)
+    ref = [torch.full_like(o, float("nan")) for o in out]
+    b.step_bound(b.bind_step(q, k, v, ref))
+    b.synchronize()
+    np.testing.assert_array_equal(a.ctx.okv_get_ctx_lens(), lens + 1)
+    for x, y in zip(out, ref):
+        assert torch.equal(x, y)
+
+
+def test_a_capture_that_begins_inside_a_step():
+    # the step begins on a list made ahead, its layers are captured; the step that is captured behind it advances the lengths by one a replay
+    lens = np.array([300, 40, 512, 90], dtype=np.int32)
+    (a, b), table = pair(2, 8, 128, 16, 4, 640)
+    a.set_batch(lens, table)
+    for i in range(2):
+        check_step(a, b, lens + i, table, i, False)
+    q, k, v, out = make_inputs(a, 92, 0, a.device)
+    torch.cuda.synchronize()
+    a.ctx.okv_step_begin()
+    a.synchronize()
+    layers, step = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(layers, stream=a.compute_stream):
+        for l in range(2):
+            a.ctx.kv_append(l, k[l], v[l])
+            a.ctx.decode_attn(l, q[l], out[l])
+        a.ctx.okv_step_end()
+    replayed_equals_described(a, b, layers, q, k, v, out, lens + 2, table)
+    bound = a.bind_step(q, k, v, out)
+    with torch.cuda.graph(step, stream=a.compute_stream):
+        a.step_bound(bound)
+    for r in range(4):
+        replayed_equals_described(a, b, step, q, k, v, out, lens + 3 + r, table)
+    a.close()
+    b.close()
