@@ -638,6 +638,10 @@ int upload_tables(okv_ctx *ctx, void *dst0, const void *src0, int64_t bytes0, vo
   return OKV_OK;
 }
 
+// Whether the device list is one for later after all.  A launch that is only recorded builds none: a list that was left for later then is to
+// be built still by whoever reads it before the first replay (behind one it is the replay's already, and building it anew changes nothing).
+bool still_stale(okv_ctx *ctx, bool now) { return !now || (ctx->list_stale && is_capturing(ctx->compute)); }
+
 // Recomputes split size, item count and merge flag from the host lengths and
 // rebuilds the device work list (adding `inc` to every device length first).
 // Unless `now`, the device list is left for later: a step builds its own when it begins, so the list of a batch that was just
@@ -677,7 +681,7 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false, bool n
     if (now) OKV_HIP(ctx, okv::launch_step_advance_classes(ctx->d_ctx_lens, ctx->d_runs, ctx->d_pair_first, ctx->d_chunk_prefix,
                                                   ctx->d_item_desc, ctx->d_seq_total, ctx->B, ctx->n_cls, ctx->split, inc,
                                                   ctx->compute));
-    ctx->list_stale = !now;
+    ctx->list_stale = still_stale(ctx, now);
     return OKV_OK;
   }
   if (const int32_t S = fixed_split(ctx)) {
@@ -697,7 +701,7 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false, bool n
     }
     if (now) OKV_HIP(ctx, okv::launch_step_advance(ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc, ctx->B, S, inc,
                                                    ctx->compute));
-    ctx->list_stale = !now;
+    ctx->list_stale = still_stale(ctx, now);
     return OKV_OK;
   }
   // equal stretches: the host walks the same arithmetic as the kernel for the counts it needs
@@ -726,7 +730,7 @@ int rebuild_worklist(okv_ctx *ctx, int32_t inc, bool upload_lens = false, bool n
                                                        ctx->d_plan, ctx->B, ctx->max_groups, kMinSpanTiles, inc, ctx->d_pair_head,
                                                        okv::head_geom(ctx->shape, ctx->d_block_table, max_pairs(ctx->max_waves)),
                                                        ((int64_t)ctx->cap_tokens + 15) / 16, ctx->compute));
-  ctx->list_stale = !now;
+  ctx->list_stale = still_stale(ctx, now);
   return OKV_OK;
 }
 

@@ -53,3 +53,36 @@ def test_lists_before_and_after_steps(T):
         st.ctx.okv_step_begin()
     same_lists(st)
     st.close()
+
+
+@pytest.mark.parametrize("T", [0, 16])
+def test_lists_before_the_first_replay(T):
+    # the first step of a batch is recorded: until it is replayed the device's list is that of the batch as described (recording a
+    # step has advanced the host's lengths; they give as many items here)
+    B, cap = 5, 700
+    lens = np.array([302, 20, 642, 7, 35], dtype=np.int32)
+    st, ref = (Stack(L=2, H=8, G=2, d=128, B=B, T=T, cap_tokens=cap) for _ in range(2))
+    table = None if not T else np.arange(B * st.max_blocks, dtype=np.int32).reshape(B, st.max_blocks)
+    q, k, v, out = make_inputs(st, 6, 0, st.device)
+    for p in st.pools + ref.pools:
+        p.zero_()
+    st.set_batch(lens[::-1].copy(), table)                       # what the arrays hold from before is another list
+    st.step(q, k, v, out)
+    for first in (lens, lens + 4):
+        st.set_batch(first, table)
+        g = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=st.compute_stream):
+            st.step(q, k, v, out)
+        for replays in range(3):
+            if replays:
+                g.replay()
+                torch.cuda.synchronize()
+            ref.set_batch(first + replays, table)
+            for _ in range(2):
+                assert np.array_equal(st.ctx.okv_get_ctx_lens(), first + replays)
+                assert np.array_equal(np.asarray(st.ctx.okv_pair_heads()), np.asarray(ref.ctx.okv_pair_heads())), replays
+                assert np.array_equal(np.asarray(st.ctx.okv_worklist(True)), np.asarray(ref.ctx.okv_worklist(True))), replays
+        st.synchronize()
+    st.close()
+    ref.close()
