@@ -133,7 +133,8 @@ struct okv_ctx {
   int32_t *d_ctx_lens2 = nullptr, *d_chunk_prefix2 = nullptr, *d_group_first2 = nullptr, *d_plan2 = nullptr;
   int4 *d_item_desc2 = nullptr;
   void *d_pair_head2 = nullptr;
-  // A context of which a step was captured makes none any more: a replay advances the device's lengths without the host.
+  // A context of which a launch was captured makes none any more: a replay advances the device's lengths without the host, and reads the
+  // arrays that it was recorded with.
   bool list_ahead = false;
   bool was_captured = false;
   bool keep_cached = true;               // the batch's keys and values of all layers fit the memory-side cache
@@ -286,7 +287,23 @@ int32_t fixed_split(const okv_ctx *ctx) { return ctx->split_override ? ctx->spli
 
 hipStream_t copy_stream(okv_ctx *ctx, int buf) { return (buf & 1) && ctx->h2d_odd ? ctx->h2d_odd : ctx->h2d; }
 
+// (The null stream is never captured; asking about it while another stream is would be an error.)
+bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (!stream) return false;
+  if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();                               // (whatever is launched there will fail and say so)
+  return false;
+}
+
+// Before a launch that takes lengths or the work list: one that is recorded keeps the arrays for good, so they are exchanged no more
+// (see next_list).  Some 50 ns a launch.
+void note_capture(okv_ctx *ctx) {
+  if (ctx->d_item_desc2 && !ctx->was_captured) ctx->was_captured = is_capturing(ctx->compute);
+}
+
 okv::AttnLaunch base_launch(okv_ctx *ctx) {
+  note_capture(ctx);
   okv::AttnLaunch a;
   a.shape = ctx->shape;
   a.batch = okv::BatchState{ctx->d_block_table, ctx->d_ctx_lens, ctx->d_chunk_prefix, ctx->d_item_desc,
@@ -427,13 +444,6 @@ int bracket_launch(okv_ctx *ctx, hipEvent_t *e0, hipEvent_t *e1) {
   return OKV_OK;
 }
 
-bool is_capturing(hipStream_t stream) {
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();                               // (the null stream, while another stream is captured)
-  return true;
-}
-
 // What the merge of a step's last layer makes on the side: the lengths and the work list of the step after this one, in arrays that the
 // step itself does not read.  That step then begins without a launch (it exchanges the two sets of arrays, so the lengths that a
 // launch is given are always those of the list beside them).  Not while the stream is being captured, nor ever after: a
@@ -448,7 +458,6 @@ const okv::NextList *next_list(okv_ctx *ctx, okv::NextList *n) {
   for (int32_t b = 0; b < ctx->B; ++b) total += (ctx->h_ctx_lens[b] + 16) >> 4;      // with the next token
   const okv::SpanPlan plan = okv::span_plan(total, ctx->max_groups, kMinSpanTiles);
   if ((int64_t)ctx->B + plan.n_groups > ctx->max_items) return nullptr;
-  if ((ctx->was_captured = is_capturing(ctx->compute))) return nullptr;      // (a capture that began inside the step)
   *n = okv::NextList{ctx->d_ctx_lens, ctx->d_ctx_lens2, ctx->d_chunk_prefix2, ctx->d_item_desc2, ctx->d_group_first2, ctx->d_plan2,
                      ctx->d_pair_head2, ctx->B, ctx->max_groups, kMinSpanTiles, (1 << 30) / std::max(ctx->B, 1),
                      okv::head_geom(ctx->shape, ctx->d_block_table, max_pairs(ctx->max_waves))};
@@ -1285,7 +1294,7 @@ int okv_step_begin(okv_ctx *ctx) {
     }
   }
   for (int32_t b = 0; b < ctx->B; ++b) ctx->h_ctx_lens[b] += 1;
-  if (ctx->d_item_desc2 && !ctx->was_captured) ctx->was_captured = is_capturing(ctx->compute);
+  note_capture(ctx);
   const bool ahead = ctx->list_ahead && !ctx->was_captured;
   const int rc = rebuild_worklist(ctx, 1, false, /*now=*/!ahead);
   if (rc) {

@@ -237,3 +237,42 @@ def test_a_capture_that_begins_inside_a_step():
         replayed_equals_described(a, b, step, q, k, v, out, lens + 3 + r, table)
     a.close()
     b.close()
+
+
+def test_a_layer_that_is_captured_reads_the_step_in_use():
+    # one layer of an eager step is captured; later steps are eager, and a replay then attends that layer at the lengths of the last of them
+    lens = np.array([300, 40, 512, 90], dtype=np.int32)
+    (a, b), table = pair(2, 8, 128, 16, 4, 640)
+    a.set_batch(lens, table)
+    check_step(a, b, lens, table, 0, False)
+    q, k, v, out = make_inputs(a, 93, 0, a.device)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    for r in range(4):
+        a.ctx.okv_step_begin()
+        a.synchronize()
+        for l in range(2):
+            if r == l == 0:
+                with torch.cuda.graph(g, stream=a.compute_stream):
+                    a.ctx.kv_append(l, k[l], v[l])
+                    a.ctx.decode_attn(l, q[l], out[l])
+                g.replay()
+                torch.cuda.synchronize()
+            else:
+                a.ctx.kv_append(l, k[l], v[l])
+                a.ctx.decode_attn(l, q[l], out[l])
+        a.ctx.okv_step_end()
+        a.synchronize()
+        b.set_batch(lens + 1 + r, table)
+        ref = [torch.full_like(o, float("nan")) for o in out]
+        b.step_bound(b.bind_step(q, k, v, ref))
+        b.synchronize()
+        for x, y in zip(out, ref):
+            assert torch.equal(x, y), r
+        out[0].fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], ref[0]), r
+    a.close()
+    b.close()
