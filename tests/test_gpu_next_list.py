@@ -276,3 +276,40 @@ def test_a_layer_that_is_captured_reads_the_step_in_use():
         assert torch.equal(out[0], ref[0]), r
     a.close()
     b.close()
+
+
+def lists_ahead(st, f):
+    """Of the merge launches of f(), which made a list ahead."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+        f()
+        st.synchronize()
+        torch.cuda.synchronize()
+    return ["NoNextList" not in e.name for e in p.events() if "attn_merge_kernel" in e.name and str(e.device_type).endswith("CUDA")]
+
+
+@pytest.mark.parametrize("together", [False, True])
+def test_no_list_is_made_ahead_for_batches_of_one_step(together):
+    st = Stack(L=1, H=8, G=8, d=64, B=2, T=16, cap_tokens=700)
+    st.pools[0].zero_()
+    table = np.arange(2 * st.max_blocks, dtype=np.int32).reshape(2, -1)
+    q, k, v, out = make_inputs(st, 5, 0, st.device)
+    bound = st.bind_step(q, k, v, out)
+
+    def batch(steps, prompt=False):
+        st.set_batch([0, 0] if prompt else [600, 311], table)
+        if prompt:
+            rows = torch.zeros((911, 8, 64), dtype=torch.float16, device=st.device)
+            st.prefill([600, 311], rows, rows)
+        for _ in range(steps):
+            if together:
+                st.step_bound(bound)
+            else:
+                st.step(q, k, v, out)
+
+    batch(1)                                             # (what the first batches are like is not known yet)
+    batch(1)
+    assert lists_ahead(st, lambda: [batch(1), batch(1, True), batch(1)]) == [False] * 3
+    assert lists_ahead(st, lambda: batch(3)) == [False, True, True]       # this one goes on: so may the next
+    assert lists_ahead(st, lambda: [batch(2), batch(2, True), batch(1)]) == [True] * 5
+    assert lists_ahead(st, lambda: [batch(1), batch(1, True)]) == [False] * 2
+    st.close()
