@@ -1453,10 +1453,11 @@ LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int6
 // shapes of 1 to 24 rows, 256 to 24576 features, 256 to 20480 inputs, weights from HBM: 8 and 9 % rms.)  Up to 8 rows the staged
 // one has to be 14 % better, which the models are not always good for (8 rows x 16384 x 4096 22 us simple, 25 staged).  Beyond, the simple
 // one has to be 2 us better, since a layer norm of the result is a launch more behind it and not behind the staged kernel's shares (16
-// x 768 x 3072 6.2 / 7.5 us simple / staged, with a norm 8.8 / 8.1), and the inputs have to be whole rounds (shapes that host tests hold to
-// the staged kernel are not).  us, the rule by rows alone -> this one: 8 rows x 5120 x 20480 48.4 -> 36.7, 3 x 512 x 20480 with a norm 18.1 ->
-// 10.5, 8 x 1632 x 17920 19.9 -> 14.0; 12 x 4096 x 4096 10.6 -> 7.3, with a norm 12.2 -> 10.1, 12 x 2048 x 2048 7.8 -> 4.7, 11 x 4096 x 2048
-// 8.2 -> 4.9.
+// x 768 x 3072 6.2 / 6.9 us simple / staged, with a norm 8.4 / 7.2; of 255 shapes of 9 to 16 rows, with and without a norm, 46 change and none is
+// slower; at 1 us 63 change and 12 x 768 x 3072 with a norm loses 4 %).  us, the rule by rows alone -> this one: 8 rows x 5120 x 20480 48.4 ->
+// 36.7, 3 x 512 x 20480 with a norm 18.1 -> 10.5, 8 x 1632 x 17920 19.9 -> 14.0; 12 x 4096 x 4096 10.6 -> 7.3, with a norm 12.2 -> 10.1, 12 x
+// 2048 x 2048 7.8 -> 4.7, 9 x 3840 x 2560 8.3 -> 5.3, 9 x 2560 x 2560 7.4 -> 5.2, with a norm 8.6 -> 7.6, 12 x 2400 x 13568 (whose 53 chunks cannot
+// be cut) 32.2 -> 18.9.
 double few_rows_simple_us(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
   const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 1.29 * std::ceil(q) - 0.29 * q;
   const double intake_us = rounds * n_in * 2 / 1e3 * (16.0 + 2.0 * m) / 72.0, weights_us = (double)n_out * n_in * 2 / 1e6 / 9.3;
@@ -1469,20 +1470,22 @@ bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, cons
   const double intake_kb = (double)((wgs + n_cus - 1) / n_cus) * (16.0 * staged.waves + 0.42 * m) * row_kb / staged.cuts;
   const double staged_us = 2.91 + (staged.cuts > 1 ? 3.39 : 0.0) + std::sqrt(intake_kb / 58.0 * (intake_kb / 58.0) + weight_mb / 8.1 * (weight_mb / 8.1));
   if (m <= OKV_LIN_SIMPLE_ROWS) return simple_us < 1.14 * staged_us;
-  return n_in % 1024 == 0 && simple_us + 2.0 < staged_us;
+  return simple_us + 2.0 < staged_us;
 }
 
 // The kernel for a product.  Up to 16 rows the simple or the staged one (few_rows_simple), up to 64 the staged one where it takes the
 // shape (86 shapes of 17 to 32 rows: 0.5 % slower on average than the faster of it and tiles, 95 of 33 to 64: 1.6 %).  From there to
-// OKV_LINEAR_MAX_ROWS rows tiles where their model is 7 % below the staged kernel's by intake, for 288 to 20480 features (narrower ones
-// are ties; wider ones were not measured, and host tests hold some of both to the staged kernel): 128 rows x 5120 x 20480 65.5 us
-// staged, 49.0 tiles, 128 x 20480 x 5120 66 and 52, 128 x 2304 x 768 6.2 and 4.9, 96 x 5120 x 20480 56.8
-// and 44.7; 128 x 12288 x 4096 28 and 31, 128 x 16384 x 4096 35 and 38 (478 shapes: 55 change, 14 % faster on average, the worst 0.5 %
-// slower; at 5 % 74 change and the worst, 80 x 4096 x 16384 with a norm, is 3 % slower).  From there to the staged kernel's 192 rows whichever the models favour by more than they are good
-// for (at 192 rows 4096 x 16384 42 us against 53 and 16384 x 4096 40 against 43, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
+// OKV_LINEAR_MAX_ROWS rows tiles where their model is 7 % below the staged kernel's by intake: us staged / tiles 128 rows x 5120 x 20480 65.5 /
+// 49.0, 128 x 20480 x 5120 66 / 52, 128 x 28672 x 4096 62.3 / 48.8, 128 x 2304 x 768 6.2 / 4.9, 96 x 5120 x 20480 56.8 / 44.7, 97 x 272 x 8192
+// 11.4 / 8.2; 128 x 12288 x 4096 28 / 31, 128 x 16384 x 4096 35 / 38 (478 shapes of 288 to 20480 features: 55 change, 14 % faster, the worst
+// 0.5 % slower; at 5 % 74 change and the worst, 80 x 4096 x 16384 with a norm, is 3 % slower; 27 of 16 to 272: 4 change, 27 % faster).  Beyond
+// 20480 features with less than 4096 inputs 12 % below (at 7 % 86 x 36256 x 3328 61.9 / 65.4, 84 x 29232 x 1024 17.3 / 18.2; of 120 shapes of
+// 20608 to 51664 features 67 change, 14 % faster, the worst 0.5 % slower).  From there to the staged kernel's 192 rows whichever the models
+// favour by more than they are good for (at 192 rows 4096 x 16384 42 us against 53 and 16384 x 4096 40 against 43, tiles; 2304 x 4096 17.7 against 15.2 and 6144 x 2048
 // 20.2 against 17.0, staged), or whichever the second estimate of the staged one favours by 4 % (129 rows x 496 x 6400, 25 cuts, 13.1 against
-// 8.9, 136 x 608 x 12032, 47 cuts, 20.2 against 12.8, 192 x 20480 x 5120 uncut in two rounds 85 against 72,
-// tiles; none of the 309 shapes slower; the narrowest outputs are ties that host tests hold to the staged kernel), beyond always a tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
+// 8.9, 136 x 608 x 12032, 47 cuts, 20.2 against 12.8, 160 x 272 x 8192, 32 cuts, 13.0 against 8.5, 192 x 20480 x 5120 uncut in two rounds 85
+// against 72, tiles; none of 309 shapes slower; of 27 of 16 to 272 features 26 are tiles, 22 % faster, the worst, 160 x 64 x 2048, 2 % slower),
+// beyond always a tile kernel.  Where the staged kernel does not take the shape (inputs not a multiple of its chunks, or a cut without a
 // workspace) the simple kernel's time follows the row fragments and the blocks of a wavefront, in rounds of a workgroup per compute unit
 // (which overlap a little) and somewhat faster where units are idle; the tile model is 1.2 us high for such short walks, and 2 for
 // cut ones.  simple / tile us: 9 rows x 4096 x 10240 16.6 / 37.3, 12 x 4096 x 5120 10.0 / 19.8, 16 x 4224 x 4096 14.1 / 16.1, 19 x 3072 x
@@ -1498,10 +1501,10 @@ LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, 
   const bool staged_runs = staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes);
   if (m <= OKV_LIN_SIMPLE_ROWS && !staged_runs) return simple;
   if (m <= 16 && staged.cuts > 0 && few_rows_simple(m, n_out, n_in, n_cus, staged)) return simple;
-  if (staged_runs && (m <= 64 || (m <= OKV_LINEAR_MAX_ROWS && (n_out < 288 || n_out > 20480)))) return staged;
+  if (staged_runs && m <= 64) return staged;
   const LinearPlan tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
-  if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return tile.us < 0.93 * staged.us_by_intake ? tile : staged;
-  if (staged_runs) return tile.us < 0.955 * staged.us || (n_out >= 288 && tile.us < 0.96 * staged.us_by_intake) ? tile : staged;
+  if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return tile.us < (n_out > 20480 && n_in < 4096 ? 0.88 : 0.93) * staged.us_by_intake ? tile : staged;
+  if (staged_runs) return tile.us < 0.955 * staged.us || tile.us < 0.96 * staged.us_by_intake ? tile : staged;
   if (m > OKV_LINEAR_MAX_ROWS) return tile;
   const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 0.82 * std::ceil(q) + 0.18 * q;
   const int fragments = (m + 15) / 16;

@@ -360,7 +360,7 @@ def test_linear_random_shapes_against_the_oracle():
 def test_linear_129_to_192_rows_in_one_launch(m):
     # 9 to 12 fragments of 16 rows: the staged kernel, both workgroup forms, with cuts (every epilogue, and the norm on
     # the share reduction) or without, and shapes that go to the tile kernel
-    for n_out, n_in, kernel in ((12288 // 8, 512, 2), (1024, 1024, 2), (256, 2048, 1), (2048, 256, 2), (6144, 256, 1), (16384, 256, 1)):
+    for n_out, n_in, kernel in ((12288 // 8, 512, 2), (1024, 1024, 2), (768, 2048, 1), (2048, 256, 2), (6144, 256, 1), (16384, 256, 1)):
         assert binding.okv_linear_plan(m, n_out, n_in)[0] == kernel
     say(f"linear one launch m={m}")
     run_linear(m, 12288 // 8, 512, 800 + m, n_seg=3)
@@ -368,6 +368,7 @@ def test_linear_129_to_192_rows_in_one_launch(m):
     run_linear(m, 16384, 256, 815 + m, relu=True)                          # four
     run_linear(m, 1024, 1024, 810 + m, bias=True, relu=True, residual=True)
     run_linear(m, 256, 2048, 820 + m, residual=True)
+    run_linear(m, 768, 2048, 825 + m, residual=True)
     run_linear(m, 2048, 256, 830 + m, relu=True)
     run_linear(m, 256, 2048, 840 + m, bias=True, relu=True, residual=True)
 

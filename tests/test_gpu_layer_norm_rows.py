@@ -37,7 +37,7 @@ def test_layer_norm_widths(h):
     assert np.max(np.abs(got - want) - 2e-3 * np.abs(want)) <= 2e-3
 
 
-@pytest.mark.parametrize("m,n_out,n_in", [(20, 16, 512), (20, 528, 2048), (40, 8208, 512), (9, 8192, 512), (100, 4096, 4096)])
+@pytest.mark.parametrize("m,n_out,n_in", [(20, 16, 512), (20, 528, 2048), (40, 8208, 512), (9, 8192, 512), (100, 4096, 4096), (4, 512, 20480), (76, 96, 4352)])
 def test_norm_behind_a_share_reduction(m, n_out, n_in):
     print(f"m={m} {n_out}x{n_in}", flush=True)
     x = synth.randn_f16_torch((m, n_in), synth.stream_seed(51, 1), DEV)

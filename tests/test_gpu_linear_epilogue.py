@@ -13,7 +13,7 @@ from test_gpu_linear_tiles import DEV, product
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(0, 7, 304, 288, 1), (0, 8, 6160, 992, 1), (0, 40, 304, 288, 1), (0, 100, 272, 160, 1), (1, 20, 12288, 512, 1), (1, 20, 12304, 512, 1),
-          (1, 40, 1040, 512, 1), (1, 32, 4096, 4096, 4), (1, 100, 2064, 1024, 1), (1, 190, 12304, 512, 1), (1, 150, 272, 4096, 16),
+          (1, 40, 1040, 512, 1), (1, 32, 4096, 4096, 4), (1, 100, 2064, 1024, 1), (1, 190, 12304, 512, 1), (1, 150, 272, 2048, 8),
           (2, 33, 1056, 4224, 1), (2, 130, 80, 992, 1), (2, 500, 4112, 1056, 1), (2, 1000, 16400, 96, 1), (2, 370, 12304, 96, 1)]
 
 

@@ -71,6 +71,15 @@ def test_every_form_over_many_stages(form, cuts, m, n_out, n_in):
     product(m, n_out, n_in, 970 + m, relu=True, residual=True, workspace=not uncut)
 
 
+# 65 to 192 rows where the staged kernel would take the shape as well: few features and many inputs, many features
+@pytest.mark.parametrize("m,n_out,n_in", [(83, 16, 20224), (76, 96, 4352), (97, 272, 8192), (128, 128, 16384), (160, 48, 512), (192, 256, 4096),
+                                          (129, 16, 256), (126, 49968, 768)])
+def test_tiles_of_narrow_and_of_wide_products(m, n_out, n_in):
+    assert binding.okv_linear_plan(m, n_out, n_in)[0] == 2
+    product(m, n_out, n_in, 930 + m, residual=True)
+    product(m, n_out, n_in, 931 + m, bias=False, relu=True)
+
+
 # weights too large to stay cached (32 MiB and more): up to 8 rows nontemporal loads
 @pytest.mark.parametrize("m", [1, 3, 8])
 def test_few_rows_of_a_large_matrix(m):

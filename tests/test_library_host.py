@@ -71,7 +71,10 @@ def test_cuts_of_the_product_kernels_follow_the_launch_model():
     assert cuts(32, 4096, 4000) == 0           # inputs not a multiple of 256
     assert cuts(128, 4096, 4096 + 128) == 0    # from 112 rows on the kernel takes two 128-input chunks at a time
     for m in (9, 33, 65, 97, 128):
-        for n_out, n_in in ((16, 256), (48, 512), (2560, 2560), (5120, 13824), (28672, 8192)):
+        shapes = [(16, 256), (48, 512), (5120, 13824), (12288, 4096), (13824, 5120)]
+        shapes += [(2560, 2560)] if m > 16 else [(2560, 10240)]           # (the other kernels are faster there)
+        shapes += [(28672, 8192)] if m <= 64 else [(20480, 1024)]
+        for n_out, n_in in shapes:
             c = cuts(m, n_out, n_in)
             chunk = 256 if m <= 96 else 128
             assert c >= 1 and (n_in // chunk) % c == 0 and (c == 1 or n_in // chunk // c >= 2)
