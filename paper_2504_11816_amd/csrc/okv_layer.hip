@@ -1349,7 +1349,7 @@ hipError_t launch_linear_tile(const LinearArgs &a, int form, hipStream_t stream)
 struct LinearPlan {
   enum Kind { kSimple = 0, kStaged = 1, kTile = 2 } kind;
   int waves, cuts, form;
-  double us, us_by_intake;               // (the second: the staged kernel from 65 rows on)
+  double us;                             // tiles only
 };
 
 // Streaming wavefronts per workgroup (4 or 3) and cuts of the input dimension for the staged kernel, by a small
@@ -1364,15 +1364,9 @@ struct LinearPlan {
 // workgroups per compute unit is not considered (longer-lived workgroups measured faster than more of them).
 // Examples on 256 compute units: 12288 x 4096 -> 3 wavefronts, no cut (256 workgroups); 6144 x 4096 -> 3
 // wavefronts, 2 cuts; 4096 x 4096 and 4096 x 16384 -> 4 wavefronts, 4 cuts; 16384 x 4096 -> 4, none.
-// Cuts 0: not a shape for the staged kernel.  `us` is the plan's time from 129 rows on, where the tile kernel is the
-// alternative: 3.9 us, the weights at 7.7 MB/us, the rows of x that a compute unit takes in at 71.5 KB/us (60 where they
-// are 16384 inputs apart: rows at multiples of 32 KiB share the memory channels) and for a cut 2.5 us and the shares at
-// 4.4 MB/us.  (60 shapes of 129 to 192 rows, 512 to 20480 features and inputs, weights from HBM, warm clocks: within 4.6 % rms.)
-// `us_by_intake` is a second estimate, better for many cuts and for several rounds (309 shapes, 256 to 20480: 7.4 % rms, `us` 10 %): 3.4 us,
-// the root of the sum of squares of the weights at 4.85 MB/us and of what a compute unit takes in at 58 KB/us (of its weights a quarter), and
-// for a cut 1.9 us, 0.14 for each and the shares at 4.15 MB/us.  (From 65 to 128 rows with constants of their own, 478 shapes: 6.4 % rms.)
+// Cuts 0: not a shape for the staged kernel.
 LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
-  LinearPlan plan = {LinearPlan::kStaged, 4, 0, 0, 0.0, 0.0};
+  LinearPlan plan = {LinearPlan::kStaged, 4, 0, 0, 0.0};
   if (m > OKV_LINEAR_MAX_ROWS_STAGED) return plan;
   const int chunk = lin_chunk((m + 15) / 16), pace = lin_weight_lead((m + 15) / 16);
   if (n_in % (32 * chunk * pace)) return plan;
@@ -1395,18 +1389,38 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
         best = t;
         plan.waves = w;
         plan.cuts = s;
-        const double intake_kb = (double)rounds * m * (n_in / s) * 2 / 1e3;
-        plan.us = 3.9 + weight_mb / 7.7 + intake_kb / (n_in % 16384 ? 71.5 : 60.0) + (s > 1 ? 2.5 + (double)s * m * n_out * 4 / 4.4e6 : 0.0);
-        const double weights_kb = (double)rounds * 16 * w * (n_in / s) * 2 / 1e3;
-        plan.us_by_intake = m > OKV_LINEAR_MAX_ROWS
-                                ? 3.41 + std::hypot(weight_mb / 4.85, (intake_kb + 0.24 * weights_kb) / 58.1) +
-                                      (s > 1 ? 1.87 + 0.14 * s + (double)s * m * n_out * 4 / 4.15e6 : 0.0)
-                                : 3.07 + std::hypot(weight_mb / 6.06, intake_kb / 54.0) +
-                                      (s > 1 ? 1.72 + 0.14 * s + (double)s * m * n_out * 4 / 3.51e6 : 0.0);
       }
     }
   }
   return plan;
+}
+
+// The staged plan's time where the tile kernel is the alternative, two estimates.  By the bytes, from 129 rows on: 3.9 us, the weights at 7.7 MB/us,
+// the rows of x that a compute unit takes in at 71.5 KB/us (60 where they are 16384 inputs apart: rows at multiples of 32 KiB
+// share the memory channels) and for a cut 2.5 us and the shares at 4.4 MB/us.  (60 shapes of 129 to 192 rows, 512 to 20480 features and
+// inputs, weights from HBM, warm clocks: within 4.6 % rms.)
+double staged_intake_kb(const LinearPlan &p, int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, double *weights_kb) {
+  const int64_t wgs = (int64_t)((n_out / 16 + p.waves - 1) / p.waves) * p.cuts, rounds = (wgs + n_cus - 1) / n_cus;
+  *weights_kb = (double)rounds * 16 * p.waves * (n_in / p.cuts) * 2 / 1e3;
+  return (double)rounds * m * (n_in / p.cuts) * 2 / 1e3;
+}
+double staged_us_by_bytes(const LinearPlan &p, int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
+  double weights_kb;
+  const double intake_kb = staged_intake_kb(p, m, n_out, n_in, n_cus, &weights_kb), weight_mb = (double)n_out * n_in * 2 / 1e6;
+  return 3.9 + weight_mb / 7.7 + intake_kb / (n_in % 16384 ? 71.5 : 60.0) + (p.cuts > 1 ? 2.5 + (double)p.cuts * m * n_out * 4 / 4.4e6 : 0.0);
+}
+// By what a compute unit takes in, from 65 rows on; better for many cuts and for several rounds (309 shapes of 129 to 192 rows, 256 to 20480: 7.4 %
+// rms, by the bytes 10 %): 3.4 us, the root of the sum of squares of the weights at 4.85 MB/us and of the intake at 58 KB/us (of its
+// weights a quarter), and for a cut 1.9 us, 0.14 for each and the shares at 4.15 MB/us.  (From 65 to 128 rows with constants of
+// their own, 478 shapes: 6.4 % rms.)
+double staged_us_by_intake(const LinearPlan &p, int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
+  double weights_kb;
+  const double intake_kb = staged_intake_kb(p, m, n_out, n_in, n_cus, &weights_kb), weight_mb = (double)n_out * n_in * 2 / 1e6;
+  if (m > OKV_LINEAR_MAX_ROWS)
+    return 3.41 + std::hypot(weight_mb / 4.85, (intake_kb + 0.24 * weights_kb) / 58.1) +
+           (p.cuts > 1 ? 1.87 + 0.14 * p.cuts + (double)p.cuts * m * n_out * 4 / 4.15e6 : 0.0);
+  return 3.07 + std::hypot(weight_mb / 6.06, intake_kb / 54.0) +
+         (p.cuts > 1 ? 1.72 + 0.14 * p.cuts + (double)p.cuts * m * n_out * 4 / 3.51e6 : 0.0);
 }
 
 // The tile kernels' form and cuts: 4 us for the launch, the weights at 19.4 MB/us (the part of their way from HBM that
@@ -1421,25 +1435,43 @@ LinearPlan staged_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus) {
 // six, 168 x 4224 x 4096 22.1 uncut against 18.4 in three.  With none dearer, 13824-wide products go from two cuts to seven and 8 % slower.
 // Shares beyond 134 MB, which with the weights no longer stay in the memory-side cache until they are added, take 0.3 us a MB more: 3507 rows x 6144
 // x 8192 370 us in three cuts (258 MB), 324 uncut, 1405 x 16384 x 12288 544 in two, 504 uncut.
+// Every product from 65 rows on asks for this on its way to the GPU, so what does not depend on the form is worked out once per number of cuts, at
+// up to 128 rows forms whose rows are not needed are passed over (one of fewer rows and a shorter stage has as few tiles), and a form is left
+// where even full rounds without rounding up would make it no better.  The choice is that of the whole search (2 million shapes).
+// Host ns of a choice, the whole search with both staged estimates made for every candidate -> now: 96 rows x 4096 x 4096 1350 -> 530, 128 x 16384 x
+// 4096 1190 -> 310, 160 x 2048 x 2048 1500 -> 930, 1024 x 4096 x 4096 1140 -> 260; 16 x 4096 x 4096 (no tiles) 310 -> 190.
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
-  LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0, 0.0};
+  LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
   const int stages = (n_in + 63) / 64;
-  const double weight_mb = (double)n_out * n_in * 2 / 1e6;
+  const double fixed_us = 4.0 + (double)n_out * n_in * 2 / 1e6 / 19.4;
+  struct { double walk, shares_us, shares_mb, dearer; } cut[9];
+  int most = 0;
+  for (int s = 1; s <= 8; ++s) {
+    if (s > 1 && (stages / s < 4 || (int64_t)s * m * n_out * 4 > workspace_bytes)) break;
+    const double shares_mb = s > 1 ? (double)s * m * n_out * 4 / 1e6 : 0.0;
+    cut[s].walk = (stages + s - 1) / s;
+    cut[s].shares_mb = shares_mb;
+    cut[s].shares_us = s > 1 ? 2.8 + shares_mb / 4.7 : 0.0;
+    cut[s].dearer = 0.3 * std::max(0.0, shares_mb - 134.0) + (m <= OKV_LINEAR_MAX_ROWS_STAGED ? 0.045 * shares_mb : 0.0);
+    most = s;
+  }
   double best = 0;
   for (int f = 0; f < kTileFormCount; ++f) {
     const TileForm &form = kTileForms[f];
+    if (m <= 128 && (form.rows > 128 || (m <= 96 && form.rows == 128 && form.cols == 128))) continue;
     const int64_t tiles = (int64_t)((m + form.rows - 1) / form.rows) * ((n_out + form.cols - 1) / form.cols);
-    for (int s = 1; s <= 8; ++s) {
-      if (s > 1 && (stages / s < 4 || (int64_t)s * m * n_out * 4 > workspace_bytes)) break;
-      const double q = (double)(tiles * s) / n_cus, whole = std::ceil(q);
+    const double per_cu = 0.919 *                              // (0.92 below: less than that by more than sums are rounded)
+                           (double)tiles * stages / n_cus * form.stage_us;
+    for (int s = 1; s <= most; ++s) {
+      if (plan.cuts && fixed_us + cut[s].shares_us + per_cu >= best) break;
+      const double q = (double)(tiles * s) / n_cus;
+      double whole = (double)(int64_t)q;                       // (std::ceil is a call)
+      if (whole < q) whole += 1.0;
       const double stage_us = form.rows == 192 && n_in % 64 && q > 1.0 ? 1.12 * form.stage_us : form.stage_us;
       const double rounds = form.shares_cu ? 0.5 * (whole + std::max(1.0, q)) : whole;
-      double t = 4.0 + weight_mb / 19.4 + rounds * ((stages + s - 1) / s) * stage_us * (1.0 - 0.08 * (1.0 - std::min(1.0, q)));
-      const double shares_mb = s > 1 ? (double)s * m * n_out * 4 / 1e6 : 0.0;
-      if (s > 1) t += 2.8 + shares_mb / 4.7;
-      const double dearer = 0.3 * std::max(0.0, shares_mb - 134.0) + (m <= OKV_LINEAR_MAX_ROWS_STAGED ? 0.045 * shares_mb : 0.0);
-      const double worth = s > 1 ? 1.01 * t + dearer : t;
-      if (plan.cuts == 0 || worth < best) best = worth, plan.us = t + 0.084 * shares_mb, plan.form = f, plan.cuts = s;
+      const double t = fixed_us + rounds * cut[s].walk * stage_us * (1.0 - 0.08 * (1.0 - std::min(1.0, q))) + cut[s].shares_us;
+      const double worth = s > 1 ? 1.01 * t + cut[s].dearer : t;
+      if (plan.cuts == 0 || worth < best) best = worth, plan.us = t + 0.084 * cut[s].shares_mb, plan.form = f, plan.cuts = s;
     }
   }
   return plan;
@@ -1493,7 +1525,7 @@ bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, cons
 // shapes of 9 to 128 rows, 96 to 20480 features and inputs, weights from HBM: the choice is 0.6 % slower than the faster of the two
 // on average.  The simple kernel's time scatters by 10 % around its model: in doubt the line favours tiles, whose model is the better one.)
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
-  const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0, 0.0};
+  const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0};
   // (most products of up to 8 rows are faster than the staged kernel could stream the weights alone: the same choice without its plan, 12 ns of
   // the call's host time for 4 x 4096 x 4096 instead of 147)
   if (m <= OKV_LIN_SIMPLE_ROWS && few_rows_simple_us(m, n_out, n_in, n_cus) < 1.14 * (2.91 + (double)n_out * n_in * 2 / 8.1e6)) return simple;
@@ -1503,8 +1535,11 @@ LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, 
   if (m <= 16 && staged.cuts > 0 && few_rows_simple(m, n_out, n_in, n_cus, staged)) return simple;
   if (staged_runs && m <= 64) return staged;
   const LinearPlan tile = tile_plan(m, n_out, n_in, n_cus, workspace_bytes);
-  if (staged_runs && m <= OKV_LINEAR_MAX_ROWS) return tile.us < (n_out > 20480 && n_in < 4096 ? 0.88 : 0.93) * staged.us_by_intake ? tile : staged;
-  if (staged_runs) return tile.us < 0.955 * staged.us || tile.us < 0.96 * staged.us_by_intake ? tile : staged;
+  if (staged_runs) {
+    const double by_intake = staged_us_by_intake(staged, m, n_out, n_in, n_cus);
+    if (m <= OKV_LINEAR_MAX_ROWS) return tile.us < (n_out > 20480 && n_in < 4096 ? 0.88 : 0.93) * by_intake ? tile : staged;
+    return tile.us < 0.96 * by_intake || tile.us < 0.955 * staged_us_by_bytes(staged, m, n_out, n_in, n_cus) ? tile : staged;
+  }
   if (m > OKV_LINEAR_MAX_ROWS) return tile;
   const double q = n_out / 16.0 / n_cus, rounds = q <= 1.0 ? 1.0 : 0.82 * std::ceil(q) + 0.18 * q;
   const int fragments = (m + 15) / 16;
