@@ -930,7 +930,7 @@ __device__ __forceinline__ void write_pair_heads(const int32_t n_groups, const i
     PairHead h = {};
     const int32_t it = group < n_groups && group < kHeadGroupsMax ? open_item[group] : -1;
     const int32_t n = it >= 0 ? open_item[group + 1] - it : 0;
-    if (n > 0) {                                         // (a batch with no keys at all has one stretch and no item)
+    if (n > 0) {                                         // (a stretch whose items are not in the table has none)
       h.item = it, h.count = n;
       const int4 d = open_desc[group];
       h.b = d.x, h.lo = d.y, h.hi = d.z, h.flags_g = d.w | (g << 8);
@@ -949,8 +949,9 @@ __device__ __forceinline__ void write_pair_heads(const int32_t n_groups, const i
   }
 }
 
-// The bookkeeping of a step for equal stretches (see step_advance_spans_kernel) for at most a sequence per thread, with an item per thread too: a thread counts and scans its sequence, and then finds
-// for one stretch the sequence that its first tile lies in.  Every item either opens a stretch or begins its sequence in mid-stretch, so
+// The bookkeeping of a step for equal stretches (see step_advance_spans_kernel) for at most a sequence per thread, with an item per thread
+// too: a thread counts and scans its sequence, and then finds for one stretch the sequence that its first tile lies in.  Every item
+// either opens a stretch or begins its sequence in mid-stretch, so
 // an item's place in the list is the number of stretches that begin before it and of sequences that begin in mid-stretch before it.
 // (There, the thread of a long sequence writes all of its items one after the other, each behind a look-up in the block table.)
 // us before -> now: one sequence of 4096 keys, 4 and 32 KV heads 9.5 -> 3.6 and 10.5 -> 4.7, two of 4000 with 8 heads 10.0 -> 4.1, 16 of up to
@@ -1483,10 +1484,9 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_kernel(int32_t *ctx
 // (span_pieces), and the first item of every stretch is noted in group_first.  plan_out receives
 // (number of stretches in use, number of items, tiles per stretch as two halves).
 //
-// The launch stands in front of every step (and of every call of the entry point without a context) and is all latency.
-// I is the type of the arithmetic on tiles: 32 bits wherever the batch at capacity fits them (a 64-bit division is a
-// few hundred instructions, and there is a chain of four), and with at most one sequence per thread a length is
-// read once and stays in its register.
+// For more than kStepThreads sequences, or more tiles than 32 bits hold; other batches have step_advance_items_kernel.  The launch stands in
+// front of the step (or of the call without a context) and is all latency.  I is the type of the arithmetic on tiles: 32 bits wherever
+// the batch at capacity fits them (a 64-bit division is a few hundred instructions, and there is a chain of four).
 template <typename I>
 __global__ __launch_bounds__(kStepThreads) void step_advance_spans_kernel(int32_t *ctx_lens, int32_t *chunk_prefix,
                                                                          int4 *item_desc, int32_t *group_first,
@@ -1501,18 +1501,15 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_spans_kernel(int32_
   __shared__ int4 open_desc[kHeadGroupsMax];
   __shared__ int2 open_blk[kHeadGroupsMax];
   const int tid = threadIdx.x;
-  const bool one_each = B <= kStepThreads;
-  const int per = one_each ? 1 : (B + kStepThreads - 1) / kStepThreads;     // consecutive sequences per thread
+  const int per = (B + kStepThreads - 1) / kStepThreads;                    // consecutive sequences per thread
   const int b0 = min(B, tid * per), b1 = min(B, b0 + per);
-  const int32_t n0 = b0 < b1 ? ctx_lens[b0] + inc : 0;
-  auto len = [&](int b) -> int32_t { return one_each ? n0 : ctx_lens[b]; };  // (after the lengths have advanced)
   // (a length no sequence can have, which only a caller's own device array could hold, does not leave the arithmetic)
   auto tiles_of = [&](int32_t n) -> I { return min(max((n >> 4) + ((n & 15) != 0), 0), most_tiles); };
   if (pair_head)
     for (int j = tid; j <= min(max_groups, kHeadGroupsMax); j += kStepThreads) open_item[j] = -1;
   I mine = 0;
   for (int b = b0; b < b1; ++b) {
-    const int32_t n = b == b0 ? n0 : ctx_lens[b] + inc;
+    const int32_t n = ctx_lens[b] + inc;
     if (inc) ctx_lens[b] = n;                                  // inc == 0: the lengths are only read
     mine += tiles_of(n);
   }
@@ -1521,7 +1518,7 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_spans_kernel(int32_
   const SpanPlanOf<I> plan = span_plan<I>(total_tiles, max_groups, min_span);
   I items_mine = 0, first = tile_first;
   for (int b = b0; b < b1; ++b) {
-    const I tiles = tiles_of(len(b));
+    const I tiles = tiles_of(ctx_lens[b]);
     I k0;
     items_mine += span_pieces<I>(first, tiles, plan.span, &k0);
     first += tiles;
@@ -1531,7 +1528,7 @@ __global__ __launch_bounds__(kStepThreads) void step_advance_spans_kernel(int32_
   first = tile_first;
   for (int b = b0; b < b1; ++b) {
     chunk_prefix[b] = at;
-    const int32_t n = len(b);
+    const int32_t n = ctx_lens[b];
     const I tiles = tiles_of(n);
     I k0;
     const int32_t cnt = span_pieces<I>(first, tiles, plan.span, &k0);
