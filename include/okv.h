@@ -300,8 +300,9 @@ const char *okv_last_error(const okv_ctx *ctx);
 int okv_set_batch(okv_ctx *ctx, int32_t B, const int32_t *block_table, const int32_t *ctx_lens);
 
 /* Opens a decode step: every sequence's length grows by one (the slot kv_append
- * fills), the split-K work list is rebuilt on the device, and for host layers
- * the first copies are enqueued if none are in flight.  With block-granular offload
+ * fills), the split-K work list is rebuilt on the device (or was made there by the last launch
+ * of the step before; a context of which a launch was captured into a graph makes none ahead any
+ * more, and each of its steps begins with a launch for it), and for host layers the first copies are enqueued if none are in flight.  With block-granular offload
  * (chunk_blocks > 0, blocks on the host) the call first waits until the previous step's
  * kernels have finished: letting the host enqueue several steps ahead made those steps
  * up to 10 % slower and erratic, and the compute stream waits for copies most of the
@@ -438,8 +439,8 @@ int okv_prefill_plan(const okv_ctx *ctx, int64_t *staged_groups, int64_t *copies
 int okv_prefill_release(okv_ctx *ctx, int32_t layer);
 
 /* Closes the prefill: OKV_ESTATE unless every layer was stored.  Waits for the stores,
- * adds n_new to the sequence lengths, rebuilds the work list and restarts the copy
- * pipeline.  Synchronous. */
+ * adds n_new to the sequence lengths (the work list is another from here on, made when it is
+ * needed) and restarts the copy pipeline.  Synchronous. */
 int okv_prefill_end(okv_ctx *ctx);
 
 /* ---- for callers that cannot allocate ------------------------------------------------------
@@ -518,8 +519,9 @@ int okv_worklist(okv_ctx *ctx, int32_t from_device, int32_t *items, int64_t max_
                  int64_t *n_items);
 
 /* With equal stretches (no split size fixed), what the wavefronts of a launch start from: one record of
- * eight int32 per (stretch, KV head) pair, pair = stretch * G + head, as the bookkeeping kernel writes them on the
- * device for the batch as it is (in okv_step_begin; in this call where no step has begun since; synchronous copy):
+ * eight int32 per (stretch, KV head) pair, pair = stretch * G + head, as they are on the device for the batch as it is
+ * (written by the launch that okv_step_begin makes, by the last merge of the step before, or by this call where no step has
+ * begun since the batch was described, stored or cut otherwise; synchronous copy):
  *   [0] the stretch's first item (index into okv_worklist's list)   [1] items of the stretch
  *   [2] that item's sequence   [3] its first key   [4] one past its last key
  *   [5] bit 0: the item ends its sequence, bit 1: it is the whole sequence; the KV head in the bits from 8 up

@@ -93,8 +93,10 @@ int okv_linear_layernorm(const void *x, const void *w_packed, const void *bias,
                          int32_t relu, void *workspace, int64_t workspace_bytes, void *stream);
 
 /* Bytes of workspace okv_linear wants for this shape on the current device (0 if it
- * would not use one); < 0 on a bad shape.  It is an fp32 copy of the result per cut of the inputs, at most 8:
- * 67 MB for 1024 rows of 4096 x 16384 (four cuts).  Less is accepted: fewer cuts, then none. */
+ * would not use one); < 0 on a bad shape.  It is an fp32 copy of the result per cut of the inputs.  Tiles are cut up to 8
+ * times (67 MB for 1024 rows of 4096 x 16384, four cuts), the staged kernel of up to 192 rows dozens of times where the
+ * features are few (20 for 3 x 512 x 20480, 40 for 32 x 256 x 20480), so the bytes are to be asked for here, products of 8
+ * rows and fewer included.  Less is accepted: fewer cuts or another kernel, which may be much slower. */
 int64_t okv_linear_workspace_bytes(int32_t m, int32_t n_out, int32_t n_in);
 
 /* What okv_linear runs for this shape with that much workspace on the current device:

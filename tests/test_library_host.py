@@ -55,7 +55,7 @@ def test_layer_header_symbols_are_exported():
 
 
 def test_cuts_of_the_product_kernels_follow_the_launch_model():
-    # okv_linear_workspace_bytes = cuts * m * n_out * 4 (0: the kernel for few rows or odd input sizes); without a
+    # okv_linear_workspace_bytes = cuts * m * n_out * 4 (0: the simple kernel, for few rows or odd input sizes); without a
     # GPU the library assumes the 256 compute units of the GPU it is written for
     def cuts(m, n_out, n_in):
         nbytes = binding.okv_linear_workspace_bytes(m, n_out, n_in)
@@ -67,7 +67,7 @@ def test_cuts_of_the_product_kernels_follow_the_launch_model():
     assert cuts(32, 4096, 16384) == 4
     assert cuts(32, 6144, 4096) == 2           # 128 groups of three tiles, two cuts
     assert cuts(128, 6144, 4096) == 2
-    assert cuts(8, 4096, 4096) == 0            # up to 8 rows: the kernel that needs no workspace
+    assert cuts(8, 4096, 4096) == 0            # few rows: the kernel that needs no workspace, here the faster one
     assert cuts(32, 4096, 4000) == 0           # inputs not a multiple of 256
     assert cuts(128, 4096, 4096 + 128) == 0    # from 112 rows on the kernel takes two 128-input chunks at a time
     for m in (9, 33, 65, 97, 128):
