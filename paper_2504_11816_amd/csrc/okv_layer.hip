@@ -1438,8 +1438,8 @@ double staged_us_by_intake(const LinearPlan &p, int32_t m, int32_t n_out, int32_
 // Every product from 65 rows on asks for this on its way to the GPU, so what does not depend on the form is worked out once per number of cuts, at
 // up to 128 rows forms whose rows are not needed are passed over (one of fewer rows and a shorter stage has as few tiles), and a form is left
 // where even full rounds without rounding up would make it no better.  The choice is that of the whole search (2 million shapes).
-// Host ns of a choice, the whole search with both staged estimates made for every candidate -> now: 96 rows x 4096 x 4096 1350 -> 530, 128 x 16384 x
-// 4096 1190 -> 310, 160 x 2048 x 2048 1500 -> 930, 1024 x 4096 x 4096 1140 -> 260; 16 x 4096 x 4096 (no tiles) 310 -> 190.
+// Host ns of a choice beside an MI355X, the whole search with both staged estimates made for every candidate -> now: 96 rows x 4096 x 4096 287
+// -> 178, 128 x 16384 x 4096 249 -> 73, 160 x 2048 x 2048 312 -> 247, 1024 x 4096 x 4096 243 -> 55; 16 x 4096 x 4096 (no tiles) 72 -> 49.
 LinearPlan tile_plan(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   LinearPlan plan = {LinearPlan::kTile, 0, 0, 0, 0.0};
   const int stages = (n_in + 63) / 64;
@@ -1526,8 +1526,8 @@ bool few_rows_simple(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, cons
 // on average.  The simple kernel's time scatters by 10 % around its model: in doubt the line favours tiles, whose model is the better one.)
 LinearPlan choose_linear(int32_t m, int32_t n_out, int32_t n_in, int32_t n_cus, int64_t workspace_bytes) {
   const LinearPlan simple = {LinearPlan::kSimple, 0, 1, 0, 0.0};
-  // (most products of up to 8 rows are faster than the staged kernel could stream the weights alone: the same choice without its plan, 12 ns of
-  // the call's host time for 4 x 4096 x 4096 instead of 147)
+  // (most products of up to 8 rows are faster than the staged kernel could stream the weights alone: the same choice without its plan, 6 ns of the
+  // call's host time for 4 x 4096 x 4096 instead of some 45)
   if (m <= OKV_LIN_SIMPLE_ROWS && few_rows_simple_us(m, n_out, n_in, n_cus) < 1.14 * (2.91 + (double)n_out * n_in * 2 / 8.1e6)) return simple;
   const LinearPlan staged = staged_plan(m, n_out, n_in, n_cus);
   const bool staged_runs = staged.cuts == 1 || (staged.cuts > 1 && (int64_t)staged.cuts * m * n_out * 4 <= workspace_bytes);
